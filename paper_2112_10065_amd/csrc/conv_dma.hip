@@ -626,6 +626,7 @@ __global__ __launch_bounds__(256) void k_conv_strip(const KArgs p)
     __builtin_amdgcn_s_barrier();
 #pragma unroll
     for (int m = 0; m < NM; ++m) read_slots(m, 0, 0, 0, 0, 0);
+    landed(0);
 
     int rr = 0, cc = 0;   // filter row and channel block of strip gg
     // one strip = three steps; SB = gg & 1 is the strip's buffer, and with it the parity of its first step
@@ -641,7 +642,7 @@ __global__ __launch_bounds__(256) void k_conv_strip(const KArgs p)
             const int ST = NSA == 2 ? (SB + ss) & 1 : ss, STN = NSA == 2 ? ST ^ 1 : (ss + 1) % 3;   // weight stages of steps i, i+1
 #pragma unroll
             for (int ks = 0; ks < 3; ++ks) {
-                landed(ks & 1);
+                if (ss > 0 || ks > 0) landed(ks & 1);   // the first slice of a strip was waited for at the end of the strip before it
 #pragma unroll
                 for (int m = 0; m < NM; ++m) {
                     read_slots(m, (ks + 1) & 1, ST, SB, ss, ks + 1);
@@ -675,6 +676,10 @@ __global__ __launch_bounds__(256) void k_conv_strip(const KArgs p)
                 multiply(1, m);
             }
         }
+        // Not left to the next strip: behind the last strip these are the reads of a step that does not exist, and a read still in
+        // flight when the loop ends lands in registers that the compiler has given to the epilogue by then (with another kernel's
+        // blocks on the CU the reads are late enough to overwrite a sum).
+        landed(0);
         rr = rrn; cc = ccn;
     };
     for (int gg = 0; gg < nstrips; gg += 2) {   // reduction channels % 128 == 0: an even number of strips per filter row

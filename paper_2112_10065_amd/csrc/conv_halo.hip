@@ -634,7 +634,15 @@ __global__ __launch_bounds__(256) void k_wgrad_halo9(const KArgs p, int tws, int
             // (issued after every second item: 170 us instead of 162 for conv1_2 at batch 32; two per item: no faster)
             if constexpr (i < NCP + NCD) { if (more) issue_copy(i); }
         });
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the stream's reads past the end have returned
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the stream's reads past the end have returned,
+        // and their registers were not free for anything else until now
+#pragma unroll
+        for (int s = 0; s < 6; ++s) { asm volatile("" : "+v"(xlo[s])); asm volatile("" : "+v"(xhi[s])); }
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            asm volatile("" : "+v"(dlo[0][k])); asm volatile("" : "+v"(dhi[0][k]));
+            asm volatile("" : "+v"(dlo[1][k])); asm volatile("" : "+v"(dhi[1][k]));
+        }
     }
     // the last matrix instructions have written their results before anything reads them (16 passes of 4 clocks)
     asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");

@@ -163,12 +163,13 @@ __global__ __launch_bounds__(256) void k_wgrad_strip(const KArgs p)
     __builtin_amdgcn_s_barrier();
 #pragma unroll
     for (int m = 0; m < NM; ++m) read_slots(m, 0, 0, 0);
+    landed(0);
 
     auto step = [&](int i, auto stc) {
         constexpr int ST = decltype(stc)::value, STN = (ST + 1) % 3;
 #pragma unroll
         for (int ks = 0; ks < 3; ++ks) {
-            landed(ks & 1);
+            if (ks > 0) landed(ks & 1);   // the first slice was waited for at the end of the step before
 #pragma unroll
             for (int m = 0; m < NM; ++m) {
                 read_slots(m, (ks + 1) & 1, ST, ks + 1);
@@ -192,6 +193,7 @@ __global__ __launch_bounds__(256) void k_wgrad_strip(const KArgs p)
             multiply(1, m);
         }
         advance();
+        landed(0);   // here and not at the start of the next step: no read is in flight when the loop ends and its registers get other uses
     };
     for (int i = 0; i < nsteps; i += 3) {
         step(i, std::integral_constant<int, 0>());

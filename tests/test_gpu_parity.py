@@ -613,6 +613,58 @@ def test_filter_gradient_pixel_strip_kernel(env, splits):
         dp.dp_set_override(2, -1, 0)
 
 
+@pytest.mark.parametrize("pass_,variant", [(0, 231), (0, 232), (1, 231), (1, 232), (1, 233), (2, 316), (2, 411)])
+def test_results_do_not_depend_on_other_streams(env, pass_, variant):
+    """The kernels that hand-order their LDS reads, beside small blocks of other kernels on the same compute units (filter gradients on two
+    other streams): bit for bit the result of the kernel alone.  An LDS read that was still in flight when the epilogue began used to
+    overwrite a sum when those blocks delayed it."""
+    dp, U, orc = env
+    n, h, c, k = (4, 112, 64, 128) if variant == 411 else (8, 56, 256, 256)
+    g = torch.Generator(device=U.DEV)
+    g.manual_seed(7)
+    rnd = lambda *s: torch.randn(s, generator=g, device=U.DEV).to(torch.bfloat16)
+    x, w, dy = rnd(n, h, h, c), rnd(k, 3, 3, c), rnd(n, h, h, k)
+    d = dp.conv_desc(n, h, h, c, k, 3, 3, (1, 1), (1, 1), dp.DP_BF16, dp.DP_RELU_IN)
+    bx, bdy = rnd(8, 56, 56, 256), rnd(8, 56, 56, 256)
+    bd = dp.conv_desc(8, 56, 56, 256, 256, 3, 3, (1, 1), (1, 1), dp.DP_BF16, 0)
+    dp.dp_set_override(2, 303, 0)    # blocks of 28 KB of LDS: they fit beside a block of the strip kernels
+    bws = [U.workspace(dp.dp_conv2d_workspace_bytes(bd, 2)) for _ in range(2)]
+    bdw = [torch.empty((256, 3, 3, 256), device=U.DEV) for _ in range(2)]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    try:
+        dp.dp_set_override(pass_, variant, 1)
+        ws = U.workspace(dp.dp_conv2d_workspace_bytes(d, pass_))
+
+        def launch():
+            out = torch.empty((n, h, h, k) if pass_ == 0 else (n, h, h, c) if pass_ == 1 else (k, 3, 3, c), device=U.DEV,
+                              dtype=torch.float32 if pass_ == 2 else torch.bfloat16)
+            if pass_ == 0:
+                dp.dp_conv2d_fwd(d, x, w, None, out, ws)
+            elif pass_ == 1:
+                dp.dp_conv2d_bwd_data_relu(d, dy, None, w, x, out, ws)
+            else:
+                dp.dp_conv2d_bwd_filter(d, x, dy, None, out, None, ws)
+            return out
+
+        ref = launch()
+        torch.cuda.synchronize()
+        wrong = 0
+        for _ in range(20):
+            outs = [launch()]
+            dp.dp_set_override(2, 303, 0)
+            for s, sw, o in zip(streams, bws, bdw):
+                for _ in range(3):
+                    dp.dp_conv2d_bwd_filter(bd, bx, bdy, None, o, None, sw, stream=s)
+            dp.dp_set_override(pass_, variant, 1)
+            outs += [launch() for _ in range(3)]
+            torch.cuda.synchronize()
+            wrong += sum(int(not torch.equal(o, ref)) for o in outs)
+        assert wrong == 0, f"{wrong} of 80 results differ from the kernel's own result alone"
+    finally:
+        for p in range(3):
+            dp.dp_set_override(p, -1, 0)
+
+
 def test_unfused_relu_gradient_flow(env):
     """dp_relu_bias_grad materialises the masked gradient once; both backward passes then take it
     with y_saved = NULL and must agree with the oracle's masked definitions."""
