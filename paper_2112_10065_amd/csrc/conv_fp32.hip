@@ -1,116 +1,291 @@
-// Plain fp32 kernels (true fp32 FMA on the vector ALUs) for the reference-precision
-// path: one thread per output element for forward / backward-data, one wavefront per
-// filter element for backward-filter.  Small correctness configuration, no tiling.
-#include "dp_kernels.h"
+// fp32 convolutions, the reference-precision path: every product and sum in fp32, on the fp32 matrix instruction
+// v_mfma_f32_16x16x4_f32 (exact fp32 operands, fp32 accumulation).
+//
+// The layers that run here are small (tens of channels, a few thousand pixels): what bounds them is latency, one chain of
+// dependent loads and sums per output, and the number of launches.  So nothing is staged: a wave owns a 16 x 16 (or 16 x 64)
+// output tile, loads its operands from the caches straight into registers, several reduction steps ahead, and the waves of a
+// block share the tile's reduction; their sums meet in LDS in wave order.  A lane of the matrix instruction supplies one
+// reduction element per operand (row l % 16, element l / 16); which element of the tensors that is does not matter as long as both
+// operands agree, so a step takes 16 consecutive reduction channels and lane group g the channels 4g .. 4g+3 of them: one 16-byte
+// load per lane and operand feeds four instructions.
+// Measured against one thread per output (forward, backward-data) and one wave per filter element, 3x3 layers, forward + backward-data
+// + both gradients back to back: 2 x 16 x 16 x 16 -> 16: 64 -> 21 us (67 us of kernels -> three launches, host-bound);
+// 3 x 38 x 38 x 15 -> 34: 175 -> 54 us; 4 x 40 x 40 x 64 -> 64: 2612 -> 94 us (20 / 28 / 46).
+#include "tile_common.h"
+#include <cstdio>
+#include <type_traits>
 
 namespace {
 
-__global__ __launch_bounds__(256) void k_f32_fwd(ConvGeom g, unsigned flags, const float *x, const float *w,
-                                                   const float *bias, float *y)
+// n / d for 0 <= n < 2^31 by one multiplication (d >= 1 fixed per launch)
+struct FastDiv {
+    unsigned mul, shift, d;
+    __host__ __device__ static FastDiv of(int dv)
+    {
+        FastDiv f{0u, 0u, (unsigned)dv};
+        if (dv > 1) {
+            unsigned lg = 0;
+            while ((1ull << lg) < (unsigned long long)dv) ++lg;   // 2^lg >= d > 2^(lg-1)
+            f.shift = lg - 1;
+            f.mul = (unsigned)(((1ull << (31 + lg)) + (unsigned)dv - 1) / (unsigned)dv);
+        }
+        return f;
+    }
+    __device__ __forceinline__ int div(int n) const { return d == 1 ? n : (int)(__umulhi((unsigned)n, mul) >> shift); }
+};
+
+struct F32Args {
+    ConvGeom g;
+    FastDiv plane, row, sh, sw, tap, cblk;   // pixels per image and per row of the pass's pixel grid, strides, filter columns, 16-channel blocks
+    int rowsA, rowsB, red;             // output channels of the pass, pixels, reduction channels
+    unsigned flags;
+    const float *w, *b, *mask;         // weights, pixel operand (x or dy), saved output that masks dy
+    const float *bias, *xin;
+    float *out;
+};
+
+// four consecutive floats of which `valid` exist; a load that does not exist reads `safe` (any valid address)
+template <bool V4> DEVFN f32x4 load4(const float *p, const float *safe, int valid)
 {
-    const long long total = (long long)g.N * g.Ho * g.Wo * g.K;
-    for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (long long)gridDim.x * blockDim.x) {
-        int k = (int)(e % g.K);
-        long long m = e / g.K;
-        int q = (int)(m % g.Wo), p = (int)((m / g.Wo) % g.Ho), n = (int)(m / ((long long)g.Wo * g.Ho));
-        float acc = (flags & KF_BIAS) ? bias[k] : 0.f;
-        for (int r = 0; r < g.R; ++r) {
-            int ih = p * g.sh - g.ph + r;
-            if ((unsigned)ih >= (unsigned)g.H) continue;
-            for (int s = 0; s < g.S; ++s) {
-                int iw = q * g.sw - g.pw + s;
-                if ((unsigned)iw >= (unsigned)g.W) continue;
-                const float *xp = x + (((size_t)n * g.H + ih) * g.W + iw) * g.C;
-                const float *wp = w + (((size_t)k * g.R + r) * g.S + s) * g.C;
-                for (int c = 0; c < g.C; ++c) acc = fmaf(xp[c], wp[c], acc);
+    f32x4 v;
+    if constexpr (V4) {   // the tensors' channel counts are multiples of 4: all or nothing, 16-byte aligned
+        v = *reinterpret_cast<const f32x4 *>(valid > 0 ? p : safe);
+        if (valid <= 0) v = f32x4{0.f, 0.f, 0.f, 0.f};
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { const float t = *(valid > e ? p + e : safe); v[e] = valid > e ? t : 0.f; }
+    }
+    return v;
+}
+
+// Forward and backward-data: D[channel][pixel] = sum over (tap, reduction channel).  DG: backward-data (pixel operand dy, filter
+// taps addressed through the stride); MASK: dy counts where the saved output is > 0.  Everything that decides which loads
+// happen is a template parameter or an address select: a branch in the loop body would make every load wait for the one before.  J: pixel fragments of 16 per wave: 1 while the grid is small, 4 where there are enough tiles
+// to fill the chip without it (the weights are then loaded once per 64 pixels).
+constexpr int kPixWaves = 4;
+template <bool DG, int J, bool V4, bool MASK>
+__global__ __launch_bounds__(64 * kPixWaves) void k_f32_pix(const F32Args p)
+{
+    constexpr int U = J == 1 ? 4 : 2;   // reduction steps whose loads are issued together
+    const ConvGeom &g = p.g;
+    __shared__ f32x4 part[kPixWaves - 1][J][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lr = lane & 15, lg = lane >> 4;
+    const int ta = (p.rowsA + 15) >> 4, tile = blockIdx.x;
+    const int a0 = (tile % ta) * 16, b0 = (tile / ta) * 16 * J;
+    const int cblocks = (p.red + 15) >> 4, steps = g.R * g.S * cblocks;
+
+    int ih0[J], iw0[J], img[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int m = b0 + j * 16 + lr, n = p.plane.div(m), rem = m - n * (int)p.plane.d, r = p.row.div(rem), c = rem - r * (int)p.row.d;
+        img[j] = m < p.rowsB ? n : -1;
+        ih0[j] = DG ? r + g.ph : r * g.sh - g.ph;
+        iw0[j] = DG ? c + g.pw : c * g.sw - g.pw;
+    }
+    f32x4 acc[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    for (int s0 = wave; s0 < steps; s0 += kPixWaves * U) {
+        f32x4 a[U], b[U][J];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int st = s0 + u * kPixWaves;
+            const bool on = st < steps;
+            const int tap = p.cblk.div(st), c = (st - tap * cblocks) * 16 + lg * 4;
+            const int tr = p.tap.div(tap), ts = tap - tr * g.S;
+            const int left = on ? p.red - c : 0;
+            if constexpr (DG) {
+                // weights [k][tap][c]: four reduction rows k = c .. c+3, channel a0 + lr
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const bool ok = left > e && a0 + lr < p.rowsA;
+                    const float t = *(ok ? p.w + ((size_t)(c + e) * g.R * g.S + tap) * g.C + a0 + lr : p.w);
+                    a[u][e] = ok ? t : 0.f;
+                }
+            } else {
+                a[u] = load4<V4>(p.w + ((size_t)(a0 + lr) * g.R * g.S + tap) * g.C + c, p.w, a0 + lr < p.rowsA ? left : 0);
+            }
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                bool ok = img[j] >= 0;
+                int hh = DG ? ih0[j] - tr : ih0[j] + tr, ww = DG ? iw0[j] - ts : iw0[j] + ts;
+                const int Hl = DG ? g.Ho : g.H, Wl = DG ? g.Wo : g.W;
+                if constexpr (DG) {
+                    ok = ok && hh >= 0 && ww >= 0;
+                    const int hq = p.sh.div(ok ? hh : 0), wq = p.sw.div(ok ? ww : 0);   // a tap counts where it meets the stride grid
+                    ok = ok && hq * g.sh == hh && wq * g.sw == ww;
+                    hh = hq; ww = wq;
+                }
+                ok = ok && (unsigned)hh < (unsigned)Hl && (unsigned)ww < (unsigned)Wl;
+                const size_t o = ok ? (((size_t)img[j] * Hl + hh) * Wl + ww) * p.red + c : 0;
+                b[u][j] = load4<V4>(p.b + o, p.b, ok ? left : 0);
+                if constexpr (MASK) {
+                    const f32x4 y = load4<V4>(p.mask + o, p.mask, ok ? left : 0);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) b[u][j][e] = y[e] > 0.f ? b[u][j][e] : 0.f;
+                }
             }
         }
-        if ((flags & KF_RELU) && !(acc > 0.f)) acc = 0.f;
-        y[e] = acc;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int j = 0; j < J; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][e], b[u][j][e], acc[j], 0, 0, 0);
+    }
+    if (wave > 0)
+#pragma unroll
+        for (int j = 0; j < J; ++j) part[wave - 1][j][lane] = acc[j];
+    __syncthreads();
+    if (wave > 0) return;
+    // register v of lane l: channel 4 * (l / 16) + v, pixel l % 16
+    const int ch = a0 + 4 * lg;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        for (int q = 0; q < kPixWaves - 1; ++q) acc[j] += part[q][j][lane];
+        const int pix = b0 + j * 16 + lr;
+        if (pix >= p.rowsB) continue;
+        const size_t o = (size_t)pix * p.rowsA + ch;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            if (ch + v >= p.rowsA) continue;
+            float r = acc[j][v];
+            if (p.flags & KF_BIAS) r += p.bias[ch + v];
+            if ((p.flags & KF_RELU) && !(r > 0.f)) r = 0.f;
+            if (p.xin != nullptr && !(p.xin[o + v] > 0.f)) r = 0.f;   // backward of the ReLU that produced the layer's input
+            p.out[o + v] = r;
+        }
     }
 }
 
-__device__ __forceinline__ float gm(const float *dy, const float *ym, size_t i)
+// Filter gradient: D[k][c] of one tap = sum over output pixels dy[m][k] * x[m at tap][c]; the reduction runs over pixels, 16 per
+// step, dealt over the block's waves.  A block owns 16 k x 16 c of one tap; one more block per 16 k (the one behind the last tap)
+// multiplies dy with ones instead of x: the bias gradient, without a launch of its own.  There are few tiles (30 for 15 -> 34
+// channels), so a block has 16 waves; bound by the address unit (4-byte loads, 16 channels of 4 pixels each).
+constexpr int kWgWaves = 16;
+template <bool MASK>
+__global__ __launch_bounds__(64 * kWgWaves) void k_f32_wgrad(const F32Args p, float *dbias)
 {
-    return (ym != nullptr && !(ym[i] > 0.f)) ? 0.f : dy[i];
-}
-
-__global__ __launch_bounds__(256) void k_f32_dgrad(ConvGeom g, const float *dy, const float *ym, const float *w, const float *xin, float *dx)
-{
-    const long long total = (long long)g.N * g.H * g.W * g.C;
-    for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (long long)gridDim.x * blockDim.x) {
-        int c = (int)(e % g.C);
-        long long m = e / g.C;
-        int wi = (int)(m % g.W), h = (int)((m / g.W) % g.H), n = (int)(m / ((long long)g.W * g.H));
-        float acc = 0.f;
-        for (int r = 0; r < g.R; ++r) {
-            int hp = h + g.ph - r;
-            if (hp < 0 || hp % g.sh != 0) continue;
-            int p = hp / g.sh;
-            if (p >= g.Ho) continue;
-            for (int s = 0; s < g.S; ++s) {
-                int wq = wi + g.pw - s;
-                if (wq < 0 || wq % g.sw != 0) continue;
-                int q = wq / g.sw;
-                if (q >= g.Wo) continue;
-                size_t gb = (((size_t)n * g.Ho + p) * g.Wo + q) * g.K;
-                for (int k = 0; k < g.K; ++k)
-                    acc = fmaf(gm(dy, ym, gb + k), w[(((size_t)k * g.R + r) * g.S + s) * g.C + c], acc);
+    constexpr int U = 4;
+    const ConvGeom &g = p.g;
+    __shared__ f32x4 part[kWgWaves - 1][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lr = lane & 15, lg = lane >> 4;
+    const int ktiles = (g.K + 15) >> 4, ctiles = (g.C + 15) >> 4, bt = blockIdx.x / ktiles, k0 = (blockIdx.x - bt * ktiles) * 16, k = k0 + lr;
+    const int tap = bt / ctiles, c = (bt - tap * ctiles) * 16 + lr;
+    const bool ones = tap >= g.R * g.S;
+    if (ones && dbias == nullptr) return;   // block-uniform
+    const int tr = tap / g.S, ts = tap - tr * g.S, steps = (p.rowsB + 15) >> 4;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int s0 = wave; s0 < steps; s0 += kWgWaves * U) {
+        float a[U][4], b[U][4];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int m0 = (s0 + u * kWgWaves) * 16 + lg * 4;   // four pixels in a row: one division, then carries
+            int n = p.plane.div(m0), rem = m0 - n * (int)p.plane.d, pp = p.row.div(rem), q = rem - pp * (int)p.row.d;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const bool in = m0 + e < p.rowsB, ok = in && k < g.K;
+                const size_t oa = ok ? (size_t)(m0 + e) * g.K + k : 0;
+                float t = p.b[oa];
+                if constexpr (MASK) t = p.mask[oa] > 0.f ? t : 0.f;
+                a[u][e] = ok ? t : 0.f;
+                const int ih = pp * g.sh - g.ph + tr, iw = q * g.sw - g.pw + ts;
+                const bool okx = in && !ones && c < g.C && (unsigned)ih < (unsigned)g.H && (unsigned)iw < (unsigned)g.W;
+                const float x = p.w[okx ? (((size_t)n * g.H + ih) * g.W + iw) * g.C + c : 0];
+                b[u][e] = okx ? x : ones ? 1.f : 0.f;
+                const bool wrap = ++q == g.Wo;
+                q = wrap ? 0 : q;
+                pp += wrap ? 1 : 0;
+                const bool next = pp == g.Ho;
+                pp = next ? 0 : pp;
+                n += next ? 1 : 0;
             }
         }
-        dx[e] = (xin == nullptr || xin[e] > 0.f) ? acc : 0.f;   // backward of the ReLU that produced the layer's input
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][e], b[u][e], acc, 0, 0, 0);
+    }
+    if (wave > 0) part[wave - 1][lane] = acc;
+    __syncthreads();
+    if (wave > 0) return;
+    for (int q = 0; q < kWgWaves - 1; ++q) acc += part[q][lane];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int kk = k0 + 4 * lg + v;
+        if (kk >= g.K) continue;
+        if (ones) { if (lr == 0) dbias[kk] = acc[v]; }
+        else if (c < g.C) p.out[((size_t)kk * g.R * g.S + tap) * g.C + c] = acc[v];
     }
 }
 
-// one wavefront per dw element; lanes stride over the output pixels, then a shuffle tree
-__global__ __launch_bounds__(256) void k_f32_wgrad(ConvGeom g, const float *x, const float *dy, const float *ym, float *dw)
-{
-    const long long total = (long long)g.K * g.R * g.S * g.C;
-    const int lane = threadIdx.x & 63;
-    const long long e = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (e >= total) return;
-    int c = (int)(e % g.C);
-    int s = (int)((e / g.C) % g.S);
-    int r = (int)((e / ((long long)g.C * g.S)) % g.R);
-    int k = (int)(e / ((long long)g.C * g.S * g.R));
-    const int M = g.N * g.Ho * g.Wo;
-    float acc = 0.f;
-    for (int m = lane; m < M; m += 64) {
-        int q = m % g.Wo, p = (m / g.Wo) % g.Ho, n = m / (g.Wo * g.Ho);
-        int ih = p * g.sh - g.ph + r, iw = q * g.sw - g.pw + s;
-        if ((unsigned)ih >= (unsigned)g.H || (unsigned)iw >= (unsigned)g.W) continue;
-        acc = fmaf(gm(dy, ym, (size_t)m * g.K + k), x[(((size_t)n * g.H + ih) * g.W + iw) * g.C + c], acc);
-    }
-    for (int o = 32; o > 0; o >>= 1) acc += __shfl_down(acc, o, 64);
-    if (lane == 0) dw[e] = acc;
-}
+bool wide_tiles(long long rowsA, long long rowsB) { return (rowsA + 15) / 16 * ((rowsB + 63) / 64) >= 1024; }   // enough 16 x 64 tiles for four blocks per CU
 
-unsigned blocks_for(long long total)
+hipError_t launch_pix(bool dg, const F32Args &a, hipStream_t st)
 {
-    long long nb = (total + 255) / 256;
-    if (nb > 65536) nb = 65536;
-    if (nb < 1) nb = 1;
-    return (unsigned)nb;
+    const long long ta = (a.rowsA + 15) / 16;
+    const bool wide = wide_tiles(a.rowsA, a.rowsB);
+    const long long tiles = ta * (wide ? ((long long)a.rowsB + 63) / 64 : ((long long)a.rowsB + 15) / 16);
+    const bool v4 = a.red % 4 == 0;
+    const dim3 grid((unsigned)tiles), block(64 * kPixWaves);
+    auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, st, a); };
+    auto pick = [&](auto dgc, auto maskc) {
+        constexpr bool DG = decltype(dgc)::value, MASK = decltype(maskc)::value;
+        if (wide && v4) run(k_f32_pix<DG, 4, true, MASK>);
+        else if (wide) run(k_f32_pix<DG, 4, false, MASK>);
+        else if (v4) run(k_f32_pix<DG, 1, true, MASK>);
+        else run(k_f32_pix<DG, 1, false, MASK>);
+    };
+    if (!dg) pick(std::false_type(), std::false_type());
+    else if (a.mask != nullptr) pick(std::true_type(), std::true_type());
+    else pick(std::true_type(), std::false_type());
+    return hipGetLastError();
 }
 
 }  // namespace
 
+void f32_kernel_name(const ConvGeom &g, int pass, bool masked, char *name, size_t name_bytes)
+{
+    if (pass == PASS_WGRAD) { snprintf(name, name_bytes, "k_f32_wgrad<%s>", masked ? "true" : "false"); return; }
+    const bool dg = pass == PASS_DGRAD, v4 = (dg ? g.K : g.C) % 4 == 0;
+    const bool wide = dg ? wide_tiles(g.C, (long long)g.N * g.H * g.W) : wide_tiles(g.K, (long long)g.N * g.Ho * g.Wo);
+    snprintf(name, name_bytes, "k_f32_pix<%s, %d, %s, %s>", dg ? "true" : "false", wide ? 4 : 1, v4 ? "true" : "false", dg && masked ? "true" : "false");
+}
+
 hipError_t f32_conv_fwd(const ConvGeom &g, unsigned flags, const float *x, const float *w, const float *bias,
                         float *y, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_f32_fwd, dim3(blocks_for((long long)g.N * g.Ho * g.Wo * g.K)), dim3(256), 0, st, g, flags, x, w, bias, y);
-    return hipGetLastError();
+    F32Args a{};
+    a.g = g; a.plane = FastDiv::of(g.Ho * g.Wo); a.row = FastDiv::of(g.Wo); a.sh = FastDiv::of(g.sh); a.sw = FastDiv::of(g.sw); a.tap = FastDiv::of(g.S);
+    a.cblk = FastDiv::of((g.C + 15) / 16);
+    a.rowsA = g.K; a.rowsB = g.N * g.Ho * g.Wo; a.red = g.C; a.flags = flags;
+    a.w = w; a.b = x; a.bias = bias; a.out = y;
+    return launch_pix(false, a, st);
 }
 
 hipError_t f32_conv_dgrad(const ConvGeom &g, const float *dy, const float *ymask, const float *w, const float *xin, float *dx, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_f32_dgrad, dim3(blocks_for((long long)g.N * g.H * g.W * g.C)), dim3(256), 0, st, g, dy, ymask, w, xin, dx);
-    return hipGetLastError();
+    F32Args a{};
+    a.g = g; a.plane = FastDiv::of(g.H * g.W); a.row = FastDiv::of(g.W); a.sh = FastDiv::of(g.sh); a.sw = FastDiv::of(g.sw); a.tap = FastDiv::of(g.S);
+    a.cblk = FastDiv::of((g.K + 15) / 16);
+    a.rowsA = g.C; a.rowsB = g.N * g.H * g.W; a.red = g.K;
+    a.w = w; a.b = dy; a.mask = ymask; a.xin = xin; a.out = dx;
+    return launch_pix(true, a, st);
 }
 
-hipError_t f32_conv_wgrad(const ConvGeom &g, const float *x, const float *dy, const float *ymask, float *dw, hipStream_t st)
+// dw and, if asked for, the bias gradient in one launch
+hipError_t f32_conv_wgrad(const ConvGeom &g, const float *x, const float *dy, const float *ymask, float *dw, float *dbias, hipStream_t st)
 {
-    long long total = (long long)g.K * g.R * g.S * g.C;
-    hipLaunchKernelGGL(k_f32_wgrad, dim3((unsigned)((total + 3) / 4)), dim3(256), 0, st, g, x, dy, ymask, dw);
+    F32Args a{};
+    a.g = g; a.plane = FastDiv::of(g.Ho * g.Wo); a.row = FastDiv::of(g.Wo);
+    a.rowsB = g.N * g.Ho * g.Wo;
+    a.w = x; a.b = dy; a.mask = ymask; a.out = dw;
+    const long long tiles = (long long)g.R * g.S * ((g.C + 15) / 16);
+    const dim3 grid((unsigned)((g.K + 15) / 16 * (tiles + (dbias != nullptr ? 1 : 0)))), block(64 * kWgWaves);
+    if (ymask != nullptr) hipLaunchKernelGGL(k_f32_wgrad<true>, grid, block, 0, st, a, dbias);
+    else hipLaunchKernelGGL(k_f32_wgrad<false>, grid, block, 0, st, a, dbias);
     return hipGetLastError();
 }

@@ -477,7 +477,11 @@ dp_status run_fwd(const ConvGeom &g, int dtype, unsigned flags, const void *x, c
 {
     TraceScope ts(PASS_FWD, st);
     if (dtype == DP_F32) {
-        ts.name("k_f32_fwd", 1);
+        if (ts.idx >= 0) {
+            char nm[96];
+            f32_kernel_name(g, PASS_FWD, false, nm, sizeof(nm));
+            ts.name(nm, 1);
+        }
         hipError_t e = f32_conv_fwd(g, kflags(flags, true), (const float *)x, (const float *)w, bias, (float *)y, st);
         return e == hipSuccess ? DP_OK : hip_fail(e, "fp32 forward launch");
     }
@@ -535,7 +539,11 @@ dp_status run_dgrad(const ConvGeom &g, int dtype, unsigned flags, const void *dy
     if (!(flags & DP_RELU_IN)) xin = nullptr;
     TraceScope ts(PASS_DGRAD, st);
     if (dtype == DP_F32) {
-        ts.name("k_f32_dgrad", 1);
+        if (ts.idx >= 0) {
+            char nm[96];
+            f32_kernel_name(g, PASS_DGRAD, ym != nullptr, nm, sizeof(nm));
+            ts.name(nm, 1);
+        }
         hipError_t e = f32_conv_dgrad(g, (const float *)dy, (const float *)ym, (const float *)w, (const float *)xin, (float *)dx, st);
         return e == hipSuccess ? DP_OK : hip_fail(e, "fp32 backward-data launch");
     }
@@ -596,12 +604,15 @@ dp_status run_wgrad(const ConvGeom &g, int dtype, const void *x, const void *dy,
     const long long rows = (long long)g.N * g.Ho * g.Wo;
     TraceScope ts(PASS_WGRAD, st);
     if (dtype == DP_F32) {
-        ts.name("k_f32_wgrad", 1);
-        if (dw != nullptr) {
-            hipError_t e = f32_conv_wgrad(g, (const float *)x, (const float *)dy, (const float *)ym, dw, st);
-            if (e != hipSuccess) return hip_fail(e, "fp32 backward-filter launch");
+        if (ts.idx >= 0) {
+            char nm[96];
+            f32_kernel_name(g, PASS_WGRAD, ym != nullptr, nm, sizeof(nm));
+            ts.name(nm, 1);
         }
-        if (db != nullptr) {
+        if (dw != nullptr) {
+            hipError_t e = f32_conv_wgrad(g, (const float *)x, (const float *)dy, (const float *)ym, dw, db, st);
+            if (e != hipSuccess) return hip_fail(e, "fp32 backward-filter launch");
+        } else if (db != nullptr) {
             hipError_t e = rbg_launch(rows, g.K, false, dy, ym, nullptr, db, (float *)ws, st);
             if (e != hipSuccess) return hip_fail(e, "bias-gradient launch");
         }
@@ -761,8 +772,7 @@ dp_status dp_conv2d_kernel_info(const dp_conv_desc *desc, int pass, char *name, 
     if ((s = check_conv(desc, &g)) != DP_OK) return s;
     if (pass < 0 || pass > 2) return fail(DP_ERR_UNSUPPORTED, "pass must be 0, 1 or 2");
     if (desc->io_dtype == DP_F32) {
-        static const char *names[3] = {"k_f32_fwd", "k_f32_dgrad", "k_f32_wgrad"};
-        if (name != nullptr && name_bytes > 0) snprintf(name, name_bytes, "%s", names[pass]);
+        if (name != nullptr && name_bytes > 0) f32_kernel_name(g, pass, false, name, name_bytes);
         if (splits != nullptr) *splits = 1;
         return DP_OK;
     }

@@ -106,13 +106,14 @@ bool dma_fused_reduce_fits(int rowsA, int rowsB, int splits);
 bool dma_plan_fuses_reduce(const GemmPlan &plan);   // the splits are summed by the main kernel: no reduction kernel follows
 void halo_kernel_name(int pass, const GemmPlan &plan, bool masked, char *name, size_t name_bytes);   // masked: backward-data with the fused input-ReLU mask
 
-// conv_fp32.hip : plain fp32 FMA kernels (reference-precision path)
+// conv_fp32.hip : fp32 matrix instructions (reference-precision path)
 hipError_t f32_conv_fwd(const ConvGeom &g, unsigned flags, const float *x, const float *w,
                         const float *bias, float *y, hipStream_t st);
 hipError_t f32_conv_dgrad(const ConvGeom &g, const float *dy, const float *ymask, const float *w, const float *xin,
                           float *dx, hipStream_t st);   // xin (may be NULL): dx *= [xin > 0]
 hipError_t f32_conv_wgrad(const ConvGeom &g, const float *x, const float *dy, const float *ymask,
-                          float *dw, hipStream_t st);
+                          float *dw, float *dbias, hipStream_t st);   // dbias may be NULL
+void f32_kernel_name(const ConvGeom &g, int pass, bool masked, char *name, size_t name_bytes);   // as a profiler prints it; masked: a saved output masks dy
 
 // pointwise.hip : ReLU-gradient / bias-gradient
 size_t rbg_workspace_bytes(long long rows, int k);

@@ -71,6 +71,17 @@ def test_fp32_strided_asymmetric(env):
     check_case(dp, U, orc, case, "fp32 strided")
 
 
+# fp32 tiles of 16 channels x 16 or 64 pixels, 16 reduction channels per step, 4 or 8 waves sharing a reduction: edges of each
+@pytest.mark.parametrize("n,h,w,c,k,r,s,st,pd", [
+    (1, 1, 1, 1, 1, 1, 1, (1, 1), (0, 0)), (1, 5, 7, 15, 17, 3, 3, (1, 1), (1, 1)), (2, 9, 8, 16, 33, 3, 3, (1, 1), (1, 1)),
+    (3, 7, 11, 36, 20, 1, 5, (1, 1), (0, 2)), (2, 13, 10, 6, 64, 3, 2, (2, 3), (1, 0)), (1, 33, 31, 64, 4, 3, 3, (1, 1), (1, 1)),
+    (4, 64, 64, 8, 24, 3, 3, (1, 1), (1, 1)), (4, 97, 99, 5, 31, 2, 2, (1, 1), (0, 0))])
+def test_fp32_tile_edges(env, n, h, w, c, k, r, s, st, pd):
+    dp, U, orc = env
+    case = U.ConvCase("f32e", n, h, w, c, k, r, s, st, pd, bf16=False, dist="he_uniform", bias=True, relu=True)
+    check_case(dp, U, orc, case, "fp32 tile edges")
+
+
 # ---- bf16 matrix-core path: shapes that span several tiles with ragged tails ---------------
 BF16_CASES = [
     # tag, n, h, w, c, k, r, s, stride, pad, bias, relu, dx_f32
