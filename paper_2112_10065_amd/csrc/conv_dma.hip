@@ -168,6 +168,35 @@ DEVFN void fused_split_reduce(const KArgs &p, int tile, int a0, int b0, int tid)
     }
 }
 
+// Walk over the flat reduction (tap, channel) of a layer whose channel count the step does not divide.  A position is the
+// channel `ch`, the filter column index `is` within the list of `ns` columns, the tap bit of the pixel masks, and the element
+// offset of the operand row; one step moves every position by BK channels, which is dt whole taps and a remainder, so each move
+// takes at most one carry into the next column and one into the next row.  No division in the loop.  Behind the last tap the
+// tap number only grows past R*S, where no mask has a bit.
+struct WalkState { int ch, is, tap, off; };
+struct WalkStep { int C, ns, dch, dis, dtap, doff, carry_tap, carry_off, wrap_tap, wrap_off; };
+// step_s / step_r_S: tap numbers between neighbouring columns / rows of the tap list; col / row: operand elements between them
+// (col_carry: what a carry into the next column adds beyond the channel's wrap); wrap: row - ns * col
+DEVFN WalkStep walk_step(int bk, int C, int ns, int S, int step_s, int step_r, int col, int carry, int wrap, int row)
+{
+    WalkStep w;
+    const int dt = bk / C, dr = ns > 0 ? dt / ns : 0;
+    w.C = C; w.ns = ns; w.dch = bk - dt * C; w.dis = dt - dr * ns;
+    w.dtap = dr * step_r * S + w.dis * step_s;
+    w.doff = w.dch + dr * row + w.dis * col;
+    w.carry_tap = step_s; w.carry_off = carry;
+    w.wrap_tap = step_r * S - ns * step_s; w.wrap_off = wrap;
+    return w;
+}
+DEVFN void walk_advance(WalkState &w, const WalkStep &st)
+{
+    w.ch += st.dch; w.is += st.dis; w.tap += st.dtap; w.off += st.doff;
+    const bool carry = w.ch >= st.C;
+    w.ch -= carry ? st.C : 0; w.is += carry ? 1 : 0; w.tap += carry ? st.carry_tap : 0; w.off += carry ? st.carry_off : 0;
+    const bool wrap = w.is >= st.ns;
+    w.is -= wrap ? st.ns : 0; w.tap += wrap ? st.wrap_tap : 0; w.off += wrap ? st.wrap_off : 0;
+}
+
 // Tiles: A [TA][BK] (weights rows), B [TB][BK] (pixel rows), unpadded, chunk-swizzled:
 // CH = BK/8 chunks per row; chunk c of row `row` sits at position c ^ ((row / RPS) % CH), RPS = rows
 // per 256 bytes.  One direct-to-LDS instruction fills RPI = 64/CH consecutive rows.
@@ -175,8 +204,13 @@ DEVFN void fused_split_reduce(const KArgs &p, int tile, int a0, int b0, int tid)
 // over the g-th part of the block's reduction range, and the groups' sums are added through LDS in group
 // order before the epilogue: a reduction split without partials in memory or a second kernel, for grids
 // too small to fill the chip with one tile per block.
-template <int TA, int TB, int BK, int WA, int WB, int NS, int KG = 1>
-__global__ __launch_bounds__(64 * WA * WB * KG) void k_fwd_dma(const KArgs p)
+// MIX: channels in whole 8s that BK does not divide.  The reduction is walked flat over (tap, channel), so a step holds chunks of
+// several taps; the weights are contiguous in that order, and a lane's pixel chunk carries its own tap and channel (WalkState).
+// The walk costs about 15 vector instructions per step and chunk class, against a 32-wide step (half the matrix work per barrier,
+// 13.1 us instead of 8.8 on 16 x 17 x 17 x 160 -> 160, 1x7) or the generic kernel (277 -> 192 us on 16 x 100 x 100 x 240 -> 208, 3x3;
+// backward-data 431 -> 191 us).
+template <int TA, int TB, int BK, int WA, int WB, int NS, int KG, bool MIX>
+DEVFN void fwd_dma_body(const KArgs &p)
 {
     constexpr int NT = 64 * WA * WB * KG, NW = WA * WB;
     constexpr int CH = BK / 8, RPI = 64 / CH, RPS = 128 / BK, ROWB = BK * 2, KS = BK / 16;
@@ -229,7 +263,7 @@ __global__ __launch_bounds__(64 * WA * WB * KG) void k_fwd_dma(const KArgs p)
         const int row = (wave * IB + q) * RPI + lane / CH;
         const int c = (lane % CH) ^ ((row / RPS) % CH);
         const u32x2 e = *reinterpret_cast<const u32x2 *>(rowtab + 2 * row);
-        voffB[q] = e.x + c * 16;
+        voffB[q] = MIX ? e.x : e.x + c * 16;
         maskB[q] = e.y;
     }
     const unsigned smem_base = lds_offset(smem) + grp * NS * STAGE;   // this group's stages
@@ -238,10 +272,40 @@ __global__ __launch_bounds__(64 * WA * WB * KG) void k_fwd_dma(const KArgs p)
     int kk = kbeg * BK;
     int tap = kk / g.C, c0 = kk - tap * g.C;
     int tr = tap / g.S, ts = tap - tr * g.S;
+    constexpr int NB = IB < 2 ? IB : 2;   // the chunk a lane fetches alternates between two values over q (8 rows of 128 bytes per copy)
+    static_assert(!MIX || BK == 64, "two chunk classes: rows of 128 bytes");
+    WalkState wk[NB];
+    const WalkStep wstep = walk_step(BK, g.C, g.S, g.S, 1, 1, g.C, 0, (g.W - g.S) * g.C, g.W * g.C);
+    if constexpr (MIX) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int row = (wave * IB + b) * RPI + lane / CH, e0 = kk + ((lane % CH) ^ ((row / RPS) % CH)) * 8;
+            const int t = e0 / g.C, r = t / g.S;
+            wk[b].ch = e0 - t * g.C; wk[b].is = t - r * g.S; wk[b].tap = t;
+            wk[b].off = (r * g.W + wk[b].is) * g.C + wk[b].ch;
+        }
+    }
     int issued = 0;
     auto issue = [&](unsigned sb) {   // loads of the next not-yet-issued step into the stage at byte offset sb
         const bool on = KG == 1 || issued < live;
         ++issued;
+        if constexpr (MIX) {
+            const int left = on ? RSC - kk : 0;   // reduction elements from this step on
+#pragma unroll
+            for (int q = 0; q < IA; ++q) {
+                const int row = (wave * IA + q) * RPI + lane / CH, c8 = ((lane % CH) ^ ((row / RPS) % CH)) * 8;
+                dma16(rw, ldsA_w + sb + q * 1024, c8 < left ? voffA[q] + (unsigned)kk * 2u : OOR);
+            }
+#pragma unroll
+            for (int q = 0; q < IB; ++q) {
+                const WalkState &w = wk[q % NB];
+                dma16(rx, ldsB_w + sb + q * 1024, on && ((maskB[q] >> min(w.tap, 31)) & 1u) ? voffB[q] + (unsigned)w.off * 2u : OOR);
+            }
+#pragma unroll
+            for (int b = 0; b < NB; ++b) walk_advance(wk[b], wstep);
+            kk += BK;
+            return;
+        }
         const unsigned ua = (unsigned)(tap * g.C + c0) * 2u;
         const unsigned ub = (unsigned)((tr * g.W + ts) * g.C + c0) * 2u;
         const unsigned bit = on ? 1u << (tap & 31) : 0u;
@@ -359,6 +423,11 @@ __global__ __launch_bounds__(64 * WA * WB * KG) void k_fwd_dma(const KArgs p)
         store_pixel_major<FA, FB>(p, acc, a0 + arow, b0 + brow, lane, blockIdx.y);
     if (p.splits > 1 && (p.flags & KF_FUSED_REDUCE)) fused_split_reduce<TA, TB, NT>(p, tile, a0, b0, tid);
 }
+
+template <int TA, int TB, int BK, int WA, int WB, int NS, int KG = 1>
+__global__ __launch_bounds__(64 * WA * WB * KG) void k_fwd_dma(const KArgs p) { fwd_dma_body<TA, TB, BK, WA, WB, NS, KG, false>(p); }
+template <int TA, int TB, int BK, int WA, int WB, int NS, int KG = 1>
+__global__ __launch_bounds__(64 * WA * WB * KG) void k_fwd_mix(const KArgs p) { fwd_dma_body<TA, TB, BK, WA, WB, NS, KG, true>(p); }
 
 // A matrix instruction pinned to its place in the instruction stream (kernels with one wave per SIMD order their
 // slots by hand: nothing else would hide a stall).
@@ -930,8 +999,11 @@ __global__ __launch_bounds__(64 * WA * WB) void k_wgrad_dma(const KArgs p)
 // backward-data (c_out % BK == 0; any stride) with the same pipeline: A = weights, reduction-major
 // [BK c_out rows][TA c_in] read through the LDS transpose read; B = dy pixel rows, K-major.
 // ---------------------------------------------------------------------------------------
-template <int TA, int TB, int BK, int WA, int WB, int NS, int KG = 1>   // KG: reduction groups per block, as in k_fwd_dma
-__global__ __launch_bounds__(64 * WA * WB * KG) void k_dgrad_dma(const KArgs p)
+// KG: reduction groups per block, as in k_fwd_dma.  MIX: c_out in whole 8s that BK does not divide, reduction walked flat over (tap,
+// c_out).  Eight reduction rows share a tap, and the rows a copy of the weights fills lie within eight, so the weights' walk is
+// wave-uniform (scalar); the pixel chunks carry a position per lane, as forward.  Strided layers only by phase (or 1x1).
+template <int TA, int TB, int BK, int WA, int WB, int NS, int KG, bool MIX>
+DEVFN void dgrad_dma_body(const KArgs &p)
 {
     constexpr int NT = 64 * WA * WB * KG, NW = WA * WB;
     constexpr int CH = BK / 8, RPI = 64 / CH, RPS = 128 / BK, ROWB = BK * 2, KS = BK / 16;
@@ -968,7 +1040,7 @@ __global__ __launch_bounds__(64 * WA * WB * KG) void k_dgrad_dma(const KArgs p)
         tap_ns = tap_s0 < g.S ? (g.S - tap_s0 + g.sw - 1) / g.sw : 0;
         ntaps = tap_nr * tap_ns;
     }
-    const int steps_tile = p.ph_on ? ntaps * (g.K / BK) : p.steps_total;
+    const int steps_tile = p.ph_on ? (MIX ? (ntaps * g.K + BK - 1) / BK : ntaps * (g.K / BK)) : p.steps_total;
     const int bbeg = blockIdx.y * p.steps_per_split, bend = min(bbeg + p.steps_per_split, steps_tile);
     const int nsteps = (max(bend - bbeg, 0) + KG - 1) / KG;
     const int kbeg = bbeg + grp * nsteps, live = max(0, min(bend - kbeg, nsteps));
@@ -1019,14 +1091,14 @@ __global__ __launch_bounds__(64 * WA * WB * KG) void k_dgrad_dma(const KArgs p)
     for (int q = 0; q < IA; ++q) {
         const int t = (wave * IA + q) * RPIA + lane / (TA / 8);
         const int c = (lane % (TA / 8)) ^ (seg_swz<TA>(t) << 2);
-        voffA[q] = ((unsigned)t * RSC + a0 + c * 8) * 2u;
+        voffA[q] = ((unsigned)(MIX ? t & 7 : t) * RSC + a0 + c * 8) * 2u;
     }
 #pragma unroll
     for (int q = 0; q < IB; ++q) {
         const int row = (wave * IB + q) * RPI + lane / CH;
         const int c = (lane % CH) ^ ((row / RPS) % CH);
         const u32x2 e = *reinterpret_cast<const u32x2 *>(rowtab + 2 * row);
-        voffB[q] = e.x + c * 16;
+        voffB[q] = MIX ? e.x : e.x + c * 16;
         maskB[q] = e.y;
     }
     const unsigned smem_base = lds_offset(smem) + grp * NS * STAGE;   // this group's stages
@@ -1042,10 +1114,58 @@ __global__ __launch_bounds__(64 * WA * WB * KG) void k_dgrad_dma(const KArgs p)
     // steady-state step; stride 1 needs none)
     auto tap_rows = [&]() { return (g.sh == 1 ? tr : tr / g.sh) * g.Wo + (g.sw == 1 ? ts : ts / g.sw); };
     int trow = tap_rows();
+    constexpr int NB = IB < 2 ? IB : 2, NGA = BK / 8 / NW;   // chunk classes of the pixel copies; groups of eight weight rows per wave
+    static_assert(!MIX || (BK == 64 && NGA >= 1 && NGA * NW * 8 == BK), "two chunk classes; whole groups of weight rows per wave");
+    WalkState wk[NB];
+    struct { int k, is, tap; } wa[NGA > 0 ? NGA : 1];
+    // the output pixel of list position (ir, is) is ir rows up and is columns left of the base: (k - (ir * Wo + is) * K) elements
+    const WalkStep wstep = walk_step(BK, g.K, tap_ns, g.S, step_s, step_r, -g.K, -2 * g.K, -(g.Wo - tap_ns) * g.K, -g.Wo * g.K);
+    if constexpr (MIX) {
+        const int ns = max(tap_ns, 1);
+        auto start = [&](int e0, int &ch, int &is, int &tp, int &ir) {
+            const int li = e0 / g.K;
+            ch = e0 - li * g.K; ir = li / ns; is = li - ir * ns;
+            tp = (tap_r0 + ir * step_r) * g.S + tap_s0 + is * step_s;
+        };
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int row = (wave * IB + b) * RPI + lane / CH;
+            int ir;
+            start(kk + ((lane % CH) ^ ((row / RPS) % CH)) * 8, wk[b].ch, wk[b].is, wk[b].tap, ir);
+            wk[b].off = wk[b].ch - (ir * g.Wo + wk[b].is) * g.K;
+        }
+#pragma unroll
+        for (int a = 0; a < NGA; ++a) {
+            int ir;
+            start(kk + (wave * NGA + a) * 8, wa[a].k, wa[a].is, wa[a].tap, ir);
+        }
+    }
     int issued = 0;
     auto issue = [&](unsigned sb) {   // sb: byte offset of the stage to fill
         const bool on = KG == 1 || issued < live;
         ++issued;
+        if constexpr (MIX) {
+#pragma unroll
+            for (int q = 0; q < IA; ++q) {
+                const auto &w = wa[q * RPIA / 8];
+                const bool in = on && w.tap < g.R * g.S;
+                dma16(rw, ldsA_w + sb + q * 1024, in ? voffA[q] + ((unsigned)w.k * RSC + (unsigned)w.tap * g.C) * 2u : OOR);
+            }
+#pragma unroll
+            for (int q = 0; q < IB; ++q) {
+                const WalkState &w = wk[q % NB];
+                dma16(rdy, ldsB_w + sb + q * 1024, on && ((maskB[q] >> min(w.tap, 31)) & 1u) ? voffB[q] + (unsigned)w.off * 2u : OOR);
+            }
+#pragma unroll
+            for (int b = 0; b < NB; ++b) walk_advance(wk[b], wstep);
+#pragma unroll
+            for (int a = 0; a < NGA; ++a) {
+                WalkState w{wa[a].k, wa[a].is, wa[a].tap, 0};
+                walk_advance(w, wstep);
+                wa[a].k = w.ch; wa[a].is = w.is; wa[a].tap = w.tap;
+            }
+            return;
+        }
         const unsigned ua = ((unsigned)c0 * RSC + (unsigned)tap * g.C) * 2u;
         const unsigned ub = (unsigned)(c0 - trow * g.K) * 2u;
         const unsigned bit = on ? 1u << (tap & 31) : 0u;
@@ -1175,7 +1295,12 @@ __global__ __launch_bounds__(64 * WA * WB * KG) void k_dgrad_dma(const KArgs p)
     if (p.splits > 1 && (p.flags & KF_FUSED_REDUCE)) fused_split_reduce<TA, TB, NT>(p, tile, a0, b0, tid);
 }
 
-struct DmaVariant { int TA, TB, BK, WA, WB, NS, KG = 1; };
+template <int TA, int TB, int BK, int WA, int WB, int NS, int KG = 1>
+__global__ __launch_bounds__(64 * WA * WB * KG) void k_dgrad_dma(const KArgs p) { dgrad_dma_body<TA, TB, BK, WA, WB, NS, KG, false>(p); }
+template <int TA, int TB, int BK, int WA, int WB, int NS, int KG = 1>
+__global__ __launch_bounds__(64 * WA * WB * KG) void k_dgrad_mix(const KArgs p) { dgrad_dma_body<TA, TB, BK, WA, WB, NS, KG, true>(p); }
+
+struct DmaVariant { int TA, TB, BK, WA, WB, NS, KG = 1; bool mix = false; };
 const DmaVariant kDma[] = {{128, 128, 64, 2, 2, 2}, {128, 128, 32, 2, 2, 2}, {128, 128, 32, 2, 2, 3}, {128, 128, 32, 2, 2, 4},
                            {64, 128, 64, 2, 2, 2}, {64, 128, 32, 2, 2, 3}, {128, 64, 64, 2, 2, 2}, {64, 64, 64, 2, 2, 3},
                            {256, 256, 64, 2, 4, 2}, {256, 128, 64, 4, 2, 2}, {128, 256, 64, 2, 4, 2}, {256, 256, 64, 4, 2, 2},
@@ -1183,8 +1308,10 @@ const DmaVariant kDma[] = {{128, 128, 64, 2, 2, 2}, {128, 128, 32, 2, 2, 2}, {12
                            {128, 32, 64, 4, 1, 6}, {256, 32, 64, 4, 1, 4}, {128, 32, 64, 4, 1, 4}, {256, 64, 32, 4, 1, 6}, {64, 32, 64, 2, 1, 8},
                            {64, 64, 128, 2, 2, 3}, {64, 128, 128, 2, 2, 2}, {128, 128, 128, 2, 2, 2}, {128, 64, 128, 2, 2, 2}, {64, 64, 128, 2, 2, 4},
                            {64, 64, 64, 2, 2, 2, 4}, {64, 64, 64, 2, 2, 2, 2}, {64, 128, 64, 2, 2, 2, 2}, {128, 64, 64, 2, 2, 2, 2},
-                           {256, 256, 64, 2, 2, 2}, {256, 128, 64, 2, 2, 3}, {128, 256, 64, 2, 2, 3}, {256, 224, 64, 4, 1, 2}};
-constexpr int kNumDma = 34, kStripVariant = 30, kStripEnd = 34;   // entries 30..33 are k_conv_strip (4 waves; its own LDS layout)
+                           {256, 256, 64, 2, 2, 2}, {256, 128, 64, 2, 2, 3}, {128, 256, 64, 2, 2, 3}, {256, 224, 64, 4, 1, 2},
+                           {64, 64, 64, 2, 2, 3, 1, true}, {64, 64, 64, 2, 2, 2, 4, true}, {64, 64, 64, 2, 2, 2, 2, true},
+                           {64, 128, 64, 2, 2, 2, 1, true}, {128, 64, 64, 2, 2, 2, 1, true}, {128, 128, 64, 2, 2, 2, 1, true}};
+constexpr int kNumDma = 40, kStripVariant = 30, kStripEnd = 34;   // entries 30..33 are k_conv_strip (4 waves; its own LDS layout)
 inline bool is_strip(int v) { return v >= kStripVariant && v < kStripEnd; }
 typedef void (*KernelFn)(const KArgs);
 KernelFn pick_dma_d(int v)
@@ -1223,6 +1350,12 @@ KernelFn pick_dma_d(int v)
     case 31: return k_conv_strip<true, 128, 256>;
     case 32: return k_conv_strip<true, 256, 128>;
     case 33: return k_conv_strip<true, 224, 256>;
+    case 34: return k_dgrad_mix<64, 64, 64, 2, 2, 3>;
+    case 35: return k_dgrad_mix<64, 64, 64, 2, 2, 2, 4>;
+    case 36: return k_dgrad_mix<64, 64, 64, 2, 2, 2, 2>;
+    case 37: return k_dgrad_mix<64, 128, 64, 2, 2, 2>;
+    case 38: return k_dgrad_mix<128, 64, 64, 2, 2, 2>;
+    case 39: return k_dgrad_mix<128, 128, 64, 2, 2, 2>;
     default: return k_dgrad_dma<64, 64, 64, 2, 2, 3>;
     }
 }
@@ -1262,6 +1395,12 @@ KernelFn pick_dma(int v)
     case 31: return k_conv_strip<false, 128, 256>;
     case 32: return k_conv_strip<false, 256, 128>;
     case 33: return k_conv_strip<false, 224, 256>;
+    case 34: return k_fwd_mix<64, 64, 64, 2, 2, 3>;
+    case 35: return k_fwd_mix<64, 64, 64, 2, 2, 2, 4>;
+    case 36: return k_fwd_mix<64, 64, 64, 2, 2, 2, 2>;
+    case 37: return k_fwd_mix<64, 128, 64, 2, 2, 2>;
+    case 38: return k_fwd_mix<128, 64, 64, 2, 2, 2>;
+    case 39: return k_fwd_mix<128, 128, 64, 2, 2, 2>;
     default: return k_fwd_dma<64, 64, 64, 2, 2, 3>;
     }
 }
@@ -1339,7 +1478,8 @@ static int phase_layout(const ConvGeom &g, int TB, int BK, int tile0[5], int *ma
         t += (int)((rows + TB - 1) / TB);
         const int r0 = (a + g.ph) % g.sh, s0 = (b + g.pw) % g.sw;
         const int nr = r0 < g.R ? (g.R - r0 + g.sh - 1) / g.sh : 0, ns = s0 < g.S ? (g.S - s0 + g.sw - 1) / g.sw : 0;
-        if (rows > 0 && nr * ns * (g.K / BK) > ms) ms = nr * ns * (g.K / BK);
+        const int steps = (nr * ns * g.K + BK - 1) / BK;   // whole steps per tap where BK divides c_out
+        if (rows > 0 && steps > ms) ms = steps;
     }
     for (int c = nph; c < 5; ++c) tile0[c] = t;
     *max_steps = ms;
@@ -1354,7 +1494,7 @@ bool dma_plan(const ConvGeom &g, int pass, int force_variant, int force_splits, 
     if (pass == PASS_FWD) {
         if (force_variant < 200 || force_variant >= 200 + kNumDma) return false;
         d = &kDma[force_variant - 200];
-        if (g.C % d->BK != 0) return false;
+        if (d->mix ? g.C % 8 != 0 || g.R * g.S > 31 : g.C % d->BK != 0) return false;
         if (is_strip(force_variant - 200) &&   // 3x3, stride 1, pad 1, c_in % 128, whole groups of 8 output channels, no reduction split
             (g.C % 128 != 0 || g.R != 3 || g.S != 3 || g.sh != 1 || g.sw != 1 || g.ph != 1 || g.pw != 1 || g.Ho != g.H || g.Wo != g.W || g.K % 8 != 0))
             return false;
@@ -1363,7 +1503,7 @@ bool dma_plan(const ConvGeom &g, int pass, int force_variant, int force_splits, 
     } else if (pass == PASS_DGRAD) {
         if (force_variant < 200 || force_variant >= 200 + kNumDma) return false;
         d = &kDma[force_variant - 200];
-        if (g.K % d->BK != 0 || g.C % 8 != 0) return false;
+        if ((d->mix ? g.K % 8 != 0 || g.R * g.S > 31 : g.K % d->BK != 0) || g.C % 8 != 0) return false;
         if (is_strip(force_variant - 200) &&   // as forward, with c_out as the reduction; bf16 gradients only (the caller checks)
             (g.K % 128 != 0 || g.R != 3 || g.S != 3 || g.sh != 1 || g.sw != 1 || g.ph != 1 || g.pw != 1 || g.Ho != g.H || g.Wo != g.W))
             return false;   // any stride: taps that miss the stride grid are masked out
@@ -1396,6 +1536,8 @@ bool dma_plan(const ConvGeom &g, int pass, int force_variant, int force_splits, 
             return true;
         }
     }
+    // natural pixel order would mix taps whose output pixels do not advance evenly
+    if (pass == PASS_DGRAD && d->mix && (g.sh > 1 || g.sw > 1) && g.R * g.S > 1) return false;
     int splits;
     if (pass != PASS_WGRAD && is_strip(pl->variant)) {
         // a split takes whole channel blocks, an even number of them (two strips are unrolled): the largest such count <= the request
@@ -1437,7 +1579,7 @@ void dma_kernel_name(int pass, const GemmPlan &pl, char *name, size_t name_bytes
     // as the profiler prints the instantiation: the forward / backward-data kernels carry the group count
     if (pass != PASS_WGRAD && is_strip(pl.variant)) snprintf(name, name_bytes, "k_conv_strip<%s, %d, %d>", pass == PASS_FWD ? "false" : "true", d.TB, d.TA);
     else if (pass == PASS_WGRAD) snprintf(name, name_bytes, "k_wgrad_dma<%d, %d, %d, %d, %d, %d>", d.TA, d.TB, d.BK, d.WA, d.WB, d.NS);
-    else snprintf(name, name_bytes, "%s<%d, %d, %d, %d, %d, %d, %d>", pass == PASS_DGRAD ? "k_dgrad_dma" : "k_fwd_dma", d.TA, d.TB, d.BK, d.WA,
+    else snprintf(name, name_bytes, "%s_%s<%d, %d, %d, %d, %d, %d, %d>", pass == PASS_DGRAD ? "k_dgrad" : "k_fwd", d.mix ? "mix" : "dma", d.TA, d.TB, d.BK, d.WA,
                   d.WB, d.NS, d.KG);
 }
 

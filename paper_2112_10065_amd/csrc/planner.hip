@@ -45,6 +45,12 @@ const Candidate kPix[] = {
     {227, 2, 0.62f, 4.5f, 2},
     {228, 1, 0.85f, 5.0f, 2},
     {229, 1, 0.85f, 5.0f, 2},
+    {234, 3, 0.65f, 4.0f},   // channels that 64 does not divide, reduction walked flat over (tap, channel): 64x64x64
+    {235, 1, 0.65f, 5.0f, 4},   // the same with 4 / 2 reduction groups per block
+    {236, 2, 0.65f, 4.5f, 2},
+    {237, 3, 0.88f, 4.5f},   // 64x128x64
+    {238, 3, 0.88f, 4.5f},   // 128x64x64
+    {239, 2, 1.12f, 5.0f},   // 128x128x64
     {400, 2, 0.75f, 5.5f},   // input patch resident in LDS: 64 x 256 tile (64 reduction channels per tap, stride 1)
     {401, 2, 1.20f, 6.0f},   // same, 128 x 256
     {402, 2, 0.75f, 5.5f},
@@ -143,6 +149,12 @@ int auto_plan_list(const ConvGeom &g, int pass, int force_splits, GemmPlan *out,
     for (int ci = 0; ci < ncand; ++ci) {
         if (pass != PASS_WGRAD && cands[ci].code >= 400 && (restr & 1)) continue;   // the input-patch kernels store bf16 only
         if (pass == PASS_DGRAD && cands[ci].code >= 230 && cands[ci].code <= 233 && (restr & 1)) continue;   // bf16 staged epilogue only
+        if (pass != PASS_WGRAD && cands[ci].code >= 234 && cands[ci].code <= 239) {
+            // whole steps per tap: the plain kernels, which spend no vector instructions on the walk (7x1 backward-data with 192
+            // channels, 16 x 17 x 17: 10.8 us plain, 12.4 flat); everything else gains (flat against the 32-wide step 8.8 / 13.1 us)
+            if ((pass == PASS_FWD ? g.C : g.K) % 64 == 0) continue;
+            if (pass == PASS_DGRAD && (restr & 1) && (g.sh > 1 || g.sw > 1)) continue;   // fp32 gradients of strided layers go in natural pixel order
+        }
         int last_splits = -1;
         for (int s : kSplits) {
             if (force_splits > 0 && s != kSplits[0]) break;

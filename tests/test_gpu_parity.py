@@ -190,6 +190,41 @@ def test_pipelined_forward_variants(env, variant, splits):
         dp.dp_set_override(1, -1, 0)
 
 
+# channel counts in whole 8s that the 64-wide step does not divide: a step spans 1 to 9 taps, the last one is partly past the reduction,
+# the walk carries over filter columns and rows; strided backward-data goes phase by phase (without a split)
+MIX_CASES = [(1, 19, 19, 80, 192, 3, 3, (1, 1), (0, 0)), (2, 9, 10, 24, 40, 3, 3, (1, 1), (1, 1)), (2, 17, 17, 160, 96, 1, 7, (1, 1), (0, 3)),
+             (1, 17, 16, 72, 160, 7, 1, (1, 1), (3, 0)), (2, 15, 14, 8, 16, 5, 5, (1, 1), (2, 2)), (2, 14, 13, 56, 72, 3, 3, (2, 2), (1, 1)),
+             (3, 11, 12, 40, 24, 1, 1, (2, 2), (0, 0)), (1, 13, 15, 104, 8, 3, 2, (2, 1), (0, 1))]
+
+
+@pytest.mark.parametrize("variant", [234, 235, 236, 237, 238, 239])
+@pytest.mark.parametrize("splits", [1, 3])
+def test_flat_reduction_variants(env, variant, splits):
+    dp, U, orc = env
+    for p in (0, 1):
+        dp.dp_set_override(p, variant, splits)
+    try:
+        for n, h, w, c, k, r, s, st, pd in MIX_CASES:
+            case = U.ConvCase("mix", n, h, w, c, k, r, s, st, pd, bf16=True, bias=True, relu=True)
+            assert dp.dp_conv2d_kernel_info(case.desc, 0)[0].startswith("k_fwd_mix<")
+            strided = st != (1, 1) and r * s > 1
+            if not (strided and splits > 1):
+                assert dp.dp_conv2d_kernel_info(case.desc, 1)[0].startswith("k_dgrad_mix<")
+            check_case(dp, U, orc, case, f"flat reduction {variant} splits {splits} c={c} k={k} {r}x{s}")
+            dx = case.run_dgrad_relu_in(None)
+            torch.cuda.synchronize()
+            ref = orc.relu_in_backward(orc.conv2d_bwd_data(case.dy, case.w, case.x.shape, stride=st, pad=pd), case.x)
+            U.assert_bf16_close(U.to_np(dx), ref, "flat reduction with the mask of the layer in front")
+            f32 = U.ConvCase("mix", n, h, w, c, k, r, s, st, pd, bf16=True, bias=True, relu=False, dx_f32=True)
+            assert dp.dp_conv2d_kernel_info(f32.desc, 1)[0].startswith("k_dgrad_mix<") == (st == (1, 1))
+            dx = f32.run_dgrad(None)
+            torch.cuda.synchronize()
+            U.assert_bf16_close(U.to_np(dx), orc.conv2d_bwd_data(f32.dy, f32.w, f32.x.shape, stride=st, pad=pd), "flat reduction, fp32 gradient")
+    finally:
+        for p in (0, 1):
+            dp.dp_set_override(p, -1, 0)
+
+
 @pytest.mark.parametrize("variant", [200, 203, 207, 210, 214, 219, 221, 226, 227, 229])
 @pytest.mark.parametrize("splits", [2, 5])
 def test_split_reduction_fused_into_the_pipelined_kernels(env, variant, splits):
