@@ -584,6 +584,11 @@ size_t wgrad_ws_bytes(const ConvGeom &g, int dtype, bool with_db)
         if (with_db) need += rbg_workspace_bytes((long long)g.N * g.Ho * g.Wo, g.K);
         return need;
     }
+    if (dtype == DP_BF16 && use_small_c(g, PASS_WGRAD) && small_c_wgrad_stem_shape(g)) {
+        need = round256(small_c_wgrad_stem_partial_bytes(g)) + round256(ybytes(g));   // partials, masked gradient
+        if (with_db) need += rbg_workspace_bytes((long long)g.N * g.Ho * g.Wo, g.K);
+        return need;
+    }
     if (dtype == DP_BF16 && use_small_c(g, PASS_WGRAD)) {
         const int kpad = small_c_kpad(g);
         return xcol_bytes(g, kpad) + round256((size_t)g.K * kpad * 4) + wgrad_ws_bytes(im2col_geom(g, kpad), dtype, with_db);
@@ -638,6 +643,32 @@ dp_status run_wgrad(const ConvGeom &g, int dtype, const void *x, const void *dy,
             db_done = true;
         }
         if (db != nullptr && !db_done) {
+            hipError_t e = rbg_launch(rows, g.K, true, dy, ym, nullptr, db, rws, st);
+            if (e != hipSuccess) return hip_fail(e, "bias-gradient launch");
+        }
+        return DP_OK;
+    }
+    if (use_small_c(g, PASS_WGRAD) && small_c_wgrad_stem_shape(g)) {
+        const size_t part = round256(small_c_wgrad_stem_partial_bytes(g));
+        void *gbuf = (char *)ws + part;
+        float *rws = (float *)((char *)gbuf + round256(ybytes(g)));
+        bool db_done = false;
+        if (ym != nullptr && dw != nullptr) {   // one pointwise pass yields the masked gradient and the bias gradient
+            hipError_t e = rbg_launch(rows, g.K, true, dy, ym, gbuf, db, rws, st);
+            if (e != hipSuccess) return hip_fail(e, "ReLU/bias-gradient launch");
+            dy = gbuf;
+            db_done = true;
+        }
+        if (dw != nullptr) {
+            if (ts.idx >= 0) {
+                char nm[96];
+                small_c_wgrad_stem_name(g, nm, sizeof(nm));
+                ts.name(nm, small_c_wgrad_stem_blocks(g));
+            }
+            ts.main_begins();
+            hipError_t e = small_c_wgrad_stem(g, (const bf16_t *)x, (const bf16_t *)dy, (float *)ws, dw, db_done ? nullptr : db, st);
+            if (e != hipSuccess) return hip_fail(e, "backward-filter launch");
+        } else if (db != nullptr) {
             hipError_t e = rbg_launch(rows, g.K, true, dy, ym, nullptr, db, rws, st);
             if (e != hipSuccess) return hip_fail(e, "bias-gradient launch");
         }
@@ -805,6 +836,11 @@ dp_status dp_conv2d_kernel_info(const dp_conv_desc *desc, int pass, char *name, 
         // asks for the bias gradient as well
         if (name != nullptr && name_bytes > 0) snprintf(name, name_bytes, "%s", pass == PASS_FWD ? small_c_fwd_kernel(g) : small_c_wgrad_kernel(g, false, true));
         if (splits != nullptr) *splits = pass == PASS_FWD ? 1 : small_c_wgrad_blocks(g, false);
+        return DP_OK;
+    }
+    if (pass == PASS_WGRAD && use_small_c(g, pass) && small_c_wgrad_stem_shape(g)) {
+        if (name != nullptr && name_bytes > 0) small_c_wgrad_stem_name(g, name, name_bytes);
+        if (splits != nullptr) *splits = small_c_wgrad_stem_blocks(g);
         return DP_OK;
     }
     if (pass != PASS_DGRAD && use_small_c(g, pass)) g = im2col_geom(g, small_c_kpad(g));

@@ -153,6 +153,12 @@ hipError_t small_c_fwd_direct(const ConvGeom &g, unsigned flags, const bf16_t *x
 // strided stems (7x7 stride 2 on RGB): forward straight from the input patch, no im2col matrix
 bool small_c_stem(const ConvGeom &g);
 hipError_t small_c_fwd_stem(const ConvGeom &g, unsigned flags, const bf16_t *x, const bf16_t *w, const float *bias, bf16_t *y, hipStream_t st);
+// their filter gradient, unmasked dy, one fp32 partial per block; db (may be NULL) receives the bias gradient
+bool small_c_wgrad_stem_shape(const ConvGeom &g);
+int small_c_wgrad_stem_blocks(const ConvGeom &g);
+size_t small_c_wgrad_stem_partial_bytes(const ConvGeom &g);
+void small_c_wgrad_stem_name(const ConvGeom &g, char *name, size_t name_bytes);
+hipError_t small_c_wgrad_stem(const ConvGeom &g, const bf16_t *x, const bf16_t *dy, float *partial, float *dw, float *db, hipStream_t st);
 int small_c_wgrad_blocks(const ConvGeom &g, bool masked);   // pixel-range blocks, each writes one fp32 partial (masked: a saved output is applied to dy)
 const char *small_c_wgrad_kernel(const ConvGeom &g, bool masked, bool with_db);   // name of the kernel that runs, as a profiler prints it
 const char *small_c_fwd_kernel(const ConvGeom &g);

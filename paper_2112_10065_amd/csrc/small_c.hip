@@ -19,6 +19,7 @@
 // direct-to-LDS loads without block barriers, the tap operand read straight from three input-row strips.
 #include "dma_common.h"
 #include <algorithm>
+#include <cstdio>
 
 namespace {
 
@@ -628,16 +629,16 @@ __global__ __launch_bounds__(256) void k_fwd_rgb3(ConvGeom g, unsigned flags, co
     }
 }
 
-// dw[k][t] = sum over blocks of partial[b][ktile][k % 64][t] in a fixed order; grid = c_out, 1024 threads:
-// thread (t, part) adds every 32nd block with four loads in flight, the 32 parts are then added in order
-// blocks K .. K + ktiles - 1 (present when the bias gradient is wanted) add db_partial[b][ktile][64] the same way
-__global__ __launch_bounds__(1024) void k_wgrad_direct_sum(int K, int rsc, int nblocks, int ktiles, const float *partial, float *dw,
+// dw[k][t] = sum over blocks of partial[b][ktile][t / 32][k % 64][t % 32] in a fixed order; grid = c_out x groups of 32 taps, 1024
+// threads: thread (t, part) adds every 32nd block with eight loads in flight, the 32 parts are then added in order
+// blocks K * groups .. K * groups + ktiles - 1 (present when the bias gradient is wanted) add db_partial[b][ktile][64] the same way
+__global__ __launch_bounds__(1024) void k_wgrad_direct_sum(int K, int rsc, int groups, int nblocks, int ktiles, const float *partial, float *dw,
                                                            const float *db_partial, float *db)
 {
     __shared__ float sm[32][33];
-    if ((int)blockIdx.x >= K) {
+    if ((int)blockIdx.x >= K * groups) {
         __shared__ float sd[16][64];
-        const int kt = blockIdx.x - K, ch = threadIdx.x & 63, part = threadIdx.x >> 6;   // 16 parts
+        const int kt = blockIdx.x - K * groups, ch = threadIdx.x & 63, part = threadIdx.x >> 6;   // 16 parts
         float s = 0.f;
         for (int b = part; b < nblocks; b += 16) s += db_partial[((size_t)b * ktiles + kt) * 64 + ch];
         sd[part][ch] = s;
@@ -650,9 +651,9 @@ __global__ __launch_bounds__(1024) void k_wgrad_direct_sum(int K, int rsc, int n
         }
         return;
     }
-    const int k = blockIdx.x, t = threadIdx.x & 31, part = threadIdx.x >> 5;
-    const size_t bstride = (size_t)ktiles * 64 * 32;
-    const float *src = partial + ((size_t)(k >> 6) * 64 + (k & 63)) * 32 + t;
+    const int tg = blockIdx.x / K, k = blockIdx.x - tg * K, t = threadIdx.x & 31, part = threadIdx.x >> 5;
+    const size_t bstride = (size_t)ktiles * groups * 64 * 32;
+    const float *src = partial + (((size_t)(k >> 6) * groups + tg) * 64 + (k & 63)) * 32 + t;
     float sa[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) sa[u] = 0.f;
@@ -667,11 +668,11 @@ __global__ __launch_bounds__(1024) void k_wgrad_direct_sum(int K, int rsc, int n
     for (; b < nblocks; b += 32) sa[0] += src[(size_t)b * bstride];
     sm[part][t] = ((sa[0] + sa[1]) + (sa[2] + sa[3])) + ((sa[4] + sa[5]) + (sa[6] + sa[7]));
     __syncthreads();
-    if (part == 0 && t < rsc) {
+    if (part == 0 && tg * 32 + t < rsc) {
         float s = 0.f;
 #pragma unroll
         for (int i = 0; i < 32; ++i) s += sm[i][t];
-        dw[(size_t)k * rsc + t] = s;
+        dw[(size_t)k * rsc + tg * 32 + t] = s;
     }
 }
 
@@ -697,71 +698,78 @@ constexpr int ST_PITCH = 512;        // bytes per patch row in LDS (data + 48 by
 constexpr int ST_ROWS = 24;          // patch rows in LDS (rows past the real patch stay zero)
 constexpr int ST_MAXSL = 12;         // reduction slices of 16 (R * 24 <= 192)
 
+// Two bytes of the buffer, zero where !ok.  The offset is made opaque: otherwise the compiler puts every load under a branch of its
+// own; and the value stays a whole register: as 16-bit values it packs pairs at once and waits for the memory at every load.
+DEVFN unsigned load_u16_or_zero(__amdgpu_buffer_rsrc_t r, unsigned off, bool ok)
+{
+    off = ok ? off : OOR;
+    asm volatile("" : "+v"(off));
+    return (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(r, off, 0, 0);
+}
+
 template <int NSL>
 __global__ __launch_bounds__(256, 2) void k_fwd_stem(const ConvGeom g, unsigned flags, const bf16_t *__restrict__ x, const bf16_t *__restrict__ w,
                                                   const float *__restrict__ bias, bf16_t *__restrict__ y, int tiles, int tiles_x, int tiles_y)
 {
     __shared__ __attribute__((aligned(16))) char patch[2][ST_ROWS * ST_PITCH];
-    __shared__ __attribute__((aligned(16))) bf16_t wlds[64 * ST_MAXSL * 16];   // [c_out][R*24 padded to the slices], zero where no weight
+    __shared__ __attribute__((aligned(1024))) bf16_t wlds[64 * ST_MAXSL * 16 + 32];   // the 64 weight rows as they lie in memory
     __shared__ float bias_lds[64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hsel = lane >> 5;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), hsel = lane >> 5;
     const int a0 = blockIdx.y * 64;
-    const int run = g.S * g.C;                       // elements of one filter row
+    const int run = g.S * g.C, per_ch = g.R * run;   // elements of one filter row, of one filter
     const int prow = 7 * g.sh + g.R, pwe = (31 * g.sw + g.S) * g.C;   // real patch: rows, elements per row
-    for (int i = tid; i < 2 * ST_ROWS * ST_PITCH / 4; i += 256) reinterpret_cast<unsigned *>(&patch[0][0])[i] = 0u;
-    for (int i = tid; i < 64 * ST_MAXSL * 16 / 2; i += 256) reinterpret_cast<unsigned *>(wlds)[i] = 0u;
     if (tid < 64) bias_lds[tid] = ((flags & KF_BIAS) && a0 + tid < g.K) ? bias[a0 + tid] : 0.f;
-    __syncthreads();
-    // weights: coalesced 2-byte loads into the padded LDS layout (reduction element 24*r + j holds w[ch][r][j]), then
-    // one 16-byte read per fragment: slice ks, channel half i; lane (channel i*32 + l%32, elements ks*16 + 8*(l/32) ..+7)
-    {
-        const int per_ch = g.R * run, total = 64 * per_ch;
-        for (int e0 = 0; e0 < total; e0 += 256 * 8) {
-            unsigned short v[8];
+    {   // 64 * per_ch * 2 <= 24 KiB, 1 KiB per copy; rows past c_out fetch zeros (the tensor is whole 16-byte chunks: c_out % 8 == 0)
+        const __amdgpu_buffer_rsrc_t rw = make_rsrc(w, (size_t)g.K * per_ch * 2);
+        const unsigned first = (unsigned)a0 * per_ch * 2u, kib = (64u * per_ch * 2u + 1023u) / 1024u;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int e = e0 + u * 256 + tid, ch = e / per_ch;
-                v[u] = (e < total && a0 + ch < g.K) ? w[(size_t)a0 * per_ch + e] : (unsigned short)0;
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int e = e0 + u * 256 + tid, ch = e / per_ch, rem = e - ch * per_ch, r = rem / run, j = rem - r * run;
-                if (e < total) wlds[ch * (ST_MAXSL * 16) + r * 24 + j] = v[u];
-            }
-        }
+        for (int i = 0; i < ST_MAXSL / 2; ++i)
+            if (i * 4u + wave < kib) dma16(rw, lds_offset(wlds) + (i * 4 + wave) * 1024, first + (i * 4 + wave) * 1024 + lane * 16);
     }
-    __syncthreads();
-    u32x4 wfr[NSL][2];
-#pragma unroll
-    for (int ks = 0; ks < NSL; ++ks)
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-            wfr[ks][i] = *reinterpret_cast<const u32x4 *>(wlds + (i * 32 + (lane & 31)) * (ST_MAXSL * 16) + ks * 16 + 8 * hsel);
-
-    // patch elements of this thread: element e = tid + 256*i -> (row, column element); fetched as 2-byte loads
-    // patch fetch: thread t takes column element t of every patch row (a row is at most 232 elements), two rows per register
-    auto fetch = [&](int tile, unsigned (&v)[ST_ROWS / 2]) {
+    // patch fetch: thread t takes column element t of every patch row (a row is at most 232 elements).  Buffer loads with an
+    // out-of-range offset where there is no image, one register per element: no branch and no use of a loaded value before the
+    // stash, so all rows are in flight while the current tile is multiplied (packed in pairs under branches, every second load
+    // waited for the memory: 51 us for 32 x 224 x 224, now 26).
+    const __amdgpu_buffer_rsrc_t rx = make_rsrc(x, (size_t)g.N * g.H * g.W * g.C * 2);
+    const unsigned row_bytes = (unsigned)(g.W * g.C) * 2u;
+    auto fetch = [&](int tile, unsigned (&v)[ST_ROWS]) {
         const int n = tile / (tiles_x * tiles_y), trem = tile - n * (tiles_x * tiles_y), ty = trem / tiles_x, tx = trem - ty * tiles_x;
         const int ih0 = ty * 8 * g.sh - g.ph, ie = (tx * 32 * g.sw - g.pw) * g.C + tid;
         const bool okc = tid < pwe && (unsigned)ie < (unsigned)(g.W * g.C);
-        const bf16_t *src = x + ((size_t)n * g.H + ih0) * g.W * g.C + ie;
+        const unsigned first = (unsigned)(n * g.H + ih0) * row_bytes + (unsigned)ie * 2u;
 #pragma unroll
         for (int r = 0; r < ST_ROWS; ++r) {
-            const bool ok = okc && r < prow && (unsigned)(ih0 + r) < (unsigned)g.H;
-            const unsigned val = ok ? src[(size_t)r * g.W * g.C] : 0u;
-            v[r >> 1] = (r & 1) ? v[r >> 1] | (val << 16) : val;
+            v[r] = load_u16_or_zero(rx, first + r * row_bytes, okc & (r < prow) & ((unsigned)(ih0 + r) < (unsigned)g.H));
         }
     };
-    auto stash = [&](int buf, const unsigned (&v)[ST_ROWS / 2]) {
-        if (tid >= pwe) return;
+    auto stash = [&](int buf, const unsigned (&v)[ST_ROWS]) {   // rows and columns past the real patch become zeros: no branches
 #pragma unroll
-        for (int r = 0; r < ST_ROWS; ++r)
-            if (r < prow) *reinterpret_cast<unsigned short *>(&patch[buf][r * ST_PITCH + tid * 2]) = (unsigned short)((r & 1) ? v[r >> 1] >> 16 : v[r >> 1] & 0xffffu);
+        for (int r = 0; r < ST_ROWS; ++r) *reinterpret_cast<unsigned short *>(&patch[buf][r * ST_PITCH + tid * 2]) = (unsigned short)v[r];
     };
-    unsigned pv[ST_ROWS / 2];
+    unsigned pv[ST_ROWS];
     int tile = blockIdx.x;
-    __syncthreads();   // zero fill done
-    if (tile < tiles) { fetch(tile, pv); stash(0, pv); }
+    fetch(tile, pv);   // the grid has at most `tiles` blocks
+    wait_vmcnt<0>();   // the weights (and the patch, issued with them) have landed
+    __syncthreads();
+    // weight fragment of slice ks, channel half i: lane (channel i*32 + l%32, reduction elements ks*16 + 8*(l/32) .. +7), element
+    // 24*r + j of the padded reduction being w[ch][r][j]
+    u32x4 wfr[NSL][2];
+#pragma unroll
+    for (int ks = 0; ks < NSL; ++ks) {
+        const int gidx = 2 * ks + hsel, r = gidx / 3, part = gidx - 3 * r, nval = r < g.R ? run - 8 * part : 0;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const bf16_t *src = wlds + (nval > 0 ? (i * 32 + (lane & 31)) * per_ch + r * run + part * 8 : 0);
+            unsigned v[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {   // read past the run (never past the array), then select: no branches
+                const unsigned lo = src[2 * q], hi = src[2 * q + 1];
+                v[q] = (lo | hi << 16) & (2 * q + 1 < nval ? 0xffffffffu : 2 * q < nval ? 0xffffu : 0u);
+            }
+            wfr[ks][i] = u32x4{v[0], v[1], v[2], v[3]};
+        }
+    }
+    stash(0, pv);
     __syncthreads();
 
     // per slice: which run / group this lane reads, and how many of its 8 elements are inside the run
@@ -837,6 +845,206 @@ __global__ __launch_bounds__(256, 2) void k_fwd_stem(const ConvGeom g, unsigned 
         }
         if (more) stash((it + 1) & 1, pv);   // the other buffer was last read two tiles ago, before the previous barrier
         __syncthreads();
+    }
+}
+
+// ---------------------------------------------------------------------------------------
+// Filter gradient of the same stems, bound by reading dy once (the im2col form wrote and read 320 bytes per output pixel next to
+// dy's 128: 128 us for 32 x 224 x 224 x 3 -> 64, now 35, of which 6.6 the sum over the
+// blocks).  A tile is 8 x 32 output pixels, one row per wave: the wave copies its 32
+// pixels x 64 c_out of dy straight into its own LDS (three buffers, so the copies of two tiles are in flight), the block fetches the
+// input patch one tile ahead through registers.  A wave multiplies all R*S*C taps (NG groups of 32) and both halves of the 64 c_out:
+// dy^T fragments through the LDS transpose read, and the tap operand straight from the patch: lane l (tap l % 32 of the group, pixels
+// 8*(l/32) .. +7 of a 16-pixel slice) reads its eight elements sw*C elements apart.  Pixels past the end of a row are selected to zero
+// when the elements are packed, whole slices and rows past the image are skipped.  The blocks are persistent; the eight waves'
+// sums meet in LDS, 32 x 32 taps at a time and in wave order, and leave as one fp32 partial per block for k_wgrad_direct_sum.
+// The bias gradient is the column sum of the dy fragments (colsum_selector).  What bounds a tile (2.4 us per CU) is issue: about 200 vector
+// and LDS instructions per 16-pixel slice next to 12 matrix instructions; reading two taps per word or fetching the patch two tiles
+// ahead took more registers than there are and gained nothing (50.7 and 61.2 us against 51.7 on 64 images).
+// ---------------------------------------------------------------------------------------
+constexpr int SW_PITCH = 512, SW_ROWS = 22, SW_DY = 4096, SW_NB = 3;
+template <int NG>
+__global__ __launch_bounds__(512, 1) void k_wgrad_stem(const ConvGeom g, const bf16_t *x, const bf16_t *dy, float *partial, float *db_partial, int tiles,
+                                                       int tiles_x, int tiles_y)
+{
+    constexpr int PATCH = SW_ROWS * SW_PITCH;
+    __shared__ __attribute__((aligned(1024))) char lds[8 * SW_NB * SW_DY + 2 * PATCH];
+    static_assert(sizeof(lds) >= 8 * 64 * 16 * sizeof(float) + 8 * 64 * sizeof(float), "the eight waves' sums of one group fit");
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), hsel = lane >> 5;
+    const int a0 = blockIdx.y * 64, rsc = g.R * g.S * g.C, run = g.S * g.C;
+    const int prow = 7 * g.sh + g.R, pwe = (31 * g.sw + g.S) * g.C;
+    const __amdgpu_buffer_rsrc_t rx = make_rsrc(x, (size_t)g.N * g.H * g.W * g.C * 2), rdy = make_rsrc(dy, (size_t)g.N * g.Ho * g.Wo * g.K * 2);
+    const unsigned base = lds_offset(lds), dbase = base + wave * (SW_NB * SW_DY), pbase = base + 8 * SW_NB * SW_DY;
+    auto place = [&](int tile, int &n, int &p0, int &q0) {
+        n = tile / (tiles_x * tiles_y);
+        const int trem = tile - n * (tiles_x * tiles_y), ty = trem / tiles_x;
+        p0 = ty * 8; q0 = (trem - ty * tiles_x) * 32;
+    };
+    // dy copies: lane l of copy q fills 16-byte position l%8 of pixel q*8 + l/8 with global chunk (l%8) ^ 4*swz(pixel)
+    auto copy_dy = [&](int tile, unsigned buf) {
+        int n, p0, q0;
+        place(tile, n, p0, q0);
+        const int p = p0 + wave;
+        const unsigned row = (unsigned)((n * g.Ho + p) * g.Wo) * g.K * 2u;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int t = q * 8 + lane / 8, c = a0 + ((lane % 8) ^ (seg_swz<64>(t) << 2)) * 8;
+            const bool ok = p < g.Ho && q0 + t < g.Wo && c < g.K;
+            dma16_nt(rdy, dbase + buf + q * 1024, ok ? row + ((unsigned)(q0 + t) * g.K + c) * 2u : OOR);
+        }
+    };
+    // patch fetch: thread t takes column element t % 256 of every second patch row
+    const int pcol = tid & 255, pr0 = tid >> 8;
+    const unsigned row_bytes = (unsigned)(g.W * g.C) * 2u;
+    auto fetch = [&](int tile, unsigned (&v)[SW_ROWS / 2]) {
+        int n, p0, q0;
+        place(tile, n, p0, q0);
+        const int ih0 = p0 * g.sh - g.ph, ie = (q0 * g.sw - g.pw) * g.C + pcol;
+        const bool okc = pcol < pwe && (unsigned)ie < (unsigned)(g.W * g.C);
+        const unsigned first = (unsigned)(n * g.H + ih0) * row_bytes + (unsigned)ie * 2u;
+#pragma unroll
+        for (int i = 0; i < SW_ROWS / 2; ++i) {
+            const int r = 2 * i + pr0;
+            v[i] = load_u16_or_zero(rx, first + r * row_bytes, okc & (r < prow) & ((unsigned)(ih0 + r) < (unsigned)g.H));
+        }
+    };
+    auto stash = [&](unsigned buf, const unsigned (&v)[SW_ROWS / 2]) {
+        const unsigned at = pbase + buf + pr0 * SW_PITCH + pcol * 2;
+#pragma unroll
+        for (int i = 0; i < SW_ROWS / 2; ++i)
+            asm volatile("ds_write_b16 %0, %1" ::"v"(at + 2 * i * SW_PITCH), "v"(v[i]) : "memory");
+    };
+
+    f32x16 acc[2][NG];
+    f32x4 accdb[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        accdb[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < NG; ++t)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][t][e] = 0.f;
+    }
+    const bf16x8 db_sel = colsum_selector(lane);
+    // transpose-read addresses of the dy fragments, as in k_wgrad_rgb3
+    const int i16 = lane & 15, tl = (lane >> 5) * 8 + (i16 >> 2), cl = ((lane >> 4) & 1) * 16 + (i16 & 3) * 4;
+    unsigned fa[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) fa[i] = dbase + tl * 128 + (((i ^ seg_swz<64>(tl)) << 6) | (cl << 1));
+    // tap operand: the element of pixel 8*(l/32) of this wave's row; taps past the filter read tap 0 (their columns are not stored)
+    const unsigned step = (unsigned)(g.sw * g.C) * 2u;   // bytes between neighbouring output pixels in a patch row
+    unsigned fx[NG];
+#pragma unroll
+    for (int t = 0; t < NG; ++t) {
+        const int tap = t * 32 + (lane & 31) < rsc ? t * 32 + (lane & 31) : 0, r = tap / run;
+        fx[t] = pbase + (wave * g.sh + r) * SW_PITCH + (tap - r * run) * 2 + hsel * 8 * step;
+    }
+
+    const int stride = gridDim.x;
+    unsigned pv[SW_ROWS / 2];
+    int tile = blockIdx.x;
+    fetch(tile, pv);              // the grid has at most `tiles` blocks
+    copy_dy(tile, 0);
+    if (tile + stride < tiles) copy_dy(tile + stride, SW_DY);
+    stash(0, pv);
+    if (tile + stride < tiles) wait_vmcnt<4>(); else wait_vmcnt<0>();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    unsigned db = 0, dn2 = 2 * SW_DY, pb = 0;   // dy buffer of this tile and of the tile after the next, patch buffer of this tile
+    for (; tile < tiles; tile += stride) {
+        const bool more = tile + stride < tiles, more2 = tile + 2 * stride < tiles;
+        if (more) fetch(tile + stride, pv);
+        if (more2) copy_dy(tile + 2 * stride, dn2);   // that buffer was read by this wave a tile ago
+        int n, p0, q0;
+        place(tile, n, p0, q0);
+        const int live = p0 + wave < g.Ho ? g.Wo - q0 : 0;   // pixels of this wave's row inside the image, from its first on
+#pragma unroll
+        for (int sl = 0; sl < 2; ++sl) {
+            if (live <= 16 * sl) break;
+            u32x2 lo[2], hi[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                lo[i] = sl == 0 ? lds_tr_read_off<0>(fa[i] + db) : lds_tr_read_off<2048>(fa[i] + db);
+                hi[i] = sl == 0 ? lds_tr_read_off<512>(fa[i] + db) : lds_tr_read_off<2048 + 512>(fa[i] + db);
+            }
+            // byte selectors that pack two elements into a word, the halves of pixels past the row's end as zeros
+            unsigned sel[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int px = 16 * sl + 8 * hsel + 2 * e;
+                sel[e] = (px < live ? 0x0100u : 0x0c0cu) | (px + 1 < live ? 0x05040000u : 0x0c0c0000u);
+            }
+            unsigned xe[2][8];
+            auto read_taps = [&](int t, unsigned (&v)[8]) {
+                const unsigned at = fx[t] + pb + sl * 16 * step;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] = lds_read_u16<0>(at + e * step);
+            };
+            read_taps(0, xe[0]);
+#pragma unroll
+            for (int t = 0; t < NG; ++t) {
+                if (t + 1 < NG) {
+                    read_taps(t + 1, xe[(t + 1) & 1]);
+                    asm volatile("s_waitcnt lgkmcnt(8)" ::: "memory");
+                } else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+                for (int e = 0; e < 8; ++e) asm volatile("" : "+v"(xe[t & 1][e]));
+                if (t == 0) {
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) { asm volatile("" : "+v"(lo[i])); asm volatile("" : "+v"(hi[i])); }
+                }
+                const unsigned *e = xe[t & 1];
+                const bf16x8 b = __builtin_bit_cast(bf16x8, u32x4{__builtin_amdgcn_perm(e[1], e[0], sel[0]), __builtin_amdgcn_perm(e[3], e[2], sel[1]),
+                                                                  __builtin_amdgcn_perm(e[5], e[4], sel[2]), __builtin_amdgcn_perm(e[7], e[6], sel[3])});
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const bf16x8 a = __builtin_bit_cast(bf16x8, u32x4{lo[i].x, lo[i].y, hi[i].x, hi[i].y});
+                    acc[i][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[i][t], 0, 0, 0);
+                    if (t == 0 && db_partial != nullptr) accdb[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, db_sel, accdb[i], 0, 0, 0);
+                }
+            }
+        }
+        if (more) {
+            stash(PATCH - pb, pv);   // the other buffer was last read before the previous barrier
+            if (more2) wait_vmcnt<4>(); else wait_vmcnt<0>();   // the next tile's dy has landed
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+        }
+        const unsigned dn1 = db + SW_DY == SW_NB * SW_DY ? 0u : db + SW_DY;
+        dn2 = db; db = dn1; pb = PATCH - pb;
+    }
+    // sums of the eight waves, 16 accumulator elements x 64 lanes at a time, added in wave order
+    float *red = reinterpret_cast<float *>(lds);   // [wave][64 lanes][16]
+    float *out = partial + ((size_t)blockIdx.x * gridDim.y + blockIdx.y) * NG * 64 * 32;
+#pragma unroll
+    for (int t = 0; t < NG; ++t)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            __syncthreads();
+#pragma unroll
+            for (int v = 0; v < 16; ++v) red[wave * 1024 + v * 64 + lane] = acc[i][t][v];
+            __syncthreads();
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int id = tid + 512 * h, v = id >> 6, l = id & 63;
+                float s = red[id];
+#pragma unroll
+                for (int wv = 1; wv < 8; ++wv) s += red[wv * 1024 + id];
+                // element v of lane l: row 8*(v/4) + 4*(l/32) + v%4 (c_out), column l%32 (tap)
+                out[(t * 64 + i * 32 + 8 * (v >> 2) + 4 * (l >> 5) + (v & 3)) * 32 + (l & 31)] = s;
+            }
+        }
+    if (db_partial != nullptr) {
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 2; ++i) store_colsum_fragment(accdb[i], red + wave * 64, i * 32, 64, lane);
+        __syncthreads();
+        if (tid < 64) {
+            float s = red[tid];
+#pragma unroll
+            for (int wv = 1; wv < 8; ++wv) s += red[wv * 64 + tid];
+            db_partial[((size_t)blockIdx.x * gridDim.y + blockIdx.y) * 64 + tid] = s;
+        }
     }
 }
 
@@ -946,7 +1154,7 @@ hipError_t small_c_wgrad_direct(const ConvGeom &g, const bf16_t *x, const bf16_t
     dp_trace_main_kernel_done(st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_wgrad_direct_sum, dim3((unsigned)(g.K + (db != nullptr ? ktiles : 0))), dim3(1024), 0, st, g.K, g.R * g.S * g.C, nb,
+    hipLaunchKernelGGL(k_wgrad_direct_sum, dim3((unsigned)(g.K + (db != nullptr ? ktiles : 0))), dim3(1024), 0, st, g.K, g.R * g.S * g.C, 1, nb,
                        ktiles, partial, dw, dbp, db);
     return hipGetLastError();
 }
@@ -992,5 +1200,41 @@ hipError_t small_c_fwd_stem(const ConvGeom &g, unsigned flags, const bf16_t *x, 
     default: return hipErrorInvalidValue;
     }
 #undef STEM_CASE
+    return hipGetLastError();
+}
+
+// Strided stems, filter gradient: one persistent block per CU over 8 x 32-pixel tiles, one partial per block.  Few pixels per tile
+// (narrow images) would make the partials larger than the im2col matrix they replace; then fewer blocks take more tiles each.
+static long long stem_tiles(const ConvGeom &g) { return (long long)g.N * ((g.Wo + 31) / 32) * ((g.Ho + 7) / 8); }
+static int stem_groups(const ConvGeom &g) { return (g.R * g.S * g.C + 31) / 32; }
+// up to 160 taps: 2 x 5 accumulator tiles are what two waves per SIMD have registers for
+bool small_c_wgrad_stem_shape(const ConvGeom &g) { return small_c_stem(g) && stem_groups(g) >= 2 && stem_groups(g) <= 5 && 7 * g.sh + g.R <= SW_ROWS; }
+int small_c_wgrad_stem_blocks(const ConvGeom &g)
+{
+    const long long part = (long long)((g.K + 63) / 64) * stem_groups(g) * 64 * 32 * 4, xcol = (long long)g.N * g.Ho * g.Wo * small_c_kpad(g) * 2;
+    return (int)std::max(1ll, std::min({stem_tiles(g), 256ll, xcol / part}));
+}
+size_t small_c_wgrad_stem_partial_bytes(const ConvGeom &g)   // filter-gradient partials, then bias-gradient partials
+{
+    return (size_t)small_c_wgrad_stem_blocks(g) * ((g.K + 63) / 64) * 64 * (stem_groups(g) * 32 + 1) * sizeof(float);
+}
+void small_c_wgrad_stem_name(const ConvGeom &g, char *name, size_t name_bytes) { snprintf(name, name_bytes, "k_wgrad_stem<%d>", stem_groups(g)); }
+
+hipError_t small_c_wgrad_stem(const ConvGeom &g, const bf16_t *x, const bf16_t *dy, float *partial, float *dw, float *db, hipStream_t st)
+{
+    const int nb = small_c_wgrad_stem_blocks(g), ktiles = (g.K + 63) / 64, ng = stem_groups(g), tiles_x = (g.Wo + 31) / 32, tiles_y = (g.Ho + 7) / 8;
+    float *dbp = db != nullptr ? partial + (size_t)nb * ktiles * ng * 64 * 32 : nullptr;
+    const dim3 grid((unsigned)nb, (unsigned)ktiles), block(512);
+#define STEM_CASE(N) case N: hipLaunchKernelGGL(k_wgrad_stem<N>, grid, block, 0, st, g, x, dy, partial, dbp, (int)stem_tiles(g), tiles_x, tiles_y); break;
+    switch (ng) {
+        STEM_CASE(2) STEM_CASE(3) STEM_CASE(4) STEM_CASE(5)
+    default: return hipErrorInvalidValue;
+    }
+#undef STEM_CASE
+    dp_trace_main_kernel_done(st);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_wgrad_direct_sum, dim3((unsigned)(g.K * ng + (db != nullptr ? ktiles : 0))), dim3(1024), 0, st, g.K, g.R * g.S * g.C, ng, nb, ktiles,
+                       partial, dw, dbp, db);
     return hipGetLastError();
 }

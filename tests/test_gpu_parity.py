@@ -119,6 +119,32 @@ def test_bf16_conv_parity(env, spec):
     check_case(dp, U, orc, case, tag)
 
 
+# strided few-channel stems: tiles of 8 x 32 output pixels with ragged rows and columns, 2 to 5 groups of 32 taps, a second tile of
+# c_out, several tiles per block (many small images), one pixel
+STEM_CASES = [(2, 61, 75, 3, 64, 7, 7, (2, 2), (3, 3)), (1, 70, 66, 3, 72, 7, 7, (2, 2), (0, 1)), (300, 14, 13, 3, 32, 7, 7, (2, 2), (3, 3)),
+              (2, 40, 41, 2, 16, 8, 8, (2, 1), (1, 2)), (1, 33, 90, 4, 8, 5, 6, (1, 1), (2, 0)), (3, 21, 20, 6, 40, 3, 4, (2, 1), (1, 1)), (1, 7, 7, 3, 8, 7, 7, (2, 2), (0, 0))]
+
+
+@pytest.mark.parametrize("n,h,w,c,k,r,s,st,pd", STEM_CASES)
+def test_strided_stems(env, n, h, w, c, k, r, s, st, pd):
+    dp, U, orc = env
+    for relu in (False, True):
+        case = U.ConvCase("stem", n, h, w, c, k, r, s, st, pd, bf16=True, bias=True, relu=relu, dx_f32=True)
+        assert dp.dp_conv2d_kernel_info(case.desc, 0)[0].startswith("k_fwd_stem<")
+        assert dp.dp_conv2d_kernel_info(case.desc, 2)[0] == f"k_wgrad_stem<{(r * s * c + 31) // 32}>"
+        check_case(dp, U, orc, case, f"stem {n}x{h}x{w}x{c} {r}x{s} relu={relu}")
+    dw, _ = case.run_wgrad(None, want_db=False)
+    # a NaN in the last image column reaches the taps that read it and no others (pixels past the row's end take no part)
+    case.x[0, h // 2, w - 1, c - 1] = np.nan
+    case.xd[0, h // 2, w - 1, c - 1] = float("nan")
+    dw_nan, _ = case.run_wgrad(None, want_db=False)
+    torch.cuda.synchronize()
+    ref, _ = orc.conv2d_bwd_filter(case.x, case.dy, case.w.shape, stride=st, pad=pd, want_db=True)
+    assert np.array_equal(np.isnan(U.to_np(dw_nan)), np.isnan(ref))
+    clean = ~np.isnan(ref)
+    assert np.array_equal(U.to_np(dw_nan)[clean], U.to_np(dw)[clean])
+
+
 @pytest.mark.parametrize("variant", [0, 1, 2, 3, 4])
 @pytest.mark.parametrize("splits", [1, 3])
 def test_every_tile_variant_and_split(env, variant, splits):
