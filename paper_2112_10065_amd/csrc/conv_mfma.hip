@@ -499,14 +499,33 @@ __global__ __launch_bounds__(256) void k_reduce_pixel_major(const KArgs p)
     const size_t total = (size_t)p.rowsB * p.rowsA;
     const size_t gstride = (size_t)gridDim.x * blockDim.x;
     if ((p.rowsA & 3) == 0) {
+        const bool small = total < ((size_t)1 << 32);   // the channel by a 32-bit remainder
         for (size_t e = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) * 4; e < total; e += gstride * 4) {
+            // bias and mask are requested with the first partial, four partials at a time are in flight; they are added in split order.
+            // (With 64-bit remainders and the loads one after the other a call took 0.6 us longer at 196 x 512.)
+            const int ch = small ? (int)((unsigned)e % (unsigned)p.rowsA) : (int)(e % p.rowsA);
+            f32x4 bv = {0.f, 0.f, 0.f, 0.f};
+            u32x2 xm = {0u, 0u};
+            if (p.flags & KF_BIAS) bv = *reinterpret_cast<const f32x4 *>(p.bias + ch);
+            if (p.flags & KF_MASK_IN) xm = *reinterpret_cast<const u32x2 *>(p.x + e);
             f32x4 s = *reinterpret_cast<const f32x4 *>(p.partial + e);
-            for (int sp = 1; sp < p.splits; ++sp) s += *reinterpret_cast<const f32x4 *>(p.partial + sp * total + e);
+            int sp = 1;
+            for (; sp + 4 <= p.splits; sp += 4) {
+                f32x4 l[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) l[u] = *reinterpret_cast<const f32x4 *>(p.partial + (size_t)(sp + u) * total + e);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) s += l[u];
+            }
+            for (; sp < p.splits; ++sp) s += *reinterpret_cast<const f32x4 *>(p.partial + (size_t)sp * total + e);
+            if (p.flags & KF_BIAS) s += bv;
             float v[4] = {s.x, s.y, s.z, s.w};
-            const int ch = (int)(e % p.rowsA);
-            if (p.flags & KF_BIAS) for (int i = 0; i < 4; ++i) v[i] += p.bias[ch + i];
             if (p.flags & KF_RELU) for (int i = 0; i < 4; ++i) v[i] = v[i] > 0.f ? v[i] : 0.f;
-            if (p.flags & KF_MASK_IN) for (int i = 0; i < 4; ++i) v[i] = mask1f(v[i], p.x[e + i]);
+            if (p.flags & KF_MASK_IN) {
+                const unsigned k0 = keep_bits(xm.x), k1 = keep_bits(xm.y);
+                v[0] = (k0 & 0xffffu) ? v[0] : 0.f; v[1] = (k0 >> 16) ? v[1] : 0.f;
+                v[2] = (k1 & 0xffffu) ? v[2] : 0.f; v[3] = (k1 >> 16) ? v[3] : 0.f;
+            }
             if (p.flags & KF_OUT_F32)
                 *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(p.out) + e) = f32x4{v[0], v[1], v[2], v[3]};
             else
