@@ -700,12 +700,15 @@ dp_status run_wgrad(const ConvGeom &g, int dtype, const void *x, const void *dy,
     float *rws = (float *)((char *)ws + part + gb);
     a.x = (const bf16_t *)x; a.dy = (const bf16_t *)dy; a.ymask = (const bf16_t *)ym; a.out = dw; a.partial = (float *)ws;
     bool db_done = false;
+    int masked_rows = 0;   // rows of column sums the masking pass left in rws, to be added by the split-reduce or the small final kernel
     if (a.plan.fast && ym != nullptr && dw != nullptr) {
-        // one pointwise pass yields both the masked gradient for the fast kernel and the bias gradient
-        hipError_t e = rbg_launch(rows, g.K, true, dy, ym, gbuf, db, rws, st);
+        // one pointwise pass yields both the masked gradient for the fast kernel and the column sums of the bias gradient
+        int rb = 1;
+        hipError_t e = rbg_launch_partial(rows, g.K, true, dy, ym, gbuf, db, rws, st, &rb);
         if (e != hipSuccess) return hip_fail(e, "ReLU/bias-gradient launch");
         a.dy = (const bf16_t *)gbuf; a.ymask = nullptr;
-        db_done = true;
+        if (db != nullptr && rb > 1) masked_rows = rb;
+        else db_done = true;
     }
     if (dw != nullptr) {
         // Unmasked gradient and a bias gradient wanted.  The pipelined kernels sum it on the matrix cores beside dW (no
@@ -715,6 +718,12 @@ dp_status run_wgrad(const ConvGeom &g, int dtype, const void *x, const void *dy,
         // a shape's first call is known only after the candidates have been measured: hence a callback.
         const bool want_db = db != nullptr && !db_done && ym == nullptr;
         PrepFn prep;
+        if (masked_rows > 0)
+            prep = [&](ConvArgs &c) -> hipError_t {
+                c.flags &= ~KF_DB; c.db_out = nullptr; c.db_partial = nullptr; c.db_rows = 0;
+                if (c.plan.splits > 1) { c.db_out = db; c.db_partial = rws; c.db_rows = masked_rows; return hipSuccess; }
+                return rbg_launch_final(g.K, masked_rows, rws, db, st);
+            };
         if (want_db)
             prep = [&](ConvArgs &c) -> hipError_t {
                 c.flags &= ~KF_DB; c.db_out = nullptr; c.db_partial = nullptr; c.db_rows = 0;
@@ -727,7 +736,7 @@ dp_status run_wgrad(const ConvGeom &g, int dtype, const void *x, const void *dy,
             };
         hipError_t e = launch_entry(a, pe, st, ts, prep);
         if (e != hipSuccess) return hip_fail(e, "backward-filter launch");
-        if (want_db) db_done = true;
+        if (want_db || masked_rows > 0) db_done = true;
     }
     if (db != nullptr && !db_done) {
         hipError_t e = rbg_launch(rows, g.K, true, dy, ym, nullptr, db, rws, st);
