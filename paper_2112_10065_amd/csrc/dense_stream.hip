@@ -14,6 +14,7 @@
 //     together with the weight loads of the same step so that the in-order load counter never waits for a young load.
 // Bias and ReLU are applied after the waves' sums are added.
 #include "dma_common.h"
+#include <algorithm>
 #include <type_traits>
 
 namespace {
@@ -364,7 +365,250 @@ __global__ __launch_bounds__(64 * DF_WAVES) void k_dense_wgrad(int N, int C, int
     }
 }
 
+// ---------------------------------------------------------------------------------------
+// Forward and backward-data of the same layers in one pass over W, for calls that ask for both (the incoming gradient is an input of such a
+// call, so neither waits for the other).  Apart, each streams W: 42 + 47 us on 25088 x 4096 at two samples; together 50
+// (4096 x 4096: 21 -> 9.7, 1024 x 1024: 11.8 -> 7.5).
+// A block owns 16 * RT output rows and a range of 64-feature column units, its waves take one unit after the other and walk down the
+// rows, 16 at a time (two direct-to-LDS loads of 8 rows x 128 bytes, NS stages per wave, no block barrier in the stream).  A
+// stage feeds both products: read by rows it is the weight operand of the forward tile (16 outputs x samples, one accumulator per row
+// tile, kept over all units of the wave), through the transpose read the operand of the gradient of the unit's 64 inputs (kept down the
+// column, stored per unit).  The 16-byte chunk c of row r sits at c ^ (r % 8), which both reads accept.  The block's
+// dy rows wait in LDS in fragment order, the unit's x fragments in registers.  y is then summed over the waves (in wave order) and leaves as
+// one partial per column range, dx as one per row range; k_dense_both_sum adds them in order and applies bias, ReLU and mask.
+// RT = 32 keeps the partials of dx few (8 * samples / 4096 of the weight bytes each way); layers too small to give every wave of
+// the chip a unit that way take RT = 8.
+// ---------------------------------------------------------------------------------------
+constexpr int DB_NS = 6;
+template <int RT>
+__global__ __launch_bounds__(64 * DF_WAVES) void k_dense_both(int N, int C, int K, int units_per_block, const bf16_t *x, const bf16_t *dy, const bf16_t *w,
+                                                              float *ypart, float *dxpart)
+{
+    constexpr int D = DB_NS - 1, STAGE = 2048, DYB = RT * 512;
+    static_assert(DF_WAVES * DB_NS * STAGE >= DF_WAVES * 8 * 64 * (int)sizeof(f32x4v), "the waves' sums of eight row tiles fit the stages");
+    static_assert(RT % 8 == 0, "row tiles are summed eight at a time");
+    __shared__ __attribute__((aligned(1024))) char lds[DF_WAVES * DB_NS * STAGE + DYB];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int o0 = blockIdx.x * RT * 16, nst = min(RT, (K - o0 + 15) / 16);
+    const int units = C / 64, ubeg = blockIdx.y * units_per_block, uend = min(ubeg + units_per_block, units);
+    const __amdgpu_buffer_rsrc_t rw = make_rsrc(w, (size_t)K * C * 2), rx = make_rsrc(x, (size_t)N * C * 2), rdy = make_rsrc(dy, (size_t)N * K * 2);
+    const unsigned base = lds_offset(lds) + wave * (DB_NS * STAGE), dybase = lds_offset(lds) + DF_WAVES * DB_NS * STAGE;
+
+    // dy fragments of the block's rows: 16-byte chunk (step, half h, sample) at step*512 + (h*16 + sample)*16 holds rows 16*step + 8*h .. +7
+    // (K is whole chunks); one load fills two steps
+#pragma unroll
+    for (int q = 0; q < RT / 2; q += DF_WAVES) {
+        const int pair = q + wave;
+        if (pair < RT / 2) {
+            const int o = o0 + pair * 32 + (lane >> 4) * 8, n = lane & 15;
+            dma16(rdy, dybase + pair * 1024, n < N && o < K ? ((unsigned)n * K + o) * 2u : OOR);
+        }
+    }
+    // weight loads: lane l of load j fills 16-byte position l%8 of stage row 8*j + l/8 with global chunk (l%8) ^ (row%8)
+    unsigned voffW[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int row = 8 * j + (lane >> 3), c = (lane & 7) ^ (row & 7);
+        voffW[j] = ((unsigned)(o0 + row) * C + c * 8) * 2u;
+    }
+    // by rows: row l%16, features 32*s + 8*(l/16) .. +7; transposed: row 8*(l>>5) + (l&15)/4 (+4: chunk ^ 4), features 32*i + 16*((l>>4)&1) + 4*(l&3) .. +3
+    unsigned fr[2], ft[2], ft4[2];
+    const int i16 = lane & 15, tl = (lane >> 5) * 8 + (i16 >> 2), cl = ((lane >> 4) & 1) * 16 + (i16 & 3) * 4;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        fr[s] = base + i16 * 128 + (((4 * s + (lane >> 4)) ^ (lane & 7)) << 4);
+        const int col = 32 * s + cl, ch = col >> 3;
+        ft[s] = base + tl * 128 + ((ch ^ (tl & 7)) << 4) + (col & 7) * 2;
+        ft4[s] = base + (tl + 4) * 128 + ((ch ^ ((tl + 4) & 7)) << 4) + (col & 7) * 2;
+    }
+    const unsigned fdy = dybase + ((lane >> 5) * 16 + i16) * 16;   // lanes of samples 16 .. 31 repeat 0 .. 15, their columns are not stored
+    const unsigned voffX = i16 < N ? ((unsigned)i16 * C + (lane >> 4) * 8) * 2u : OOR;
+
+    f32x4v accy[RT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) accy[t] = f32x4v{0.f, 0.f, 0.f, 0.f};
+    bool first = true;
+    for (int u = ubeg + wave; first || u < uend; u += DF_WAVES) {
+        const bool live = u < uend;   // a wave without a unit still meets the barrier below
+        const unsigned ucol = (unsigned)u * 128u;
+        u32x4 xf[2];
+        auto issue = [&](int step, int stage) {
+            const unsigned soff = (unsigned)(step * 16) * (unsigned)C * 2u + ucol;
+            int row = o0 + (lane >> 3);
+            asm volatile("" : "+v"(row));   // computed here and not kept for all steps across the units
+#pragma unroll
+            for (int j = 0; j < 2; ++j) dma16_soff(rw, base + stage * STAGE + j * 1024, row + step * 16 + 8 * j < K ? voffW[j] : OOR, soff);
+        };
+        if (live) {
+#pragma unroll
+            for (int s = 0; s < 2; ++s) xf[s] = __builtin_amdgcn_raw_buffer_load_b128(rx, i16 < N ? voffX + ucol + s * 64 : OOR, 0, 0);
+#pragma unroll
+            for (int t = 0; t < D; ++t)
+                if (t < nst) issue(t, t);
+        }
+        if (first) {   // this wave's dy chunks have landed (they are older than the loads above), then everybody's
+            if (live && nst >= D) wait_vmcnt<2 * D>(); else wait_vmcnt<0>();
+            __builtin_amdgcn_s_barrier();
+            first = false;
+        }
+        if (!live) break;
+        f32x16 accx[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) accx[i][v] = 0.f;
+        for_constant<RT>([&](auto tc) {   // stage and fragment offsets are instruction immediates
+            constexpr int t = decltype(tc)::value, st = (t % DB_NS) * STAGE;
+            if (t < nst) {
+                constexpr int P = 2;
+                if (nst - 1 - t >= D - 1) wait_vmcnt<(D - 1) * P>();
+                else if (nst - 1 - t == D - 2) wait_vmcnt<(D - 2) * P>();
+                else if (nst - 1 - t == D - 3) wait_vmcnt<(D - 3) * P>();
+                else wait_vmcnt<0>();
+                if (t + D < nst) issue(t + D, (t + D) % DB_NS);   // the stage of step t - 1, whose reads have returned
+                u32x4 a[2], yf;
+                u32x2 lo[2], hi[2];
+#pragma unroll
+                for (int s = 0; s < 2; ++s) a[s] = lds_read16<st>(fr[s]);
+#pragma unroll
+                for (int s = 0; s < 2; ++s) { lo[s] = lds_read_tr_off<st>(ft[s]); hi[s] = lds_read_tr_off<st>(ft4[s]); }
+                yf = lds_read16<t * 512>(fdy);
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                asm volatile("" : "+v"(a[0]), "+v"(a[1]), "+v"(yf));
+                asm volatile("" : "+v"(lo[0]), "+v"(hi[0]), "+v"(lo[1]), "+v"(hi[1]));
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    accy[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[s]), __builtin_bit_cast(bf16x8, xf[s]), accy[t], 0, 0, 0);
+                    accx[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, u32x4{lo[s].x, lo[s].y, hi[s].x, hi[s].y}),
+                                                                      __builtin_bit_cast(bf16x8, yf), accx[s], 0, 0, 0);
+                }
+            }
+        });
+        // element v of lane l: feature 32*i + 8*(v/4) + 4*(l/32) + v%4 of the unit, sample l%32
+        if ((lane & 31) < N) {
+            float *dst = dxpart + ((size_t)blockIdx.x * N + (lane & 31)) * C + u * 64 + 4 * (lane >> 5);
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int gq = 0; gq < 4; ++gq)
+                    *reinterpret_cast<f32x4v *>(dst + 32 * i + 8 * gq) = f32x4v{accx[i][4 * gq], accx[i][4 * gq + 1], accx[i][4 * gq + 2], accx[i][4 * gq + 3]};
+        }
+    }
+    // y: the eight waves' sums of eight row tiles at a time; wave v adds tile v in wave order
+    f32x4v *red = reinterpret_cast<f32x4v *>(lds);   // [wave][tile][lane]
+#pragma unroll
+    for (int t0 = 0; t0 < RT; t0 += 8) {
+        __syncthreads();   // the stages (or the tiles before) have been read
+#pragma unroll
+        for (int t = 0; t < 8; ++t) red[(wave * 8 + t) * 64 + lane] = accy[t0 + t];
+        __syncthreads();
+        f32x4v s = red[wave * 64 + lane];
+#pragma unroll
+        for (int wv = 1; wv < DF_WAVES; ++wv) s += red[(wv * 8 + wave) * 64 + lane];
+        // element v of lane l: output row 4*(l/16) + v of the tile, sample l%16
+        const int o = o0 + (t0 + wave) * 16 + 4 * (lane >> 4);
+        if (i16 < N && o < K) *reinterpret_cast<f32x4v *>(ypart + ((size_t)blockIdx.y * N + i16) * K + o) = s;
+    }
+}
+
+// dx and y from the partials of k_dense_both: thread (group of four, part) adds every eighth partial, the eight parts are added in
+// order; blocks 0 .. nbx - 1 take dx, the others y
+__global__ __launch_bounds__(256) void k_dense_both_sum(int N, int C, int K, int nbx, int row_parts, int col_parts, unsigned flags_y, unsigned flags_dx,
+                                                        const float *dxpart, const float *ypart, const float *bias, const bf16_t *xin, bf16_t *y, void *dx)
+{
+    __shared__ f32x4v sm[8][32];
+    const bool is_dx = (int)blockIdx.x < nbx;
+    const int width = is_dx ? C : K, parts = is_dx ? row_parts : col_parts;
+    const float *src = is_dx ? dxpart : ypart;
+    const int q = threadIdx.x & 31, part = threadIdx.x >> 5, total = N * width;
+    const int e = ((is_dx ? blockIdx.x : blockIdx.x - nbx) * 32 + q) * 4;
+    f32x4v s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
+    if (e < total) {
+        int b = part;
+        for (; b + 8 < parts; b += 16) {
+            s0 += *reinterpret_cast<const f32x4v *>(src + (size_t)b * total + e);
+            s1 += *reinterpret_cast<const f32x4v *>(src + (size_t)(b + 8) * total + e);
+        }
+        if (b < parts) s0 += *reinterpret_cast<const f32x4v *>(src + (size_t)b * total + e);
+    }
+    sm[part][q] = s0 + s1;
+    __syncthreads();
+    if (part != 0 || e >= total) return;
+    f32x4v s = sm[0][q];
+#pragma unroll
+    for (int i = 1; i < 8; ++i) s += sm[i][q];
+    float v[4] = {s[0], s[1], s[2], s[3]};
+    if (is_dx) {
+        if (flags_dx & KF_MASK_IN) {
+            const u32x2 xm = *reinterpret_cast<const u32x2 *>(xin + e);
+            const bf16_t xv[4] = {(bf16_t)xm.x, (bf16_t)(xm.x >> 16), (bf16_t)xm.y, (bf16_t)(xm.y >> 16)};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = mask1f(v[i], xv[i]);
+        }
+        if (flags_dx & KF_OUT_F32) *reinterpret_cast<f32x4v *>(reinterpret_cast<float *>(dx) + e) = f32x4v{v[0], v[1], v[2], v[3]};
+        else *reinterpret_cast<u32x2 *>(reinterpret_cast<bf16_t *>(dx) + e) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+        return;
+    }
+    const int o = e % K;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if (flags_y & KF_BIAS) v[i] += bias[o + i];
+        if (flags_y & KF_RELU) v[i] = fmaxf(v[i], 0.f);
+    }
+    *reinterpret_cast<u32x2 *>(y + e) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+}
+
 }  // namespace
+
+// shapes the fused pass takes: at most 16 samples (one matrix tile; beyond that the partials of dx outweigh the second read of W), input
+// features in whole units, output features in whole 8s
+bool dense_both_shape(const ConvGeom &g)
+{
+    return g.R == 1 && g.S == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0 && g.H == 1 && g.W == 1 && g.N <= 16 && g.C % 64 == 0 && g.C >= 512 &&
+           g.K % 8 == 0 && (unsigned long long)g.K * g.C * 2 < (1ull << 32);
+}
+static void dense_both_split(const ConvGeom &g, int *rt, int *row_parts, int *units_per_block, int *col_parts)
+{
+    const int units = g.C / 64;
+    *rt = (long long)((g.K + 511) / 512) * units >= 2048 ? 32 : 8;   // a unit for every wave of one block per CU
+    *row_parts = (g.K + *rt * 16 - 1) / (*rt * 16);
+    int cp = std::max(1, 256 / *row_parts);
+    if (cp > (units + DF_WAVES - 1) / DF_WAVES) cp = (units + DF_WAVES - 1) / DF_WAVES;
+    *units_per_block = (units + cp - 1) / cp;
+    *col_parts = (units + *units_per_block - 1) / *units_per_block;
+}
+size_t dense_both_partial_bytes(const ConvGeom &g)
+{
+    int rt, rp, upb, cp;
+    dense_both_split(g, &rt, &rp, &upb, &cp);
+    return ((size_t)rp * g.N * g.C + (size_t)cp * g.N * g.K) * sizeof(float);
+}
+hipError_t dense_both(const ConvGeom &g, const bf16_t *x, const bf16_t *dy, const bf16_t *w, float *partial, hipStream_t st)
+{
+    int rt, rp, upb, cp;
+    dense_both_split(g, &rt, &rp, &upb, &cp);
+    float *ypart = partial + (size_t)rp * g.N * g.C;
+    const dim3 grid((unsigned)rp, (unsigned)cp), block(64 * DF_WAVES);
+    if (rt == 32) hipLaunchKernelGGL(k_dense_both<32>, grid, block, 0, st, g.N, g.C, g.K, upb, x, dy, w, ypart, partial);
+    else hipLaunchKernelGGL(k_dense_both<8>, grid, block, 0, st, g.N, g.C, g.K, upb, x, dy, w, ypart, partial);
+    return hipGetLastError();
+}
+hipError_t dense_both_sum(const ConvGeom &g, unsigned flags_y, unsigned flags_dx, const float *partial, const float *bias, const bf16_t *xin, bf16_t *y,
+                          void *dx, hipStream_t st)
+{
+    int rt, rp, upb, cp;
+    dense_both_split(g, &rt, &rp, &upb, &cp);
+    const int nbx = (g.N * g.C / 4 + 31) / 32, nby = (g.N * g.K / 4 + 31) / 32;
+    hipLaunchKernelGGL(k_dense_both_sum, dim3((unsigned)(nbx + nby)), dim3(256), 0, st, g.N, g.C, g.K, nbx, rp, cp, flags_y, flags_dx, partial,
+                       partial + (size_t)rp * g.N * g.C, bias, xin, y, dx);
+    return hipGetLastError();
+}
+const char *dense_both_name(const ConvGeom &g)
+{
+    int rt, rp, upb, cp;
+    dense_both_split(g, &rt, &rp, &upb, &cp);
+    return rt == 32 ? "k_dense_both<32>" : "k_dense_both<8>";
+}
 
 // shapes the streaming dense forward takes: a 1x1 layer over at most 16 pixel rows (beyond that the activation operand, which
 // every block re-reads, outweighs the weights), input features in whole 64-feature steps

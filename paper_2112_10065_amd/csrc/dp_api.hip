@@ -869,7 +869,8 @@ size_t dp_conv2d_workspace_bytes(const dp_conv_desc *desc, int pass)
     return dgrad_ws_bytes(g, dgrad_restr(desc->flags));
 }
 
-size_t dp_linear_workspace_bytes(const dp_linear_desc *desc)
+// what the three passes one after the other need
+static size_t linear_passes_ws_bytes(const dp_linear_desc *desc)
 {
     ConvGeom g;
     if (check_linear(desc, &g) != DP_OK) return 0;
@@ -881,6 +882,14 @@ size_t dp_linear_workspace_bytes(const dp_linear_desc *desc)
         }
     }
     return need;
+}
+
+size_t dp_linear_workspace_bytes(const dp_linear_desc *desc)
+{
+    ConvGeom g;
+    if (check_linear(desc, &g) != DP_OK) return 0;
+    const size_t need = linear_passes_ws_bytes(desc);
+    return desc->io_dtype == DP_BF16 && dense_both_shape(g) ? std::max(need, dense_both_partial_bytes(g)) : need;
 }
 
 dp_status dp_conv2d_fwd(const dp_conv_desc *desc, const void *x, const void *w, const float *bias, void *y, void *ws,
@@ -989,10 +998,32 @@ dp_status dp_linear_fwd_bwd(const dp_linear_desc *desc, const void *x, const voi
     if ((s = check_opt(y_saved, "y_saved")) != DP_OK || (s = check_opt(y, "y")) != DP_OK || (s = check_opt(dx, "dx")) != DP_OK ||
         (s = check_opt(dW, "dW")) != DP_OK || (s = check_opt(dbias, "dbias")) != DP_OK || (s = check_opt(ws, "ws")) != DP_OK)
         return s;
-    size_t need = dp_linear_workspace_bytes(desc);
+    size_t need = linear_passes_ws_bytes(desc);
     if (need > 0 && (ws == nullptr || ws_bytes < need)) return fail(DP_ERR_WORKSPACE, "dense layer needs %zu workspace bytes, got %zu", need, ws_bytes);
     if ((s = ensure_init()) != DP_OK) return s;
     hipStream_t st = (hipStream_t)hip_stream;
+    // forward and backward-data asked for together read W once (a workspace of the passes' size only, a saved output that masks dy, a
+    // forced variant or outputs in the place of inputs: one after the other)
+    if (y != nullptr && dx != nullptr && y_saved == nullptr && desc->io_dtype == DP_BF16 && dense_both_shape(g) && g_force_variant[PASS_FWD].load() < 0 &&
+        g_force_variant[PASS_DGRAD].load() < 0 && ws != nullptr && ws_bytes >= dense_both_partial_bytes(g) && y != x && y != dy && y != W && dx != x &&
+        dx != dy && dx != W && y != dx) {
+        hipError_t e;
+        {
+            TraceScope ts(PASS_FWD, st);
+            ts.name(dense_both_name(g), 1);
+            e = dense_both(g, (const bf16_t *)x, (const bf16_t *)dy, (const bf16_t *)W, (float *)ws, st);
+            dp_trace_main_kernel_done(st);
+        }
+        if (e == hipSuccess) {
+            TraceScope ts(PASS_DGRAD, st);
+            ts.name("k_dense_both_sum", 1);
+            e = dense_both_sum(g, kflags(desc->flags, true), ((desc->flags & DP_DX_F32) ? KF_OUT_F32 : 0u) | ((desc->flags & DP_RELU_IN) ? KF_MASK_IN : 0u),
+                               (const float *)ws, bias, (const bf16_t *)x, (bf16_t *)y, dx, st);
+            dp_trace_main_kernel_done(st);
+        }
+        if (e != hipSuccess) return hip_fail(e, "dense forward / backward-data launch");
+        y = dx = nullptr;
+    }
     // the passes run back to back on one stream and reuse the same workspace
     if (y != nullptr && (s = run_fwd(g, desc->io_dtype, desc->flags, x, W, bias, y, ws, ws_bytes, st)) != DP_OK) return s;
     if (dx != nullptr && (s = run_dgrad(g, desc->io_dtype, desc->flags, dy, y_saved, W, x, dx, ws, ws_bytes, st)) != DP_OK) return s;

@@ -862,6 +862,38 @@ def test_linear_parity(env, n, i, o, bf16):
 
 
 # ---- ReLU / bias gradient -----------------------------------------------------------------
+# forward and backward-data in one call read the weights once: 64-feature units (one, fewer than the waves, several per wave), row ranges of
+# 128 and 512 outputs with ragged ends, one sample to a full tile; 17 samples, a saved output or the passes' workspace: one after the other
+@pytest.mark.parametrize("n,i,o", [(1, 512, 8), (2, 576, 128), (16, 1024, 136), (3, 4160, 1000), (5, 16448, 4008), (16, 33088, 2056), (17, 1024, 136)])
+@pytest.mark.parametrize("dx_f32", [False, True])
+def test_dense_forward_and_backward_data_in_one_call(env, n, i, o, dx_f32):
+    dp, U, orc = env
+    from paper_2112_10065_amd import synth
+    x, w, b = synth.linear_tensors("both", n, i, o)
+    xb, wb, dyb = (synth.f32_to_bf16_bits(a) for a in (x, w, synth.upstream_grad("both", (n, o))))
+    x, w, dy = (synth.bf16_bits_to_f32(a) for a in (xb, wb, dyb))
+    xd, wd, dyd, bd = U.bf16_dev(xb), U.bf16_dev(wb), U.bf16_dev(dyb), torch.from_numpy(b).to(U.DEV)
+    desc = dp.linear_desc(n, i, o, dp.DP_BF16, dp.DP_BIAS | dp.DP_RELU | dp.DP_RELU_IN | (dp.DP_DX_F32 if dx_f32 else 0))
+    ref_y = np.maximum(x.astype(np.float64) @ w.T.astype(np.float64) + b, 0)
+    ref_dx = orc.relu_in_backward(dy.astype(np.float64) @ w.astype(np.float64), x)
+    ws = U.workspace(dp.dp_linear_workspace_bytes(desc))
+    for again in range(2):
+        y = torch.full((n, o), 5.0, dtype=torch.bfloat16, device=U.DEV)
+        dx = torch.full((n, i), 5.0, dtype=torch.float32 if dx_f32 else torch.bfloat16, device=U.DEV)
+        dw, db = torch.full((o, i), 5.0, device=U.DEV), torch.full((o,), 5.0, device=U.DEV)
+        dp.dp_trace_begin()
+        dp.dp_linear_fwd_bwd(desc, x=xd, W=wd, bias=bd, dy=dyd, y=y, dx=dx, dW=dw, dbias=db, ws=ws)
+        names = [r["kernel"] for r in dp.dp_trace_end()]
+        assert ("k_dense_both_sum" in names) == (n <= 16) and len(names) == 3
+        U.assert_bf16_close(U.to_np(y), ref_y, "y")
+        U.assert_bf16_close(U.to_np(dx), ref_dx, "dx")
+        U.assert_bf16_close(U.to_np(dw), dy.T @ x, "dw")
+        U.assert_bf16_close(U.to_np(db), dy.sum(0), "db")
+        if again:
+            assert torch.equal(y, y0) and torch.equal(dx, dx0)
+        y0, dx0 = y, dx
+
+
 @pytest.mark.parametrize("rows,k,bf16", [(1000, 64, True), (777, 512, True), (50, 4096, True), (33, 1000, True),
                                          (300, 24, True), (65, 12, True), (130, 16, False)])
 def test_relu_bias_grad(env, rows, k, bf16):
