@@ -23,17 +23,37 @@
 
 namespace {
 
+// a row-map entry: the pixel (below 2^28: a tensor has fewer than 2^31 elements and whole 8s of channels), and with p.ph_on == 2
+// whether the pixels to the right and below belong to it
+constexpr int kRowPixel = 0x0fffffff, kRowRight = 1 << 28, kRowBelow = 1 << 29;
+
 template <int FA, int FB, int TA, int TB, int NT>
 DEVFN void store_staged(const KArgs &p, const f32x16 (&acc)[FA][FB], bf16_t *stage, const float *bias_lds, int a0, int b0,
                         int arow, int brow, int tid, bool writer = true, const int *rowpix = nullptr, bool all_zero = false)
 {
     // all_zero: the tile's sums are known to be zero (no tap reaches it), so the input-ReLU mask need not be read
     // rowpix (LDS, backward-data): output row of each tile row, -1 for none; else tile row i is output row b0 + i
-    auto out_row = [&](int pix) { const int gp = rowpix != nullptr ? rowpix[pix] : b0 + pix; return (rowpix != nullptr || gp < p.rowsB) ? gp : -1; };
+    auto out_row = [&](int pix) {
+        const int gp = rowpix != nullptr ? rowpix[pix] : b0 + pix;
+        return rowpix != nullptr ? (gp < 0 ? -1 : gp & kRowPixel) : gp < p.rowsB ? gp : -1;
+    };
     // `writer`: this wave holds finished sums (false for the extra reduction groups of a block, which only
     // help with the copy-out below)
     constexpr int LSO = TA + 8;
     const int lane = tid & 63;
+    if (rowpix != nullptr && p.ph_on == 2) {   // the neighbours that no tap reaches are zero: stored first, they wait for nothing
+        bf16_t *zero_out = reinterpret_cast<bf16_t *>(p.out) + a0;
+        const size_t W = p.g.W, rowsA = p.rowsA;
+        for (int id = tid; id < TB * (TA / 8); id += NT) {
+            const int pix = id / (TA / 8), cc = (id % (TA / 8)) * 8, rp = rowpix[pix];
+            if (rp < 0 || a0 + cc >= p.rowsA) continue;
+            bf16_t *dst = zero_out + (size_t)(rp & kRowPixel) * rowsA + cc;
+            const u32x4 z = {0, 0, 0, 0};
+            if (rp & kRowRight) *reinterpret_cast<u32x4 *>(dst + rowsA) = z;
+            if (rp & kRowBelow) *reinterpret_cast<u32x4 *>(dst + W * rowsA) = z;
+            if ((rp & kRowRight) && (rp & kRowBelow)) *reinterpret_cast<u32x4 *>(dst + (W + 1) * rowsA) = z;
+        }
+    }
     if (writer)
 #pragma unroll
     for (int i = 0; i < FA; ++i)
@@ -1082,7 +1102,9 @@ DEVFN void dgrad_dma_body(const KArgs &p)
             }
         }
         rowtab[2 * tid + 1] = mask;
-        rowpix[tid] = valid ? (n * g.H + hh) * g.W + ww : -1;
+        int entry = valid ? (n * g.H + hh) * g.W + ww : -1;
+        if (p.ph_on == 2 && valid) entry |= (g.sw == 2 && ww + 1 < g.W ? kRowRight : 0) | (g.sh == 2 && hh + 1 < g.H ? kRowBelow : 0);
+        rowpix[tid] = entry;
     }
     __syncthreads();
 
@@ -1519,18 +1541,21 @@ bool dma_plan(const ConvGeom &g, int pass, int force_variant, int force_splits, 
     } else return false;
     pl->fast = true; pl->dma = true; pl->TA = d->TA; pl->TB = d->TB; pl->BK = d->BK;
     pl->vecA = pl->vecB = true;
-    pl->phase = false;
+    pl->phase = pl->fill = false;
     pl->tilesA = (rowsA + d->TA - 1) / d->TA;
     pl->tilesB = (rowsB + d->TB - 1) / d->TB;
     pl->steps_total = (red + d->BK - 1) / d->BK;
-    if (pass == PASS_DGRAD && (g.sh > 1 || g.sw > 1) && g.sh <= 2 && g.sw <= 2 && g.R * g.S > 1 && force_splits <= 1) {
-        // no reduction split asked for: walk the pixels phase by phase and multiply only the taps that can hit
-        // (a 1x1 filter gains nothing: its backward-data is bound by writing dx, three quarters of it zeros)
+    if (pass == PASS_DGRAD && (g.sh > 1 || g.sw > 1) && g.sh <= 2 && g.sw <= 2 && force_splits <= 1) {
+        // no reduction split asked for: walk the pixels phase by phase and multiply only the taps that can hit.  A 1x1 filter
+        // without padding reaches the first phase only: its tiles alone run, and store the zeros of the other phases next to their own
+        // pixels (64 x 56 x 56 x 256 <- 512, stride 2, masked: all pixels multiplied 104 us, every phase with tiles of its own 88, this
+        // 37)
         int tile0[5], max_steps;
         phase_layout(g, d->TB, d->BK, tile0, &max_steps);
         if (max_steps > 0 && tile0[4] > 0) {
             pl->phase = true;
-            pl->tilesB = tile0[4];
+            pl->fill = g.R * g.S == 1 && g.ph == 0 && g.pw == 0;
+            pl->tilesB = pl->fill ? tile0[1] : tile0[4];
             pl->steps_total = pl->steps_per_split = max_steps;
             pl->splits = 1;
             return true;
@@ -1556,6 +1581,11 @@ bool dma_plan(const ConvGeom &g, int pass, int force_variant, int force_splits, 
     if (splits < 1) splits = 1;
     pl->steps_per_split = (pl->steps_total + splits - 1) / splits;
     pl->splits = (pl->steps_total + pl->steps_per_split - 1) / pl->steps_per_split;
+    // backward-filter: a split count that the rounding of the steps took off a multiple of the 8 XCDs goes back up to it (the last
+    // splits are empty and add zeros): otherwise neighbouring splits of the tiles drift over the dies and each pixel range is read into
+    // several L2s (64 x 56 x 56 x 256 -> 512, 1x1 / 2: 47 splits 47.6 us,
+    // 48 splits 30.7; 64 x 28 x 28 x 128 -> 512: 61 splits 30, 64 splits 21)
+    if (pass == PASS_WGRAD && splits % 8 == 0 && pl->splits < splits) pl->splits = (pl->splits + 7) / 8 * 8;
     return true;
 }
 
@@ -1600,7 +1630,7 @@ hipError_t dma_launch(const ConvArgs &a, hipStream_t st)
         if (!(a.flags & KF_OUT_F32) && (p.rowsA & 7) == 0) {   // the staged bf16 epilogue carries the row map
             int max_steps;
             phase_layout(a.g, a.plan.TB, a.plan.BK, p.ph_tile0, &max_steps);
-            p.ph_on = 1;
+            p.ph_on = a.plan.fill ? 2 : 1;
         } else {   // fp32 gradients: the same tiles in natural pixel order, all taps (masked)
             p.tilesB = (p.rowsB + a.plan.TB - 1) / a.plan.TB;
             p.steps_total = p.steps_per_split = (p.red + a.plan.BK - 1) / a.plan.BK;

@@ -41,6 +41,7 @@ struct GemmPlan {
     bool halo = false;    // input-patch kernel (conv_halo.hip); implies dma
     int blocks = 0;       // persistent kernels: blocks per row tile (0: one per CU)
     bool phase = false;   // strided backward-data walks the input pixels stride phase by stride phase (conv_dma.hip)
+    bool fill = false;    // phase, 1x1 filter: only the first phase has tiles, they store the zeros of the others
     bool wstrip = false;  // filter gradient with the x strip shared by the taps of a filter row (conv_wstrip.hip); implies dma
     bool db_wave = false; // input-patch filter gradient: one more wave per block can sum the bias gradient (at most 15 taps)
     bool fused_reduce = false;   // pipelined forward / backward-data with splits > 1: no second kernel, the last block of a tile reduces (conv_dma.hip)

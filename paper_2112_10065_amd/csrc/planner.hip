@@ -35,7 +35,7 @@ const Candidate kPix[] = {
     {205, 4, 0.85f, 4.0f},
     {213, 3, 1.30f, 4.5f},
     {210, 1, 1.15f, 6.0f},   // 128x256x64, 8 waves
-    {212, 2, 1.30f, 4.5f},   // 64x256x64
+    {212, 2, 1.30f, 8.0f},   // 64x256x64 (memory-bound 1x1 layers: 48 us forward, 89 masked backward-data where 64x128 takes 35 and 52)
     {221, 1, 0.70f, 4.0f},   // reduction step 128 (channels % 128 only): fewer, longer steps for small grids
     {225, 1, 0.70f, 4.0f},
     {222, 1, 1.10f, 4.5f},
@@ -92,7 +92,7 @@ bool family_plan(const ConvGeom &g, int pass, int code, int splits, GemmPlan *pl
     return fast_plan(g, pass, code, splits, pl);
 }
 
-double price(const ConvGeom &g, int pass, const Candidate &c, const GemmPlan &pl)
+double price(const ConvGeom &g, int pass, const Candidate &c, const GemmPlan &pl, int restr)
 {
     const double blocks = (double)pl.tilesA * pl.tilesB * pl.splits;
     const double conc = 256.0 * c.bpc;
@@ -108,7 +108,10 @@ double price(const ConvGeom &g, int pass, const Candidate &c, const GemmPlan &pl
     // a step of reduction length 32 costs about half of a 64 step for the pixel passes
     double t_step = c.t_step;
     if (pass != PASS_WGRAD && pl.BK == 32) t_step *= 0.6;
-    const double t_block = c.t0 + (pl.steps_per_split + c.kg - 1) / c.kg * t_step * share;
+    // the saved input of a masked tile, read while nothing else runs on the CU (the strip kernels fetch it ahead): 128 KB at a CU's
+    // share of the memory rate (64 x 56 x 56 x 256 <- 128, 1x1: 256 x 256 tiles 59 us, 64 x 128 tiles 52)
+    const bool lone_mask = pass == PASS_DGRAD && (restr & 2) && c.bpc == 1 && pl.splits == 1 && c.code >= 200 && c.code < 230;
+    const double t_block = c.t0 + (lone_mask ? 3.5 * pl.TA * pl.TB / 65536.0 : 0.0) + (pl.steps_per_split + c.kg - 1) / c.kg * t_step * share;
     double t = 3.0 + waves * t_block;
     if (pl.splits > 1) {
         double out_elems = pass == PASS_FWD ? (double)g.N * g.Ho * g.Wo * g.K
@@ -172,7 +175,7 @@ int auto_plan_list(const ConvGeom &g, int pass, int force_splits, GemmPlan *out,
             if (!(restr & 4) && cands[ci].code >= 230 && cands[ci].code <= 233 && (long long)cand.tilesA * cand.tilesB * cand.splits < 160) continue;
             last_splits = cand.splits;
             if (force_splits <= 0 && cand.splits > 1 && cand.steps_per_split < 4) break;
-            if (n < 512) { all[n].t = price(g, pass, cands[ci], cand); all[n].pl = cand; all[n].code = cands[ci].code; ++n; }
+            if (n < 512) { all[n].t = price(g, pass, cands[ci], cand, restr); all[n].pl = cand; all[n].code = cands[ci].code; ++n; }
         }
     }
     // selection sort of the few that are wanted; per tile variant only its two cheapest splits
