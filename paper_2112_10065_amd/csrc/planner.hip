@@ -47,10 +47,10 @@ const Candidate kPix[] = {
     {229, 1, 0.85f, 5.0f, 2},
     {234, 3, 0.65f, 4.0f},   // channels that 64 does not divide, reduction walked flat over (tap, channel): 64x64x64
     {235, 1, 0.65f, 5.0f, 4},   // the same with 4 / 2 reduction groups per block
-    {236, 2, 0.65f, 4.5f, 2},
+    {236, 2, 0.80f, 4.5f, 2},
     {237, 3, 0.88f, 4.5f},   // 64x128x64
     {238, 3, 0.88f, 4.5f},   // 128x64x64
-    {239, 2, 1.12f, 5.0f},   // 128x128x64
+    {239, 2, 0.88f, 5.0f},   // 128x128x64
     {400, 2, 0.75f, 5.5f},   // input patch resident in LDS: 64 x 256 tile (64 reduction channels per tap, stride 1)
     {401, 2, 1.20f, 6.0f},   // same, 128 x 256
     {402, 2, 0.75f, 5.5f},
@@ -147,6 +147,7 @@ int auto_plan_list(const ConvGeom &g, int pass, int force_splits, GemmPlan *out,
             }
         }
     }
+    const bool flat = g.R * g.S <= 31 && g.C % 8 == 0 && (pass == PASS_FWD || (g.K % 8 == 0 && ((g.sh == 1 && g.sw == 1) || (!(restr & 1) && force_splits <= 1 && g.sh <= 2 && g.sw <= 2))));
     const Candidate *cands = pass == PASS_WGRAD ? kWg : kPix;
     const int ncand = pass == PASS_WGRAD ? (int)(sizeof(kWg) / sizeof(kWg[0])) : (int)(sizeof(kPix) / sizeof(kPix[0]));
     for (int ci = 0; ci < ncand; ++ci) {
@@ -166,8 +167,9 @@ int auto_plan_list(const ConvGeom &g, int pass, int force_splits, GemmPlan *out,
             if (pass == PASS_WGRAD && force_splits <= 0 && s > 8 && (s % 8) != 0) continue;
             GemmPlan cand;
             if (!family_plan(g, pass, cands[ci].code, force_splits > 0 ? force_splits : s, &cand)) break;
-            // reduction step 32 only where 64 does not divide the channel count
-            if (pass != PASS_WGRAD && cand.BK == 32 && ((pass == PASS_FWD ? g.C : g.K) % 64) == 0) break;
+            // reduction step 32 only where neither whole 64-wide steps nor the flat walk apply (flat against 32-wide: 43 -> 33.5 us for
+            // 16 x 28 x 28 x 288 -> 448, 7x1; 81 -> 63 us for 16 x 60 x 60 x 224 -> 160, 3x3)
+            if (pass != PASS_WGRAD && cand.BK == 32 && (((pass == PASS_FWD ? g.C : g.K) % 64) == 0 || flat)) break;
             if (cand.splits == last_splits) continue;   // the request was clamped to the same plan
             // pixel-strip kernels on a grid of few blocks: each block streams its weights alone, which times well on a warm
             // cache (the measured choice) and badly inside a step
