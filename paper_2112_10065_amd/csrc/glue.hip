@@ -26,11 +26,20 @@ __global__ __launch_bounds__(256) void k_pool(int n, int h, int w, int c, const 
     const long long total = (long long)n * hg * wg * cv;
     const long long id = (long long)blockIdx.x * 256 + threadIdx.x;
     if (id >= total) return;
-    const int ci = (int)(id % cv) * V;
-    long long r = id / cv;
-    const int q = (int)(r % wg);
-    r /= wg;
-    const int p = (int)(r % hg), ni = (int)(r / hg);
+    // 32-bit divisions where they do: the three 64-bit ones took more instructions than the rest of the thread and bound the kernel
+    // (8 x 224 x 224 x 64: forward 19 -> 10.6 us,
+    // backward 23 -> 18.8 us, warm)
+    int ci, q, p, ni;
+    if (total < (1ll << 32)) {
+        const unsigned i = (unsigned)id, r = i / (unsigned)cv, r2 = r / (unsigned)wg;
+        ci = (int)(i - r * cv) * V; q = (int)(r - r2 * wg); ni = (int)(r2 / (unsigned)hg); p = (int)r2 - ni * hg;
+    } else {
+        long long r = id / cv;
+        ci = (int)(id % cv) * V;
+        q = (int)(r % wg);
+        r /= wg;
+        p = (int)(r % hg); ni = (int)(r / hg);
+    }
     const size_t row0 = ((size_t)ni * h + 2 * p) * w + 2 * q;   // pixel index of window position (0, 0)
     if (BWD && (p >= ho || q >= wo)) {                           // partial window: no gradient reaches it
         P z;
