@@ -380,7 +380,7 @@ __global__ __launch_bounds__(64 * DF_WAVES) void k_dense_wgrad(int N, int C, int
 // the chip a unit that way take RT = 8.
 // ---------------------------------------------------------------------------------------
 constexpr int DB_NS = 6;
-template <int RT>
+template <int RT, bool Y>   // Y: also the forward product
 __global__ __launch_bounds__(64 * DF_WAVES) void k_dense_both(int N, int C, int K, int units_per_block, const bf16_t *x, const bf16_t *dy, const bf16_t *w,
                                                               float *ypart, float *dxpart)
 {
@@ -424,9 +424,9 @@ __global__ __launch_bounds__(64 * DF_WAVES) void k_dense_both(int N, int C, int 
     const unsigned fdy = dybase + ((lane >> 5) * 16 + i16) * 16;   // lanes of samples 16 .. 31 repeat 0 .. 15, their columns are not stored
     const unsigned voffX = i16 < N ? ((unsigned)i16 * C + (lane >> 4) * 8) * 2u : OOR;
 
-    f32x4v accy[RT];
+    f32x4v accy[Y ? RT : 1];
 #pragma unroll
-    for (int t = 0; t < RT; ++t) accy[t] = f32x4v{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < (Y ? RT : 1); ++t) accy[t] = f32x4v{0.f, 0.f, 0.f, 0.f};
     bool first = true;
     for (int u = ubeg + wave; first || u < uend; u += DF_WAVES) {
         const bool live = u < uend;   // a wave without a unit still meets the barrier below
@@ -441,7 +441,7 @@ __global__ __launch_bounds__(64 * DF_WAVES) void k_dense_both(int N, int C, int 
         };
         if (live) {
 #pragma unroll
-            for (int s = 0; s < 2; ++s) xf[s] = __builtin_amdgcn_raw_buffer_load_b128(rx, i16 < N ? voffX + ucol + s * 64 : OOR, 0, 0);
+            for (int s = 0; s < 2; ++s) if (Y) xf[s] = __builtin_amdgcn_raw_buffer_load_b128(rx, i16 < N ? voffX + ucol + s * 64 : OOR, 0, 0);
 #pragma unroll
             for (int t = 0; t < D; ++t)
                 if (t < nst) issue(t, t);
@@ -469,16 +469,16 @@ __global__ __launch_bounds__(64 * DF_WAVES) void k_dense_both(int N, int C, int 
                 u32x4 a[2], yf;
                 u32x2 lo[2], hi[2];
 #pragma unroll
-                for (int s = 0; s < 2; ++s) a[s] = lds_read16<st>(fr[s]);
+                for (int s = 0; s < 2; ++s) if (Y) a[s] = lds_read16<st>(fr[s]);
 #pragma unroll
                 for (int s = 0; s < 2; ++s) { lo[s] = lds_read_tr_off<st>(ft[s]); hi[s] = lds_read_tr_off<st>(ft4[s]); }
                 yf = lds_read16<t * 512>(fdy);
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                asm volatile("" : "+v"(a[0]), "+v"(a[1]), "+v"(yf));
-                asm volatile("" : "+v"(lo[0]), "+v"(hi[0]), "+v"(lo[1]), "+v"(hi[1]));
+                if constexpr (Y) asm volatile("" : "+v"(a[0]), "+v"(a[1]));
+                asm volatile("" : "+v"(yf), "+v"(lo[0]), "+v"(hi[0]), "+v"(lo[1]), "+v"(hi[1]));
 #pragma unroll
                 for (int s = 0; s < 2; ++s) {
-                    accy[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[s]), __builtin_bit_cast(bf16x8, xf[s]), accy[t], 0, 0, 0);
+                    if constexpr (Y) accy[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[s]), __builtin_bit_cast(bf16x8, xf[s]), accy[t], 0, 0, 0);
                     accx[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, u32x4{lo[s].x, lo[s].y, hi[s].x, hi[s].y}),
                                                                       __builtin_bit_cast(bf16x8, yf), accx[s], 0, 0, 0);
                 }
@@ -494,13 +494,14 @@ __global__ __launch_bounds__(64 * DF_WAVES) void k_dense_both(int N, int C, int 
                     *reinterpret_cast<f32x4v *>(dst + 32 * i + 8 * gq) = f32x4v{accx[i][4 * gq], accx[i][4 * gq + 1], accx[i][4 * gq + 2], accx[i][4 * gq + 3]};
         }
     }
+    if constexpr (!Y) return;
     // y: the eight waves' sums of eight row tiles at a time; wave v adds tile v in wave order
     f32x4v *red = reinterpret_cast<f32x4v *>(lds);   // [wave][tile][lane]
 #pragma unroll
     for (int t0 = 0; t0 < RT; t0 += 8) {
         __syncthreads();   // the stages (or the tiles before) have been read
 #pragma unroll
-        for (int t = 0; t < 8; ++t) red[(wave * 8 + t) * 64 + lane] = accy[t0 + t];
+        for (int t = 0; t < 8; ++t) red[(wave * 8 + t) * 64 + lane] = accy[Y ? t0 + t : 0];
         __syncthreads();
         f32x4v s = red[wave * 64 + lane];
 #pragma unroll
@@ -567,6 +568,13 @@ bool dense_both_shape(const ConvGeom &g)
     return g.R == 1 && g.S == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0 && g.H == 1 && g.W == 1 && g.N <= 16 && g.C % 64 == 0 && g.C >= 512 &&
            g.K % 8 == 0 && (unsigned long long)g.K * g.C * 2 < (1ull << 32);
 }
+// Backward-data alone: against the pipelined tiles and their split reduction it pays where the weights are many and the partials of dx few.
+// Measured new / old: 25088 x 4096 2 samples 35.0 / 37.7 us, 16 samples 44.2 / 40.6; 4096 x 4096 2 samples 7.9 / 13.7, 8 samples 9.8 / 14.0;
+// 12800 x 2048 2 samples 11.3 / 14.0, 16 samples 20.4 / 14.6; 8192 x 512 7.0 / 6.8; 1024 x 1024 7.3 / 6.9
+bool dense_dgrad_split_shape(const ConvGeom &g)
+{
+    return dense_both_shape(g) && g.K % 64 == 0 && g.N <= 8 && g.K >= 1024 && (long long)g.K * g.C >= (4 << 20);
+}
 static void dense_both_split(const ConvGeom &g, int *rt, int *row_parts, int *units_per_block, int *col_parts)
 {
     const int units = g.C / 64;
@@ -583,14 +591,14 @@ size_t dense_both_partial_bytes(const ConvGeom &g)
     dense_both_split(g, &rt, &rp, &upb, &cp);
     return ((size_t)rp * g.N * g.C + (size_t)cp * g.N * g.K) * sizeof(float);
 }
-hipError_t dense_both(const ConvGeom &g, const bf16_t *x, const bf16_t *dy, const bf16_t *w, float *partial, hipStream_t st)
+hipError_t dense_both(const ConvGeom &g, const bf16_t *x, const bf16_t *dy, const bf16_t *w, float *partial, bool with_y, hipStream_t st)
 {
     int rt, rp, upb, cp;
     dense_both_split(g, &rt, &rp, &upb, &cp);
     float *ypart = partial + (size_t)rp * g.N * g.C;
     const dim3 grid((unsigned)rp, (unsigned)cp), block(64 * DF_WAVES);
-    if (rt == 32) hipLaunchKernelGGL(k_dense_both<32>, grid, block, 0, st, g.N, g.C, g.K, upb, x, dy, w, ypart, partial);
-    else hipLaunchKernelGGL(k_dense_both<8>, grid, block, 0, st, g.N, g.C, g.K, upb, x, dy, w, ypart, partial);
+    auto *kernel = rt == 32 ? (with_y ? k_dense_both<32, true> : k_dense_both<32, false>) : (with_y ? k_dense_both<8, true> : k_dense_both<8, false>);
+    hipLaunchKernelGGL(kernel, grid, block, 0, st, g.N, g.C, g.K, upb, x, dy, w, ypart, partial);
     return hipGetLastError();
 }
 hipError_t dense_both_sum(const ConvGeom &g, unsigned flags_y, unsigned flags_dx, const float *partial, const float *bias, const bf16_t *xin, bf16_t *y,
@@ -598,16 +606,16 @@ hipError_t dense_both_sum(const ConvGeom &g, unsigned flags_y, unsigned flags_dx
 {
     int rt, rp, upb, cp;
     dense_both_split(g, &rt, &rp, &upb, &cp);
-    const int nbx = (g.N * g.C / 4 + 31) / 32, nby = (g.N * g.K / 4 + 31) / 32;
+    const int nbx = (g.N * g.C / 4 + 31) / 32, nby = y != nullptr ? (g.N * g.K / 4 + 31) / 32 : 0;
     hipLaunchKernelGGL(k_dense_both_sum, dim3((unsigned)(nbx + nby)), dim3(256), 0, st, g.N, g.C, g.K, nbx, rp, cp, flags_y, flags_dx, partial,
                        partial + (size_t)rp * g.N * g.C, bias, xin, y, dx);
     return hipGetLastError();
 }
-const char *dense_both_name(const ConvGeom &g)
+const char *dense_both_name(const ConvGeom &g, bool with_y)
 {
     int rt, rp, upb, cp;
     dense_both_split(g, &rt, &rp, &upb, &cp);
-    return rt == 32 ? "k_dense_both<32>" : "k_dense_both<8>";
+    return rt == 32 ? (with_y ? "k_dense_both<32, true>" : "k_dense_both<32, false>") : (with_y ? "k_dense_both<8, true>" : "k_dense_both<8, false>");
 }
 
 // shapes the streaming dense forward takes: a 1x1 layer over at most 16 pixel rows (beyond that the activation operand, which

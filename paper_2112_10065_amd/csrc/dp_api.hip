@@ -556,6 +556,16 @@ dp_status run_dgrad(const ConvGeom &g, int dtype, unsigned flags, const void *dy
         dp_trace_main_kernel_done(st);
         return e == hipSuccess ? DP_OK : hip_fail(e, "backward-data launch");
     }
+    if (g_force_variant[PASS_DGRAD].load() < 0 && ym == nullptr && dense_dgrad_split_shape(g) && ws != nullptr && ws_bytes >= dense_both_partial_bytes(g)) {
+        ts.name(dense_both_name(g, false), 1);
+        ts.main_begins();
+        hipError_t e = dense_both(g, nullptr, (const bf16_t *)dy, (const bf16_t *)w, (float *)ws, false, st);
+        dp_trace_main_kernel_done(st);
+        if (e == hipSuccess)
+            e = dense_both_sum(g, 0, ((flags & DP_DX_F32) ? KF_OUT_F32 : 0u) | (xin != nullptr ? KF_MASK_IN : 0u), (const float *)ws, nullptr,
+                               (const bf16_t *)xin, nullptr, dx, st);
+        return e == hipSuccess ? DP_OK : hip_fail(e, "backward-data launch");
+    }
     ConvArgs a{};
     a.g = g; a.pass = PASS_DGRAD; a.flags = ((flags & DP_DX_F32) ? KF_OUT_F32 : 0u) | (xin != nullptr ? KF_MASK_IN : 0u);
     a.x = (const bf16_t *)xin;
@@ -1010,8 +1020,8 @@ dp_status dp_linear_fwd_bwd(const dp_linear_desc *desc, const void *x, const voi
         hipError_t e;
         {
             TraceScope ts(PASS_FWD, st);
-            ts.name(dense_both_name(g), 1);
-            e = dense_both(g, (const bf16_t *)x, (const bf16_t *)dy, (const bf16_t *)W, (float *)ws, st);
+            ts.name(dense_both_name(g, true), 1);
+            e = dense_both(g, (const bf16_t *)x, (const bf16_t *)dy, (const bf16_t *)W, (float *)ws, true, st);
             dp_trace_main_kernel_done(st);
         }
         if (e == hipSuccess) {

@@ -148,11 +148,13 @@ const char *dense_wgrad_stream_name(const ConvGeom &g);
 hipError_t dense_wgrad_stream(const ConvGeom &g, const bf16_t *x, const bf16_t *dy, float *dw, float *db, hipStream_t st);
 bool dense_dgrad_stream_shape(const ConvGeom &g);
 hipError_t dense_dgrad_stream(const ConvGeom &g, unsigned flags, const bf16_t *dy, const bf16_t *w, const bf16_t *xin, void *dx, hipStream_t st);
-// forward and backward-data in one pass over the weights; the second call adds the partials and applies the epilogues
+// forward and backward-data in one pass over the weights (with_y false: backward-data alone, then y is NULL in the second call); the
+// second call adds the partials and applies the epilogues
 bool dense_both_shape(const ConvGeom &g);
+bool dense_dgrad_split_shape(const ConvGeom &g);   // backward-data alone takes it
 size_t dense_both_partial_bytes(const ConvGeom &g);
-const char *dense_both_name(const ConvGeom &g);
-hipError_t dense_both(const ConvGeom &g, const bf16_t *x, const bf16_t *dy, const bf16_t *w, float *partial, hipStream_t st);
+const char *dense_both_name(const ConvGeom &g, bool with_y);
+hipError_t dense_both(const ConvGeom &g, const bf16_t *x, const bf16_t *dy, const bf16_t *w, float *partial, bool with_y, hipStream_t st);
 hipError_t dense_both_sum(const ConvGeom &g, unsigned flags_y, unsigned flags_dx, const float *partial, const float *bias, const bf16_t *xin, bf16_t *y,
                           void *dx, hipStream_t st);
 bool small_c_direct(const ConvGeom &g);

@@ -894,6 +894,23 @@ def test_dense_forward_and_backward_data_in_one_call(env, n, i, o, dx_f32):
         y0, dx0 = y, dx
 
 
+# backward-data alone through the same walk: many weights, few samples (row ranges of 128 and 512 outputs)
+@pytest.mark.parametrize("n,i,o,name", [(8, 4160, 1024, "k_dense_both<8, false>"), (3, 16448, 4032, "k_dense_both<32, false>"), (1, 2048, 2048, "k_dense_both<8, false>")])
+@pytest.mark.parametrize("dx_f32", [False, True])
+def test_dense_backward_data_by_row_ranges(env, n, i, o, name, dx_f32):
+    dp, U, orc = env
+    from paper_2112_10065_amd import synth
+    x, w, _ = synth.linear_tensors("rows", n, i, o)
+    xb, wb, dyb = (synth.f32_to_bf16_bits(a) for a in (x, w, synth.upstream_grad("rows", (n, o))))
+    x, w, dy = (synth.bf16_bits_to_f32(a) for a in (xb, wb, dyb))
+    desc = dp.linear_desc(n, i, o, dp.DP_BF16, dp.DP_RELU_IN | (dp.DP_DX_F32 if dx_f32 else 0))
+    dx = torch.full((n, i), 5.0, dtype=torch.float32 if dx_f32 else torch.bfloat16, device=U.DEV)
+    dp.dp_trace_begin()
+    dp.dp_linear_fwd_bwd(desc, x=U.bf16_dev(xb), W=U.bf16_dev(wb), dy=U.bf16_dev(dyb), dx=dx, ws=U.workspace(dp.dp_linear_workspace_bytes(desc)))
+    assert [r["kernel"] for r in dp.dp_trace_end()] == [name]
+    U.assert_bf16_close(U.to_np(dx), orc.relu_in_backward(dy.astype(np.float64) @ w.astype(np.float64), x), "dx")
+
+
 @pytest.mark.parametrize("rows,k,bf16", [(1000, 64, True), (777, 512, True), (50, 4096, True), (33, 1000, True),
                                          (300, 24, True), (65, 12, True), (130, 16, False)])
 def test_relu_bias_grad(env, rows, k, bf16):
