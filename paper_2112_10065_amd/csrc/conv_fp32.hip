@@ -165,10 +165,12 @@ __global__ __launch_bounds__(64 * kPixWaves) void k_f32_pix(const F32Args p)
 // multiplies dy with ones instead of x: the bias gradient, without a launch of its own.  There are few tiles (30 for 15 -> 34
 // channels), so a block has 16 waves; bound by the address unit (4-byte loads, 16 channels of 4 pixels each).
 constexpr int kWgWaves = 16;
-template <bool MASK>
+// U: steps per wave whose loads are issued together.  A layer with few pixels has one or two steps for each of the waves and
+// takes no more (the waves of a tile share one CU, whose load rate bounds them: 2 x 16 x 16 pixels with four, two of them empty, 8.7 us, with
+// two 6.2 us).
+template <bool MASK, int U>
 __global__ __launch_bounds__(64 * kWgWaves) void k_f32_wgrad(const F32Args p, float *dbias)
 {
-    constexpr int U = 4;
     const ConvGeom &g = p.g;
     __shared__ f32x4 part[kWgWaves - 1][64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -222,6 +224,8 @@ __global__ __launch_bounds__(64 * kWgWaves) void k_f32_wgrad(const F32Args p, fl
     }
 }
 
+int wgrad_unroll(int pixels) { return pixels <= 16 * kWgWaves ? 1 : pixels <= 2 * 16 * kWgWaves ? 2 : 4; }
+
 bool wide_tiles(long long rowsA, long long rowsB) { return (rowsA + 15) / 16 * ((rowsB + 63) / 64) >= 1024; }   // enough 16 x 64 tiles for four blocks per CU
 
 hipError_t launch_pix(bool dg, const F32Args &a, hipStream_t st)
@@ -249,7 +253,7 @@ hipError_t launch_pix(bool dg, const F32Args &a, hipStream_t st)
 
 void f32_kernel_name(const ConvGeom &g, int pass, bool masked, char *name, size_t name_bytes)
 {
-    if (pass == PASS_WGRAD) { snprintf(name, name_bytes, "k_f32_wgrad<%s>", masked ? "true" : "false"); return; }
+    if (pass == PASS_WGRAD) { snprintf(name, name_bytes, "k_f32_wgrad<%s, %d>", masked ? "true" : "false", wgrad_unroll(g.N * g.Ho * g.Wo)); return; }
     const bool dg = pass == PASS_DGRAD, v4 = (dg ? g.K : g.C) % 4 == 0;
     const bool wide = dg ? wide_tiles(g.C, (long long)g.N * g.H * g.W) : wide_tiles(g.K, (long long)g.N * g.Ho * g.Wo);
     snprintf(name, name_bytes, "k_f32_pix<%s, %d, %s, %s>", dg ? "true" : "false", wide ? 4 : 1, v4 ? "true" : "false", dg && masked ? "true" : "false");
@@ -285,7 +289,12 @@ hipError_t f32_conv_wgrad(const ConvGeom &g, const float *x, const float *dy, co
     a.w = x; a.b = dy; a.mask = ymask; a.out = dw;
     const long long tiles = (long long)g.R * g.S * ((g.C + 15) / 16);
     const dim3 grid((unsigned)((g.K + 15) / 16 * (tiles + (dbias != nullptr ? 1 : 0)))), block(64 * kWgWaves);
-    if (ymask != nullptr) hipLaunchKernelGGL(k_f32_wgrad<true>, grid, block, 0, st, a, dbias);
-    else hipLaunchKernelGGL(k_f32_wgrad<false>, grid, block, 0, st, a, dbias);
+    auto pick = [&](auto maskc) {
+        constexpr bool MASK = decltype(maskc)::value;
+        const int u = wgrad_unroll(a.rowsB);
+        hipLaunchKernelGGL((u == 1 ? k_f32_wgrad<MASK, 1> : u == 2 ? k_f32_wgrad<MASK, 2> : k_f32_wgrad<MASK, 4>), grid, block, 0, st, a, dbias);
+    };
+    if (ymask != nullptr) pick(std::true_type());
+    else pick(std::false_type());
     return hipGetLastError();
 }
