@@ -125,10 +125,18 @@ def _ptr(t):
     return t.data_ptr()
 
 
+def _current_stream():
+    """Handle of the current device's current stream.  torch.cuda.current_stream() builds a Stream object on every call, most of
+    the host time of a small layer's call; once the device is initialised the handle is read directly."""
+    import torch
+    if torch.cuda.is_initialized():
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
+
+
 def _stream(stream):
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     return stream if isinstance(stream, int) else stream.cuda_stream
 
 

@@ -1086,3 +1086,13 @@ def test_wrn101_2_layers_sampled(env, li):
     from paper_2112_10065_amd import workloads
     l = workloads.wrn101_2_convs()[li]
     _sampled_layer_check(dp, U, orc, l, 1 if l.h > 100 else 2, "wrn101_2")
+
+
+def test_calls_without_a_stream_take_the_current_one(env):
+    dp, U, orc = env
+    torch.cuda.init()
+    assert dp._stream(None) == torch.cuda.current_stream().cuda_stream
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert dp._stream(None) == side.cuda_stream != 0
+    assert dp._stream(None) == torch.cuda.current_stream().cuda_stream
