@@ -556,6 +556,15 @@ DEVFN void reduce_second(int blk, const float *partial2, float *out2, int total2
     float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
     if (col < total2) {
         int b = part;
+        // sixteen loads in flight (one block per 32 columns walks all rows: 512 rows of 192 with four took 8.6 us, 5.1 with sixteen);
+        // same sums in the same order as the loop below
+        for (; b + 120 < rows; b += 128) {
+            float v[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) v[u] = partial2[(size_t)(b + 8 * u) * total2 + col];
+#pragma unroll
+            for (int u = 0; u < 16; u += 4) { s0 += v[u]; s1 += v[u + 1]; s2 += v[u + 2]; s3 += v[u + 3]; }
+        }
         for (; b + 24 < rows; b += 32) {
             s0 += partial2[(size_t)b * total2 + col];
             s1 += partial2[(size_t)(b + 8) * total2 + col];

@@ -127,6 +127,13 @@ __global__ __launch_bounds__(256) void k_rbg_final(int k, int row_blocks, const 
     float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
     if (col < k) {
         int b = part;
+        for (; b + 120 < row_blocks; b += 128) {   // sixteen loads in flight, the same sums in the same order as the loop below
+            float v[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) v[u] = ws[(size_t)(b + 8 * u) * k + col];
+#pragma unroll
+            for (int u = 0; u < 16; u += 4) { s0 += v[u]; s1 += v[u + 1]; s2 += v[u + 2]; s3 += v[u + 3]; }
+        }
         for (; b + 24 < row_blocks; b += 32) {
             s0 += ws[(size_t)b * k + col];
             s1 += ws[(size_t)(b + 8) * k + col];
