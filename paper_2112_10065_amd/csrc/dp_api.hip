@@ -36,6 +36,7 @@ std::atomic<int> g_force_variant[3] = {{-1}, {-1}, {-1}};
 std::atomic<int> g_force_splits[3] = {{0}, {0}, {0}};
 std::atomic<int> g_autotune{0};
 thread_local bool g_analytic_only = false;   // the descriptor of the running call asks for DP_DETERMINISTIC
+thread_local bool g_tight_splits = false;    // the running call's scratch does not hold the empty filter-gradient splits that round a count up to whole eights
 std::once_flag g_init_once;
 hipError_t g_init_err = hipSuccess;
 
@@ -270,7 +271,7 @@ PlanRef plan_entry(const ConvGeom &g, int pass, int restr = 0)
     static std::unordered_map<PlanKey, PlanRef, PlanKeyHash> cache;
     const int fv = g_force_variant[pass].load(), fs = g_force_splits[pass].load();
     const int at = g_analytic_only ? 0 : g_autotune.load();
-    PlanKey key = {{g.N, g.H, g.W, g.C, g.K, g.R, g.S, g.sh, g.sw, g.ph, g.pw, g.Ho, g.Wo, pass, fv, fs, at | (restr << 2)}};
+    PlanKey key = {{g.N, g.H, g.W, g.C, g.K, g.R, g.S, g.sh, g.sw, g.ph, g.pw, g.Ho, g.Wo, pass, fv, fs, at | (restr << 2) | (g_tight_splits ? 1 << 8 : 0)}};
     std::lock_guard<std::mutex> lock(g_plan_mu);
     auto it = cache.find(key);
     if (it != cache.end()) return it->second;
@@ -278,6 +279,8 @@ PlanRef plan_entry(const ConvGeom &g, int pass, int restr = 0)
     PlanRef ep = std::make_shared<PlanEntry>();
     PlanEntry &e = *ep;
     plan_uncached(g, pass, fv, fs, &e.plan, restr);
+    if (g_tight_splits && pass == PASS_WGRAD && e.plan.dma && !e.plan.halo && !e.plan.wstrip)
+        e.plan.splits = (e.plan.steps_total + e.plan.steps_per_split - 1) / e.plan.steps_per_split;
     e.part_cap = mfma_partial_bytes(g, pass, e.plan);
     if (at != 0 && fv < 0 && e.plan.fast) {
         GemmPlan list[kTuneCandidates];
@@ -966,7 +969,12 @@ dp_status dp_conv2d_bwd_filter_noalloc(const dp_conv_desc *desc, const void *x, 
     g_analytic_only = true;
     if ((s = check_ptr(x, "x")) != DP_OK || (s = check_ptr(dy, "dy")) != DP_OK || (s = check_ptr(dw, "dw")) != DP_OK) return s;
     if ((s = check_opt(y_saved, "y_saved")) != DP_OK || (s = check_opt(dbias, "dbias")) != DP_OK) return s;
-    const size_t need = wgrad_ws_bytes(g, desc->io_dtype, dbias != nullptr);
+    size_t need = wgrad_ws_bytes(g, desc->io_dtype, dbias != nullptr);
+    struct Tight { ~Tight() { g_tight_splits = false; } } until_return;
+    if (need > kNoAllocScratchBytes) {
+        g_tight_splits = true;
+        need = wgrad_ws_bytes(g, desc->io_dtype, dbias != nullptr);
+    }
     if (need > kNoAllocScratchBytes)
         return fail(DP_ERR_WORKSPACE, "backward-filter of this layer needs %zu scratch bytes, the built-in scratch holds %zu: use dp_conv2d_bwd_filter with a workspace",
                     need, kNoAllocScratchBytes);

@@ -47,3 +47,22 @@ def test_noalloc_rejects_what_does_not_fit():
     with pytest.raises(dp.DpError) as ei:
         dp.dp_conv2d_bwd_filter_noalloc(d, a, a, None, a, a)
     assert ei.value.status == dp.DP_ERR_WORKSPACE
+
+
+def test_noalloc_takes_what_fits_without_the_empty_splits():
+    """63 splits of the reduction fit the built-in scratch, the empty one that makes them whole eights does not: same sums."""
+    from paper_2112_10065_amd import binding as dp
+    import gpu_util as U
+    dp.dp_set_autotune(False)
+    d = dp.conv_desc(8, 63, 63, 256, 256, 1, 1, (1, 1), (0, 0), dp.DP_BF16, 0)
+    need = dp.dp_conv2d_workspace_bytes(d, dp.DP_PASS_WGRAD)
+    assert need > dp.DP_NOALLOC_SCRATCH_BYTES and dp.dp_conv2d_kernel_info(d, 2)[1] == 64
+    gen = torch.Generator(device=U.DEV).manual_seed(3)
+    x, dy = (torch.randn((8, 63, 63, 256), generator=gen, device=U.DEV).bfloat16() for _ in range(2))
+    dw, want = (torch.full((256, 1, 1, 256), 7.0, device=U.DEV) for _ in range(2))
+    db, want_db = (torch.full((256,), 7.0, device=U.DEV) for _ in range(2))
+    dp.dp_conv2d_bwd_filter(d, x, dy, None, want, want_db, U.workspace(need))
+    dp.dp_conv2d_bwd_filter_noalloc(d, x, dy, None, dw, db)
+    torch.cuda.synchronize()
+    assert torch.equal(dw, want) and torch.equal(db, want_db)
+    assert dp.dp_conv2d_kernel_info(d, 2)[1] == 64
