@@ -50,7 +50,7 @@ def test_noalloc_rejects_what_does_not_fit():
 
 
 def test_noalloc_takes_what_fits_without_the_empty_splits():
-    """63 splits of the reduction fit the built-in scratch, the empty one that makes them whole eights does not: same sums."""
+    """63 splits of the reduction fit the built-in scratch, the empty one that makes them whole eights does not: same partials."""
     from paper_2112_10065_amd import binding as dp
     import gpu_util as U
     dp.dp_set_autotune(False)
@@ -64,5 +64,7 @@ def test_noalloc_takes_what_fits_without_the_empty_splits():
     dp.dp_conv2d_bwd_filter(d, x, dy, None, want, want_db, U.workspace(need))
     dp.dp_conv2d_bwd_filter_noalloc(d, x, dy, None, dw, db)
     torch.cuda.synchronize()
-    assert torch.equal(dw, want) and torch.equal(db, want_db)
+    # the reduction associates 63 and 64 partials differently: at most 64 roundings of 2^-24 apart, below the fp32 bar of 1e-5
+    U.assert_f32_close(U.to_np(dw), U.to_np(want), "dw")
+    U.assert_f32_close(U.to_np(db), U.to_np(want_db), "db")
     assert dp.dp_conv2d_kernel_info(d, 2)[1] == 64
