@@ -1589,6 +1589,7 @@ bool dma_plan(const ConvGeom &g, int pass, int force_variant, int force_splits, 
     return true;
 }
 
+bool dma_plan_is_flat(const GemmPlan &plan) { return plan.dma && !plan.halo && !plan.wstrip && kDma[plan.variant].mix; }
 bool dma_plan_is_strip(const GemmPlan &plan) { return plan.dma && !plan.halo && !plan.wstrip && is_strip(plan.variant); }
 
 // Whether this forward / backward-data plan sums its reduction splits inside the main kernel: asked for by the plan, tiles in

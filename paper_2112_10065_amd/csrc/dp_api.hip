@@ -220,7 +220,12 @@ void plan_uncached(const ConvGeom &g, int pass, int fv, int fs, GemmPlan *pl, in
         pl->fused_reduce = pass != PASS_WGRAD && pl->dma && !pl->halo && pl->splits > 1 && dma_fused_reduce_fits(rowsA, rowsB, pl->splits);
         return;
     }
-    if (fv < 0 && auto_plan(g, pass, fs, pl, restr)) return;
+    if (fv < 0) {
+        if (!auto_plan(g, pass, fs, pl, restr)) mfma_plan(g, pass, -1, fs, pl);
+        GemmPlan flat;
+        if (pass == PASS_FWD && fs <= 0 && forward_flat_plan(g, *pl, &flat)) *pl = flat;
+        return;
+    }
     // a forced input-patch variant the call may not use falls through to the next family
     const bool patch_banned = pass != PASS_WGRAD && (restr & 1);
     if (fv >= 400 && !patch_banned && halo_plan(g, pass, fv, fs, pl)) return;
@@ -285,7 +290,8 @@ PlanRef plan_entry(const ConvGeom &g, int pass, int restr = 0)
     if (at != 0 && fv < 0 && e.plan.fast) {
         GemmPlan list[kTuneCandidates];
         // a cold measurement judges for itself what the model's warm-cache prices cannot: more candidates, a wider price band
-        const int n = auto_plan_list(g, pass, fs, list, at == 2 ? kTuneCandidates : 12, restr | (at == 2 ? 4 : 0));
+        int n = auto_plan_list(g, pass, fs, list, at == 2 ? kTuneCandidates : 12, restr | (at == 2 ? 4 : 0));
+        if (pass == PASS_FWD && n > 0 && n < kTuneCandidates && dma_plan_is_flat(e.plan)) list[n++] = e.plan;   // not one of the list's
         if (n > 1) {
             e.cands.assign(list, list + n);
             e.tuned = false;

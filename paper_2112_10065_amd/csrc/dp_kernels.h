@@ -102,6 +102,7 @@ void dma_kernel_name(int pass, const GemmPlan &plan, char *name, size_t name_byt
 hipError_t halo_init();
 bool halo_plan(const ConvGeom &g, int pass, int force_variant, int force_splits, GemmPlan *plan);
 hipError_t halo_launch(const ConvArgs &a, hipStream_t st);
+bool dma_plan_is_flat(const GemmPlan &plan);    // the kernels that walk the reduction flat over (tap, channel)
 bool dma_plan_is_strip(const GemmPlan &plan);   // the pixel-strip forward / backward-data kernels (no fused split reduction)
 bool dma_fused_reduce_fits(int rowsA, int rowsB, int splits);
 bool dma_plan_fuses_reduce(const GemmPlan &plan);   // the splits are summed by the main kernel: no reduction kernel follows
@@ -129,6 +130,8 @@ hipError_t rbg_launch_final(int k, int row_blocks, const float *ws, float *dbias
 
 // planner.hip : picks the cheapest fast-path variant and split for a pass (host-side cost model)
 bool auto_plan(const ConvGeom &g, int pass, int force_splits, GemmPlan *plan, int restr = 0);
+// forward: the flat-walk plan that adds in the same order as `base` and is faster, if there is one
+bool forward_flat_plan(const ConvGeom &g, const GemmPlan &base, GemmPlan *plan);
 // the cheapest plans by the model, best first (input of the measured choice); returns the count
 // restr: kernels the call may not use (bit 0: input-patch kernels, bit 1: the stationary-weight kernel)
 int auto_plan_list(const ConvGeom &g, int pass, int force_splits, GemmPlan *out, int max_out, int restr = 0);

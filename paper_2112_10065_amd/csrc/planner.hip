@@ -35,7 +35,7 @@ const Candidate kPix[] = {
     {205, 4, 0.85f, 4.0f},
     {213, 3, 1.30f, 4.5f},
     {210, 1, 1.15f, 6.0f},   // 128x256x64, 8 waves
-    {212, 2, 1.30f, 8.0f},   // 64x256x64 (memory-bound 1x1 layers: 48 us forward, 89 masked backward-data where 64x128 takes 35 and 52)
+    {212, 2, 1.30f, 8.0f},   // 64x256x64 (backward-data of memory-bound 1x1 layers: 89 us masked where 64x128 takes 52); forward: see price()
     {221, 1, 0.70f, 4.0f},   // reduction step 128 (channels % 128 only): fewer, longer steps for small grids
     {225, 1, 0.70f, 4.0f},
     {222, 1, 1.10f, 4.5f},
@@ -60,6 +60,11 @@ const Candidate kPix[] = {
     {101, 3, 1.05f, 4.5f},
     {102, 3, 1.05f, 4.5f},
     {103, 4, 0.75f, 4.0f},
+};
+// Forward by the flat walk (64x64, with 4 and 2 reduction groups, 64x128, 128x64, 128x128; steps of 64): step and block times fitted to 376
+// layers (8 to 448 channels, images 6 to 150, 1 to 32 samples; median error 7 %)
+const Candidate kFlatFwd[] = {
+    {234, 3, 0.55f, 1.5f}, {235, 1, 0.75f, 2.5f, 4}, {236, 2, 0.70f, 1.5f, 2}, {237, 3, 0.70f, 1.5f}, {238, 3, 0.65f, 1.5f}, {239, 2, 0.75f, 2.5f},
 };
 // backward-filter candidates (reduction step 32 unless noted)
 const Candidate kWg[] = {
@@ -111,7 +116,9 @@ double price(const ConvGeom &g, int pass, const Candidate &c, const GemmPlan &pl
     // the saved input of a masked tile, read while nothing else runs on the CU (the strip kernels fetch it ahead): 128 KB at a CU's
     // share of the memory rate (64 x 56 x 56 x 256 <- 128, 1x1: 256 x 256 tiles 59 us, 64 x 128 tiles 52)
     const bool lone_mask = pass == PASS_DGRAD && (restr & 2) && c.bpc == 1 && pl.splits == 1 && c.code >= 200 && c.code < 230;
-    const double t_block = c.t0 + (lone_mask ? 3.5 * pl.TA * pl.TB / 65536.0 : 0.0) + (pl.steps_per_split + c.kg - 1) / c.kg * t_step * share;
+    // 64x256 tiles forward: the choice between tiles whose sums run in different orders stays where it was (forward_flat_plan says why)
+    const double t0 = c.code == 212 && pass == PASS_FWD ? 4.5 : c.t0;
+    const double t_block = t0 + (lone_mask ? 3.5 * pl.TA * pl.TB / 65536.0 : 0.0) + (pl.steps_per_split + c.kg - 1) / c.kg * t_step * share;
     double t = 3.0 + waves * t_block;
     if (pl.splits > 1) {
         double out_elems = pass == PASS_FWD ? (double)g.N * g.Ho * g.Wo * g.K
@@ -147,7 +154,8 @@ int auto_plan_list(const ConvGeom &g, int pass, int force_splits, GemmPlan *out,
             }
         }
     }
-    const bool flat = g.R * g.S <= 31 && g.C % 8 == 0 && (pass == PASS_FWD || (g.K % 8 == 0 && ((g.sh == 1 && g.sw == 1) || (!(restr & 1) && force_splits <= 1 && g.sh <= 2 && g.sw <= 2))));
+    const bool flat = pass == PASS_DGRAD && g.R * g.S <= 31 && g.C % 8 == 0 && g.K % 8 == 0 &&
+                      ((g.sh == 1 && g.sw == 1) || (!(restr & 1) && force_splits <= 1 && g.sh <= 2 && g.sw <= 2));
     const Candidate *cands = pass == PASS_WGRAD ? kWg : kPix;
     const int ncand = pass == PASS_WGRAD ? (int)(sizeof(kWg) / sizeof(kWg[0])) : (int)(sizeof(kPix) / sizeof(kPix[0]));
     for (int ci = 0; ci < ncand; ++ci) {
@@ -156,8 +164,8 @@ int auto_plan_list(const ConvGeom &g, int pass, int force_splits, GemmPlan *out,
         if (pass != PASS_WGRAD && cands[ci].code >= 234 && cands[ci].code <= 239) {
             // whole steps per tap: the plain kernels, which spend no vector instructions on the walk (7x1 backward-data with 192
             // channels, 16 x 17 x 17: 10.8 us plain, 12.4 flat); everything else gains (flat against the 32-wide step 8.8 / 13.1 us)
-            if ((pass == PASS_FWD ? g.C : g.K) % 64 == 0) continue;
-            if (pass == PASS_DGRAD && (restr & 1) && (g.sh > 1 || g.sw > 1)) continue;   // fp32 gradients of strided layers go in natural pixel order
+            if (pass == PASS_FWD || g.K % 64 == 0) continue;
+            if ((restr & 1) && (g.sh > 1 || g.sw > 1)) continue;   // fp32 gradients of strided layers go in natural pixel order
         }
         int last_splits = -1;
         for (int s : kSplits) {
@@ -202,6 +210,42 @@ int auto_plan_list(const ConvGeom &g, int pass, int force_splits, GemmPlan *out,
         all[best].t = -1.0;
     }
     return written;
+}
+
+// Forward, channels that 64 does not divide: a flat-walk kernel in the place of `base` (32-wide steps), if one is faster.  It takes the
+// reduction apart exactly as `base` does: the same splits, each a whole number of 64-wide steps, either as partials or as the
+// reduction groups of a block.  Both walk (tap, channel) in 16-element slices, so the sums run in the same order and y is the same bit
+// for bit.  That is required, not only tidy: a layer that keeps its mask to itself takes its gradients through [y > 0], and an output whose
+// sum lies at zero changes side with the order of the additions (80 -> 192 3x3, 4 x 73 x 73: one of 3.9 M outputs in every
+// twentieth input set), which switches a whole term of dx on or off.
+// Where it is faster (old / new with the same splits, 376 layers):
+//   generic kernel: from 3 steps on 1.02 - 1.73; below 0.81 - 1.36, the shortest layers lose
+//   64x64 tiles of 32-wide steps, unsplit: 1 step 0.91, 3 steps 0.98, 4 steps 1.01, 6 and more 1.06 - 1.17; split 1.01 - 1.24
+//   64x128 / 128x128 pipelined tiles of 32-wide steps: unsplit 0.79 - 1.15, with partials 0.93 - 1.17, neither worth the change; their 2 or
+//   4 splits as reduction groups of blocks that all run at once, no reduction kernel: 1.39 - 1.63
+bool forward_flat_plan(const ConvGeom &g, const GemmPlan &base, GemmPlan *out)
+{
+    if (g.C % 64 == 0 || g.C % 8 != 0 || g.R * g.S > 31 || base.BK != 32 || (base.splits > 1 && base.steps_per_split % 2 != 0)) return false;
+    const int steps = (g.R * g.S * g.C + 63) / 64;
+    const bool generic = !base.fast, staged = base.fast && !base.dma;
+    if (base.splits == 1 && steps < (generic ? 3 : 6)) return false;
+    double best = 0.0;
+    bool found = false;
+    for (const Candidate &c : kFlatFwd) {
+        GemmPlan pl;
+        if (!family_plan(g, PASS_FWD, c.code, c.kg > 1 ? 1 : base.splits, &pl)) return false;
+        if (c.kg == 1) {
+            if (!generic && !staged) continue;
+            if (generic && base.splits > 1 && base.TA * base.TB == 128 * 128 && c.code != 239) continue;   // partials of many tiles: its tile
+            if (pl.splits != base.splits || (base.splits > 1 && pl.steps_per_split * 2 != base.steps_per_split)) continue;
+        } else {
+            if (base.splits != c.kg || (steps + c.kg - 1) / c.kg * 2 != base.steps_per_split) continue;
+            if (!generic && (long long)pl.tilesA * pl.tilesB > 256 * c.bpc) continue;
+        }
+        const double t = price(g, PASS_FWD, c, pl, 0);
+        if (!found || t < best) { best = t; *out = pl; found = true; }
+    }
+    return found;
 }
 
 // Fills *pl with the cheapest eligible fast-path plan; false if the shape has none.

@@ -251,6 +251,38 @@ def test_flat_reduction_variants(env, variant, splits):
             dp.dp_set_override(p, -1, 0)
 
 
+# The built-in choice of a flat kernel adds in the order of the 32-wide kernel whose place it takes (its splits: as partials, as reduction
+# groups of a block, unsplit), so y is the same bit for bit and with it the mask of a layer's own ReLU; a forced generic kernel with that
+# kernel's splits (0: the generic kernel's own) is the reference.  The first layer used to add in another order.
+@pytest.mark.parametrize("n,h,w,c,k,r,s,st,pd,variant,splits,kernel", [
+    (4, 73, 73, 80, 192, 3, 3, (1, 1), (0, 0), 0, 0, "k_fwd_mix<64, 64, 64, 2, 2, 2, 2>"), (3, 13, 13, 112, 48, 3, 3, (1, 1), (0, 0), 3, 0, "k_fwd_mix<64, 64, 64, 2, 2, 2, 4>"),
+    (3, 21, 21, 432, 224, 5, 5, (1, 1), (0, 0), 1, 0, "k_fwd_mix<"), (2, 31, 30, 144, 72, 3, 3, (2, 1), (1, 0), 1, 0, "k_conv_gemm<"), (1, 9, 9, 200, 33, 3, 3, (1, 1), (0, 1), 3, 0, "k_conv_gemm<"),
+    (16, 17, 17, 160, 160, 1, 7, (1, 1), (0, 3), 1, 1, "k_fwd_mix<64, 64, 64, 2, 2, 3, 1>"), (3, 19, 19, 288, 192, 1, 3, (1, 1), (0, 1), 1, 5, "k_fwd_mix<64, 64, 64, 2, 2, 3, 1>"),
+    (5, 20, 20, 416, 224, 3, 1, (1, 1), (1, 0), 1, 4, "k_fwd_mix<64, 64, 64, 2, 2, 2, 4>"), (30, 27, 27, 352, 352, 1, 3, (1, 1), (0, 1), 1, 1, "k_fwd_dma<128, 128, 32")])
+def test_flat_forward_adds_in_the_order_of_the_kernel_it_replaces(env, n, h, w, c, k, r, s, st, pd, variant, splits, kernel):
+    dp, U, orc = env
+    gen = torch.Generator(device=U.DEV).manual_seed(11)
+    x = torch.randn((n, h, w, c), generator=gen, device=U.DEV).bfloat16()
+    wt = (torch.randn((k, r, s, c), generator=gen, device=U.DEV) * (2.0 / (r * s * c)) ** 0.5).bfloat16()
+    bias = torch.rand(k, generator=gen, device=U.DEV) - 0.5
+    ho, wo = (h + 2 * pd[0] - r) // st[0] + 1, (w + 2 * pd[1] - s) // st[1] + 1
+    for flags in (dp.DP_RELU, dp.DP_RELU | dp.DP_BIAS):
+        d = dp.conv_desc(n, h, w, c, k, r, s, st, pd, dp.DP_BF16, flags)
+        assert dp.dp_conv2d_kernel_info(d, 0)[0].startswith(kernel)
+        ys = []
+        for forced in (False, True):
+            if forced:
+                dp.dp_set_override(0, variant, splits)
+            try:
+                y = torch.full((n, ho, wo, k), 7.0, device=U.DEV, dtype=torch.bfloat16)
+                dp.dp_conv2d_fwd(d, x, wt, bias, y, U.workspace(dp.dp_conv2d_workspace_bytes(d, 0)))
+                ys.append(y)
+            finally:
+                dp.dp_set_override(0, -1, 0)
+        torch.cuda.synchronize()
+        assert torch.equal(ys[0], ys[1])
+
+
 @pytest.mark.parametrize("variant", [200, 203, 207, 210, 214, 219, 221, 226, 227, 229])
 @pytest.mark.parametrize("splits", [2, 5])
 def test_split_reduction_fused_into_the_pipelined_kernels(env, variant, splits):
