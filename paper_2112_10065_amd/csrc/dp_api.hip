@@ -221,9 +221,10 @@ void plan_uncached(const ConvGeom &g, int pass, int fv, int fs, GemmPlan *pl, in
         return;
     }
     if (fv < 0) {
-        if (!auto_plan(g, pass, fs, pl, restr)) mfma_plan(g, pass, -1, fs, pl);
+        double time = 0.0;
+        if (!auto_plan(g, pass, fs, pl, restr, &time)) mfma_plan(g, pass, -1, fs, pl);
         GemmPlan flat;
-        if (pass == PASS_FWD && fs <= 0 && forward_flat_plan(g, *pl, &flat)) *pl = flat;
+        if (fs <= 0 && ((pass == PASS_FWD && forward_flat_plan(g, *pl, &flat)) || (pass == PASS_DGRAD && backward_flat_plan(g, *pl, time, restr, &flat)))) *pl = flat;
         return;
     }
     // a forced input-patch variant the call may not use falls through to the next family
@@ -291,7 +292,7 @@ PlanRef plan_entry(const ConvGeom &g, int pass, int restr = 0)
         GemmPlan list[kTuneCandidates];
         // a cold measurement judges for itself what the model's warm-cache prices cannot: more candidates, a wider price band
         int n = auto_plan_list(g, pass, fs, list, at == 2 ? kTuneCandidates : 12, restr | (at == 2 ? 4 : 0));
-        if (pass == PASS_FWD && n > 0 && n < kTuneCandidates && dma_plan_is_flat(e.plan)) list[n++] = e.plan;   // not one of the list's
+        if (pass != PASS_WGRAD && n > 0 && n < kTuneCandidates && dma_plan_is_flat(e.plan)) list[n++] = e.plan;   // not one of the list's
         if (n > 1) {
             e.cands.assign(list, list + n);
             e.tuned = false;

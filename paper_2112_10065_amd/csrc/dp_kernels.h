@@ -129,12 +129,14 @@ hipError_t rbg_launch_partial(long long rows, int k, bool bf16, const void *dy, 
 hipError_t rbg_launch_final(int k, int row_blocks, const float *ws, float *dbias, hipStream_t st);
 
 // planner.hip : picks the cheapest fast-path variant and split for a pass (host-side cost model)
-bool auto_plan(const ConvGeom &g, int pass, int force_splits, GemmPlan *plan, int restr = 0);
+bool auto_plan(const ConvGeom &g, int pass, int force_splits, GemmPlan *plan, int restr = 0, double *time = nullptr);
 // forward: the flat-walk plan that adds in the same order as `base` and is faster, if there is one
 bool forward_flat_plan(const ConvGeom &g, const GemmPlan &base, GemmPlan *plan);
+// backward-data: a flat-walk plan faster than `base`, whose price is `time`
+bool backward_flat_plan(const ConvGeom &g, const GemmPlan &base, double time, int restr, GemmPlan *plan);
 // the cheapest plans by the model, best first (input of the measured choice); returns the count
 // restr: kernels the call may not use (bit 0: input-patch kernels, bit 1: the stationary-weight kernel)
-int auto_plan_list(const ConvGeom &g, int pass, int force_splits, GemmPlan *out, int max_out, int restr = 0);
+int auto_plan_list(const ConvGeom &g, int pass, int force_splits, GemmPlan *out, int max_out, int restr = 0, double *times = nullptr);
 
 // small_c.hip : explicit im2col for layers with very few input channels (c_in % 8 != 0, R*S*C <= 256)
 int small_c_kpad(const ConvGeom &g);   // padded reduction length, 0 if the layer does not qualify

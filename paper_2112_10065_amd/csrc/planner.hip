@@ -45,12 +45,6 @@ const Candidate kPix[] = {
     {227, 2, 0.62f, 4.5f, 2},
     {228, 1, 0.85f, 5.0f, 2},
     {229, 1, 0.85f, 5.0f, 2},
-    {234, 3, 0.65f, 4.0f},   // channels that 64 does not divide, reduction walked flat over (tap, channel): 64x64x64
-    {235, 1, 0.65f, 5.0f, 4},   // the same with 4 / 2 reduction groups per block
-    {236, 2, 0.80f, 4.5f, 2},
-    {237, 3, 0.88f, 4.5f},   // 64x128x64
-    {238, 3, 0.88f, 4.5f},   // 128x64x64
-    {239, 2, 0.88f, 5.0f},   // 128x128x64
     {400, 2, 0.75f, 5.5f},   // input patch resident in LDS: 64 x 256 tile (64 reduction channels per tap, stride 1)
     {401, 2, 1.20f, 6.0f},   // same, 128 x 256
     {402, 2, 0.75f, 5.5f},
@@ -65,6 +59,10 @@ const Candidate kPix[] = {
 // layers (8 to 448 channels, images 6 to 150, 1 to 32 samples; median error 7 %)
 const Candidate kFlatFwd[] = {
     {234, 3, 0.55f, 1.5f}, {235, 1, 0.75f, 2.5f, 4}, {236, 2, 0.70f, 1.5f, 2}, {237, 3, 0.70f, 1.5f}, {238, 3, 0.65f, 1.5f}, {239, 2, 0.75f, 2.5f},
+};
+// The same for backward-data, 385 layers (median error 5 - 10 %).  A reduction split costs 1.5 us more than price() says.
+const Candidate kFlatBwd[] = {
+    {234, 3, 0.75f, 3.0f}, {235, 1, 1.00f, 4.0f, 4}, {236, 2, 0.90f, 3.0f, 2}, {237, 3, 0.95f, 3.5f}, {238, 3, 0.95f, 3.5f}, {239, 2, 1.00f, 5.0f},
 };
 // backward-filter candidates (reduction step 32 unless noted)
 const Candidate kWg[] = {
@@ -133,7 +131,7 @@ double price(const ConvGeom &g, int pass, const Candidate &c, const GemmPlan &pl
 
 // Eligible fast-path plans of a pass, cheapest first by the model, at most two split counts per tile
 // variant; returns how many were written (0: the shape has no fast-path plan).
-int auto_plan_list(const ConvGeom &g, int pass, int force_splits, GemmPlan *out, int max_out, int restr)
+int auto_plan_list(const ConvGeom &g, int pass, int force_splits, GemmPlan *out, int max_out, int restr, double *times)
 {
     struct Priced { double t; GemmPlan pl; int code; };
     Priced all[512];
@@ -154,19 +152,11 @@ int auto_plan_list(const ConvGeom &g, int pass, int force_splits, GemmPlan *out,
             }
         }
     }
-    const bool flat = pass == PASS_DGRAD && g.R * g.S <= 31 && g.C % 8 == 0 && g.K % 8 == 0 &&
-                      ((g.sh == 1 && g.sw == 1) || (!(restr & 1) && force_splits <= 1 && g.sh <= 2 && g.sw <= 2));
     const Candidate *cands = pass == PASS_WGRAD ? kWg : kPix;
     const int ncand = pass == PASS_WGRAD ? (int)(sizeof(kWg) / sizeof(kWg[0])) : (int)(sizeof(kPix) / sizeof(kPix[0]));
     for (int ci = 0; ci < ncand; ++ci) {
         if (pass != PASS_WGRAD && cands[ci].code >= 400 && (restr & 1)) continue;   // the input-patch kernels store bf16 only
         if (pass == PASS_DGRAD && cands[ci].code >= 230 && cands[ci].code <= 233 && (restr & 1)) continue;   // bf16 staged epilogue only
-        if (pass != PASS_WGRAD && cands[ci].code >= 234 && cands[ci].code <= 239) {
-            // whole steps per tap: the plain kernels, which spend no vector instructions on the walk (7x1 backward-data with 192
-            // channels, 16 x 17 x 17: 10.8 us plain, 12.4 flat); everything else gains (flat against the 32-wide step 8.8 / 13.1 us)
-            if (pass == PASS_FWD || g.K % 64 == 0) continue;
-            if ((restr & 1) && (g.sh > 1 || g.sw > 1)) continue;   // fp32 gradients of strided layers go in natural pixel order
-        }
         int last_splits = -1;
         for (int s : kSplits) {
             if (force_splits > 0 && s != kSplits[0]) break;
@@ -175,9 +165,8 @@ int auto_plan_list(const ConvGeom &g, int pass, int force_splits, GemmPlan *out,
             if (pass == PASS_WGRAD && force_splits <= 0 && s > 8 && (s % 8) != 0) continue;
             GemmPlan cand;
             if (!family_plan(g, pass, cands[ci].code, force_splits > 0 ? force_splits : s, &cand)) break;
-            // reduction step 32 only where neither whole 64-wide steps nor the flat walk apply (flat against 32-wide: 43 -> 33.5 us for
-            // 16 x 28 x 28 x 288 -> 448, 7x1; 81 -> 63 us for 16 x 60 x 60 x 224 -> 160, 3x3)
-            if (pass != PASS_WGRAD && cand.BK == 32 && (((pass == PASS_FWD ? g.C : g.K) % 64) == 0 || flat)) break;
+            // reduction step 32 only where 64 does not divide the channel count
+            if (pass != PASS_WGRAD && cand.BK == 32 && ((pass == PASS_FWD ? g.C : g.K) % 64) == 0) break;
             if (cand.splits == last_splits) continue;   // the request was clamped to the same plan
             // pixel-strip kernels on a grid of few blocks: each block streams its weights alone, which times well on a warm
             // cache (the measured choice) and badly inside a step
@@ -206,7 +195,11 @@ int auto_plan_list(const ConvGeom &g, int pass, int force_splits, GemmPlan *out,
         int u = 0;
         while (u < nused && used_code[u] != all[best].code) ++u;
         if (u == nused && nused < 64) { used_code[nused] = all[best].code; used_cnt[nused] = 0; ++nused; }
-        if (u < 64 && used_cnt[u] < 2) { out[written++] = all[best].pl; ++used_cnt[u]; }
+        if (u < 64 && used_cnt[u] < 2) {
+            if (times != nullptr) times[written] = all[best].t;
+            out[written++] = all[best].pl;
+            ++used_cnt[u];
+        }
         all[best].t = -1.0;
     }
     return written;
@@ -248,8 +241,40 @@ bool forward_flat_plan(const ConvGeom &g, const GemmPlan &base, GemmPlan *out)
     return found;
 }
 
-// Fills *pl with the cheapest eligible fast-path plan; false if the shape has none.
-bool auto_plan(const ConvGeom &g, int pass, int force_splits, GemmPlan *pl, int restr)
+// Backward-data, c_out in whole 8s that 64 does not divide: a flat-walk kernel in the place of `base` (32-wide steps; `time` its price) where
+// that is faster.  Nothing depends on the order of these sums, so the splits are free.  Measured over 385 layers:
+//   generic kernel: 1.01 - 5.9 times as fast; up to 32 input channels and under 3 steps 0.70 - 1.54, left alone
+//   64x64 register-staged tiles: 0.74 - 0.89 up to 7 steps, 0.93 - 1.15 beyond, left alone; 128x128 pipelined: 0.80 - 1.09, left alone
+//   64x128 pipelined, unit stride: unsplit 0.76 - 1.07, left alone; split 0.96 - 1.5, taken where the prices are 8 % apart (then 1.04 - 1.5)
+//   64x128 pipelined, stride 2 (by phase): split 1.2 - 1.5; unsplit from 5 steps on and in one block per CU 1.14 - 1.25, else 0.86 - 1.18
+bool backward_flat_plan(const ConvGeom &g, const GemmPlan &base, double time, int restr, GemmPlan *out)
 {
-    return auto_plan_list(g, pass, force_splits, pl, 1, restr) == 1;
+    if (g.K % 64 == 0 || g.K % 8 != 0 || g.C % 8 != 0 || g.R * g.S > 31 || base.BK != 32) return false;
+    const bool strided = g.sh > 1 || g.sw > 1, generic = !base.fast;
+    if (strided && ((restr & 1) || g.sh > 2 || g.sw > 2)) return false;   // fp32 gradients of strided layers go in natural pixel order
+    const int steps = (g.R * g.S * g.K + 63) / 64;
+    if (generic) {
+        if (g.C <= 32 && steps < 3) return false;
+    } else {
+        if (!base.dma || base.TA != 64 || base.TB != 128) return false;
+        if (base.splits == 1 && (!strided || g.R * g.S == 1 || steps < 5)) return false;
+    }
+    double best = 0.0;
+    bool found = false;
+    for (const Candidate &c : kFlatBwd)
+        for (int s : kSplits) {
+            GemmPlan pl;
+            if ((s > 1 && (strided || c.kg > 1)) || !family_plan(g, PASS_DGRAD, c.code, s, &pl)) break;
+            if (pl.splits > 1 && pl.steps_per_split < 4) break;
+            if (!generic && base.splits == 1 && c.code == 234 && (long long)pl.tilesA * pl.tilesB > 256) return false;
+            const double t = price(g, PASS_DGRAD, c, pl, restr) + (pl.splits > 1 ? 1.5 : 0.0);
+            if (!found || t < best) { best = t; *out = pl; found = true; }
+        }
+    return found && (generic || strided || best < 0.92 * time);
+}
+
+// Fills *pl with the cheapest eligible fast-path plan; false if the shape has none.
+bool auto_plan(const ConvGeom &g, int pass, int force_splits, GemmPlan *pl, int restr, double *time)
+{
+    return auto_plan_list(g, pass, force_splits, pl, 1, restr, time) == 1;
 }

@@ -200,3 +200,21 @@ def test_pixel_strip_plan_rules(dp):
     finally:
         dp.dp_set_override(1, -1, 0)
 
+
+
+def test_flat_walk_backward_data_plan_rules(dp):
+    """Host logic of the kernel choice (no GPU call): where 64 does not divide c_out, the flat-walk kernels take the place of the generic
+    kernel and of split 64x128 tiles of 32-wide steps, and of no kernel that is faster than they are."""
+    def name(n, h, c, k, r, s, stride=(1, 1), pad=(0, 0)):
+        return dp.dp_conv2d_kernel_info(dp.conv_desc(n, h, h, c, k, r, s, stride, pad, dp.DP_BF16, dp.DP_RELU | dp.DP_RELU_IN), 1)[0]
+    assert name(30, 27, 352, 352, 1, 3, pad=(0, 1)).startswith("k_dgrad_dma<128, 128, 32")       # flat 42 us against 29
+    assert name(25, 30, 384, 352, 1, 7, pad=(0, 3)).startswith("k_dgrad_dma<128, 128, 32")       # 82 against 60
+    assert name(25, 17, 288, 352, 1, 3, pad=(0, 1)).startswith("k_dgrad_dma<64, 128, 32")        # 19.7 against 17.7
+    assert name(27, 11, 96, 96, 1, 3, pad=(0, 1)).startswith("k_conv_fast<1, 64, 64, 32")        # 7.7 against 6.0
+    assert name(7, 11, 96, 288, 1, 3, pad=(0, 1)).startswith("k_conv_fast<1, 64, 64, 32")        # 10.1 against 8.9
+    assert name(6, 9, 16, 16, 1, 1).startswith("k_conv_gemm<1")
+    assert name(15, 56, 208, 400, 3, 3, pad=(1, 1)).startswith("k_dgrad_mix<")                   # 118 against 282
+    assert name(5, 109, 144, 240, 5, 5, (2, 2), (1, 1)).startswith("k_dgrad_mix<")               # 89 against 540
+    assert name(12, 14, 320, 288, 1, 7, pad=(0, 3)).startswith("k_dgrad_mix<")                   # 14.3 against 20.4 in five splits
+    assert name(2, 17, 400, 288, 3, 3, (2, 2), (1, 1)).startswith("k_dgrad_mix<")                # 12 against 18
+    assert not name(16, 17, 160, 192, 7, 1, pad=(3, 0)).startswith("k_dgrad_mix<")               # 64 divides c_out
