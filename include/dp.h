@@ -80,8 +80,10 @@ typedef struct {
     uint32_t flags;   /* DP_BIAS, DP_RELU, DP_DX_F32, DP_RELU_IN */
 } dp_linear_desc;
 
-/* Bytes of device scratch the given pass (DP_PASS_*) of this layer needs.
- * 0 is a valid answer.  Returns 0 for an invalid descriptor. */
+/* Bytes of device scratch with which the given pass (DP_PASS_*) of this layer runs its fastest kernels.
+ * 0 is a valid answer.  Returns 0 for an invalid descriptor.  Some layers have a slower form that takes less
+ * (down to nothing): a call with less scratch runs that form, and is rejected with DP_ERR_WORKSPACE only if no form
+ * fits.  The sums of two forms are associated differently, so their results can differ in the last bits. */
 size_t dp_conv2d_workspace_bytes(const dp_conv_desc *desc, int pass);
 size_t dp_linear_workspace_bytes(const dp_linear_desc *desc);
 

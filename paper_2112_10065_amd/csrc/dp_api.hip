@@ -151,7 +151,7 @@ bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 constexpr long long kMaxElems = (1ll << 31) - 1;
 constexpr unsigned kKnownFlags = DP_BIAS | DP_RELU | DP_DETERMINISTIC | DP_DX_F32 | DP_RELU_IN;
 // kernels a backward-data call may not use: bit 0 the input-patch kernels (they stage bf16, the caller wants fp32),
-// bit 1 the stationary-weight kernel (it has no fused input-ReLU mask)
+// bit 1 the stationary-weight kernel (it has no fused input-ReLU mask); dgrad_choice adds bit 4 (dp_kernels.h)
 int dgrad_restr(unsigned flags) { return ((flags & DP_DX_F32) ? 1 : 0) | ((flags & DP_RELU_IN) ? 2 : 0); }
 
 dp_status check_conv(const dp_conv_desc *d, ConvGeom *g)
@@ -211,6 +211,7 @@ void plan_uncached(const ConvGeom &g, int pass, int fv, int fs, GemmPlan *pl, in
     pl->halo = false;
     pl->wstrip = false;
     pl->fused_reduce = false;
+    pl->over_generic = false;
     // 1000 + v: variant v with the split reduction fused into the main kernel (pipelined forward / backward-data).  Only a forced
     // variant asks for it: in a chain of calls it measured no faster than the second kernel it saves (-0.2 .. +3.5 us per call),
     // because partial sums cross compute dies through memory (write-through stores, a device-scope counter, device-scope loads)
@@ -224,7 +225,11 @@ void plan_uncached(const ConvGeom &g, int pass, int fv, int fs, GemmPlan *pl, in
         double time = 0.0;
         if (!auto_plan(g, pass, fs, pl, restr, &time)) mfma_plan(g, pass, -1, fs, pl);
         GemmPlan flat;
-        if (fs <= 0 && ((pass == PASS_FWD && forward_flat_plan(g, *pl, &flat)) || (pass == PASS_DGRAD && backward_flat_plan(g, *pl, time, restr, &flat)))) *pl = flat;
+        if (fs <= 0 && ((pass == PASS_FWD && forward_flat_plan(g, *pl, &flat)) ||
+                        (pass == PASS_DGRAD && !(restr & RESTR_BASE) && backward_flat_plan(g, *pl, time, restr, &flat)))) {
+            flat.over_generic = !pl->fast;
+            *pl = flat;
+        }
         return;
     }
     // a forced input-patch variant the call may not use falls through to the next family
@@ -536,12 +541,41 @@ dp_status run_fwd(const ConvGeom &g, int dtype, unsigned flags, const void *x, c
     return e == hipSuccess ? DP_OK : hip_fail(e, "forward launch");
 }
 
+// Scratch of one backward-data call: split partials and room for the masked gradient (reserved whether or not this call masks; a flat
+// kernel in the place of the generic one, which masks while it loads, asks for it only when it is used).
+size_t dgrad_need(const ConvGeom &g, PlanEntry &pe, bool saved)
+{
+    const GemmPlan pl = current_plan(pe);
+    return round256(pe.part_cap) + (pl.fast && (saved || !pl.over_generic) ? round256(ybytes(g)) : 0);
+}
+
+// The plan of a call that has `ws_bytes` of scratch and the bytes it takes: the fastest one, or the base plan where that one's scratch is
+// not there (the flat kernels and the rules after them may ask for more than the kernels they replace).
+PlanRef dgrad_choice(const ConvGeom &g, int restr, bool saved, size_t ws_bytes, size_t *need)
+{
+    PlanRef ep = plan_entry(g, PASS_DGRAD, restr);
+    *need = dgrad_need(g, *ep, saved);
+    if (ws_bytes >= *need) return ep;
+    PlanRef base = plan_entry(g, PASS_DGRAD, restr | RESTR_BASE);
+    const size_t b = dgrad_need(g, *base, saved);
+    if (b < *need) { *need = b; return base; }
+    return ep;
+}
+
+// what the fastest plan takes, with and without a saved output (the query), and the least a call can do with
 size_t dgrad_ws_bytes(const ConvGeom &g, int restr)
 {
-    const PlanRef pep = plan_entry(g, PASS_DGRAD, restr);
-    size_t need = round256(pep->part_cap);
-    if (current_plan(*pep).fast) need += round256(ybytes(g));   // room for the masked gradient
-    return need;
+    size_t with, without;
+    dgrad_choice(g, restr, true, (size_t)-1, &with);
+    dgrad_choice(g, restr, false, (size_t)-1, &without);
+    return std::max(with, without);
+}
+size_t dgrad_least_ws_bytes(const ConvGeom &g, int restr)
+{
+    size_t with, without;
+    dgrad_choice(g, restr, true, 0, &with);
+    dgrad_choice(g, restr, false, 0, &without);
+    return std::max(with, without);
 }
 
 // xin: the layer's saved input when flags has DP_RELU_IN (dx *= [xin > 0]), else ignored
@@ -579,10 +613,10 @@ dp_status run_dgrad(const ConvGeom &g, int dtype, unsigned flags, const void *dy
     ConvArgs a{};
     a.g = g; a.pass = PASS_DGRAD; a.flags = ((flags & DP_DX_F32) ? KF_OUT_F32 : 0u) | (xin != nullptr ? KF_MASK_IN : 0u);
     a.x = (const bf16_t *)xin;
-    const PlanRef pep = plan_entry(g, PASS_DGRAD, dgrad_restr(flags));
+    size_t need = 0;
+    const PlanRef pep = dgrad_choice(g, dgrad_restr(flags), ym != nullptr, ws != nullptr ? ws_bytes : 0, &need);
     PlanEntry &pe = *pep;
     a.plan = current_plan(pe);
-    size_t need = dgrad_ws_bytes(g, dgrad_restr(flags));
     if (need > 0 && (ws == nullptr || ws_bytes < need)) return fail(DP_ERR_WORKSPACE, "backward-data needs %zu workspace bytes, got %zu", need, ws_bytes);
     a.dy = (const bf16_t *)dy; a.ymask = (const bf16_t *)ym; a.w = (const bf16_t *)w; a.out = dx; a.partial = (float *)ws;
     if (a.plan.fast && ym != nullptr) {
@@ -889,15 +923,15 @@ size_t dp_conv2d_workspace_bytes(const dp_conv_desc *desc, int pass)
     return dgrad_ws_bytes(g, dgrad_restr(desc->flags));
 }
 
-// what the three passes one after the other need
-static size_t linear_passes_ws_bytes(const dp_linear_desc *desc)
+// what the three passes one after the other need (least: with the backward-data plan that asks for least)
+static size_t linear_passes_ws_bytes(const dp_linear_desc *desc, bool least)
 {
     ConvGeom g;
     if (check_linear(desc, &g) != DP_OK) return 0;
     size_t need = wgrad_ws_bytes(g, desc->io_dtype, true);
     if (desc->io_dtype == DP_BF16) {
         for (int pass = 0; pass < 2; ++pass) {
-            size_t b = pass == PASS_DGRAD ? dgrad_ws_bytes(g, dgrad_restr(desc->flags)) : fwd_ws_bytes(g);
+            size_t b = pass == PASS_FWD ? fwd_ws_bytes(g) : least ? dgrad_least_ws_bytes(g, dgrad_restr(desc->flags)) : dgrad_ws_bytes(g, dgrad_restr(desc->flags));
             if (b > need) need = b;
         }
     }
@@ -908,7 +942,7 @@ size_t dp_linear_workspace_bytes(const dp_linear_desc *desc)
 {
     ConvGeom g;
     if (check_linear(desc, &g) != DP_OK) return 0;
-    const size_t need = linear_passes_ws_bytes(desc);
+    const size_t need = linear_passes_ws_bytes(desc, false);
     return desc->io_dtype == DP_BF16 && dense_both_shape(g) ? std::max(need, dense_both_partial_bytes(g)) : need;
 }
 
@@ -945,7 +979,8 @@ dp_status dp_conv2d_bwd_data_relu(const dp_conv_desc *desc, const void *dy, cons
     if (desc->flags & DP_RELU_IN) { if ((s = check_ptr(x_saved, "x_saved (DP_RELU_IN)")) != DP_OK) return s; }
     if ((s = check_opt(y_saved, "y_saved")) != DP_OK || (s = check_opt(ws, "ws")) != DP_OK) return s;
     if (desc->io_dtype == DP_BF16) {
-        size_t need = dgrad_ws_bytes(g, dgrad_restr(desc->flags));
+        size_t need = 0;
+        dgrad_choice(g, dgrad_restr(desc->flags), y_saved != nullptr, ws != nullptr ? ws_bytes : 0, &need);
         if (need > 0 && (ws == nullptr || ws_bytes < need)) return fail(DP_ERR_WORKSPACE, "backward-data needs %zu workspace bytes, got %zu", need, ws_bytes);
     }
     if ((s = ensure_init()) != DP_OK) return s;
@@ -1023,7 +1058,7 @@ dp_status dp_linear_fwd_bwd(const dp_linear_desc *desc, const void *x, const voi
     if ((s = check_opt(y_saved, "y_saved")) != DP_OK || (s = check_opt(y, "y")) != DP_OK || (s = check_opt(dx, "dx")) != DP_OK ||
         (s = check_opt(dW, "dW")) != DP_OK || (s = check_opt(dbias, "dbias")) != DP_OK || (s = check_opt(ws, "ws")) != DP_OK)
         return s;
-    size_t need = linear_passes_ws_bytes(desc);
+    size_t need = linear_passes_ws_bytes(desc, true);
     if (need > 0 && (ws == nullptr || ws_bytes < need)) return fail(DP_ERR_WORKSPACE, "dense layer needs %zu workspace bytes, got %zu", need, ws_bytes);
     if ((s = ensure_init()) != DP_OK) return s;
     hipStream_t st = (hipStream_t)hip_stream;

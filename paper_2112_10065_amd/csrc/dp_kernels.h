@@ -19,6 +19,11 @@ enum : unsigned {
 
 enum { PASS_FWD = 0, PASS_DGRAD = 1, PASS_WGRAD = 2 };
 
+// bits of the planner's `restr` (0 - 2: auto_plan_list)
+enum {
+    RESTR_BASE = 16,   // the kernels and prices that need least scratch: no flat-walk kernel in backward-data
+};
+
 // Geometry of one conv layer plus its implicit-GEMM view for one pass.
 //   fwd   : A rows = c_out,  B rows = output pixels (n,p,q), reduction = (r,s,c)
 //   dgrad : A rows = c_in,   B rows = input pixels  (n,h,w), reduction = (r,s,k)
@@ -44,6 +49,7 @@ struct GemmPlan {
     bool fill = false;    // phase, 1x1 filter: only the first phase has tiles, they store the zeros of the others
     bool wstrip = false;  // filter gradient with the x strip shared by the taps of a filter row (conv_wstrip.hip); implies dma
     bool db_wave = false; // input-patch filter gradient: one more wave per block can sum the bias gradient (at most 15 taps)
+    bool over_generic = false;   // a flat-walk kernel on a layer that the generic kernel would run otherwise
     bool fused_reduce = false;   // pipelined forward / backward-data with splits > 1: no second kernel, the last block of a tile reduces (conv_dma.hip)
 };
 

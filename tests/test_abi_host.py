@@ -218,3 +218,19 @@ def test_flat_walk_backward_data_plan_rules(dp):
     assert name(12, 14, 320, 288, 1, 7, pad=(0, 3)).startswith("k_dgrad_mix<")                   # 14.3 against 20.4 in five splits
     assert name(2, 17, 400, 288, 3, 3, (2, 2), (1, 1)).startswith("k_dgrad_mix<")                # 12 against 18
     assert not name(16, 17, 160, 192, 7, 1, pad=(3, 0)).startswith("k_dgrad_mix<")               # 64 divides c_out
+
+
+def test_backward_data_scratch_is_optional_where_a_slower_form_needs_none(dp):
+    """A layer that 64 does not divide ran without scratch on the generic kernel; a faster kernel that wants some does not take that away.
+    Valid calls get as far as the missing GPU."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("would launch on the addresses made up here")
+    d = dp.conv_desc(6, 126, 126, 240, 400, 3, 3, (1, 1), (1, 1), dp.DP_BF16, dp.DP_RELU_IN)
+    assert dp.dp_conv2d_workspace_bytes(d, 1) > 0
+    for saved in (None, A):
+        assert dp.lib.dp_conv2d_bwd_data_relu(C.byref(d), A, saved, A, A, A, None, 0, None) == dp.DP_ERR_HIP
+    # a layer that always wanted scratch is rejected as before
+    d = dp.conv_desc(2, 56, 56, 64, 64, 3, 3, (1, 1), (1, 1), dp.DP_BF16, 0)
+    assert dp.dp_conv2d_workspace_bytes(d, 1) > 0
+    assert dp.lib.dp_conv2d_bwd_data(C.byref(d), A, None, A, A, None, 0, None) == dp.DP_ERR_WORKSPACE

@@ -283,6 +283,29 @@ def test_flat_forward_adds_in_the_order_of_the_kernel_it_replaces(env, n, h, w, 
         assert torch.equal(ys[0], ys[1])
 
 
+# Backward-data with the scratch of the query and with none: layers that ran without scratch before a faster kernel wanted some still do
+# (a saved output is then applied by the generic kernel while it loads dy)
+@pytest.mark.parametrize("n,h,w,c,k,r,s,st,pd,masked", [(4, 20, 20, 48, 48, 3, 3, (1, 1), (1, 1), "k_dgrad_mix<"), (1, 40, 41, 112, 48, 3, 3, (1, 1), (1, 1), "k_dgrad_mix<"),
+                                                        (2, 21, 20, 72, 16, 5, 5, (2, 2), (1, 1), "k_dgrad_mix<"), (2, 30, 30, 112, 112, 1, 1, (1, 1), (0, 0), "k_conv_gemm<")])
+def test_backward_data_without_scratch(env, n, h, w, c, k, r, s, st, pd, masked):
+    dp, U, orc = env
+    case = U.ConvCase("noscratch", n, h, w, c, k, r, s, st, pd, bf16=True, bias=False, relu=True)
+    ys = torch.from_numpy(np.maximum(orc.conv2d_fwd(case.x, case.w, None, relu=True, stride=st, pad=pd), 0)).to(U.DEV).bfloat16()
+    need = dp.dp_conv2d_workspace_bytes(case.desc, 1)
+    for saved in (None, ys):
+        ref = orc.conv2d_bwd_data(case.dy, case.w, case.x.shape, y_saved=None if saved is None else U.to_np(saved), stride=st, pad=pd)
+        for ws in (U.workspace(need), None):
+            dx = torch.full((n, h, w, c), 3.0, device=U.DEV, dtype=torch.bfloat16)
+            dp.dp_trace_begin()
+            try:
+                dp.dp_conv2d_bwd_data(case.desc, case.dyd, saved, case.wd, dx, ws)
+            finally:
+                names = [row["kernel"] for row in dp.dp_trace_end()]
+            U.assert_bf16_close(U.to_np(dx), ref, f"saved {saved is not None} scratch {ws is not None}")
+            want = "k_dgrad_mix<" if saved is None else masked if ws is not None else "k_conv_gemm<"
+            assert len(names) == 1 and names[0].startswith(want), names
+
+
 @pytest.mark.parametrize("variant", [200, 203, 207, 210, 214, 219, 221, 226, 227, 229])
 @pytest.mark.parametrize("splits", [2, 5])
 def test_split_reduction_fused_into_the_pipelined_kernels(env, variant, splits):
