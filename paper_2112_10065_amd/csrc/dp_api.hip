@@ -151,7 +151,7 @@ bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 constexpr long long kMaxElems = (1ll << 31) - 1;
 constexpr unsigned kKnownFlags = DP_BIAS | DP_RELU | DP_DETERMINISTIC | DP_DX_F32 | DP_RELU_IN;
 // kernels a backward-data call may not use: bit 0 the input-patch kernels (they stage bf16, the caller wants fp32),
-// bit 1 the stationary-weight kernel (it has no fused input-ReLU mask); dgrad_choice adds bit 4 (dp_kernels.h)
+// bit 1 the stationary-weight kernel (it has no fused input-ReLU mask); dgrad_choice adds bits 3 and 4 (dp_kernels.h)
 int dgrad_restr(unsigned flags) { return ((flags & DP_DX_F32) ? 1 : 0) | ((flags & DP_RELU_IN) ? 2 : 0); }
 
 dp_status check_conv(const dp_conv_desc *d, ConvGeom *g)
@@ -553,6 +553,7 @@ size_t dgrad_need(const ConvGeom &g, PlanEntry &pe, bool saved)
 // not there (the flat kernels and the rules after them may ask for more than the kernels they replace).
 PlanRef dgrad_choice(const ConvGeom &g, int restr, bool saved, size_t ws_bytes, size_t *need)
 {
+    if (saved && g.K % 64 != 0) restr |= RESTR_SAVED;   // the plans of other layers do not depend on it
     PlanRef ep = plan_entry(g, PASS_DGRAD, restr);
     *need = dgrad_need(g, *ep, saved);
     if (ws_bytes >= *need) return ep;

@@ -284,7 +284,7 @@ def test_flat_forward_adds_in_the_order_of_the_kernel_it_replaces(env, n, h, w, 
 
 
 # Backward-data with the scratch of the query and with none: layers that ran without scratch before a faster kernel wanted some still do
-# (a saved output is then applied by the generic kernel while it loads dy)
+# (a saved output is then applied by the generic kernel while it loads dy); the shortest masked layers keep the generic kernel anyway
 @pytest.mark.parametrize("n,h,w,c,k,r,s,st,pd,masked", [(4, 20, 20, 48, 48, 3, 3, (1, 1), (1, 1), "k_dgrad_mix<"), (1, 40, 41, 112, 48, 3, 3, (1, 1), (1, 1), "k_dgrad_mix<"),
                                                         (2, 21, 20, 72, 16, 5, 5, (2, 2), (1, 1), "k_dgrad_mix<"), (2, 30, 30, 112, 112, 1, 1, (1, 1), (0, 0), "k_conv_gemm<")])
 def test_backward_data_without_scratch(env, n, h, w, c, k, r, s, st, pd, masked):
