@@ -1581,11 +1581,6 @@ bool dma_plan(const ConvGeom &g, int pass, int force_variant, int force_splits, 
     if (splits < 1) splits = 1;
     pl->steps_per_split = (pl->steps_total + splits - 1) / splits;
     pl->splits = (pl->steps_total + pl->steps_per_split - 1) / pl->steps_per_split;
-    // backward-filter: a split count that the rounding of the steps took off a multiple of the 8 XCDs goes back up to it (the last
-    // splits are empty and add zeros): otherwise neighbouring splits of the tiles drift over the dies and each pixel range is read into
-    // several L2s (64 x 56 x 56 x 256 -> 512, 1x1 / 2: 47 splits 47.6 us,
-    // 48 splits 30.7; 64 x 28 x 28 x 128 -> 512: 61 splits 30, 64 splits 21)
-    if (pass == PASS_WGRAD && splits % 8 == 0 && pl->splits < splits) pl->splits = (pl->splits + 7) / 8 * 8;
     return true;
 }
 

@@ -276,6 +276,21 @@ GemmPlan current_plan(PlanEntry &pe)
     return pe.plan;
 }
 
+// Filter gradients of the pipelined kernels whose rounded steps took the split count off a multiple of the 8 XCDs may run with empty splits
+// that make it one again (they add zeros): otherwise neighbouring splits of the tiles drift over the dies and each pixel range is read
+// into several L2s.  That matters where the operands are more than the L2s hold together, 32 MB (as it is / rounded over 2900 drawn
+// layers: from 32 MB and 20 splits on 0.98 - 2.1, 1.35 in the mean; 20 - 30 MB 0.84 - 1.6; below, and with 7 or 13 - 15 splits, mostly slower,
+// down to 0.75).
+// The planner prices the splits that do something.
+void round_wgrad_splits(const ConvGeom &g, GemmPlan &pl)
+{
+    if (!pl.dma || pl.halo || pl.wstrip || pl.splits <= 16) return;
+    const size_t rows = std::min((long long)g.H, (long long)g.Ho * g.R), cols = std::min((long long)g.W, (long long)g.Wo * g.S);   // of x that a tap reads
+    const size_t operands = 2 * (g.N * rows * cols * g.C + (size_t)g.N * g.Ho * g.Wo * g.K);
+    const int up = (pl.splits + 7) / 8 * 8;
+    if (operands >= 32000000 && (up - pl.splits) * 6 <= up) pl.splits = up;
+}
+
 // restr: see dgrad_restr
 PlanRef plan_entry(const ConvGeom &g, int pass, int restr = 0)
 {
@@ -290,8 +305,8 @@ PlanRef plan_entry(const ConvGeom &g, int pass, int restr = 0)
     PlanRef ep = std::make_shared<PlanEntry>();
     PlanEntry &e = *ep;
     plan_uncached(g, pass, fv, fs, &e.plan, restr);
-    if (g_tight_splits && pass == PASS_WGRAD && e.plan.dma && !e.plan.halo && !e.plan.wstrip)
-        e.plan.splits = (e.plan.steps_total + e.plan.steps_per_split - 1) / e.plan.steps_per_split;
+    const bool round_splits = pass == PASS_WGRAD && fv < 0 && fs <= 0 && !g_tight_splits;
+    if (round_splits) round_wgrad_splits(g, e.plan);
     e.part_cap = mfma_partial_bytes(g, pass, e.plan);
     if (at != 0 && fv < 0 && e.plan.fast) {
         GemmPlan list[kTuneCandidates];
@@ -301,7 +316,8 @@ PlanRef plan_entry(const ConvGeom &g, int pass, int restr = 0)
         if (n > 1) {
             e.cands.assign(list, list + n);
             e.tuned = false;
-            for (const GemmPlan &c : e.cands) {
+            for (GemmPlan &c : e.cands) {
+                if (round_splits) round_wgrad_splits(g, c);
                 const size_t b = mfma_partial_bytes(g, pass, c);
                 if (b > e.part_cap) e.part_cap = b;
             }

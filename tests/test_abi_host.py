@@ -234,3 +234,19 @@ def test_backward_data_scratch_is_optional_where_a_slower_form_needs_none(dp):
     d = dp.conv_desc(2, 56, 56, 64, 64, 3, 3, (1, 1), (1, 1), dp.DP_BF16, 0)
     assert dp.dp_conv2d_workspace_bytes(d, 1) > 0
     assert dp.lib.dp_conv2d_bwd_data(C.byref(d), A, None, A, A, None, 0, None) == dp.DP_ERR_WORKSPACE
+
+
+def test_filter_gradient_split_rounding_rules(dp):
+    """Host logic of the kernel choice (no GPU call): the empty splits that make a count a multiple of eight come after the choice of the
+    plan, with operands of 32 MB and more and more than 16 splits only."""
+    def info(n, h, w, c, k, r, s, stride=1, pad=(0, 0)):
+        return dp.dp_conv2d_kernel_info(dp.conv_desc(n, h, w, c, k, r, s, (stride, stride), pad, dp.DP_BF16, 0), 2)
+    assert info(64, 56, 56, 256, 512, 1, 1, 2) == ("k_wgrad_dma<64, 128, 64, 2, 2, 2>", 48)          # 47 of them work: 47.6 -> 30.7 us
+    assert info(45, 58, 58, 256, 256, 1, 1) == ("k_wgrad_dma<64, 128, 64, 2, 2, 2>", 96)             # 95: 79 -> 38
+    assert info(17, 18, 18, 192, 224, 1, 7, pad=(0, 3)) == ("k_wgrad_dma<64, 128, 64, 2, 2, 2>", 15)   # 16 splits: 18.8 -> 22.5
+    assert info(3, 27, 27, 256, 1024, 1, 1) == ("k_wgrad_dma<64, 128, 64, 2, 2, 2>", 7)              # 8: 12.9 -> 13.6
+    assert info(4, 61, 66, 192, 128, 3, 3, pad=(1, 1)) == ("k_wgrad_dma<64, 128, 64, 2, 2, 2>", 23)  # 24: 24.1 -> 26.5
+    # priced with their empty splits these lost their plan to the register-staged kernel or to fewer splits
+    assert info(1, 43, 48, 64, 128, 3, 3, pad=(1, 1)) == ("k_wgrad_dma<64, 64, 32, 2, 2, 2>", 13)    # 9.0 against 15.2
+    assert info(2, 29, 29, 128, 384, 1, 3, pad=(0, 1)) == ("k_wgrad_dma<64, 128, 32, 2, 2, 2>", 14)  # 12.2 against 16.7
+    assert info(9, 46, 46, 640, 320, 1, 1) == ("k_wgrad_dma<64, 128, 64, 2, 2, 2>", 32)              # 30 of them work
