@@ -36,7 +36,7 @@ std::atomic<int> g_force_variant[3] = {{-1}, {-1}, {-1}};
 std::atomic<int> g_force_splits[3] = {{0}, {0}, {0}};
 std::atomic<int> g_autotune{0};
 thread_local bool g_analytic_only = false;   // the descriptor of the running call asks for DP_DETERMINISTIC
-thread_local bool g_tight_splits = false;    // the running call's scratch does not hold the empty filter-gradient splits that round a count up to whole eights
+thread_local bool g_tight_splits = false;    // filter gradients in the form that asks for least scratch (TightSplits)
 std::once_flag g_init_once;
 hipError_t g_init_err = hipSuccess;
 
@@ -647,6 +647,34 @@ dp_status run_dgrad(const ConvGeom &g, int dtype, unsigned flags, const void *dy
     return e == hipSuccess ? DP_OK : hip_fail(e, "backward-data launch");
 }
 
+// While it lives, filter gradients on this thread take the form that asks for least scratch (without the empty splits of round_wgrad_splits): for
+// calls whose scratch does not hold more
+struct TightSplits {
+    const bool before = g_tight_splits;
+    explicit TightSplits(bool on) { if (on) g_tight_splits = true; }
+    ~TightSplits() { g_tight_splits = before; }
+    TightSplits(const TightSplits &) = delete;
+};
+
+size_t wgrad_ws_bytes(const ConvGeom &g, int dtype, bool with_db);
+// a few-channel layer through the im2col matrix
+size_t im2col_wgrad_ws_bytes(const ConvGeom &g, int dtype, bool with_db)
+{
+    const int kpad = small_c_kpad(g);
+    return xcol_bytes(g, kpad) + round256((size_t)g.K * kpad * 4) + wgrad_ws_bytes(im2col_geom(g, kpad), dtype, with_db);
+}
+// a strided stem: partials of its own kernel, masked gradient, bias-gradient sums
+size_t stem_wgrad_ws_bytes(const ConvGeom &g, bool with_db)
+{
+    return round256(small_c_wgrad_stem_partial_bytes(g)) + round256(ybytes(g)) + (with_db ? rbg_workspace_bytes((long long)g.N * g.Ho * g.Wo, g.K) : 0);
+}
+// the stem kernel runs, unless the scratch is short and the im2col matrix of a few pixels is smaller than the kernel's one partial
+bool use_stem_wgrad(const ConvGeom &g, int dtype, bool with_db)
+{
+    return use_small_c(g, PASS_WGRAD) && small_c_wgrad_stem_shape(g) &&
+           !(g_tight_splits && im2col_wgrad_ws_bytes(g, dtype, with_db) < stem_wgrad_ws_bytes(g, with_db));
+}
+
 size_t wgrad_ws_bytes(const ConvGeom &g, int dtype, bool with_db)
 {
     size_t need = 0;
@@ -655,15 +683,8 @@ size_t wgrad_ws_bytes(const ConvGeom &g, int dtype, bool with_db)
         if (with_db) need += rbg_workspace_bytes((long long)g.N * g.Ho * g.Wo, g.K);
         return need;
     }
-    if (dtype == DP_BF16 && use_small_c(g, PASS_WGRAD) && small_c_wgrad_stem_shape(g)) {
-        need = round256(small_c_wgrad_stem_partial_bytes(g)) + round256(ybytes(g));   // partials, masked gradient
-        if (with_db) need += rbg_workspace_bytes((long long)g.N * g.Ho * g.Wo, g.K);
-        return need;
-    }
-    if (dtype == DP_BF16 && use_small_c(g, PASS_WGRAD)) {
-        const int kpad = small_c_kpad(g);
-        return xcol_bytes(g, kpad) + round256((size_t)g.K * kpad * 4) + wgrad_ws_bytes(im2col_geom(g, kpad), dtype, with_db);
-    }
+    if (dtype == DP_BF16 && use_stem_wgrad(g, dtype, with_db)) return stem_wgrad_ws_bytes(g, with_db);
+    if (dtype == DP_BF16 && use_small_c(g, PASS_WGRAD)) return im2col_wgrad_ws_bytes(g, dtype, with_db);
     if (dtype == DP_BF16) {
         const PlanRef pep = plan_entry(g, PASS_WGRAD);
         need = round256(pep->part_cap);
@@ -673,11 +694,20 @@ size_t wgrad_ws_bytes(const ConvGeom &g, int dtype, bool with_db)
     return need;
 }
 
+// the least a call can do with
+size_t wgrad_least_ws_bytes(const ConvGeom &g, int dtype, bool with_db)
+{
+    const TightSplits tight(true);
+    return wgrad_ws_bytes(g, dtype, with_db);
+}
+
 // workspace layout: [split partials | masked gradient (fast path) | bias-gradient scratch]
 dp_status run_wgrad(const ConvGeom &g, int dtype, const void *x, const void *dy, const void *ym, float *dw, float *db,
                     void *ws, size_t ws_bytes, hipStream_t st)
 {
     size_t need = wgrad_ws_bytes(g, dtype, db != nullptr);
+    const TightSplits tight(need > (ws != nullptr ? ws_bytes : 0));
+    if (g_tight_splits) need = wgrad_ws_bytes(g, dtype, db != nullptr);
     if (need > 0 && (ws == nullptr || ws_bytes < need)) return fail(DP_ERR_WORKSPACE, "backward-filter needs %zu workspace bytes, got %zu", need, ws_bytes);
     const long long rows = (long long)g.N * g.Ho * g.Wo;
     TraceScope ts(PASS_WGRAD, st);
@@ -719,7 +749,7 @@ dp_status run_wgrad(const ConvGeom &g, int dtype, const void *x, const void *dy,
         }
         return DP_OK;
     }
-    if (use_small_c(g, PASS_WGRAD) && small_c_wgrad_stem_shape(g)) {
+    if (use_stem_wgrad(g, dtype, db != nullptr)) {
         const size_t part = round256(small_c_wgrad_stem_partial_bytes(g));
         void *gbuf = (char *)ws + part;
         float *rws = (float *)((char *)gbuf + round256(ybytes(g)));
@@ -940,12 +970,12 @@ size_t dp_conv2d_workspace_bytes(const dp_conv_desc *desc, int pass)
     return dgrad_ws_bytes(g, dgrad_restr(desc->flags));
 }
 
-// what the three passes one after the other need (least: with the backward-data plan that asks for least)
+// what the three passes one after the other need (least: with the plans that ask for least)
 static size_t linear_passes_ws_bytes(const dp_linear_desc *desc, bool least)
 {
     ConvGeom g;
     if (check_linear(desc, &g) != DP_OK) return 0;
-    size_t need = wgrad_ws_bytes(g, desc->io_dtype, true);
+    size_t need = least ? wgrad_least_ws_bytes(g, desc->io_dtype, true) : wgrad_ws_bytes(g, desc->io_dtype, true);
     if (desc->io_dtype == DP_BF16) {
         for (int pass = 0; pass < 2; ++pass) {
             size_t b = pass == PASS_FWD ? fwd_ws_bytes(g) : least ? dgrad_least_ws_bytes(g, dgrad_restr(desc->flags)) : dgrad_ws_bytes(g, dgrad_restr(desc->flags));
@@ -1012,7 +1042,7 @@ dp_status dp_conv2d_bwd_filter(const dp_conv_desc *desc, const void *x, const vo
     if ((s = check_conv(desc, &g)) != DP_OK) return s;
     if ((s = check_ptr(x, "x")) != DP_OK || (s = check_ptr(dy, "dy")) != DP_OK || (s = check_ptr(dw, "dw")) != DP_OK) return s;
     if ((s = check_opt(y_saved, "y_saved")) != DP_OK || (s = check_opt(dbias, "dbias")) != DP_OK || (s = check_opt(ws, "ws")) != DP_OK) return s;
-    size_t need = wgrad_ws_bytes(g, desc->io_dtype, dbias != nullptr);
+    size_t need = wgrad_least_ws_bytes(g, desc->io_dtype, dbias != nullptr);
     if (need > 0 && (ws == nullptr || ws_bytes < need)) return fail(DP_ERR_WORKSPACE, "backward-filter needs %zu workspace bytes, got %zu", need, ws_bytes);
     if ((s = ensure_init()) != DP_OK) return s;
     return run_wgrad(g, desc->io_dtype, x, dy, y_saved, dw, dbias, ws, ws_bytes, (hipStream_t)hip_stream);
@@ -1028,12 +1058,7 @@ dp_status dp_conv2d_bwd_filter_noalloc(const dp_conv_desc *desc, const void *x, 
     g_analytic_only = true;
     if ((s = check_ptr(x, "x")) != DP_OK || (s = check_ptr(dy, "dy")) != DP_OK || (s = check_ptr(dw, "dw")) != DP_OK) return s;
     if ((s = check_opt(y_saved, "y_saved")) != DP_OK || (s = check_opt(dbias, "dbias")) != DP_OK) return s;
-    size_t need = wgrad_ws_bytes(g, desc->io_dtype, dbias != nullptr);
-    struct Tight { ~Tight() { g_tight_splits = false; } } until_return;
-    if (need > kNoAllocScratchBytes) {
-        g_tight_splits = true;
-        need = wgrad_ws_bytes(g, desc->io_dtype, dbias != nullptr);
-    }
+    size_t need = wgrad_least_ws_bytes(g, desc->io_dtype, dbias != nullptr);
     if (need > kNoAllocScratchBytes)
         return fail(DP_ERR_WORKSPACE, "backward-filter of this layer needs %zu scratch bytes, the built-in scratch holds %zu: use dp_conv2d_bwd_filter with a workspace",
                     need, kNoAllocScratchBytes);

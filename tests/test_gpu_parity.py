@@ -145,6 +145,20 @@ def test_strided_stems(env, n, h, w, c, k, r, s, st, pd):
     assert np.array_equal(U.to_np(dw_nan)[clean], U.to_np(dw)[clean])
 
 
+@pytest.mark.parametrize("n,h,w,c,k,r,s,st,pd,short", [(1, 7, 9, 2, 8, 7, 6, (2, 2), (0, 1), 20480), (2, 9, 13, 2, 8, 7, 9, (2, 3), (1, 1), 25600)])
+def test_smallest_stems_with_the_scratch_of_the_im2col_matrix(env, n, h, w, c, k, r, s, st, pd, short):
+    dp, U, orc = env
+    case = U.ConvCase("stemws", n, h, w, c, k, r, s, st, pd, bf16=True, bias=False, relu=False, dx_f32=True)
+    full = dp.dp_conv2d_workspace_bytes(case.desc, 2)
+    assert full > short
+    ref, ref_db = orc.conv2d_bwd_filter(case.x, case.dy, case.w.shape, stride=st, pad=pd, want_db=True)
+    for ws in (full, short):
+        dw, db = case.run_wgrad(None, ws=U.workspace(ws))
+        torch.cuda.synchronize()
+        U.assert_bf16_close(U.to_np(dw), ref, f"dw {ws}")
+        U.assert_bf16_close(U.to_np(db), ref_db, f"db {ws}")
+
+
 @pytest.mark.parametrize("variant", [0, 1, 2, 3, 4])
 @pytest.mark.parametrize("splits", [1, 3])
 def test_every_tile_variant_and_split(env, variant, splits):
