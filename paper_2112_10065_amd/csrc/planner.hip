@@ -8,6 +8,7 @@
 //   t            = launch + waves(blocks / concurrent) * t_block + t_reduce(splits)
 //   t_reduce     = second kernel that sums the fp32 partials: launch + (splits + 1) * out bytes / BW
 #include "dp_kernels.h"
+#include <algorithm>
 #include <cmath>
 
 namespace {
@@ -35,7 +36,7 @@ const Candidate kPix[] = {
     {205, 4, 0.85f, 4.0f},
     {213, 3, 1.30f, 4.5f},
     {210, 1, 1.15f, 6.0f},   // 128x256x64, 8 waves
-    {212, 2, 1.30f, 8.0f},   // 64x256x64 (backward-data of memory-bound 1x1 layers: 89 us masked where 64x128 takes 52); forward: see price()
+    {212, 2, 1.30f, 4.5f},   // 64x256x64
     {221, 1, 0.70f, 4.0f},   // reduction step 128 (channels % 128 only): fewer, longer steps for small grids
     {225, 1, 0.70f, 4.0f},
     {222, 1, 1.10f, 4.5f},
@@ -111,13 +112,19 @@ double price(const ConvGeom &g, int pass, const Candidate &c, const GemmPlan &pl
     // a step of reduction length 32 costs about half of a 64 step for the pixel passes
     double t_step = c.t_step;
     if (pass != PASS_WGRAD && pl.BK == 32) t_step *= 0.6;
-    // the saved input of a masked tile, read while nothing else runs on the CU (the strip kernels fetch it ahead): 128 KB at a CU's
-    // share of the memory rate (64 x 56 x 56 x 256 <- 128, 1x1: 256 x 256 tiles 59 us, 64 x 128 tiles 52)
-    const bool lone_mask = pass == PASS_DGRAD && (restr & 2) && c.bpc == 1 && pl.splits == 1 && c.code >= 200 && c.code < 230;
-    // 64x256 tiles forward: the choice between tiles whose sums run in different orders stays where it was (forward_flat_plan says why)
-    const double t0 = c.code == 212 && pass == PASS_FWD ? 4.5 : c.t0;
-    const double t_block = t0 + (lone_mask ? 3.5 * pl.TA * pl.TB / 65536.0 : 0.0) + (pl.steps_per_split + c.kg - 1) / c.kg * t_step * share;
+    // 64x256 tiles in backward-data, short reductions and more than one round: prologue and epilogue weigh more (45 drawn layers against the
+    // tiles that replace them: 0.95 - 3.7, 1.25 in the mean).  Not forward: its sums keep their order (forward_flat_plan)
+    const bool wide = c.code == 212 && pass == PASS_DGRAD && !(restr & RESTR_BASE) && (g.R * g.S == 1 || blocks > conc);
+    const double t_block = (wide ? 8.0 : c.t0) + (pl.steps_per_split + c.kg - 1) / c.kg * t_step * share;
     double t = 3.0 + waves * t_block;
+    // The saved input of a masked backward-data tile, read while nothing else runs on the CU and the next tile waits (the strip kernels
+    // fetch it ahead, a single round of blocks has no next tile): 3.5 us for the 128 KB of a 256x256 tile at a CU's share of the memory
+    // rate.  It decides only by 5 % (10 % for fp32 gradients): nearer, the tiles that replace these are as often slower (64 x 56 x 56 x 256 <- 128,
+    // 1x1: 59 us, 52; 60 drawn layers 0.97 - 1.4, 1.13 in the mean).  Not where the input-patch kernels would win by it: they read
+    // the mask no better (24 x 65 x 65 x 256 <- 64: 31 us, 46)
+    const bool lone_mask = pass == PASS_DGRAD && (restr & 2) && !(restr & RESTR_BASE) && c.bpc == 1 && pl.splits == 1 && blocks > 256.0 &&
+                           c.code >= 200 && c.code < 230 && (g.K != 64 || g.sh > 1 || g.sw > 1);
+    if (lone_mask) t = std::max(t, ((restr & 1) ? 0.90 : 0.95) * (3.0 + waves * (t_block + 3.5 * pl.TA * pl.TB / 65536.0)));
     if (pl.splits > 1) {
         double out_elems = pass == PASS_FWD ? (double)g.N * g.Ho * g.Wo * g.K
                          : pass == PASS_DGRAD ? (double)g.N * g.H * g.W * g.C
