@@ -252,7 +252,8 @@ bool forward_flat_plan(const ConvGeom &g, const GemmPlan &base, GemmPlan *out)
 // that is faster.  Nothing depends on the order of these sums, so the splits are free.  Measured over 385 layers:
 //   generic kernel: 1.01 - 5.9 times as fast; up to 32 input channels and under 3 steps 0.70 - 1.54, left alone.  With a saved output
 //     the generic kernel masks dy while it loads and a flat one needs a pass over dy first (2 us and the traffic, 3 - 12 us for a small gradient):
-//     under 7 steps 0.33 - 2.2, from there on 1.08 - 3.9, but for small gradients that the generic kernel splits (0.74 - 1.2)
+//     under 7 steps 0.33 - 2.2, from there on 1.08 - 3.9, but for small gradients of 1x1 layers and of those that the
+//     generic kernel splits (0.74 - 1.2)
 //   64x64 register-staged tiles: 0.74 - 0.89 up to 7 steps, 0.93 - 1.15 beyond, left alone; 128x128 pipelined: 0.80 - 1.09, left alone
 //   64x128 pipelined, unit stride: unsplit 0.76 - 1.07, left alone; split 0.96 - 1.5, taken where the prices are 8 % apart (then 1.04 - 1.5)
 //   64x128 pipelined, stride 2 (by phase): split 1.2 - 1.5; unsplit from 5 steps on and in one block per CU 1.14 - 1.25, else 0.86 - 1.18
@@ -264,7 +265,7 @@ bool backward_flat_plan(const ConvGeom &g, const GemmPlan &base, double time, in
     const int steps = (g.R * g.S * g.K + 63) / 64;
     if (generic) {
         if (g.C <= 32 && steps < 3) return false;
-        if ((restr & RESTR_SAVED) && (steps < 7 || (base.splits > 1 && (long long)g.N * g.Ho * g.Wo * g.K < 98304))) return false;
+        if ((restr & RESTR_SAVED) && (steps < 7 || ((base.splits > 1 || g.R * g.S == 1) && (long long)g.N * g.Ho * g.Wo * g.K < 98304))) return false;
     } else {
         if (!base.dma || base.TA != 64 || base.TB != 128) return false;
         if (base.splits == 1 && (!strided || g.R * g.S == 1 || steps < 5)) return false;
