@@ -1508,7 +1508,7 @@ static int phase_layout(const ConvGeom &g, int TB, int BK, int tile0[5], int *ma
     return nph;
 }
 
-bool dma_plan(const ConvGeom &g, int pass, int force_variant, int force_splits, GemmPlan *pl)
+bool dma_plan(const ConvGeom &g, int pass, int force_variant, int force_splits, GemmPlan *pl, bool f32_out)
 {
     if (g.R * g.S > 32) return false;
     int rowsA, rowsB, red;
@@ -1545,11 +1545,11 @@ bool dma_plan(const ConvGeom &g, int pass, int force_variant, int force_splits, 
     pl->tilesA = (rowsA + d->TA - 1) / d->TA;
     pl->tilesB = (rowsB + d->TB - 1) / d->TB;
     pl->steps_total = (red + d->BK - 1) / d->BK;
-    if (pass == PASS_DGRAD && (g.sh > 1 || g.sw > 1) && g.sh <= 2 && g.sw <= 2 && force_splits <= 1) {
+    if (pass == PASS_DGRAD && (g.sh > 1 || g.sw > 1) && g.sh <= 2 && g.sw <= 2 && force_splits <= 1 && !(f32_out && g.R * g.S == 1)) {
         // no reduction split asked for: walk the pixels phase by phase and multiply only the taps that can hit.  A 1x1 filter
         // without padding reaches the first phase only: its tiles alone run, and store the zeros of the other phases next to their own
         // pixels (64 x 56 x 56 x 256 <- 512, stride 2, masked: all pixels multiplied 104 us, every phase with tiles of its own 88, this
-        // 37)
+        // 37).  fp32 gradients are stored in natural pixel order: a 1x1 filter is planned that way too, with its splits.
         int tile0[5], max_steps;
         phase_layout(g, d->TB, d->BK, tile0, &max_steps);
         if (max_steps > 0 && tile0[4] > 0) {

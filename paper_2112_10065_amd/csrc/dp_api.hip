@@ -238,7 +238,7 @@ void plan_uncached(const ConvGeom &g, int pass, int fv, int fs, GemmPlan *pl, in
     // the pixel-strip kernel stages bf16 only: not for fp32 input gradients
     // (nor the flat-reduction kernels for fp32 input gradients of strided layers)
     const bool f32_banned = pass == PASS_DGRAD && (restr & 1) && ((fv >= 230 && fv <= 233) || (fv >= 234 && fv <= 239 && (g.sh > 1 || g.sw > 1)));
-    if (fv >= 200 && !f32_banned && dma_plan(g, pass, fv, fs, pl)) return;
+    if (fv >= 200 && !f32_banned && dma_plan(g, pass, fv, fs, pl, pass == PASS_DGRAD && (restr & 1))) return;
     if (fv >= 100 && fast_plan(g, pass, fv, fs, pl)) return;
     mfma_plan(g, pass, fv >= 100 ? -1 : fv, fs, pl);
 }

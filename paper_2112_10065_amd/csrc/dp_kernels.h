@@ -101,7 +101,7 @@ bool plan_sums_bias_gradient(const GemmPlan &plan);
 
 // conv_dma.hip : multi-stage direct-to-LDS pipeline (forward, c_in % 64 == 0)
 hipError_t dma_init();
-bool dma_plan(const ConvGeom &g, int pass, int force_variant, int force_splits, GemmPlan *plan);
+bool dma_plan(const ConvGeom &g, int pass, int force_variant, int force_splits, GemmPlan *plan, bool f32_out = false);   // f32_out: fp32 input gradient
 hipError_t dma_launch(const ConvArgs &a, hipStream_t st);
 void dma_kernel_name(int pass, const GemmPlan &plan, char *name, size_t name_bytes);
 

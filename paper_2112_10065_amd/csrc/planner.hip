@@ -87,12 +87,12 @@ const Candidate kWg[] = {
 };
 const int kSplits[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 48, 64, 96, 128, 192, 256};
 
-bool family_plan(const ConvGeom &g, int pass, int code, int splits, GemmPlan *pl)
+bool family_plan(const ConvGeom &g, int pass, int code, int splits, GemmPlan *pl, int restr = 0)
 {
     pl->halo = false;
     pl->wstrip = false;
     if (code >= 400) return halo_plan(g, pass, code, splits, pl);
-    if (code >= 200) return dma_plan(g, pass, code, splits, pl);
+    if (code >= 200) return dma_plan(g, pass, code, splits, pl, (restr & 1) != 0);
     return fast_plan(g, pass, code, splits, pl);
 }
 
@@ -150,12 +150,12 @@ int auto_plan_list(const ConvGeom &g, int pass, int force_splits, GemmPlan *out,
         if (rowsB <= 64) {
             for (int code : {207, 103}) {
                 GemmPlan one;
-                if (!family_plan(g, pass, code, 1, &one)) continue;
+                if (!family_plan(g, pass, code, 1, &one, restr)) continue;
                 const long long tiles = (long long)one.tilesA * one.tilesB;
                 int splits = (int)((512 + tiles - 1) / tiles), max_splits = one.steps_total / 8;
                 if (max_splits < 1) max_splits = 1;
                 if (splits > max_splits) splits = max_splits;
-                if (family_plan(g, pass, code, splits, &all[n].pl)) { all[n].t = 0.0; all[n].code = code; ++n; break; }
+                if (family_plan(g, pass, code, splits, &all[n].pl, restr)) { all[n].t = 0.0; all[n].code = code; ++n; break; }
             }
         }
     }
@@ -171,7 +171,7 @@ int auto_plan_list(const ConvGeom &g, int pass, int force_splits, GemmPlan *out,
             // split count is a multiple of the 8 XCDs
             if (pass == PASS_WGRAD && force_splits <= 0 && s > 8 && (s % 8) != 0) continue;
             GemmPlan cand;
-            if (!family_plan(g, pass, cands[ci].code, force_splits > 0 ? force_splits : s, &cand)) break;
+            if (!family_plan(g, pass, cands[ci].code, force_splits > 0 ? force_splits : s, &cand, restr)) break;
             // reduction step 32 only where 64 does not divide the channel count
             if (pass != PASS_WGRAD && cand.BK == 32 && ((pass == PASS_FWD ? g.C : g.K) % 64) == 0) break;
             if (cand.splits == last_splits) continue;   // the request was clamped to the same plan
@@ -275,7 +275,7 @@ bool backward_flat_plan(const ConvGeom &g, const GemmPlan &base, double time, in
     for (const Candidate &c : kFlatBwd)
         for (int s : kSplits) {
             GemmPlan pl;
-            if ((s > 1 && (strided || c.kg > 1)) || !family_plan(g, PASS_DGRAD, c.code, s, &pl)) break;
+            if ((s > 1 && (strided || c.kg > 1)) || !family_plan(g, PASS_DGRAD, c.code, s, &pl, restr)) break;
             if (pl.splits > 1 && pl.steps_per_split < 4) break;
             if (!generic && base.splits == 1 && c.code == 234 && (long long)pl.tilesA * pl.tilesB > 256) return false;
             const double t = price(g, PASS_DGRAD, c, pl, restr) + (pl.splits > 1 ? 1.5 : 0.0);
