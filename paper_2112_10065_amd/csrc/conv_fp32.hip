@@ -58,6 +58,36 @@ template <bool V4> DEVFN f32x4 load4(const float *p, const float *safe, int vali
     return v;
 }
 
+// One output from the taps that reach it, one after the other: what a tile's product does not give when a weight is infinite or NaN.  A tap
+// outside the image (or off the stride grid) supplies a zero to the matrix instruction, and zero times infinity is NaN.  Costs what a
+// plain loop costs, and only where the product is NaN.
+template <bool DG, bool MASK> DEVFN float sum_of_reached_taps(const F32Args &p, int pix, int ch)
+{
+    const ConvGeom &g = p.g;
+    const int n = p.plane.div(pix), rem = pix - n * (int)p.plane.d, pr = p.row.div(rem), pc = rem - pr * (int)p.row.d;
+    const int Hl = DG ? g.Ho : g.H, Wl = DG ? g.Wo : g.W;
+    float s = 0.f;
+    for (int r = 0; r < g.R; ++r)
+        for (int t = 0; t < g.S; ++t) {
+            int hh = DG ? pr + g.ph - r : pr * g.sh - g.ph + r, ww = DG ? pc + g.pw - t : pc * g.sw - g.pw + t;
+            if constexpr (DG) {
+                if (hh < 0 || ww < 0) continue;
+                const int hq = p.sh.div(hh), wq = p.sw.div(ww);
+                if (hq * g.sh != hh || wq * g.sw != ww) continue;
+                hh = hq; ww = wq;
+            }
+            if ((unsigned)hh >= (unsigned)Hl || (unsigned)ww >= (unsigned)Wl) continue;
+            const size_t o = (((size_t)n * Hl + hh) * Wl + ww) * p.red;
+            const int tap = r * g.S + t;
+            for (int c = 0; c < p.red; ++c) {
+                float b = p.b[o + c];
+                if constexpr (MASK) b = p.mask[o + c] > 0.f ? b : 0.f;
+                s = fmaf(b, p.w[DG ? ((size_t)c * g.R * g.S + tap) * g.C + ch : ((size_t)ch * g.R * g.S + tap) * g.C + c], s);
+            }
+        }
+    return s;
+}
+
 // Forward and backward-data: D[channel][pixel] = sum over (tap, reduction channel).  DG: backward-data (pixel operand dy, filter
 // taps addressed through the stride); MASK: dy counts where the saved output is > 0.  Everything that decides which loads
 // happen is a template parameter or an address select: a branch in the loop body would make every load wait for the one before.  J: pixel fragments of 16 per wave: 1 while the grid is small, 4 where there are enough tiles
@@ -142,21 +172,34 @@ __global__ __launch_bounds__(64 * kPixWaves) void k_f32_pix(const F32Args p)
     if (wave > 0) return;
     // register v of lane l: channel 4 * (l / 16) + v, pixel l % 16
     const int ch = a0 + 4 * lg;
+    auto store = [&](const F32Args &q, float r, int pix, int c) {
+        const size_t o = (size_t)pix * q.rowsA + c;
+        if (q.flags & KF_BIAS) r += q.bias[c];
+        if ((q.flags & KF_RELU) && !(r > 0.f)) r = 0.f;
+        if (q.xin != nullptr && !(q.xin[o] > 0.f)) r = 0.f;   // backward of the ReLU that produced the layer's input
+        q.out[o] = r;
+    };
+    unsigned nan = 0;   // products that are NaN: bit 4 * j + v
 #pragma unroll
     for (int j = 0; j < J; ++j) {
         for (int q = 0; q < kPixWaves - 1; ++q) acc[j] += part[q][j][lane];
         const int pix = b0 + j * 16 + lr;
         if (pix >= p.rowsB) continue;
-        const size_t o = (size_t)pix * p.rowsA + ch;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             if (ch + v >= p.rowsA) continue;
-            float r = acc[j][v];
-            if (p.flags & KF_BIAS) r += p.bias[ch + v];
-            if ((p.flags & KF_RELU) && !(r > 0.f)) r = 0.f;
-            if (p.xin != nullptr && !(p.xin[o + v] > 0.f)) r = 0.f;   // backward of the ReLU that produced the layer's input
-            p.out[o + v] = r;
+            nan |= acc[j][v] != acc[j][v] ? 1u << (4 * j + v) : 0u;
+            store(p, acc[j][v], pix, ch + v);
         }
+    }
+    if (nan == 0) return;
+    // rare, and at no cost in registers to the rest: a loop of its own, the arguments read afresh
+    auto args = (const __attribute__((address_space(4))) F32Args *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    const F32Args &q = *(const F32Args *)args;
+    for (; nan != 0; nan &= nan - 1) {
+        const int e = __ffs(nan) - 1, pix = b0 + (e >> 2) * 16 + lr, c = ch + (e & 3);
+        store(q, sum_of_reached_taps<DG, MASK>(q, pix, c), pix, c);
     }
 }
 
@@ -168,8 +211,9 @@ constexpr int kWgWaves = 16;
 // U: steps per wave whose loads are issued together.  A layer with few pixels has one or two steps for each of the waves and
 // takes no more (the waves of a tile share one CU, whose load rate bounds them: 2 x 16 x 16 pixels with four, two of them empty, 8.7 us, with
 // two 6.2 us).
-template <bool MASK, int U>
-__global__ __launch_bounds__(64 * kWgWaves) void k_f32_wgrad(const F32Args p, float *dbias)
+// PAD: a tap can lie outside the image.
+template <bool MASK, int U, bool PAD>
+__global__ __launch_bounds__(64 * kWgWaves, U == 4 ? 4 : 8) void k_f32_wgrad(const F32Args p, float *dbias)
 {
     const ConvGeom &g = p.g;
     __shared__ f32x4 part[kWgWaves - 1][64];
@@ -189,13 +233,14 @@ __global__ __launch_bounds__(64 * kWgWaves) void k_f32_wgrad(const F32Args p, fl
             int n = p.plane.div(m0), rem = m0 - n * (int)p.plane.d, pp = p.row.div(rem), q = rem - pp * (int)p.row.d;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const bool in = m0 + e < p.rowsB, ok = in && k < g.K;
+                // both operands are zero where the tap is outside the image (an infinite dy times zero is NaN)
+                const int ih = pp * g.sh - g.ph + tr, iw = q * g.sw - g.pw + ts;
+                const bool in = m0 + e < p.rowsB && (!PAD || ones || ((unsigned)ih < (unsigned)g.H && (unsigned)iw < (unsigned)g.W)), ok = in && k < g.K;
                 const size_t oa = ok ? (size_t)(m0 + e) * g.K + k : 0;
                 float t = p.b[oa];
                 if constexpr (MASK) t = p.mask[oa] > 0.f ? t : 0.f;
                 a[u][e] = ok ? t : 0.f;
-                const int ih = pp * g.sh - g.ph + tr, iw = q * g.sw - g.pw + ts;
-                const bool okx = in && !ones && c < g.C && (unsigned)ih < (unsigned)g.H && (unsigned)iw < (unsigned)g.W;
+                const bool okx = in && !ones && c < g.C;
                 const float x = p.w[okx ? (((size_t)n * g.H + ih) * g.W + iw) * g.C + c : 0];
                 b[u][e] = okx ? x : ones ? 1.f : 0.f;
                 const bool wrap = ++q == g.Wo;
@@ -224,6 +269,7 @@ __global__ __launch_bounds__(64 * kWgWaves) void k_f32_wgrad(const F32Args p, fl
     }
 }
 
+bool wgrad_padded(const ConvGeom &g) { return g.ph > 0 || g.pw > 0; }
 int wgrad_unroll(int pixels) { return pixels <= 16 * kWgWaves ? 1 : pixels <= 2 * 16 * kWgWaves ? 2 : 4; }
 
 bool wide_tiles(long long rowsA, long long rowsB) { return (rowsA + 15) / 16 * ((rowsB + 63) / 64) >= 1024; }   // enough 16 x 64 tiles for four blocks per CU
@@ -253,7 +299,7 @@ hipError_t launch_pix(bool dg, const F32Args &a, hipStream_t st)
 
 void f32_kernel_name(const ConvGeom &g, int pass, bool masked, char *name, size_t name_bytes)
 {
-    if (pass == PASS_WGRAD) { snprintf(name, name_bytes, "k_f32_wgrad<%s, %d>", masked ? "true" : "false", wgrad_unroll(g.N * g.Ho * g.Wo)); return; }
+    if (pass == PASS_WGRAD) { snprintf(name, name_bytes, "k_f32_wgrad<%s, %d, %s>", masked ? "true" : "false", wgrad_unroll(g.N * g.Ho * g.Wo), wgrad_padded(g) ? "true" : "false"); return; }
     const bool dg = pass == PASS_DGRAD, v4 = (dg ? g.K : g.C) % 4 == 0;
     const bool wide = dg ? wide_tiles(g.C, (long long)g.N * g.H * g.W) : wide_tiles(g.K, (long long)g.N * g.Ho * g.Wo);
     snprintf(name, name_bytes, "k_f32_pix<%s, %d, %s, %s>", dg ? "true" : "false", wide ? 4 : 1, v4 ? "true" : "false", dg && masked ? "true" : "false");
@@ -289,12 +335,15 @@ hipError_t f32_conv_wgrad(const ConvGeom &g, const float *x, const float *dy, co
     a.w = x; a.b = dy; a.mask = ymask; a.out = dw;
     const long long tiles = (long long)g.R * g.S * ((g.C + 15) / 16);
     const dim3 grid((unsigned)((g.K + 15) / 16 * (tiles + (dbias != nullptr ? 1 : 0)))), block(64 * kWgWaves);
-    auto pick = [&](auto maskc) {
-        constexpr bool MASK = decltype(maskc)::value;
+    auto pick = [&](auto maskc, auto padc) {
+        constexpr bool MASK = decltype(maskc)::value, PAD = decltype(padc)::value;
         const int u = wgrad_unroll(a.rowsB);
-        hipLaunchKernelGGL((u == 1 ? k_f32_wgrad<MASK, 1> : u == 2 ? k_f32_wgrad<MASK, 2> : k_f32_wgrad<MASK, 4>), grid, block, 0, st, a, dbias);
+        hipLaunchKernelGGL((u == 1 ? k_f32_wgrad<MASK, 1, PAD> : u == 2 ? k_f32_wgrad<MASK, 2, PAD> : k_f32_wgrad<MASK, 4, PAD>), grid, block, 0, st, a, dbias);
     };
-    if (ymask != nullptr) pick(std::true_type());
-    else pick(std::false_type());
+    const bool pad = wgrad_padded(g);
+    if (ymask != nullptr && pad) pick(std::true_type(), std::true_type());
+    else if (ymask != nullptr) pick(std::true_type(), std::false_type());
+    else if (pad) pick(std::false_type(), std::true_type());
+    else pick(std::false_type(), std::false_type());
     return hipGetLastError();
 }

@@ -82,6 +82,34 @@ def test_fp32_tile_edges(env, n, h, w, c, k, r, s, st, pd):
     check_case(dp, U, orc, case, "fp32 tile edges")
 
 
+# A weight or gradient that is infinite or NaN reaches the outputs its taps reach and no others: a tap outside the image or off the stride grid
+# takes no part
+@pytest.mark.parametrize("n,h,w,c,k,r,s,st,pd", [(2, 7, 6, 5, 7, 3, 3, (1, 1), (1, 1)), (2, 9, 8, 8, 16, 3, 3, (2, 2), (1, 1)), (1, 6, 7, 3, 4, 5, 2, (1, 3), (2, 1)),
+                                                 (4, 97, 99, 20, 33, 3, 3, (1, 1), (1, 1)), (4, 97, 99, 20, 36, 3, 3, (2, 2), (1, 1))])
+def test_fp32_non_finite_values_stay_where_their_taps_reach(env, n, h, w, c, k, r, s, st, pd):
+    dp, U, orc = env
+    def same(got, ref, what):
+        got = U.to_np(got)
+        assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref)), what
+        ok = np.isfinite(ref)
+        assert ok.any() and not ok.all(), what
+        U.assert_f32_close(got[ok], ref[ok], what)
+    for bad in (np.inf, np.nan):
+        case = U.ConvCase("f32inf", n, h, w, c, k, r, s, st, pd, bf16=False, dist="he_uniform", bias=False, relu=False)
+        case.w[1, 0, 0, 1] = bad
+        case.wd[1, 0, 0, 1] = float(bad)
+        with np.errstate(invalid="ignore"):
+            same(case.run_fwd(), orc.conv2d_fwd(case.x, case.w, None, relu=False, stride=st, pad=pd), f"y {bad}")
+            same(case.run_dgrad(None), orc.conv2d_bwd_data(case.dy, case.w, case.x.shape, stride=st, pad=pd), f"dx {bad}")
+            case = U.ConvCase("f32inf", n, h, w, c, k, r, s, st, pd, bf16=False, dist="he_uniform", bias=False, relu=False)
+            case.dy[0, 0, 0, 2] = bad
+            case.dyd[0, 0, 0, 2] = float(bad)
+            dw, db = case.run_wgrad(None)
+            ref, ref_db = orc.conv2d_bwd_filter(case.x, case.dy, case.w.shape, stride=st, pad=pd, want_db=True)
+            same(dw, ref, f"dw {bad}")
+            same(db, ref_db, f"db {bad}")
+
+
 # ---- bf16 matrix-core path: shapes that span several tiles with ragged tails ---------------
 BF16_CASES = [
     # tag, n, h, w, c, k, r, s, stride, pad, bias, relu, dx_f32
