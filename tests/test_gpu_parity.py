@@ -71,7 +71,7 @@ def test_fp32_strided_asymmetric(env):
     check_case(dp, U, orc, case, "fp32 strided")
 
 
-# fp32 tiles of 16 channels x 16 or 64 pixels, 16 reduction channels per step, 4 or 8 waves sharing a reduction: edges of each
+# fp32 tiles of 16 channels x 16 or 64 pixels, 16 reduction channels per step, 4 (filter gradient 16) waves sharing a reduction: edges of each
 @pytest.mark.parametrize("n,h,w,c,k,r,s,st,pd", [
     (1, 1, 1, 1, 1, 1, 1, (1, 1), (0, 0)), (1, 5, 7, 15, 17, 3, 3, (1, 1), (1, 1)), (2, 9, 8, 16, 33, 3, 3, (1, 1), (1, 1)),
     (3, 7, 11, 36, 20, 1, 5, (1, 1), (0, 2)), (2, 13, 10, 6, 64, 3, 2, (2, 3), (1, 0)), (1, 33, 31, 64, 4, 3, 3, (1, 1), (1, 1)),
@@ -80,6 +80,20 @@ def test_fp32_tile_edges(env, n, h, w, c, k, r, s, st, pd):
     dp, U, orc = env
     case = U.ConvCase("f32e", n, h, w, c, k, r, s, st, pd, bf16=False, dist="he_uniform", bias=True, relu=True)
     check_case(dp, U, orc, case, "fp32 tile edges")
+
+
+# tiles of 16 x 64 pixels: both directions, with and without the layer's mask, 16-byte and single loads, strided
+@pytest.mark.parametrize("n,h,w,c,k,r,s,st,pd", [(4, 97, 99, 20, 36, 3, 3, (1, 1), (1, 1)), (4, 97, 99, 19, 33, 3, 3, (1, 1), (1, 1)), (4, 97, 99, 20, 36, 3, 2, (2, 2), (1, 0)),
+                                                 (4, 97, 99, 17, 35, 2, 3, (2, 1), (0, 1))])
+def test_fp32_wide_tiles(env, n, h, w, c, k, r, s, st, pd):
+    dp, U, orc = env
+    v4 = {0: c % 4 == 0, 1: k % 4 == 0}
+    for relu in (False, True):
+        case = U.ConvCase("f32w", n, h, w, c, k, r, s, st, pd, bf16=False, dist="he_uniform", bias=True, relu=relu)
+        if st == (1, 1):
+            assert dp.dp_conv2d_kernel_info(case.desc, 0)[0] == f"k_f32_pix<false, 4, {'true' if v4[0] else 'false'}, false>"
+        assert dp.dp_conv2d_kernel_info(case.desc, 1)[0] == f"k_f32_pix<true, 4, {'true' if v4[1] else 'false'}, false>"
+        check_case(dp, U, orc, case, "fp32 wide tiles")
 
 
 # A weight or gradient that is infinite or NaN reaches the outputs its taps reach and no others: a tap outside the image or off the stride grid
