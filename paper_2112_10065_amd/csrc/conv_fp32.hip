@@ -12,6 +12,7 @@
 // + both gradients back to back: 2 x 16 x 16 x 16 -> 16: 64 -> 21 us (67 us of kernels -> three launches, host-bound);
 // 3 x 38 x 38 x 15 -> 34: 175 -> 54 us; 4 x 40 x 40 x 64 -> 64: 2612 -> 94 us (20 / 28 / 46).
 #include "tile_common.h"
+#include <algorithm>
 #include <cstdio>
 #include <type_traits>
 
@@ -38,6 +39,7 @@ struct F32Args {
     ConvGeom g;
     FastDiv plane, row, sh, sw, tap, cblk;   // pixels per image and per row of the pass's pixel grid, strides, filter columns, 16-channel blocks
     int rowsA, rowsB, red;             // output channels of the pass, pixels, reduction channels
+    int tile0;                         // first tile of this launch
     unsigned flags;
     const float *w, *b, *mask;         // weights, pixel operand (x or dy), saved output that masks dy
     const float *bias, *xin;
@@ -101,15 +103,16 @@ __global__ __launch_bounds__(64 * kPixWaves) void k_f32_pix(const F32Args p)
     __shared__ f32x4 part[kPixWaves - 1][J][64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lr = lane & 15, lg = lane >> 4;
-    const int ta = (p.rowsA + 15) >> 4, tile = blockIdx.x;
+    const int ta = (p.rowsA + 15) >> 4, tile = p.tile0 + blockIdx.x;
     const int a0 = (tile % ta) * 16, b0 = (tile / ta) * 16 * J;
     const int cblocks = (p.red + 15) >> 4, steps = g.R * g.S * cblocks;
 
     int ih0[J], iw0[J], img[J];
 #pragma unroll
     for (int j = 0; j < J; ++j) {
-        const int m = b0 + j * 16 + lr, n = p.plane.div(m), rem = m - n * (int)p.plane.d, r = p.row.div(rem), c = rem - r * (int)p.row.d;
-        img[j] = m < p.rowsB ? n : -1;
+        const int m = (int)((unsigned)b0 + j * 16 + lr);   // pixels past the last may be past 2^31: compared unsigned
+        const int n = p.plane.div(m), rem = m - n * (int)p.plane.d, r = p.row.div(rem), c = rem - r * (int)p.row.d;
+        img[j] = (unsigned)m < (unsigned)p.rowsB ? n : -1;
         ih0[j] = DG ? r + g.ph : r * g.sh - g.ph;
         iw0[j] = DG ? c + g.pw : c * g.sw - g.pw;
     }
@@ -183,8 +186,8 @@ __global__ __launch_bounds__(64 * kPixWaves) void k_f32_pix(const F32Args p)
 #pragma unroll
     for (int j = 0; j < J; ++j) {
         for (int q = 0; q < kPixWaves - 1; ++q) acc[j] += part[q][j][lane];
-        const int pix = b0 + j * 16 + lr;
-        if (pix >= p.rowsB) continue;
+        const int pix = (int)((unsigned)b0 + j * 16 + lr);
+        if ((unsigned)pix >= (unsigned)p.rowsB) continue;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             if (ch + v >= p.rowsA) continue;
@@ -235,7 +238,7 @@ __global__ __launch_bounds__(64 * kWgWaves, U == 4 ? 4 : 8) void k_f32_wgrad(con
             for (int e = 0; e < 4; ++e) {
                 // both operands are zero where the tap is outside the image (an infinite dy times zero is NaN)
                 const int ih = pp * g.sh - g.ph + tr, iw = q * g.sw - g.pw + ts;
-                const bool in = m0 + e < p.rowsB && (!PAD || ones || ((unsigned)ih < (unsigned)g.H && (unsigned)iw < (unsigned)g.W)), ok = in && k < g.K;
+                const bool in = (unsigned)m0 + e < (unsigned)p.rowsB && (!PAD || ones || ((unsigned)ih < (unsigned)g.H && (unsigned)iw < (unsigned)g.W)), ok = in && k < g.K;
                 const size_t oa = ok ? (size_t)(m0 + e) * g.K + k : 0;
                 float t = p.b[oa];
                 if constexpr (MASK) t = p.mask[oa] > 0.f ? t : 0.f;
@@ -280,8 +283,15 @@ hipError_t launch_pix(bool dg, const F32Args &a, hipStream_t st)
     const bool wide = wide_tiles(a.rowsA, a.rowsB);
     const long long tiles = ta * (wide ? ((long long)a.rowsB + 63) / 64 : ((long long)a.rowsB + 15) / 16);
     const bool v4 = a.red % 4 == 0;
-    const dim3 grid((unsigned)tiles), block(64 * kPixWaves);
-    auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, st, a); };
+    // a grid holds fewer than 2^32 threads: a layer of few channels and more than 2^30 pixels takes several launches
+    constexpr long long kMaxTiles = (1ll << 32) / (64 * kPixWaves) - 1;
+    auto run = [&](auto kernel) {
+        F32Args part = a;
+        for (long long t0 = 0; t0 < tiles; t0 += kMaxTiles) {
+            part.tile0 = (int)t0;
+            hipLaunchKernelGGL(kernel, dim3((unsigned)std::min(kMaxTiles, tiles - t0)), dim3(64 * kPixWaves), 0, st, part);
+        }
+    };
     auto pick = [&](auto dgc, auto maskc) {
         constexpr bool DG = decltype(dgc)::value, MASK = decltype(maskc)::value;
         if (wide && v4) run(k_f32_pix<DG, 4, true, MASK>);

@@ -96,6 +96,22 @@ def test_fp32_wide_tiles(env, n, h, w, c, k, r, s, st, pd):
         check_case(dp, U, orc, case, "fp32 wide tiles")
 
 
+def test_fp32_more_pixels_than_one_grid_holds(env):
+    """One channel over more than 2^30 pixels (blocks of 256 threads for 64 pixels): more threads than a launch takes."""
+    dp, U, orc = env
+    side = 32800
+    x = torch.arange(side * side, device=U.DEV, dtype=torch.int32).bitwise_and_(0xffff).float().view(1, side, side, 1)
+    y, wt = torch.zeros_like(x), torch.full((1, 1, 1, 1), 3.0, device=U.DEV)
+    d = dp.conv_desc(1, side, side, 1, 1, 1, 1, (1, 1), (0, 0), dp.DP_F32, 0)
+    dp.dp_conv2d_fwd(d, x, wt, None, y, None)
+    torch.cuda.synchronize()
+    assert torch.equal(y, x * 3.0)
+    y.zero_()
+    dp.dp_conv2d_bwd_data(d, x, None, wt, y, None)
+    torch.cuda.synchronize()
+    assert torch.equal(y, x * 3.0)
+
+
 # A weight or gradient that is infinite or NaN reaches the outputs its taps reach and no others: a tap outside the image or off the stride grid
 # takes no part
 @pytest.mark.parametrize("n,h,w,c,k,r,s,st,pd", [(2, 7, 6, 5, 7, 3, 3, (1, 1), (1, 1)), (2, 9, 8, 8, 16, 3, 3, (2, 2), (1, 1)), (1, 6, 7, 3, 4, 5, 2, (1, 3), (2, 1)),
