@@ -376,7 +376,7 @@ __global__ __launch_bounds__(64 * DF_WAVES) void k_dense_wgrad(int N, int C, int
 // column, stored per unit).  The 16-byte chunk c of row r sits at c ^ (r % 8), which both reads accept.  The block's
 // dy rows wait in LDS in fragment order, the unit's x fragments in registers.  y is then summed over the waves (in wave order) and leaves as
 // one partial per column range, dx as one per row range; k_dense_both_sum adds them in order and applies bias, ReLU and mask.
-// RT = 32 keeps the partials of dx few (8 * samples / 4096 of the weight bytes each way); layers too small to give every wave of
+// RT = 32 keeps the partials of dx few (16 * samples / 4096 of the weight bytes each way); layers too small to give every wave of
 // the chip a unit that way take RT = 8.
 // ---------------------------------------------------------------------------------------
 constexpr int DB_NS = 6;
@@ -585,11 +585,11 @@ static void dense_both_split(const ConvGeom &g, int *rt, int *row_parts, int *un
     *units_per_block = (units + cp - 1) / cp;
     *col_parts = (units + *units_per_block - 1) / *units_per_block;
 }
-size_t dense_both_partial_bytes(const ConvGeom &g)
+size_t dense_both_partial_bytes(const ConvGeom &g, bool with_y)
 {
     int rt, rp, upb, cp;
     dense_both_split(g, &rt, &rp, &upb, &cp);
-    return ((size_t)rp * g.N * g.C + (size_t)cp * g.N * g.K) * sizeof(float);
+    return ((size_t)rp * g.N * g.C + (with_y ? (size_t)cp * g.N * g.K : 0)) * sizeof(float);
 }
 hipError_t dense_both(const ConvGeom &g, const bf16_t *x, const bf16_t *dy, const bf16_t *w, float *partial, bool with_y, hipStream_t st)
 {

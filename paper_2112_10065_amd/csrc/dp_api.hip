@@ -579,12 +579,13 @@ PlanRef dgrad_choice(const ConvGeom &g, int restr, bool saved, size_t ws_bytes, 
     return ep;
 }
 
-// what the fastest plan takes, with and without a saved output (the query), and the least a call can do with
+// what the fastest form takes, with and without a saved output (the query), and the least a call can do with
 size_t dgrad_ws_bytes(const ConvGeom &g, int restr)
 {
     size_t with, without;
     dgrad_choice(g, restr, true, (size_t)-1, &with);
     dgrad_choice(g, restr, false, (size_t)-1, &without);
+    if (g_force_variant[PASS_DGRAD].load() < 0 && dense_dgrad_split_shape(g)) without = std::max(without, dense_both_partial_bytes(g, false));
     return std::max(with, without);
 }
 size_t dgrad_least_ws_bytes(const ConvGeom &g, int restr)
@@ -617,7 +618,7 @@ dp_status run_dgrad(const ConvGeom &g, int dtype, unsigned flags, const void *dy
         dp_trace_main_kernel_done(st);
         return e == hipSuccess ? DP_OK : hip_fail(e, "backward-data launch");
     }
-    if (g_force_variant[PASS_DGRAD].load() < 0 && ym == nullptr && dense_dgrad_split_shape(g) && ws != nullptr && ws_bytes >= dense_both_partial_bytes(g)) {
+    if (g_force_variant[PASS_DGRAD].load() < 0 && ym == nullptr && dense_dgrad_split_shape(g) && ws != nullptr && ws_bytes >= dense_both_partial_bytes(g, false)) {
         ts.name(dense_both_name(g, false), 1);
         ts.main_begins();
         hipError_t e = dense_both(g, nullptr, (const bf16_t *)dy, (const bf16_t *)w, (float *)ws, false, st);
@@ -931,6 +932,11 @@ dp_status dp_conv2d_kernel_info(const dp_conv_desc *desc, int pass, char *name, 
         if (splits != nullptr) *splits = 1;
         return DP_OK;
     }
+    if (pass == PASS_DGRAD && g_force_variant[PASS_DGRAD].load() < 0 && dense_dgrad_split_shape(g)) {   // likewise
+        if (name != nullptr && name_bytes > 0) snprintf(name, name_bytes, "%s", dense_both_name(g, false));
+        if (splits != nullptr) *splits = 1;
+        return DP_OK;
+    }
     if (pass == PASS_FWD && g_force_variant[PASS_FWD].load() < 0 && dense_fwd_stream_shape(g)) {
         if (name != nullptr && name_bytes > 0) snprintf(name, name_bytes, "%s", dense_fwd_stream_name(g));
         if (splits != nullptr) *splits = 1;
@@ -990,7 +996,7 @@ size_t dp_linear_workspace_bytes(const dp_linear_desc *desc)
     ConvGeom g;
     if (check_linear(desc, &g) != DP_OK) return 0;
     const size_t need = linear_passes_ws_bytes(desc, false);
-    return desc->io_dtype == DP_BF16 && dense_both_shape(g) ? std::max(need, dense_both_partial_bytes(g)) : need;
+    return desc->io_dtype == DP_BF16 && dense_both_shape(g) ? std::max(need, dense_both_partial_bytes(g, true)) : need;
 }
 
 dp_status dp_conv2d_fwd(const dp_conv_desc *desc, const void *x, const void *w, const float *bias, void *y, void *ws,
@@ -1107,7 +1113,7 @@ dp_status dp_linear_fwd_bwd(const dp_linear_desc *desc, const void *x, const voi
     // forward and backward-data asked for together read W once (a workspace of the passes' size only, a saved output that masks dy, a
     // forced variant or outputs in the place of inputs: one after the other)
     if (y != nullptr && dx != nullptr && y_saved == nullptr && desc->io_dtype == DP_BF16 && dense_both_shape(g) && g_force_variant[PASS_FWD].load() < 0 &&
-        g_force_variant[PASS_DGRAD].load() < 0 && ws != nullptr && ws_bytes >= dense_both_partial_bytes(g) && y != x && y != dy && y != W && dx != x &&
+        g_force_variant[PASS_DGRAD].load() < 0 && ws != nullptr && ws_bytes >= dense_both_partial_bytes(g, true) && y != x && y != dy && y != W && dx != x &&
         dx != dy && dx != W && y != dx) {
         hipError_t e;
         {

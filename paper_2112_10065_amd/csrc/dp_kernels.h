@@ -164,7 +164,7 @@ hipError_t dense_dgrad_stream(const ConvGeom &g, unsigned flags, const bf16_t *d
 // second call adds the partials and applies the epilogues
 bool dense_both_shape(const ConvGeom &g);
 bool dense_dgrad_split_shape(const ConvGeom &g);   // backward-data alone takes it
-size_t dense_both_partial_bytes(const ConvGeom &g);
+size_t dense_both_partial_bytes(const ConvGeom &g, bool with_y);
 const char *dense_both_name(const ConvGeom &g, bool with_y);
 hipError_t dense_both(const ConvGeom &g, const bf16_t *x, const bf16_t *dy, const bf16_t *w, float *partial, bool with_y, hipStream_t st);
 hipError_t dense_both_sum(const ConvGeom &g, unsigned flags_y, unsigned flags_dx, const float *partial, const float *bias, const bf16_t *xin, bf16_t *y,

@@ -1038,6 +1038,37 @@ def test_dense_backward_data_by_row_ranges(env, n, i, o, name, dx_f32):
     U.assert_bf16_close(U.to_np(dx), orc.relu_in_backward(dy.astype(np.float64) @ w.astype(np.float64), x), "dx")
 
 
+def test_dense_backward_data_is_profiled_and_queried_as_it_runs(env):
+    """The scratch of the queries is that of the row-range walk, so the layer profile times it and a 1x1 layer's own call, the dense call and the
+    kernel name agree; with less scratch the tile kernels run."""
+    dp, U, orc = env
+    ld = dp.linear_desc(8, 25088, 4096, dp.DP_BF16, 0)
+    dp.dp_trace_begin()
+    try:
+        dp.dp_profile_layer(linear=ld, batches=(8,), warmup=0, iters=1)
+    finally:
+        names = [r["kernel"] for r in dp.dp_trace_end() if r["pass"] == 1]
+    assert names and set(names) == {"k_dense_both<32, false>"}
+    n, i, o = 8, 4160, 1024
+    gen = torch.Generator(device=U.DEV).manual_seed(5)
+    w, dy = (torch.randn(s, generator=gen, device=U.DEV).bfloat16() for s in ((o, i), (n, o)))
+    ld, cd = dp.linear_desc(n, i, o, dp.DP_BF16, 0), dp.conv_desc(n, 1, 1, i, o, 1, 1, (1, 1), (0, 0), dp.DP_BF16, 0)
+    name = dp.dp_conv2d_kernel_info(cd, 1)[0]
+    assert name == "k_dense_both<8, false>"
+    outs = []
+    for run in (lambda dx: dp.dp_linear_fwd_bwd(ld, W=w, dy=dy, dx=dx, ws=U.workspace(dp.dp_linear_workspace_bytes(ld))),
+                lambda dx: dp.dp_conv2d_bwd_data(cd, dy, None, w, dx, U.workspace(dp.dp_conv2d_workspace_bytes(cd, 1)))):
+        dx = torch.full((n, i), 5.0, device=U.DEV, dtype=torch.bfloat16)
+        dp.dp_trace_begin()
+        try:
+            run(dx)
+        finally:
+            assert [r["kernel"] for r in dp.dp_trace_end()] == [name]
+        outs.append(dx)
+    torch.cuda.synchronize()
+    assert torch.equal(*outs)
+
+
 @pytest.mark.parametrize("rows,k,bf16", [(1000, 64, True), (777, 512, True), (50, 4096, True), (33, 1000, True),
                                          (300, 24, True), (65, 12, True), (130, 16, False)])
 def test_relu_bias_grad(env, rows, k, bf16):
