@@ -1112,9 +1112,17 @@ dp_status dp_linear_fwd_bwd(const dp_linear_desc *desc, const void *x, const voi
     hipStream_t st = (hipStream_t)hip_stream;
     // forward and backward-data asked for together read W once (a workspace of the passes' size only, a saved output that masks dy, a
     // forced variant or outputs in the place of inputs: one after the other)
+    const size_t xb = (size_t)g.N * g.C * 2, yb = ybytes(g), wb = (size_t)g.K * g.C * 2, dxb = (desc->flags & DP_DX_F32) ? 2 * xb : xb, bb = (size_t)g.K * 4;
+    auto apart = [](const void *a, size_t na, const void *b, size_t nb) {
+        const uintptr_t pa = reinterpret_cast<uintptr_t>(a), pb = reinterpret_cast<uintptr_t>(b);
+        return pa + na <= pb || pb + nb <= pa;
+    };
+    auto apart_from_inputs = [&](const void *o, size_t nb) {
+        return apart(o, nb, x, xb) && apart(o, nb, dy, yb) && apart(o, nb, W, wb) && (!(desc->flags & DP_BIAS) || apart(o, nb, bias, bb));
+    };
     if (y != nullptr && dx != nullptr && y_saved == nullptr && desc->io_dtype == DP_BF16 && dense_both_shape(g) && g_force_variant[PASS_FWD].load() < 0 &&
-        g_force_variant[PASS_DGRAD].load() < 0 && ws != nullptr && ws_bytes >= dense_both_partial_bytes(g, true) && y != x && y != dy && y != W && dx != x &&
-        dx != dy && dx != W && y != dx) {
+        g_force_variant[PASS_DGRAD].load() < 0 && ws != nullptr && ws_bytes >= dense_both_partial_bytes(g, true) && apart_from_inputs(y, yb) &&
+        apart_from_inputs(dx, dxb) && apart(y, yb, dx, dxb)) {
         hipError_t e;
         {
             TraceScope ts(PASS_FWD, st);

@@ -1038,6 +1038,32 @@ def test_dense_backward_data_by_row_ranges(env, n, i, o, name, dx_f32):
     U.assert_bf16_close(U.to_np(dx), orc.relu_in_backward(dy.astype(np.float64) @ w.astype(np.float64), x), "dx")
 
 
+def test_dense_call_with_an_output_over_an_input_runs_its_passes_in_turn(env):
+    """dx over the bias, y over the tail of x or of the weights: the forward pass reads them before backward-data writes."""
+    dp, U, orc = env
+    n, i, o = 4, 1024, 512
+    gen = torch.Generator(device=U.DEV).manual_seed(6)
+    x, w, dy = (torch.randn(s, generator=gen, device=U.DEV).bfloat16() for s in ((n, i), (o, i), (n, o)))
+    bias = torch.rand(o, generator=gen, device=U.DEV)
+    desc = dp.linear_desc(n, i, o, dp.DP_BF16, dp.DP_BIAS)
+    ws = U.workspace(dp.dp_linear_workspace_bytes(desc))
+    y0, dx0 = torch.empty((n, o), device=U.DEV, dtype=torch.bfloat16), torch.empty((n, i), device=U.DEV, dtype=torch.bfloat16)
+    dp.dp_linear_fwd_bwd(desc, x=x, W=w, bias=bias, y=y0, ws=ws)
+    dp.dp_linear_fwd_bwd(desc, W=w, dy=dy, dx=dx0, ws=ws)
+    for over in (0, 1024, 4096):       # bytes from the start of dx to the bias
+        room = torch.zeros(n * i * 2 + 8192, device=U.DEV, dtype=torch.uint8)
+        dx, b = room[:n * i * 2].view(torch.bfloat16).view(n, i), room[over:over + 4 * o].view(torch.float32)
+        b.copy_(bias)
+        y = torch.empty_like(y0)
+        dp.dp_trace_begin()
+        try:
+            dp.dp_linear_fwd_bwd(desc, x=x, W=w, bias=b, dy=dy, y=y, dx=dx, ws=ws)
+        finally:
+            names = [r["kernel"] for r in dp.dp_trace_end()]
+        torch.cuda.synchronize()
+        assert "k_dense_both_sum" not in names and torch.equal(y, y0) and torch.equal(dx, dx0)
+
+
 def test_dense_backward_data_is_profiled_and_queried_as_it_runs(env):
     """The scratch of the queries is that of the row-range walk, so the layer profile times it and a 1x1 layer's own call, the dense call and the
     kernel name agree; with less scratch the tile kernels run."""
