@@ -84,12 +84,13 @@ template <> __device__ __forceinline__ bf16_t from_f32<bf16_t>(float v) { return
 // (lane-strided, up to 64*CACHE classes; longer rows re-read the tail); maximum, exponential sum and
 // gradient are reduced by shuffles.  Row losses add up per wavefront in row order, the 16 wavefront sums in
 // wavefront order.  Bound by latency: all loads of a row, the label's score among them, are issued together at clamped indices
-// and selected afterwards (under conditions the compiler waited for each: 2 x 1000 12 -> 4.0 us, 32 x 1000 23 -> 11 us).
-template <typename T>
+// and selected afterwards (under conditions the compiler waited for each: 2 x 1000 12 -> 4.0 us, 32 x 1000 23 -> 11 us).  CACHE is
+// the least of 1, 2, 4, 8, 12, 16 that holds the row: registers past its end would only add zeros to the sum, and cost exponentials
+// (warm, 16 / least, fp32: 32 x 10 8.0 / 4.5 us, 100 x 128 19.3 / 9.1, 100 x 500 24.0 / 17.7, 32 x 640 10.1 / 9.2).
+template <typename T, int CACHE>
 __global__ __launch_bounds__(1024) void k_softmax_xent(int n, int classes, const T *__restrict__ z, const int *__restrict__ labels,
                                                         float *__restrict__ loss, T *__restrict__ dz)
 {
-    constexpr int CACHE = 16;
     __shared__ float part[16];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const float inv_n = 1.0f / (float)n;
@@ -137,6 +138,14 @@ __global__ __launch_bounds__(1024) void k_softmax_xent(int n, int classes, const
         for (int i = 0; i < 16; ++i) s += part[i];
         *loss = s * inv_n;
     }
+}
+
+template <typename T>
+void launch_softmax_xent(int n, int classes, const T *z, const int *labels, float *loss, T *dz, hipStream_t st)
+{
+    auto *kernel = classes <= 64 ? k_softmax_xent<T, 1> : classes <= 128 ? k_softmax_xent<T, 2> : classes <= 256 ? k_softmax_xent<T, 4> :
+                   classes <= 512 ? k_softmax_xent<T, 8> : classes <= 768 ? k_softmax_xent<T, 12> : k_softmax_xent<T, 16>;
+    hipLaunchKernelGGL(kernel, dim3(1), dim3(1024), 0, st, n, classes, z, labels, loss, dz);
 }
 
 // U vectors of 4 elements per thread, all loads issued before the first store; the last count % 4 elements
@@ -243,8 +252,8 @@ extern "C" dp_status dp_softmax_xent(int32_t n, int32_t classes, int32_t io_dtyp
     if (io_dtype != DP_F32 && io_dtype != DP_BF16) { dp_set_error("softmax cross-entropy: unknown io_dtype %d", io_dtype); return DP_ERR_UNSUPPORTED; }
     if (n < 1 || classes < 1) { dp_set_error("softmax cross-entropy: n and classes must be positive"); return DP_ERR_BAD_DESC; }
     hipStream_t st = (hipStream_t)hip_stream;
-    if (io_dtype == DP_BF16) hipLaunchKernelGGL(k_softmax_xent<bf16_t>, dim3(1), dim3(1024), 0, st, n, classes, (const bf16_t *)z, labels, loss, (bf16_t *)dz);
-    else hipLaunchKernelGGL(k_softmax_xent<float>, dim3(1), dim3(1024), 0, st, n, classes, (const float *)z, labels, loss, (float *)dz);
+    if (io_dtype == DP_BF16) launch_softmax_xent(n, classes, (const bf16_t *)z, labels, loss, (bf16_t *)dz, st);
+    else launch_softmax_xent(n, classes, (const float *)z, labels, loss, (float *)dz, st);
     return launched("softmax cross-entropy");
 }
 

@@ -100,6 +100,12 @@ def test_softmax_xent(env, n, classes, bf16):
     assert float(loss2[0]) == float(loss[0])
 
 
+@pytest.mark.parametrize("classes", [64, 65, 128, 129, 256, 257, 512, 513, 768, 769])
+@pytest.mark.parametrize("bf16", [True, False], ids=["bf16", "f32"])
+def test_softmax_xent_at_the_edges_of_the_row_registers(env, classes, bf16):
+    test_softmax_xent(env, 18, classes, bf16)
+
+
 @pytest.mark.parametrize("count", [1, 7, 4096 + 3, 1 << 20, 25088 * 4096])
 @pytest.mark.parametrize("with_bf16", [True, False])
 def test_sgd_update(env, count, with_bf16):
