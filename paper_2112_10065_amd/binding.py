@@ -127,10 +127,14 @@ def _ptr(t):
 
 def _current_stream():
     """Handle of the current device's current stream.  torch.cuda.current_stream() builds a Stream object on every call, most of
-    the host time of a small layer's call; once the device is initialised the handle is read directly."""
+    the host time of a small layer's call; once the device is initialised the handle is read directly, if this torch has the two
+    functions for it (they are not part of its public interface)."""
     import torch
     if torch.cuda.is_initialized():
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:
+            pass
     return torch.cuda.current_stream().cuda_stream
 
 

@@ -32,6 +32,21 @@ def test_struct_sizes_match_header(dp):
     assert C.sizeof(dp.dp_profile_row) == 48
 
 
+@pytest.mark.parametrize("initialised,raw,want", [(True, True, 7), (True, False, 9), (False, True, 9)])
+def test_current_stream_without_the_private_functions(dp, monkeypatch, initialised, raw, want):
+    import types
+    import torch
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: initialised)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=9))
+    private = types.SimpleNamespace(_cuda_getDevice=lambda: 0)
+    if raw:
+        private._cuda_getCurrentRawStream = lambda device: 7
+    monkeypatch.setattr(torch, "_C", private)
+    got = dp._current_stream()
+    monkeypatch.undo()
+    assert got == want
+
+
 A = 0x1000  # fake, 16-byte aligned, never dereferenced: validation fails first
 
 
