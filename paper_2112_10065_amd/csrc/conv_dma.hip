@@ -227,8 +227,8 @@ DEVFN void walk_advance(WalkState &w, const WalkStep &st)
 // MIX: channels in whole 8s that BK does not divide.  The reduction is walked flat over (tap, channel), so a step holds chunks of
 // several taps; the weights are contiguous in that order, and a lane's pixel chunk carries its own tap and channel (WalkState).
 // The walk costs about 15 vector instructions per step and chunk class, against a 32-wide step (half the matrix work per barrier,
-// 13.1 us instead of 8.8 on 16 x 17 x 17 x 160 -> 160, 1x7) or the generic kernel (277 -> 192 us on 16 x 100 x 100 x 240 -> 208, 3x3;
-// backward-data 431 -> 191 us).
+// 12.4 -> 10.8 us on 16 x 17 x 17 x 160 -> 160, 1x7) or the generic kernel (276 -> 202 us on 16 x 100 x 100 x 240 -> 208, 3x3;
+// backward-data 436 -> 208 us).
 template <int TA, int TB, int BK, int WA, int WB, int NS, int KG, bool MIX>
 DEVFN void fwd_dma_body(const KArgs &p)
 {

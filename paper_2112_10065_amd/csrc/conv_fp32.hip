@@ -9,8 +9,8 @@
 // operands agree, so a step takes 16 consecutive reduction channels and lane group g the channels 4g .. 4g+3 of them: one 16-byte
 // load per lane and operand feeds four instructions.
 // Measured against one thread per output (forward, backward-data) and one wave per filter element, 3x3 layers, forward + backward-data
-// + both gradients back to back: 2 x 16 x 16 x 16 -> 16: 64 -> 21 us (67 us of kernels -> three launches, host-bound);
-// 3 x 38 x 38 x 15 -> 34: 175 -> 54 us; 4 x 40 x 40 x 64 -> 64: 2612 -> 94 us (20 / 28 / 46).
+// + both gradients back to back, in a graph: 2 x 16 x 16 x 16 -> 16: 63.5 -> 14.6 us (5.0 / 5.6 / 7.2 alone);
+// 3 x 38 x 38 x 15 -> 34: 180 -> 52 us (9.2 / 12.4 / 33.4); 4 x 40 x 40 x 64 -> 64: 2603 -> 93 us (21 / 28 / 46).
 #include "tile_common.h"
 #include <algorithm>
 #include <cstdio>
@@ -18,7 +18,8 @@
 
 namespace {
 
-// n / d for 0 <= n < 2^31 by one multiplication (d >= 1 fixed per launch)
+// n / d for 0 <= n < 2^31 by one multiplication (d >= 1 fixed per launch): the reciprocal rounded up (Granlund and Montgomery,
+// "Division by invariant integers using multiplication", 1994)
 struct FastDiv {
     unsigned mul, shift, d;
     __host__ __device__ static FastDiv of(int dv)
