@@ -377,16 +377,18 @@ __global__ __launch_bounds__(64 * DF_WAVES) void k_dense_wgrad(int N, int C, int
 // dy rows wait in LDS in fragment order, the unit's x fragments in registers.  y is then summed over the waves (in wave order) and leaves as
 // one partial per column range, dx as one per row range; k_dense_both_sum adds them in order and applies bias, ReLU and mask.
 // RT = 32 keeps the partials of dx few (16 * samples / 4096 of the weight bytes each way); layers too small to give every wave of
-// the chip a unit that way take RT = 8.
+// the chip a unit that way take RT = 8, those with fewer such units than CUs RT = 2: there the chain of a wave's row tiles is the time.
+// Both kernels, two passes apart / RT = 8 / RT = 2: 512 x 184, 16 samples 7.8 / 9.4 / 8.1 us; 1024 x 160, 16 samples 8.3 / 9.7 / 8.1; over 140
+// drawn layers under 256 units RT = 2 is 0.97 - 1.4 times as fast as the passes apart, RT = 8 0.83 - 1.3; at 500 units the two are even.
 // ---------------------------------------------------------------------------------------
 constexpr int DB_NS = 6;
 template <int RT, bool Y>   // Y: also the forward product
 __global__ __launch_bounds__(64 * DF_WAVES) void k_dense_both(int N, int C, int K, int units_per_block, const bf16_t *x, const bf16_t *dy, const bf16_t *w,
                                                               float *ypart, float *dxpart)
 {
-    constexpr int D = DB_NS - 1, STAGE = 2048, DYB = RT * 512;
+    constexpr int D = DB_NS - 1, STAGE = 2048, DYB = RT * 512, TG = RT < 8 ? RT : 8;   // TG: row tiles whose sums meet in LDS at a time
     static_assert(DF_WAVES * DB_NS * STAGE >= DF_WAVES * 8 * 64 * (int)sizeof(f32x4v), "the waves' sums of eight row tiles fit the stages");
-    static_assert(RT % 8 == 0, "row tiles are summed eight at a time");
+    static_assert(RT % 2 == 0 && RT % TG == 0, "dy is fetched two row tiles at a time; whole groups of tiles are summed");
     __shared__ __attribute__((aligned(1024))) char lds[DF_WAVES * DB_NS * STAGE + DYB];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int o0 = blockIdx.x * RT * 16, nst = min(RT, (K - o0 + 15) / 16);
@@ -495,17 +497,18 @@ __global__ __launch_bounds__(64 * DF_WAVES) void k_dense_both(int N, int C, int 
         }
     }
     if constexpr (!Y) return;
-    // y: the eight waves' sums of eight row tiles at a time; wave v adds tile v in wave order
+    // y: the eight waves' sums of TG row tiles at a time; wave v adds tile v in wave order
     f32x4v *red = reinterpret_cast<f32x4v *>(lds);   // [wave][tile][lane]
 #pragma unroll
-    for (int t0 = 0; t0 < RT; t0 += 8) {
+    for (int t0 = 0; t0 < RT; t0 += TG) {
         __syncthreads();   // the stages (or the tiles before) have been read
 #pragma unroll
-        for (int t = 0; t < 8; ++t) red[(wave * 8 + t) * 64 + lane] = accy[Y ? t0 + t : 0];
+        for (int t = 0; t < TG; ++t) red[(wave * TG + t) * 64 + lane] = accy[Y ? t0 + t : 0];
         __syncthreads();
+        if (wave >= TG) continue;
         f32x4v s = red[wave * 64 + lane];
 #pragma unroll
-        for (int wv = 1; wv < DF_WAVES; ++wv) s += red[(wv * 8 + wave) * 64 + lane];
+        for (int wv = 1; wv < DF_WAVES; ++wv) s += red[(wv * TG + wave) * 64 + lane];
         // element v of lane l: output row 4*(l/16) + v of the tile, sample l%16
         const int o = o0 + (t0 + wave) * 16 + 4 * (lane >> 4);
         if (i16 < N && o < K) *reinterpret_cast<f32x4v *>(ypart + ((size_t)blockIdx.y * N + i16) * K + o) = s;
@@ -578,7 +581,8 @@ bool dense_dgrad_split_shape(const ConvGeom &g)
 static void dense_both_split(const ConvGeom &g, int *rt, int *row_parts, int *units_per_block, int *col_parts)
 {
     const int units = g.C / 64;
-    *rt = (long long)((g.K + 511) / 512) * units >= 2048 ? 32 : 8;   // a unit for every wave of one block per CU
+    // 32: a unit for every wave of one block per CU; 2: never without y, see dense_dgrad_split_shape
+    *rt = (long long)((g.K + 511) / 512) * units >= 2048 ? 32 : (long long)((g.K + 127) / 128) * units >= 256 ? 8 : 2;
     *row_parts = (g.K + *rt * 16 - 1) / (*rt * 16);
     int cp = std::max(1, 256 / *row_parts);
     if (cp > (units + DF_WAVES - 1) / DF_WAVES) cp = (units + DF_WAVES - 1) / DF_WAVES;
@@ -597,7 +601,8 @@ hipError_t dense_both(const ConvGeom &g, const bf16_t *x, const bf16_t *dy, cons
     dense_both_split(g, &rt, &rp, &upb, &cp);
     float *ypart = partial + (size_t)rp * g.N * g.C;
     const dim3 grid((unsigned)rp, (unsigned)cp), block(64 * DF_WAVES);
-    auto *kernel = rt == 32 ? (with_y ? k_dense_both<32, true> : k_dense_both<32, false>) : (with_y ? k_dense_both<8, true> : k_dense_both<8, false>);
+    auto *kernel = rt == 32 ? (with_y ? k_dense_both<32, true> : k_dense_both<32, false>) : rt == 2 ? k_dense_both<2, true> :
+                   (with_y ? k_dense_both<8, true> : k_dense_both<8, false>);
     hipLaunchKernelGGL(kernel, grid, block, 0, st, g.N, g.C, g.K, upb, x, dy, w, ypart, partial);
     return hipGetLastError();
 }
@@ -615,7 +620,7 @@ const char *dense_both_name(const ConvGeom &g, bool with_y)
 {
     int rt, rp, upb, cp;
     dense_both_split(g, &rt, &rp, &upb, &cp);
-    return rt == 32 ? (with_y ? "k_dense_both<32, true>" : "k_dense_both<32, false>") : (with_y ? "k_dense_both<8, true>" : "k_dense_both<8, false>");
+    return rt == 32 ? (with_y ? "k_dense_both<32, true>" : "k_dense_both<32, false>") : rt == 2 ? "k_dense_both<2, true>" : (with_y ? "k_dense_both<8, true>" : "k_dense_both<8, false>");
 }
 
 // shapes the streaming dense forward takes: a 1x1 layer over at most 16 pixel rows (beyond that the activation operand, which

@@ -1021,6 +1021,25 @@ def test_dense_forward_and_backward_data_in_one_call(env, n, i, o, dx_f32):
         y0, dx0 = y, dx
 
 
+# row ranges of 32 outputs (fewer 128 x 64 units of weights than CUs) and of 128 from there on: ranges of one tile and a ragged one
+@pytest.mark.parametrize("n,i,o,name", [(1, 512, 40, "k_dense_both<2, true>"), (16, 640, 16, "k_dense_both<2, true>"), (15, 4032, 512, "k_dense_both<2, true>"),
+                                        (16, 4096, 512, "k_dense_both<8, true>")])
+def test_dense_in_one_call_by_short_row_ranges(env, n, i, o, name):
+    dp, U, orc = env
+    names, end = [], dp.dp_trace_end
+
+    def traced():
+        rows = end()
+        names.extend(r["kernel"] for r in rows)
+        return rows
+    dp.dp_trace_end = traced
+    try:
+        test_dense_forward_and_backward_data_in_one_call(env, n, i, o, False)
+    finally:
+        dp.dp_trace_end = end
+    assert name in names
+
+
 # backward-data alone through the same walk: many weights, few samples (row ranges of 128 and 512 outputs)
 @pytest.mark.parametrize("n,i,o,name", [(8, 4160, 1024, "k_dense_both<8, false>"), (3, 16448, 4032, "k_dense_both<32, false>"), (1, 2048, 2048, "k_dense_both<8, false>")])
 @pytest.mark.parametrize("dx_f32", [False, True])
