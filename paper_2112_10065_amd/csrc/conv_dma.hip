@@ -1533,6 +1533,7 @@ bool dma_plan(const ConvGeom &g, int pass, int force_variant, int force_splits, 
         rowsA = g.C; rowsB = g.N * g.H * g.W; red = g.R * g.S * g.K;
     } else if (pass == PASS_WGRAD) {
         if (force_variant == 316) return wstrip_plan(g, force_splits, pl);
+        if (force_variant == 317 || force_variant == 318) return wwin_plan(g, force_variant == 317 ? 128 : 256, force_splits, pl);
         if (force_variant < 300 || force_variant >= 300 + kNumDmaW) return false;
         d = &kDmaW[force_variant - 300];
         if (g.K % 8 || g.C % 8) return false;
@@ -1584,8 +1585,8 @@ bool dma_plan(const ConvGeom &g, int pass, int force_variant, int force_splits, 
     return true;
 }
 
-bool dma_plan_is_flat(const GemmPlan &plan) { return plan.dma && !plan.halo && !plan.wstrip && kDma[plan.variant].mix; }
-bool dma_plan_is_strip(const GemmPlan &plan) { return plan.dma && !plan.halo && !plan.wstrip && is_strip(plan.variant); }
+bool dma_plan_is_flat(const GemmPlan &plan) { return plan.dma && !plan.halo && !plan.wstrip && !plan.wwin && kDma[plan.variant].mix; }
+bool dma_plan_is_strip(const GemmPlan &plan) { return plan.dma && !plan.halo && !plan.wstrip && !plan.wwin && is_strip(plan.variant); }
 
 // Whether this forward / backward-data plan sums its reduction splits inside the main kernel: asked for by the plan, tiles in
 // natural pixel order, and few enough tiles that a range of the counter ring is not handed out again for at least 64 later launches.
@@ -1601,6 +1602,7 @@ bool dma_plan_fuses_reduce(const GemmPlan &plan)
 void dma_kernel_name(int pass, const GemmPlan &pl, char *name, size_t name_bytes)
 {
     if (pl.wstrip) { snprintf(name, name_bytes, "k_wgrad_strip"); return; }
+    if (pl.wwin) { wwin_kernel_name(pl, name, name_bytes); return; }
     const DmaVariant &d = pass == PASS_WGRAD ? kDmaW[pl.variant] : kDma[pl.variant];
     // as the profiler prints the instantiation: the forward / backward-data kernels carry the group count
     if (pass != PASS_WGRAD && is_strip(pl.variant)) snprintf(name, name_bytes, "k_conv_strip<%s, %d, %d>", pass == PASS_FWD ? "false" : "true", d.TB, d.TA);

@@ -210,6 +210,7 @@ void plan_uncached(const ConvGeom &g, int pass, int fv, int fs, GemmPlan *pl, in
     pl->dma = false;
     pl->halo = false;
     pl->wstrip = false;
+    pl->wwin = false;
     pl->fused_reduce = false;
     pl->over_generic = false;
     // 1000 + v: variant v with the split reduction fused into the main kernel (pipelined forward / backward-data).  Only a forced
@@ -230,6 +231,7 @@ void plan_uncached(const ConvGeom &g, int pass, int fv, int fs, GemmPlan *pl, in
             flat.over_generic = !pl->fast;
             *pl = flat;
         }
+        if (fs <= 0 && pass == PASS_WGRAD && !(restr & RESTR_BASE) && wgrad_window_plan(g, *pl, time, &flat)) *pl = flat;
         return;
     }
     // a forced input-patch variant the call may not use falls through to the next family
@@ -284,7 +286,7 @@ GemmPlan current_plan(PlanEntry &pe)
 // The planner prices the splits that do something.
 void round_wgrad_splits(const ConvGeom &g, GemmPlan &pl)
 {
-    if (!pl.dma || pl.halo || pl.wstrip || pl.splits <= 16) return;
+    if (!pl.dma || pl.halo || pl.wstrip || pl.wwin || pl.splits <= 16) return;
     const size_t rows = std::min((long long)g.H, (long long)g.Ho * g.R), cols = std::min((long long)g.W, (long long)g.Wo * g.S);   // of x that a tap reads
     const size_t operands = 2 * (g.N * rows * cols * g.C + (size_t)g.N * g.Ho * g.Wo * g.K);
     const int up = (pl.splits + 7) / 8 * 8;
@@ -304,7 +306,7 @@ PlanRef plan_entry(const ConvGeom &g, int pass, int restr = 0)
     if (cache.size() > 4096) cache.clear();
     PlanRef ep = std::make_shared<PlanEntry>();
     PlanEntry &e = *ep;
-    plan_uncached(g, pass, fv, fs, &e.plan, restr);
+    plan_uncached(g, pass, fv, fs, &e.plan, restr | (pass == PASS_WGRAD && g_tight_splits ? RESTR_BASE : 0));
     const bool round_splits = pass == PASS_WGRAD && fv < 0 && fs <= 0 && !g_tight_splits;
     if (round_splits) round_wgrad_splits(g, e.plan);
     e.part_cap = mfma_partial_bytes(g, pass, e.plan);
@@ -312,6 +314,13 @@ PlanRef plan_entry(const ConvGeom &g, int pass, int restr = 0)
         GemmPlan list[kTuneCandidates];
         // a cold measurement judges for itself what the model's warm-cache prices cannot: more candidates, a wider price band
         int n = auto_plan_list(g, pass, fs, list, at == 2 ? kTuneCandidates : 12, restr | (at == 2 ? 4 : 0));
+        if (pass == PASS_WGRAD && n > 0 && fs <= 0 && !g_tight_splits) {
+            GemmPlan win[2];
+            double times[2];
+            const int m = wgrad_window_plans(g, win, times);
+            if (n + m > kTuneCandidates) n = kTuneCandidates - m;   // in the place of the model's last
+            for (int i = 0; i < m; ++i) list[n++] = win[i];
+        }
         if (pass != PASS_WGRAD && n > 0 && n < kTuneCandidates && dma_plan_is_flat(e.plan)) list[n++] = e.plan;   // not one of the list's
         if (n > 1) {
             e.cands.assign(list, list + n);
@@ -336,7 +345,7 @@ PlanRef plan_entry(const ConvGeom &g, int pass, int restr = 0)
 bool plan_sums_bias_gradient(const GemmPlan &plan)
 {
     if (plan.halo) return plan.db_wave && plan.splits <= 512;   // input-patch kernel: one extra wave per block
-    return plan.dma && !plan.wstrip && plan.splits <= 512;
+    return plan.dma && !plan.wstrip && !(plan.wwin && !plan.row_taps) && plan.splits <= 512;
 }
 
 namespace {
@@ -345,6 +354,7 @@ hipError_t launch_plan(const ConvArgs &a, hipStream_t st)
 {
     if (a.plan.halo) return halo_launch(a, st);
     if (a.plan.wstrip) return wstrip_launch(a, st);
+    if (a.plan.wwin) return wwin_launch(a, st);
     if (a.plan.dma) return dma_launch(a, st);
     return a.plan.fast ? fast_launch(a, st) : mfma_launch(a, st);
 }
@@ -473,7 +483,7 @@ size_t round256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 dp_status ensure_init()
 {
-    std::call_once(g_init_once, [] { g_init_err = mfma_init(); if (g_init_err == hipSuccess) g_init_err = fast_init(); if (g_init_err == hipSuccess) g_init_err = dma_init(); if (g_init_err == hipSuccess) g_init_err = halo_init(); if (g_init_err == hipSuccess) g_init_err = wstrip_init(); });
+    std::call_once(g_init_once, [] { g_init_err = mfma_init(); if (g_init_err == hipSuccess) g_init_err = fast_init(); if (g_init_err == hipSuccess) g_init_err = dma_init(); if (g_init_err == hipSuccess) g_init_err = halo_init(); if (g_init_err == hipSuccess) g_init_err = wstrip_init(); if (g_init_err == hipSuccess) g_init_err = wwin_init(); });
     if (g_init_err != hipSuccess) return hip_fail(g_init_err, "library initialisation (is a gfx950 device present?)");
     return DP_OK;
 }
@@ -698,8 +708,9 @@ size_t wgrad_ws_bytes(const ConvGeom &g, int dtype, bool with_db)
 // the least a call can do with
 size_t wgrad_least_ws_bytes(const ConvGeom &g, int dtype, bool with_db)
 {
+    const size_t usual = wgrad_ws_bytes(g, dtype, with_db);   // the window kernel's few splits may take less than the kernels without it
     const TightSplits tight(true);
-    return wgrad_ws_bytes(g, dtype, with_db);
+    return std::min(usual, wgrad_ws_bytes(g, dtype, with_db));
 }
 
 // workspace layout: [split partials | masked gradient (fast path) | bias-gradient scratch]
@@ -1048,7 +1059,8 @@ dp_status dp_conv2d_bwd_filter(const dp_conv_desc *desc, const void *x, const vo
     if ((s = check_conv(desc, &g)) != DP_OK) return s;
     if ((s = check_ptr(x, "x")) != DP_OK || (s = check_ptr(dy, "dy")) != DP_OK || (s = check_ptr(dw, "dw")) != DP_OK) return s;
     if ((s = check_opt(y_saved, "y_saved")) != DP_OK || (s = check_opt(dbias, "dbias")) != DP_OK || (s = check_opt(ws, "ws")) != DP_OK) return s;
-    size_t need = wgrad_least_ws_bytes(g, desc->io_dtype, dbias != nullptr);
+    size_t need = wgrad_ws_bytes(g, desc->io_dtype, dbias != nullptr);
+    if (need > 0 && (ws == nullptr || ws_bytes < need)) need = wgrad_least_ws_bytes(g, desc->io_dtype, dbias != nullptr);
     if (need > 0 && (ws == nullptr || ws_bytes < need)) return fail(DP_ERR_WORKSPACE, "backward-filter needs %zu workspace bytes, got %zu", need, ws_bytes);
     if ((s = ensure_init()) != DP_OK) return s;
     return run_wgrad(g, desc->io_dtype, x, dy, y_saved, dw, dbias, ws, ws_bytes, (hipStream_t)hip_stream);

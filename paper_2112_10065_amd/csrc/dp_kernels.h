@@ -49,6 +49,8 @@ struct GemmPlan {
     bool phase = false;   // strided backward-data walks the input pixels stride phase by stride phase (conv_dma.hip)
     bool fill = false;    // phase, 1x1 filter: only the first phase has tiles, they store the zeros of the others
     bool wstrip = false;  // filter gradient with the x strip shared by the taps of a filter row (conv_wstrip.hip); implies dma
+    bool wwin = false;    // filter gradient with one window of x for all taps of a block (conv_wwin.hip); implies dma
+    bool row_taps = false;   // wwin: three taps of one filter row per wave
     bool db_wave = false; // input-patch filter gradient: one more wave per block can sum the bias gradient (at most 15 taps)
     bool over_generic = false;   // a flat-walk kernel on a layer that the generic kernel would run otherwise
     bool fused_reduce = false;   // pipelined forward / backward-data with splits > 1: no second kernel, the last block of a tile reduces (conv_dma.hip)
@@ -80,6 +82,12 @@ void dp_trace_main_kernel_done(hipStream_t st);
 hipError_t wstrip_init();
 bool wstrip_plan(const ConvGeom &g, int force_splits, GemmPlan *pl);
 hipError_t wstrip_launch(const ConvArgs &a, hipStream_t st);
+
+// conv_wwin.hip
+hipError_t wwin_init();
+bool wwin_plan(const ConvGeom &g, int slots_per_chunk, int force_splits, GemmPlan *pl);
+void wwin_kernel_name(const GemmPlan &pl, char *name, size_t name_bytes);
+hipError_t wwin_launch(const ConvArgs &a, hipStream_t st);
 
 // conv_mfma.hip
 hipError_t mfma_init();                                      // raises dynamic LDS limits
@@ -141,6 +149,9 @@ bool auto_plan(const ConvGeom &g, int pass, int force_splits, GemmPlan *plan, in
 bool forward_flat_plan(const ConvGeom &g, const GemmPlan &base, GemmPlan *plan);
 // backward-data: a flat-walk plan faster than `base`, whose price is `time`
 bool backward_flat_plan(const ConvGeom &g, const GemmPlan &base, double time, int restr, GemmPlan *plan);
+// filter gradient: the window kernel's two cheapest plans, and whether it takes the place of `base`, whose price is `time`
+int wgrad_window_plans(const ConvGeom &g, GemmPlan out[2], double times[2]);
+bool wgrad_window_plan(const ConvGeom &g, const GemmPlan &base, double time, GemmPlan *out);
 // the cheapest plans by the model, best first (input of the measured choice); returns the count
 // restr: kernels the call may not use (bit 0: input-patch kernels, bit 1: the stationary-weight kernel)
 int auto_plan_list(const ConvGeom &g, int pass, int force_splits, GemmPlan *out, int max_out, int restr = 0, double *times = nullptr);

@@ -91,9 +91,20 @@ bool family_plan(const ConvGeom &g, int pass, int code, int splits, GemmPlan *pl
 {
     pl->halo = false;
     pl->wstrip = false;
+    pl->wwin = false;
     if (code >= 400) return halo_plan(g, pass, code, splits, pl);
     if (code >= 200) return dma_plan(g, pass, code, splits, pl, (restr & 1) != 0);
     return fast_plan(g, pass, code, splits, pl);
+}
+
+// Window kernel of the filter gradient: fitted to 1140 timings of 3x3 layers (chunks of 256 and of 128 slots; median error 3 %, 8 % for nine
+// of ten) and 290 of other filters (6 %, 16 %).  A chunk costs more when all CUs run one: the matrix cores then hold the clock down.
+double price_window(const ConvGeom &g, const GemmPlan &pl)
+{
+    const double blocks = (double)pl.tilesA * pl.tilesB * pl.splits, rounds = std::ceil(blocks / 256.0);
+    const double busy = std::min(1.0, std::max(0.0, blocks / 128.0 - 1.0)), out_mb = (double)g.K * g.R * g.S * g.C * 4e-6;
+    const double step = !pl.row_taps ? 0.70 : pl.BK == 256 ? 1.52 + 0.21 * busy : 0.86 + 0.09 * busy, t0 = !pl.row_taps ? 7.5 : 3.8;
+    return 3.0 + rounds * (t0 + pl.steps_per_split * step) + (pl.splits > 1 ? 3.0 + 0.45 * (pl.splits + 1) * out_mb : 0.45 * out_mb);
 }
 
 double price(const ConvGeom &g, int pass, const Candidate &c, const GemmPlan &pl, int restr)
@@ -282,6 +293,45 @@ bool backward_flat_plan(const ConvGeom &g, const GemmPlan &base, double time, in
             if (!found || t < best) { best = t; *out = pl; found = true; }
         }
     return found && (generic || strided || best < 0.92 * time);
+}
+
+// The window kernel's two cheapest plans, best first; returns how many there are.  Chunks of 256 slots where the window fits (never slower
+// than 128 in the timings behind price_window), up to eight splits or what fills the chip once or twice.
+int wgrad_window_plans(const ConvGeom &g, GemmPlan out[2], double times[2])
+{
+    GemmPlan pl;
+    const int code = family_plan(g, PASS_WGRAD, 318, 1, &pl) ? 318 : 317;
+    if (!family_plan(g, PASS_WGRAD, code, 1, &pl)) return 0;
+    const int tiles = pl.tilesA * pl.tilesB, wanted[] = {1, 2, 3, 4, 5, 6, 8, 256 / tiles, 512 / tiles};
+    int n = 0;
+    for (int s : wanted) {
+        if (s < 1 || !family_plan(g, PASS_WGRAD, code, s, &pl) || (pl.splits > 1 && pl.steps_per_split < 2)) continue;
+        const double t = price_window(g, pl);
+        if ((n > 0 && out[0].splits == pl.splits) || (n > 1 && out[1].splits == pl.splits)) continue;
+        if (n == 0 || t < times[0]) {
+            if (n > 0) { out[1] = out[0]; times[1] = times[0]; }
+            out[0] = pl; times[0] = t;
+            n = std::min(n + 1, 2);
+        } else if (n == 1 || t < times[1]) {
+            out[1] = pl; times[1] = t;
+            n = 2;
+        }
+    }
+    return n;
+}
+
+// Filter gradient: the window kernel in the place of `base` (price `time`) where its price lies that far below.  The factors are what the
+// other kernels' prices are worth on 230 layers timed both ways: pipelined tiles take 0.7 - 1.1 of their price split and down to 0.6 unsplit,
+// register-staged ones 1.1 - 1.6, the input-patch kernels 1.4 - 2.2.  Taken on 48 of 175 layers that both run: 0.98 - 2.0 times as fast.
+bool wgrad_window_plan(const ConvGeom &g, const GemmPlan &base, double time, GemmPlan *out)
+{
+    GemmPlan pl[2];
+    double t[2];
+    if (!base.fast || wgrad_window_plans(g, pl, t) == 0) return false;
+    const double worth = !pl[0].row_taps ? 0.8 : base.halo ? 1.35 : !base.dma ? 1.0 : base.splits == 1 ? 0.75 : 0.92;
+    if (t[0] >= worth * time) return false;
+    *out = pl[0];
+    return true;
 }
 
 // Fills *pl with the cheapest eligible fast-path plan; false if the shape has none.

@@ -812,6 +812,57 @@ def test_filter_gradient_pixel_strip_kernel(env, splits):
         dp.dp_set_override(2, -1, 0)
 
 
+@pytest.mark.parametrize("slots,splits", [(128, 1), (128, 3), (256, 1), (256, 2)])
+def test_filter_gradient_window_kernel(env, slots, splits):
+    """Unit-stride filter gradients with one window of x for all taps of a block: channels below, at and above a tile, images smaller than a
+    chunk and chunks that end inside a row, no, usual and wide padding, rows that nearly fill the window, filters of one to three tap
+    blocks (chunks of 128 slots only); with the fused bias gradient and behind a saved output."""
+    dp, U, orc = env
+    dp.dp_set_override(2, 317 if slots == 128 else 318, splits)
+    try:
+        for tag, n, h, w, c, k, r, s, pd in (("win_a", 2, 7, 7, 64, 64, 3, 3, (1, 1)), ("win_b", 1, 14, 14, 40, 72, 3, 3, (0, 0)), ("win_c", 3, 9, 30, 32, 136, 3, 3, (1, 1)),
+                                             ("win_d", 1, 4, 110, 72, 8, 3, 3, (1, 1)), ("win_e", 20, 2, 3, 8, 64, 3, 3, (2, 2)), ("win_f", 2, 17, 17, 48, 40, 1, 7, (0, 3)),
+                                             ("win_g", 1, 17, 17, 32, 64, 7, 1, (3, 0)), ("win_h", 2, 11, 12, 24, 64, 5, 5, (2, 2)), ("win_i", 1, 9, 9, 8, 16, 2, 5, (1, 3))):
+            case = U.ConvCase(tag, n, h, w, c, k, r, s, (1, 1), pd, bf16=True, bias=True, relu=True)
+            name, got_splits = dp.dp_conv2d_kernel_info(case.desc, 2)
+            if slots == 256 and (r, s) != (3, 3):
+                assert not name.startswith("k_wgrad_win")
+                continue
+            assert name.startswith(f"k_wgrad_win<{slots}") and 1 <= got_splits <= splits
+            y = case.run_fwd()
+            for saved in (None, y):
+                dw, db = case.run_wgrad(saved)
+                torch.cuda.synchronize()
+                rdw, rdb = orc.conv2d_bwd_filter(case.x, case.dy, case.w.shape, y_saved=None if saved is None else U.to_np(y), stride=(1, 1), pad=pd, want_db=True)
+                # sums of at most 2^13 exact products of bf16 numbers in fp32
+                assert U.errs(U.to_np(dw), rdw)[0] <= 2e-6 and U.errs(U.to_np(db), rdb)[0] <= 2e-6, (tag, saved is None)
+        for tag, w, c, k, st in (("win_s2", 14, 32, 64, (2, 2)), ("win_c12", 14, 12, 64, (1, 1)), ("win_w300", 300, 32, 64, (1, 1))):
+            case = U.ConvCase(tag, 1, 5, w, c, k, 3, 3, st, (1, 1), bf16=True, bias=True, relu=True)
+            assert not dp.dp_conv2d_kernel_info(case.desc, 2)[0].startswith("k_wgrad_win")
+    finally:
+        dp.dp_set_override(2, -1, 0)
+
+
+def test_filter_gradient_window_kernel_by_default_and_with_less_scratch(env):
+    """A middle layer takes the window kernel by itself; with the scratch that the kernels without it ask for or less, the call still runs
+    wherever one of the two fits, and gives the same gradients."""
+    dp, U, orc = env
+    big = U.ConvCase("win_default", 6, 60, 60, 128, 192, 3, 3, (1, 1), (1, 1), bf16=True, bias=False, relu=False)
+    assert dp.dp_conv2d_kernel_info(big.desc, 2)[0].startswith("k_wgrad_win<256")
+    usual, _ = big.run_wgrad(None, want_db=False)
+    need = dp.dp_conv2d_workspace_bytes(big.desc, 2)
+    torch.cuda.synchronize()
+    for nbytes in (need, need - 256, need // 2):
+        dw = torch.zeros_like(usual)
+        try:
+            dp.dp_conv2d_bwd_filter(big.desc, big.xd, big.dyd, None, dw, None, U.workspace(nbytes)[:nbytes])
+        except dp.DpError:
+            assert nbytes < need
+            continue
+        torch.cuda.synchronize()
+        assert U.errs(U.to_np(dw), U.to_np(usual))[0] <= 2e-6
+
+
 @pytest.mark.parametrize("pass_,variant", [(0, 231), (0, 232), (1, 231), (1, 232), (1, 233), (2, 316), (2, 411)])
 def test_results_do_not_depend_on_other_streams(env, pass_, variant):
     """The kernels that hand-order their LDS reads, beside small blocks of other kernels on the same compute units (filter gradients on two
