@@ -1513,6 +1513,7 @@ bool dma_plan(const ConvGeom &g, int pass, int force_variant, int force_splits, 
     if (g.R * g.S > 32) return false;
     int rowsA, rowsB, red;
     const DmaVariant *d;
+    if (pass != PASS_WGRAD && force_variant >= 250 && force_variant < 260) return !f32_out && win_plan(g, pass, force_variant - 250, pl);
     if (pass == PASS_FWD) {
         if (force_variant < 200 || force_variant >= 200 + kNumDma) return false;
         d = &kDma[force_variant - 200];
@@ -1585,8 +1586,8 @@ bool dma_plan(const ConvGeom &g, int pass, int force_variant, int force_splits, 
     return true;
 }
 
-bool dma_plan_is_flat(const GemmPlan &plan) { return plan.dma && !plan.halo && !plan.wstrip && !plan.wwin && kDma[plan.variant].mix; }
-bool dma_plan_is_strip(const GemmPlan &plan) { return plan.dma && !plan.halo && !plan.wstrip && !plan.wwin && is_strip(plan.variant); }
+bool dma_plan_is_flat(const GemmPlan &plan) { return plan.dma && !plan.halo && !plan.wstrip && !plan.wwin && !plan.win && kDma[plan.variant].mix; }
+bool dma_plan_is_strip(const GemmPlan &plan) { return plan.dma && !plan.halo && !plan.wstrip && !plan.wwin && !plan.win && is_strip(plan.variant); }
 
 // Whether this forward / backward-data plan sums its reduction splits inside the main kernel: asked for by the plan, tiles in
 // natural pixel order, and few enough tiles that a range of the counter ring is not handed out again for at least 64 later launches.
@@ -1595,7 +1596,7 @@ bool dma_fused_reduce_fits(int rowsA, int rowsB, int splits) { return (rowsA & 3
 
 bool dma_plan_fuses_reduce(const GemmPlan &plan)
 {
-    return plan.fused_reduce && plan.dma && !plan.halo && !plan.wstrip && plan.splits > 1 && !is_strip(plan.variant) && !plan.phase &&
+    return plan.fused_reduce && plan.dma && !plan.halo && !plan.wstrip && !plan.win && plan.splits > 1 && !is_strip(plan.variant) && !plan.phase &&
            plan.tilesA * plan.tilesB <= kTicketRing / 64;
 }
 
@@ -1603,6 +1604,7 @@ void dma_kernel_name(int pass, const GemmPlan &pl, char *name, size_t name_bytes
 {
     if (pl.wstrip) { snprintf(name, name_bytes, "k_wgrad_strip"); return; }
     if (pl.wwin) { wwin_kernel_name(pl, name, name_bytes); return; }
+    if (pl.win) { win_kernel_name(pass, pl, name, name_bytes); return; }
     const DmaVariant &d = pass == PASS_WGRAD ? kDmaW[pl.variant] : kDma[pl.variant];
     // as the profiler prints the instantiation: the forward / backward-data kernels carry the group count
     if (pass != PASS_WGRAD && is_strip(pl.variant)) snprintf(name, name_bytes, "k_conv_strip<%s, %d, %d>", pass == PASS_FWD ? "false" : "true", d.TB, d.TA);

@@ -37,24 +37,6 @@ struct WinGeom {
     short at[kTapBlocks * kTapsPerBlock];   // the slot of a tap in its block's window
 };
 
-DEVFN void wait_copies(int n)   // until at most n copies are outstanding
-{
-    switch (n) {
-    case 18: wait_vmcnt<18>(); break;
-    case 15: wait_vmcnt<15>(); break;
-    case 12: wait_vmcnt<12>(); break;
-    case 10: wait_vmcnt<10>(); break;
-    case 9: wait_vmcnt<9>(); break;
-    case 8: wait_vmcnt<8>(); break;
-    case 6: wait_vmcnt<6>(); break;
-    case 5: wait_vmcnt<5>(); break;
-    case 4: wait_vmcnt<4>(); break;
-    case 3: wait_vmcnt<3>(); break;
-    case 2: wait_vmcnt<2>(); break;
-    default: wait_vmcnt<0>();
-    }
-}
-
 constexpr int ROWA = 128, ROWX = 64;   // bytes per slot in LDS
 
 // the fragments of one 16-slot slice: two of dy, one of x per tap

@@ -51,6 +51,26 @@ template <int N> DEVFN void wait_vmcnt()
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
+// the same for a count known only at run time (uniform); counts not listed wait for everything
+DEVFN void wait_copies(int n)
+{
+    switch (n) {
+    case 12: wait_vmcnt<12>(); break;
+    case 11: wait_vmcnt<11>(); break;
+    case 10: wait_vmcnt<10>(); break;
+    case 9: wait_vmcnt<9>(); break;
+    case 8: wait_vmcnt<8>(); break;
+    case 7: wait_vmcnt<7>(); break;
+    case 6: wait_vmcnt<6>(); break;
+    case 5: wait_vmcnt<5>(); break;
+    case 4: wait_vmcnt<4>(); break;
+    case 3: wait_vmcnt<3>(); break;
+    case 2: wait_vmcnt<2>(); break;
+    case 1: wait_vmcnt<1>(); break;
+    default: wait_vmcnt<0>();
+    }
+}
+
 template <int OFF> DEVFN u32x4 lds_read16(unsigned addr)
 {
     u32x4 v;

@@ -152,6 +152,8 @@ constexpr long long kMaxElems = (1ll << 31) - 1;
 constexpr unsigned kKnownFlags = DP_BIAS | DP_RELU | DP_DETERMINISTIC | DP_DX_F32 | DP_RELU_IN;
 // kernels a backward-data call may not use: bit 0 the input-patch kernels (they stage bf16, the caller wants fp32),
 // bit 1 the stationary-weight kernel (it has no fused input-ReLU mask); dgrad_choice adds bits 3 and 4 (dp_kernels.h)
+// a ReLU whose backward is left to the layer behind (DP_RELU_IN: x is such a layer's output) does not feel in which order y is summed
+int fwd_restr(unsigned flags) { return (flags & DP_RELU) && !(flags & DP_RELU_IN) ? RESTR_ORDER : 0; }
 int dgrad_restr(unsigned flags) { return ((flags & DP_DX_F32) ? 1 : 0) | ((flags & DP_RELU_IN) ? 2 : 0); }
 
 dp_status check_conv(const dp_conv_desc *d, ConvGeom *g)
@@ -211,6 +213,7 @@ void plan_uncached(const ConvGeom &g, int pass, int fv, int fs, GemmPlan *pl, in
     pl->halo = false;
     pl->wstrip = false;
     pl->wwin = false;
+    pl->win = false;
     pl->fused_reduce = false;
     pl->over_generic = false;
     // 1000 + v: variant v with the split reduction fused into the main kernel (pipelined forward / backward-data).  Only a forced
@@ -226,9 +229,16 @@ void plan_uncached(const ConvGeom &g, int pass, int fv, int fs, GemmPlan *pl, in
         double time = 0.0;
         if (!auto_plan(g, pass, fs, pl, restr, &time)) mfma_plan(g, pass, -1, fs, pl);
         GemmPlan flat;
-        if (fs <= 0 && ((pass == PASS_FWD && forward_flat_plan(g, *pl, &flat)) ||
-                        (pass == PASS_DGRAD && !(restr & RESTR_BASE) && backward_flat_plan(g, *pl, time, restr, &flat)))) {
+        double flat_time = 0.0;
+        if (fs <= 0 && ((pass == PASS_FWD && forward_flat_plan(g, *pl, &flat, &flat_time)) ||
+                        (pass == PASS_DGRAD && !(restr & RESTR_BASE) && backward_flat_plan(g, *pl, time, restr, &flat, &flat_time)))) {
             flat.over_generic = !pl->fast;
+            *pl = flat;
+            time = flat_time;
+        }
+        const bool window = pass == PASS_FWD ? !(restr & RESTR_ORDER) : pass == PASS_DGRAD && !(restr & (RESTR_BASE | 1));   // bit 0: fp32 gradients
+        if (fs <= 0 && window && pixel_window_plan(g, pass, *pl, time, &flat)) {
+            flat.over_generic = pl->over_generic;
             *pl = flat;
         }
         if (fs <= 0 && pass == PASS_WGRAD && !(restr & RESTR_BASE) && wgrad_window_plan(g, *pl, time, &flat)) *pl = flat;
@@ -314,14 +324,15 @@ PlanRef plan_entry(const ConvGeom &g, int pass, int restr = 0)
         GemmPlan list[kTuneCandidates];
         // a cold measurement judges for itself what the model's warm-cache prices cannot: more candidates, a wider price band
         int n = auto_plan_list(g, pass, fs, list, at == 2 ? kTuneCandidates : 12, restr | (at == 2 ? 4 : 0));
-        if (pass == PASS_WGRAD && n > 0 && fs <= 0 && !g_tight_splits) {
+        if (pass != PASS_WGRAD && n > 0 && n < kTuneCandidates && dma_plan_is_flat(e.plan)) list[n++] = e.plan;   // not one of the list's
+        const bool window = pass == PASS_WGRAD ? !g_tight_splits : pass == PASS_FWD ? !(restr & RESTR_ORDER) : !(restr & (RESTR_BASE | 1));
+        if (window && n > 0 && fs <= 0) {
             GemmPlan win[2];
             double times[2];
-            const int m = wgrad_window_plans(g, win, times);
+            const int m = pass == PASS_WGRAD ? wgrad_window_plans(g, win, times) : pixel_window_plans(g, pass, win, times);
             if (n + m > kTuneCandidates) n = kTuneCandidates - m;   // in the place of the model's last
             for (int i = 0; i < m; ++i) list[n++] = win[i];
         }
-        if (pass != PASS_WGRAD && n > 0 && n < kTuneCandidates && dma_plan_is_flat(e.plan)) list[n++] = e.plan;   // not one of the list's
         if (n > 1) {
             e.cands.assign(list, list + n);
             e.tuned = false;
@@ -355,6 +366,7 @@ hipError_t launch_plan(const ConvArgs &a, hipStream_t st)
     if (a.plan.halo) return halo_launch(a, st);
     if (a.plan.wstrip) return wstrip_launch(a, st);
     if (a.plan.wwin) return wwin_launch(a, st);
+    if (a.plan.win) return win_launch(a, st);
     if (a.plan.dma) return dma_launch(a, st);
     return a.plan.fast ? fast_launch(a, st) : mfma_launch(a, st);
 }
@@ -483,7 +495,7 @@ size_t round256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 dp_status ensure_init()
 {
-    std::call_once(g_init_once, [] { g_init_err = mfma_init(); if (g_init_err == hipSuccess) g_init_err = fast_init(); if (g_init_err == hipSuccess) g_init_err = dma_init(); if (g_init_err == hipSuccess) g_init_err = halo_init(); if (g_init_err == hipSuccess) g_init_err = wstrip_init(); if (g_init_err == hipSuccess) g_init_err = wwin_init(); });
+    std::call_once(g_init_once, [] { g_init_err = mfma_init(); if (g_init_err == hipSuccess) g_init_err = fast_init(); if (g_init_err == hipSuccess) g_init_err = dma_init(); if (g_init_err == hipSuccess) g_init_err = halo_init(); if (g_init_err == hipSuccess) g_init_err = wstrip_init(); if (g_init_err == hipSuccess) g_init_err = wwin_init(); if (g_init_err == hipSuccess) g_init_err = win_init(); });
     if (g_init_err != hipSuccess) return hip_fail(g_init_err, "library initialisation (is a gfx950 device present?)");
     return DP_OK;
 }
@@ -511,7 +523,9 @@ size_t fwd_ws_bytes(const ConvGeom &g)
         const int kpad = small_c_kpad(g);
         return xcol_bytes(g, kpad) + round256((size_t)g.K * kpad * 2) + fwd_ws_bytes(im2col_geom(g, kpad));
     }
-    return plan_entry(g, PASS_FWD)->part_cap;
+    // the query does not depend on the flags: what either plan takes (a plan with partials is not the window kernel's, so the two are one)
+    const size_t part = plan_entry(g, PASS_FWD)->part_cap;
+    return part > 0 ? part : plan_entry(g, PASS_FWD, RESTR_ORDER)->part_cap;
 }
 
 // ---- the three passes on a validated geometry --------------------------------------
@@ -557,7 +571,7 @@ dp_status run_fwd(const ConvGeom &g, int dtype, unsigned flags, const void *x, c
     }
     ConvArgs a{};
     a.g = g; a.pass = PASS_FWD; a.flags = kflags(flags, true);
-    const PlanRef pep = plan_entry(g, PASS_FWD);
+    const PlanRef pep = plan_entry(g, PASS_FWD, fwd_restr(flags));
     PlanEntry &pe = *pep;
     a.plan = current_plan(pe);
     size_t need = pe.part_cap;
@@ -971,7 +985,7 @@ dp_status dp_conv2d_kernel_info(const dp_conv_desc *desc, int pass, char *name, 
         return DP_OK;
     }
     if (pass != PASS_DGRAD && use_small_c(g, pass)) g = im2col_geom(g, small_c_kpad(g));
-    const GemmPlan pl = current_plan(*plan_entry(g, pass, pass == PASS_DGRAD ? dgrad_restr(desc->flags) : 0));
+    const GemmPlan pl = current_plan(*plan_entry(g, pass, pass == PASS_DGRAD ? dgrad_restr(desc->flags) : pass == PASS_FWD ? fwd_restr(desc->flags) : 0));
     if (name != nullptr && name_bytes > 0) plan_kernel_name(pass, pl, pass == PASS_DGRAD && (desc->flags & DP_RELU_IN) != 0, name, name_bytes);
     if (splits != nullptr) *splits = pass != PASS_WGRAD && dma_plan_fuses_reduce(pl) ? -pl.splits : pl.splits;
     return DP_OK;

@@ -22,6 +22,7 @@ enum { PASS_FWD = 0, PASS_DGRAD = 1, PASS_WGRAD = 2 };
 // bits of the planner's `restr` (0 - 2: auto_plan_list)
 enum {
     RESTR_SAVED = 8,   // backward-data with a saved output to mask dy by: the generic kernel does that while it loads, the others need a pass
+    RESTR_ORDER = 32,  // forward of a layer that keeps its ReLU's mask to itself: the kernels may not add in another order (forward_flat_plan says why)
     RESTR_BASE = 16,   // the kernels and prices that need least scratch: no flat-walk kernel in backward-data
 };
 
@@ -49,6 +50,7 @@ struct GemmPlan {
     bool phase = false;   // strided backward-data walks the input pixels stride phase by stride phase (conv_dma.hip)
     bool fill = false;    // phase, 1x1 filter: only the first phase has tiles, they store the zeros of the others
     bool wstrip = false;  // filter gradient with the x strip shared by the taps of a filter row (conv_wstrip.hip); implies dma
+    bool win = false;     // forward / backward-data with one window of pixels for all taps (conv_win.hip); implies dma
     bool wwin = false;    // filter gradient with one window of x for all taps of a block (conv_wwin.hip); implies dma
     bool row_taps = false;   // wwin: three taps of one filter row per wave
     bool db_wave = false; // input-patch filter gradient: one more wave per block can sum the bias gradient (at most 15 taps)
@@ -82,6 +84,13 @@ void dp_trace_main_kernel_done(hipStream_t st);
 hipError_t wstrip_init();
 bool wstrip_plan(const ConvGeom &g, int force_splits, GemmPlan *pl);
 hipError_t wstrip_launch(const ConvArgs &a, hipStream_t st);
+
+// conv_win.hip
+hipError_t win_init();
+bool win_plan(const ConvGeom &g, int pass, int variant, GemmPlan *pl);
+void win_kernel_name(int pass, const GemmPlan &pl, char *name, size_t name_bytes);
+hipError_t win_launch(const ConvArgs &a, hipStream_t st);
+bool win_work(const ConvGeom &g, int pass, int variant, int *rounds, int *rows);   // channel rounds of a block, window rows copied in each
 
 // conv_wwin.hip
 hipError_t wwin_init();
@@ -146,9 +155,12 @@ hipError_t rbg_launch_final(int k, int row_blocks, const float *ws, float *dbias
 // planner.hip : picks the cheapest fast-path variant and split for a pass (host-side cost model)
 bool auto_plan(const ConvGeom &g, int pass, int force_splits, GemmPlan *plan, int restr = 0, double *time = nullptr);
 // forward: the flat-walk plan that adds in the same order as `base` and is faster, if there is one
-bool forward_flat_plan(const ConvGeom &g, const GemmPlan &base, GemmPlan *plan);
+bool forward_flat_plan(const ConvGeom &g, const GemmPlan &base, GemmPlan *plan, double *time);
 // backward-data: a flat-walk plan faster than `base`, whose price is `time`
-bool backward_flat_plan(const ConvGeom &g, const GemmPlan &base, double time, int restr, GemmPlan *plan);
+bool backward_flat_plan(const ConvGeom &g, const GemmPlan &base, double time, int restr, GemmPlan *plan, double *flat_time);
+// forward / backward-data: the window kernel's two cheapest plans, and whether it takes the place of `base`, whose price is `time`
+int pixel_window_plans(const ConvGeom &g, int pass, GemmPlan out[2], double times[2]);
+bool pixel_window_plan(const ConvGeom &g, int pass, const GemmPlan &base, double time, GemmPlan *out);
 // filter gradient: the window kernel's two cheapest plans, and whether it takes the place of `base`, whose price is `time`
 int wgrad_window_plans(const ConvGeom &g, GemmPlan out[2], double times[2]);
 bool wgrad_window_plan(const ConvGeom &g, const GemmPlan &base, double time, GemmPlan *out);

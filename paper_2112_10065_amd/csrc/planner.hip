@@ -92,6 +92,7 @@ bool family_plan(const ConvGeom &g, int pass, int code, int splits, GemmPlan *pl
     pl->halo = false;
     pl->wstrip = false;
     pl->wwin = false;
+    pl->win = false;
     if (code >= 400) return halo_plan(g, pass, code, splits, pl);
     if (code >= 200) return dma_plan(g, pass, code, splits, pl, (restr & 1) != 0);
     return fast_plan(g, pass, code, splits, pl);
@@ -234,7 +235,7 @@ int auto_plan_list(const ConvGeom &g, int pass, int force_splits, GemmPlan *out,
 //   64x64 tiles of 32-wide steps, unsplit: 1 step 0.91, 3 steps 0.98, 4 steps 1.01, 6 and more 1.06 - 1.17; split 1.01 - 1.24
 //   64x128 / 128x128 pipelined tiles of 32-wide steps: unsplit 0.79 - 1.15, with partials 0.93 - 1.17, neither worth the change; their 2 or
 //   4 splits as reduction groups of blocks that all run at once, no reduction kernel: 1.39 - 1.63
-bool forward_flat_plan(const ConvGeom &g, const GemmPlan &base, GemmPlan *out)
+bool forward_flat_plan(const ConvGeom &g, const GemmPlan &base, GemmPlan *out, double *time)
 {
     if (g.C % 64 == 0 || g.C % 8 != 0 || g.R * g.S > 31 || base.BK != 32 || (base.splits > 1 && base.steps_per_split % 2 != 0)) return false;
     const int steps = (g.R * g.S * g.C + 63) / 64;
@@ -256,6 +257,7 @@ bool forward_flat_plan(const ConvGeom &g, const GemmPlan &base, GemmPlan *out)
         const double t = price(g, PASS_FWD, c, pl, 0);
         if (!found || t < best) { best = t; *out = pl; found = true; }
     }
+    *time = best;
     return found;
 }
 
@@ -268,7 +270,7 @@ bool forward_flat_plan(const ConvGeom &g, const GemmPlan &base, GemmPlan *out)
 //   64x64 register-staged tiles: 0.74 - 0.89 up to 7 steps, 0.93 - 1.15 beyond, left alone; 128x128 pipelined: 0.80 - 1.09, left alone
 //   64x128 pipelined, unit stride: unsplit 0.76 - 1.07, left alone; split 0.96 - 1.5, taken where the prices are 8 % apart (then 1.04 - 1.5)
 //   64x128 pipelined, stride 2 (by phase): split 1.2 - 1.5; unsplit from 5 steps on and in one block per CU 1.14 - 1.25, else 0.86 - 1.18
-bool backward_flat_plan(const ConvGeom &g, const GemmPlan &base, double time, int restr, GemmPlan *out)
+bool backward_flat_plan(const ConvGeom &g, const GemmPlan &base, double time, int restr, GemmPlan *out, double *flat_time)
 {
     if (g.K % 64 == 0 || g.K % 8 != 0 || g.C % 8 != 0 || g.R * g.S > 31 || base.BK != 32) return false;
     const bool strided = g.sh > 1 || g.sw > 1, generic = !base.fast;
@@ -292,10 +294,71 @@ bool backward_flat_plan(const ConvGeom &g, const GemmPlan &base, double time, in
             const double t = price(g, PASS_DGRAD, c, pl, restr) + (pl.splits > 1 ? 1.5 : 0.0);
             if (!found || t < best) { best = t; *out = pl; found = true; }
         }
+    *flat_time = best;
     return found && (generic || strided || best < 0.92 * time);
 }
 
-// The window kernel's two cheapest plans, best first; returns how many there are.  Chunks of 256 slots where the window fits (never slower
+// Forward / backward-data by the window kernel (conv_win.hip): us = c0 + rounds of blocks * (c1 + rounds of channels * (c2 + c3 taps + c4 window rows)),
+// fitted to 2420 timings (310 layers; median error 2 - 4 %, 5 - 9 % for nine of ten)
+struct WindowPrice { float c0, c1, c2, c3, c4; };
+const WindowPrice kWindowPrice[2][6] = {
+    {{-0.6f, 7.5f, 0.13f, 0.280f, 0.0023f}, {1.5f, 4.1f, 0.48f, 0.098f, 0.0007f}, {1.9f, 3.1f, 0.45f, 0.090f, 0.0006f}, {1.4f, 4.0f, 0.44f, 0.188f, 0.0001f},
+     {1.2f, 4.4f, 0.29f, 0.196f, 0.0011f}, {1.2f, 5.7f, 0.39f, 0.143f, 0.0014f}},
+    {{-0.3f, 7.0f, 0.0f, 0.307f, 0.0034f}, {1.5f, 4.9f, 0.39f, 0.103f, 0.0006f}, {1.9f, 3.1f, 0.38f, 0.101f, 0.0006f}, {1.4f, 4.8f, 0.36f, 0.189f, 0.0003f},
+     {1.3f, 5.3f, 0.18f, 0.189f, 0.0017f}, {1.0f, 5.5f, 0.34f, 0.160f, 0.0015f}}};
+
+// its two cheapest plans, best first; returns how many there are
+int pixel_window_plans(const ConvGeom &g, int pass, GemmPlan out[2], double times[2])
+{
+    int n = 0;
+    for (int v = 0; v < 6; ++v) {
+        GemmPlan pl;
+        int rounds, rows;   // channel rounds of a block, window rows copied per round
+        if (!family_plan(g, pass, 250 + v, 1, &pl) || !win_work(g, pass, v, &rounds, &rows)) continue;
+        const WindowPrice &c = kWindowPrice[pass == PASS_FWD ? 0 : 1][v];
+        const double waves = std::ceil((double)pl.tilesA * pl.tilesB / 256.0);
+        double t = c.c0 + waves * (c.c1 + rounds * (c.c2 + c.c3 * g.R * g.S + c.c4 * rows));
+        // backward-data with 32 channels to a tile fetches half a line per weight row: beyond the 4 MB of an L2 that counts twice
+        // (14 x 14, 512 -> 512, one sample: 14.7 us for a fitted 10.5)
+        if (v == 2 && pass == PASS_DGRAD && (long long)g.K * g.R * g.S * g.C * 2 > 2000000) t *= 1.4;
+        if (n == 0 || t < times[0]) {
+            if (n > 0) { out[1] = out[0]; times[1] = times[0]; }
+            out[0] = pl; times[0] = t;
+            n = std::min(n + 1, 2);
+        } else if (n == 1 || t < times[1]) {
+            out[1] = pl; times[1] = t;
+            n = 2;
+        }
+    }
+    return n;
+}
+
+// The window kernel in the place of `base` (price `time`), where its own price lies 8 % below what the other's is worth: the prices were made to rank
+// the kernels among themselves and are off by a launch's floor and a factor, fitted per family to 510 passes timed both ways (median error 3 - 6 %;
+// register-staged and flat kernels by a factor alone).
+bool pixel_window_plan(const ConvGeom &g, int pass, const GemmPlan &base, double time, GemmPlan *out)
+{
+    GemmPlan pl[2];
+    double t[2];
+    if (!base.fast || time <= 0.0 || pixel_window_plans(g, pass, pl, t) == 0) return false;
+    const bool fwd = pass == PASS_FWD, split = base.splits > 1;
+    double floor_us = 0.0, factor = 0.0;   // not in the place of unsplit flat or register-staged kernels forward, nor of flat ones backward
+    if (base.halo) { floor_us = fwd ? 0.3 : -1.6; factor = fwd ? 1.13 : 1.34; }
+    else if (dma_plan_is_strip(base)) { floor_us = -4.4; factor = fwd ? 1.11 : 1.24; }
+    else if (dma_plan_is_flat(base)) factor = fwd && split ? 0.9 : 0.0;
+    else if (!base.dma) { floor_us = fwd ? 0.0 : -3.6; factor = !fwd ? 1.03 : split ? 0.76 : 0.0; }
+    else if (fwd) { floor_us = split ? -7.0 : -4.6; factor = split ? 1.3 : 1.08; }
+    else { floor_us = split ? -6.0 : -4.4; factor = split ? 1.3 : 1.25; }
+    // more than one round of blocks: the last one is priced as full, the others' is not; three or four taps: little is saved on the window, and
+    // the shortest layers lie at the floor of a launch
+    const long long tiles = (long long)pl[0].tilesA * pl[0].tilesB;
+    const double margin = g.R * g.S < 5 ? 0.75 : tiles > 512 ? 0.78 : tiles > 256 ? 0.85 : 0.92;
+    if (t[0] >= margin * (floor_us + factor * time)) return false;
+    *out = pl[0];
+    return true;
+}
+
+// The filter gradient's window kernel: its two cheapest plans, best first; returns how many there are.  Chunks of 256 slots where the window fits (never slower
 // than 128 in the timings behind price_window), up to eight splits or what fills the chip once or twice.
 int wgrad_window_plans(const ConvGeom &g, GemmPlan out[2], double times[2])
 {

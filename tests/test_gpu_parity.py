@@ -812,6 +812,55 @@ def test_filter_gradient_pixel_strip_kernel(env, splits):
         dp.dp_set_override(2, -1, 0)
 
 
+@pytest.mark.parametrize("variant", [250, 251, 252, 253, 254, 255])
+def test_pixel_window_kernel(env, variant):
+    """Forward and backward-data with one window of pixels for all taps: output channels below, at and above a tile, reduction channels that end
+    inside a block of 64 and one to eight blocks of them (waves without a block of their own), images smaller than a tile, no, usual and
+    wide padding, rows that nearly fill the window, filters with fewer taps than tap groups and with an uneven share; with bias, ReLU and the
+    fused input-ReLU mask, and without."""
+    dp, U, orc = env
+    for p in (0, 1):
+        dp.dp_set_override(p, variant, 0)
+    try:
+        for tag, n, h, w, c, k, r, s, pd in (("pw_a", 2, 7, 7, 64, 64, 3, 3, (1, 1)), ("pw_b", 1, 14, 14, 40, 72, 3, 3, (0, 0)), ("pw_c", 2, 9, 30, 200, 136, 3, 3, (1, 1)),
+                                             ("pw_d", 1, 4, 56, 72, 128, 3, 3, (1, 1)), ("pw_e", 20, 2, 3, 8, 64, 3, 3, (2, 2)), ("pw_f", 2, 17, 17, 160, 192, 1, 7, (0, 3)),
+                                             ("pw_g", 1, 13, 13, 96, 64, 7, 1, (3, 0)), ("pw_h", 1, 11, 12, 24, 64, 5, 5, (2, 2)), ("pw_i", 1, 9, 9, 8, 16, 2, 5, (1, 3)),
+                                             ("pw_j", 1, 6, 9, 512, 48, 1, 3, (0, 1))):
+            for front in (False, True):   # bias, ReLU and the mask of the ReLU in front, or a bare convolution
+                case = U.ConvCase(tag, n, h, w, c, k, r, s, (1, 1), pd, bf16=True, bias=front, relu=False)
+                if front:
+                    case.desc.flags |= dp.DP_RELU | dp.DP_RELU_IN
+                names = [dp.dp_conv2d_kernel_info(case.desc, p)[0] for p in (0, 1)]
+                if tag in {252: ("pw_d",), 253: ("pw_c", "pw_d", "pw_g", "pw_h")}.get(variant, ()):   # two windows of that many rows do not fit
+                    assert not any("k_conv_win" in name for name in names)
+                    continue
+                assert all("k_conv_win" in name for name in names), tag
+                y = case.run_fwd(U.workspace(256))
+                dx = case.run_dgrad_relu_in(None) if front else case.run_dgrad(None)
+                torch.cuda.synchronize()
+                ref = orc.conv2d_bwd_data(case.dy, case.w, case.x.shape, y_saved=None, pad=pd)
+                if front:
+                    ref = ref * (case.x > 0)
+                # outputs rounded to bf16: relative error 2^-9 each, half of that in the mean
+                assert U.errs(U.to_np(y), orc.conv2d_fwd(case.x, case.w, case.b if front else None, relu=front, pad=pd))[0] <= 2.5e-3, (tag, front)
+                assert U.errs(U.to_np(dx), ref)[0] <= 2.5e-3, (tag, front)
+        for tag, c, st, dx_f32 in (("pw_s2", 64, (2, 2), False), ("pw_c12", 12, (1, 1), False), ("pw_f32", 64, (1, 1), True)):   # not this kernel's
+            case = U.ConvCase(tag, 1, 9, 9, c, 64, 3, 3, st, (1, 1), bf16=True, bias=True, relu=True, dx_f32=dx_f32)
+            assert "k_conv_win" not in dp.dp_conv2d_kernel_info(case.desc, 1)[0]
+    finally:
+        for p in (0, 1):
+            dp.dp_set_override(p, -1, 0)
+
+
+def test_forward_that_keeps_its_mask_keeps_the_order_of_its_sums(env):
+    """The window kernel adds by tap groups.  A layer whose own ReLU masks its gradients (DP_RELU without DP_RELU_IN) does not take it."""
+    dp, U, orc = env
+    desc = lambda flags: dp.conv_desc(4, 28, 28, 512, 512, 3, 3, (1, 1), (1, 1), dp.DP_BF16, flags)
+    assert "k_conv_win" in dp.dp_conv2d_kernel_info(desc(dp.DP_BIAS | dp.DP_RELU | dp.DP_RELU_IN), 0)[0]
+    assert "k_conv_win" in dp.dp_conv2d_kernel_info(desc(0), 0)[0]
+    assert "k_conv_win" not in dp.dp_conv2d_kernel_info(desc(dp.DP_BIAS | dp.DP_RELU), 0)[0]
+
+
 @pytest.mark.parametrize("slots,splits", [(128, 1), (128, 3), (256, 1), (256, 2)])
 def test_filter_gradient_window_kernel(env, slots, splits):
     """Unit-stride filter gradients with one window of x for all taps of a block: channels below, at and above a tile, images smaller than a
