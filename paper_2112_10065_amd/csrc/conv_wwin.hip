@@ -24,7 +24,7 @@ namespace {
 
 constexpr int kWaves = 12, kTables = 4, kMaxStages = 3, kTapBlocks = 4, kTapsPerBlock = 9;
 constexpr int dy_copies(int T) { return T / 8; }   // copies of one KB
-constexpr int lane_copies(int T) { return T == 128 ? 4 : 6; }   // most copies of a wave per chunk
+constexpr int lane_copies(int T) { return T == 128 ? 5 : 6; }   // most copies of a wave per chunk
 constexpr int kLdsBytes = 160 * 1024, kSumBytes = 3 * 3 * 4 * 3 * 64 * 16;   // the sums of three slice groups for one half of the tiles
 
 struct WinGeom {

@@ -865,16 +865,17 @@ def test_forward_that_keeps_its_mask_keeps_the_order_of_its_sums(env):
 def test_filter_gradient_window_kernel(env, slots, splits):
     """Unit-stride filter gradients with one window of x for all taps of a block: channels below, at and above a tile, images smaller than a
     chunk and chunks that end inside a row, no, usual and wide padding, rows that nearly fill the window, filters of one to three tap
-    blocks (chunks of 128 slots only); with the fused bias gradient and behind a saved output."""
+    blocks (those and the widest rows with chunks of 128 slots only); with the fused bias gradient and behind a saved output."""
     dp, U, orc = env
     dp.dp_set_override(2, 317 if slots == 128 else 318, splits)
     try:
         for tag, n, h, w, c, k, r, s, pd in (("win_a", 2, 7, 7, 64, 64, 3, 3, (1, 1)), ("win_b", 1, 14, 14, 40, 72, 3, 3, (0, 0)), ("win_c", 3, 9, 30, 32, 136, 3, 3, (1, 1)),
                                              ("win_d", 1, 4, 110, 72, 8, 3, 3, (1, 1)), ("win_e", 20, 2, 3, 8, 64, 3, 3, (2, 2)), ("win_f", 2, 17, 17, 48, 40, 1, 7, (0, 3)),
-                                             ("win_g", 1, 17, 17, 32, 64, 7, 1, (3, 0)), ("win_h", 2, 11, 12, 24, 64, 5, 5, (2, 2)), ("win_i", 1, 9, 9, 8, 16, 2, 5, (1, 3))):
+                                             ("win_g", 1, 17, 17, 32, 64, 7, 1, (3, 0)), ("win_h", 2, 11, 12, 24, 64, 5, 5, (2, 2)), ("win_i", 1, 9, 9, 8, 16, 2, 5, (1, 3)),
+                                             ("win_j", 1, 3, 224, 32, 64, 3, 3, (1, 1))):
             case = U.ConvCase(tag, n, h, w, c, k, r, s, (1, 1), pd, bf16=True, bias=True, relu=True)
             name, got_splits = dp.dp_conv2d_kernel_info(case.desc, 2)
-            if slots == 256 and (r, s) != (3, 3):
+            if slots == 256 and ((r, s) != (3, 3) or w > 150):
                 assert not name.startswith("k_wgrad_win")
                 continue
             assert name.startswith(f"k_wgrad_win<{slots}") and 1 <= got_splits <= splits
