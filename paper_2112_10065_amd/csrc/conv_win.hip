@@ -14,7 +14,9 @@
 // Where a copy's data lies depends on the tile only: all offsets are computed before the loop, steps ride in the scalar offset.
 // Measured (us, before: the best of the other kernels with their reduction kernel): 512 -> 512 on 28 x 28, 8 samples, forward 39.1 -> 34.5, masked
 // backward-data 41.7 -> 36.6; 4 samples 28.2 -> 24.0 and 29.6 -> 25.2; 512 -> 512 on 14 x 14, 8 samples 22.5 -> 15.6 and 25.6 -> 17.9; 288 -> 384 on
-// 35 x 35, 4 samples 32.4 -> 18.4 and 23.3 -> 19.5.  What bounds it: LDS (reads of 1.25 - 1.5 fragments per matrix instruction and the copies,
+// 35 x 35, 4 samples 32.4 -> 18.4 and 23.3 -> 19.5.  Tiles of 96 channels (three waves side by side, four tap groups) for channel counts that 64 and 128
+// divide badly, or that fill the chip better so: backward-data 192 -> 80 on 73 x 73, 4 samples 23.6 -> 14.5; forward 272 -> 96 there 25.3 -> 19.4,
+// 384 -> 288 on 26 x 26, 11 samples 28.3 -> 21.6, 512 -> 512 on 28 x 28, 8 samples 33 -> 28.  What bounds it: LDS (reads of 1.25 - 1.5 fragments per matrix instruction and the copies,
 // 115 bytes per clock together), and 6 us of launch, first copies, sums and stores.
 #include "dma_common.h"
 #include <cstdio>
@@ -75,7 +77,7 @@ template <bool DG, int FA, int FB> struct Frags {
 // Backward-data with tiles of two fragments' width and height: the waves go in pairs that share 64 channels and take two of the four slices each.
 // A wave's weights are then 32 reduction rows of 128 bytes instead of 64 of 64 (copies of 64-byte rows run at half the rate), and four
 // fragment reads serve four matrix instructions instead of three two.
-template <bool DG, int WA, int FB> constexpr int win_fa() { return DG && WA >= 2 && FB == 2 ? 2 : 1; }
+template <bool DG, int WA, int FB> constexpr int win_fa() { return DG && WA % 2 == 0 && FB == 2 ? 2 : 1; }
 
 template <bool DG, int WA, int CBP, int FB>
 __global__ __launch_bounds__(kThreads) void k_conv_win(const KArgs p, const WinArgs q)
@@ -86,7 +88,8 @@ __global__ __launch_bounds__(kThreads) void k_conv_win(const KArgs p, const WinA
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const ConvGeom &g = p.g;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int grp = wave % G, wc = wave / G % WCH, sp = wave / G / WCH % FA, cbp = wave / G / WA;   // taps, channels, slices, channel block
+    // four tap groups would meet the four SIMDs one to one, and the group with a tap more would be one SIMD's alone: each row of waves shifts by one
+    const int grp = G == 4 ? (wave + wave / 4) % 4 : wave % G, wc = wave / G % WCH, sp = wave / G / WCH % FA, cbp = wave / G / WA;   // taps, channels, slices, channel block
     const int tile = logical_block(blockIdx.x, gridDim.x), tb = tile / p.tilesA, a0 = (tile - tb * p.tilesA) * TA, u0 = tb * TB;
     const int RS = g.R * g.S, RSC = RS * g.C, win_bytes = q.wrows * 128, rounds = (q.ncb + CBP - 1) / CBP;
     const int each = RS / G, more = RS - G * each, tap0 = grp * each + min(grp, more), nt = each + (grp < more ? 1 : 0);   // this wave's taps
@@ -262,9 +265,9 @@ __global__ __launch_bounds__(kThreads) void k_conv_win(const KArgs p, const WinA
     if (mask)
 #pragma unroll
         for (int i = 0; i < ITERS; ++i) xm[i] = __builtin_amdgcn_raw_buffer_load_b128(rin, voffO[i], 0, 0);
-    // Every wave leaves its sums, two fragments at a time; all threads add the groups' in order and stage the finished values.
+    // Every wave leaves its sums, two fragments at a time (one, of an odd number); all threads add the groups' in order and stage the finished values.
     const int kg = (cbp * FA + sp) * G + grp;
-    constexpr int NF = FA * FB, FP = NF < 2 ? NF : 2, QUADS = WCH * FP * 4 * 64;   // fragments per pass, groups of four values per pass
+    constexpr int NF = FA * FB, FP = NF % 2 != 0 ? 1 : 2, QUADS = WCH * FP * 4 * 64;   // fragments per pass, groups of four values per pass
     f32x4 *sum = reinterpret_cast<f32x4 *>(smem);                                  // [group][channel wave][fragment][quad][lane]
     bf16_t *stage = reinterpret_cast<bf16_t *>(smem + KG * QUADS * 16);
 #pragma unroll
@@ -302,8 +305,8 @@ __global__ __launch_bounds__(kThreads) void k_conv_win(const KArgs p, const WinA
 
 typedef void (*WinFn)(const KArgs, const WinArgs);
 struct WinVariant { int WA, CBP, FB; };
-const WinVariant kWin[] = {{4, 1, 4}, {2, 1, 2}, {1, 2, 1}, {2, 2, 2}, {4, 1, 2}, {2, 1, 4}};
-constexpr int kNumWin = 6;
+const WinVariant kWin[] = {{4, 1, 4}, {2, 1, 2}, {1, 2, 1}, {2, 2, 2}, {4, 1, 2}, {2, 1, 4}, {3, 1, 2}, {3, 1, 3}, {3, 1, 4}};
+constexpr int kNumWin = 9;
 template <bool DG> WinFn pick(int v)
 {
     switch (v) {
@@ -312,7 +315,10 @@ template <bool DG> WinFn pick(int v)
     case 2: return k_conv_win<DG, 1, 2, 1>;
     case 3: return k_conv_win<DG, 2, 2, 2>;
     case 4: return k_conv_win<DG, 4, 1, 2>;
-    default: return k_conv_win<DG, 2, 1, 4>;
+    case 5: return k_conv_win<DG, 2, 1, 4>;
+    case 6: return k_conv_win<DG, 3, 1, 2>;
+    case 7: return k_conv_win<DG, 3, 1, 3>;
+    default: return k_conv_win<DG, 3, 1, 4>;
     }
 }
 
@@ -337,7 +343,7 @@ bool win_args(const ConvGeom &g, bool dg, const WinVariant &d, WinArgs *q, long 
     const long long wrows = (TB + (long long)(g.R - 1) * q->P + g.S - 1 + 7) / 8 * 8;
     if (*slots >= 0x3fffffffLL || wrows > kMaxWindowCopies * kWaves * 8) return false;
     q->wrows = (int)wrows;
-    const int sums = kWaves * (d.FB < 2 ? 1 : 2) * kSlot + TB * (TA + 8) * 2, tiles = kWeightBytes + 2 * d.CBP * q->wrows * 128, extra = (TB + TA) * 4;
+    const int sums = kWaves * (d.FB % 2 != 0 ? 1 : 2) * kSlot + TB * (TA + 8) * 2, tiles = kWeightBytes + 2 * d.CBP * q->wrows * 128, extra = (TB + TA) * 4;
     if (sums > tiles || tiles + extra > kLdsBytes) return false;   // the row map and the bias behind the tiles outlive the sums
     *lds = (size_t)tiles + extra;
     return true;

@@ -299,19 +299,21 @@ bool backward_flat_plan(const ConvGeom &g, const GemmPlan &base, double time, in
 }
 
 // Forward / backward-data by the window kernel (conv_win.hip): us = c0 + rounds of blocks * (c1 + rounds of channels * (c2 + c3 taps + c4 window rows)),
-// fitted to 2420 timings (310 layers; median error 2 - 4 %, 5 - 9 % for nine of ten)
+// fitted to 2420 timings (310 layers; median error 2 - 4 %, 5 - 9 % for nine of ten), the tiles of 96 channels to 570 (130 layers; 2 - 3 %, 6 - 9 %)
 struct WindowPrice { float c0, c1, c2, c3, c4; };
-const WindowPrice kWindowPrice[2][6] = {
+const WindowPrice kWindowPrice[2][9] = {
     {{-0.6f, 7.5f, 0.13f, 0.280f, 0.0023f}, {1.5f, 4.1f, 0.48f, 0.098f, 0.0007f}, {1.9f, 3.1f, 0.45f, 0.090f, 0.0006f}, {1.4f, 4.0f, 0.44f, 0.188f, 0.0001f},
-     {1.2f, 4.4f, 0.29f, 0.196f, 0.0011f}, {1.2f, 5.7f, 0.39f, 0.143f, 0.0014f}},
+     {1.2f, 4.4f, 0.29f, 0.196f, 0.0011f}, {1.2f, 5.7f, 0.39f, 0.143f, 0.0014f},
+     {1.0f, 4.0f, 0.29f, 0.173f, 0.0008f}, {0.8f, 5.3f, 0.40f, 0.194f, 0.0005f}, {-0.3f, 7.2f, 0.35f, 0.222f, 0.0013f}},
     {{-0.3f, 7.0f, 0.0f, 0.307f, 0.0034f}, {1.5f, 4.9f, 0.39f, 0.103f, 0.0006f}, {1.9f, 3.1f, 0.38f, 0.101f, 0.0006f}, {1.4f, 4.8f, 0.36f, 0.189f, 0.0003f},
-     {1.3f, 5.3f, 0.18f, 0.189f, 0.0017f}, {1.0f, 5.5f, 0.34f, 0.160f, 0.0015f}}};
+     {1.3f, 5.3f, 0.18f, 0.189f, 0.0017f}, {1.0f, 5.5f, 0.34f, 0.160f, 0.0015f},
+     {1.3f, 3.6f, 0.18f, 0.200f, 0.0006f}, {1.0f, 5.1f, 0.17f, 0.213f, 0.0013f}, {0.4f, 5.9f, 0.0f, 0.262f, 0.0024f}}};
 
 // its two cheapest plans, best first; returns how many there are
 int pixel_window_plans(const ConvGeom &g, int pass, GemmPlan out[2], double times[2])
 {
     int n = 0;
-    for (int v = 0; v < 6; ++v) {
+    for (int v = 0; v < 9; ++v) {
         GemmPlan pl;
         int rounds, rows;   // channel rounds of a block, window rows copied per round
         if (!family_plan(g, pass, 250 + v, 1, &pl) || !win_work(g, pass, v, &rounds, &rows)) continue;
@@ -342,18 +344,21 @@ bool pixel_window_plan(const ConvGeom &g, int pass, const GemmPlan &base, double
     double t[2];
     if (!base.fast || time <= 0.0 || pixel_window_plans(g, pass, pl, t) == 0) return false;
     const bool fwd = pass == PASS_FWD, split = base.splits > 1;
-    double floor_us = 0.0, factor = 0.0;   // not in the place of unsplit flat or register-staged kernels forward, nor of flat ones backward
+    double floor_us = 0.0, factor = 0.0;   // not in the place of unsplit register-staged kernels forward
     if (base.halo) { floor_us = fwd ? 0.3 : -1.6; factor = fwd ? 1.13 : 1.34; }
-    else if (dma_plan_is_strip(base)) { floor_us = -4.4; factor = fwd ? 1.11 : 1.24; }
-    else if (dma_plan_is_flat(base)) factor = fwd && split ? 0.9 : 0.0;
+    else if (dma_plan_is_strip(base)) { floor_us = -4.4; factor = fwd ? 1.11 : 1.16; }
+    else if (dma_plan_is_flat(base)) factor = 1.0;
     else if (!base.dma) { floor_us = fwd ? 0.0 : -3.6; factor = !fwd ? 1.03 : split ? 0.76 : 0.0; }
     else if (fwd) { floor_us = split ? -7.0 : -4.6; factor = split ? 1.3 : 1.08; }
     else { floor_us = split ? -6.0 : -4.4; factor = split ? 1.3 : 1.25; }
+    double worth = floor_us + factor * time;
+    if (fwd && base.dma && base.BK == 32) worth = std::max(worth, 1.5 * time - 14.0);   // 32-wide steps: 1.3 - 1.6 of the price for long layers, 0.75 for short ones
+    if (base.dma && base.BK != 32 && !base.halo && !dma_plan_is_strip(base)) worth = std::min(worth, (fwd ? 1.0 : 1.05) * time);   // long: 0.8 - 1.0, 0.95 - 1.15
     // more than one round of blocks: the last one is priced as full, the others' is not; three or four taps: little is saved on the window, and
     // the shortest layers lie at the floor of a launch
     const long long tiles = (long long)pl[0].tilesA * pl[0].tilesB;
     const double margin = g.R * g.S < 5 ? 0.75 : tiles > 512 ? 0.78 : tiles > 256 ? 0.85 : 0.92;
-    if (t[0] >= margin * (floor_us + factor * time)) return false;
+    if (t[0] >= margin * worth) return false;
     *out = pl[0];
     return true;
 }

@@ -812,7 +812,7 @@ def test_filter_gradient_pixel_strip_kernel(env, splits):
         dp.dp_set_override(2, -1, 0)
 
 
-@pytest.mark.parametrize("variant", [250, 251, 252, 253, 254, 255])
+@pytest.mark.parametrize("variant", [250, 251, 252, 253, 254, 255, 256, 257, 258])
 def test_pixel_window_kernel(env, variant):
     """Forward and backward-data with one window of pixels for all taps: output channels below, at and above a tile, reduction channels that end
     inside a block of 64 and one to eight blocks of them (waves without a block of their own), images smaller than a tile, no, usual and
