@@ -344,10 +344,11 @@ bool pixel_window_plan(const ConvGeom &g, int pass, const GemmPlan &base, double
     double t[2];
     if (!base.fast || time <= 0.0 || pixel_window_plans(g, pass, pl, t) == 0) return false;
     const bool fwd = pass == PASS_FWD, split = base.splits > 1;
-    double floor_us = 0.0, factor = 0.0;   // not in the place of unsplit register-staged kernels forward
+    if (!fwd && base.BK == 32 && pl[0].variant >= 6 && g.R * g.S < 5) return false;   // 96-channel tiles were fitted from 7 taps on
+    double floor_us = 0.0, factor = 0.0;   // not in the place of unsplit register-staged kernels forward, nor of flat ones backward with few taps
     if (base.halo) { floor_us = fwd ? 0.3 : -1.6; factor = fwd ? 1.13 : 1.34; }
     else if (dma_plan_is_strip(base)) { floor_us = -4.4; factor = fwd ? 1.11 : 1.16; }
-    else if (dma_plan_is_flat(base)) factor = 1.0;
+    else if (dma_plan_is_flat(base)) factor = fwd || g.R * g.S > 8 ? 1.0 : 0.0;   // backward-data: 3x3 and 5x5 1.17 - 1.78 times as fast, fewer taps 1.1 - 1.4 and no further checked
     else if (!base.dma) { floor_us = fwd ? 0.0 : -3.6; factor = !fwd ? 1.03 : split ? 0.76 : 0.0; }
     else if (fwd) { floor_us = split ? -7.0 : -4.6; factor = split ? 1.3 : 1.08; }
     else { floor_us = split ? -6.0 : -4.4; factor = split ? 1.3 : 1.25; }
