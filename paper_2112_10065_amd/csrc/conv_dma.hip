@@ -1604,7 +1604,7 @@ void dma_kernel_name(int pass, const GemmPlan &pl, char *name, size_t name_bytes
 {
     if (pl.wstrip) { snprintf(name, name_bytes, "k_wgrad_strip"); return; }
     if (pl.wwin) { wwin_kernel_name(pl, name, name_bytes); return; }
-    if (pl.win) { win_kernel_name(pass, pl, name, name_bytes); return; }
+    if (pl.win) { win_kernel_name(pass, pl, false, name, name_bytes); return; }
     const DmaVariant &d = pass == PASS_WGRAD ? kDmaW[pl.variant] : kDma[pl.variant];
     // as the profiler prints the instantiation: the forward / backward-data kernels carry the group count
     if (pass != PASS_WGRAD && is_strip(pl.variant)) snprintf(name, name_bytes, "k_conv_strip<%s, %d, %d>", pass == PASS_FWD ? "false" : "true", d.TB, d.TA);

@@ -23,7 +23,7 @@
 
 namespace {
 
-constexpr int kWaves = 12, kThreads = 64 * kWaves, kMaxWindowCopies = 4, kLdsBytes = 160 * 1024, kSlot = 4096, kWeightBytes = kWaves * 2 * kSlot;
+constexpr int kWaves = 12, kThreads = 64 * kWaves, kMaxWindowCopies = 3, kLdsBytes = 160 * 1024, kSlot = 4096, kWeightBytes = kWaves * 2 * kSlot;
 
 struct WinArgs {
     int P, HP;                 // slots per image row, slot rows per image
@@ -79,7 +79,11 @@ template <bool DG, int FA, int FB> struct Frags {
 // fragment reads serve four matrix instructions instead of three two.
 template <bool DG, int WA, int FB> constexpr int win_fa() { return DG && WA % 2 == 0 && FB == 2 ? 2 : 1; }
 
-template <bool DG, int WA, int CBP, int FB>
+// SAVED (backward-data): dy counts where the saved output p.ymask is positive.  The window then goes through registers, dy and the saved output side by
+// side, and is masked on its way to LDS: once per window, in the place of a pass over dy in memory and the launch of it.
+// The kernel takes 5 - 16 % longer for it, the pass 2.8 us and 0.4 us per MB of dy: 192 -> 80 on 73 x 73, 4 samples 22.5 -> 15.6 us with the pass,
+// 192 -> 64 on 48 x 48, 7 samples 17.4 -> 13.1, 128 -> 64 on 29 x 29, 14 samples 13.4 -> 10.0.
+template <bool DG, int WA, int CBP, int FB, bool SAVED>
 __global__ __launch_bounds__(kThreads) void k_conv_win(const KArgs p, const WinArgs q)
 {
 #if __HIP_DEVICE_COMPILE__   // the host pass only needs the launch stub (and silently drops it when it sees this body)
@@ -118,19 +122,36 @@ __global__ __launch_bounds__(kThreads) void k_conv_win(const KArgs p, const WinA
         place(u0 + q.first, row, n, h, w);
         voffW[i] = n >= 0 && n < g.N && h < q.Hs && w < q.Ws ? (unsigned)(((n * q.Hs + h) * q.Ws + w) * q.CR + c * 8) * 2u : OOR;
     }
+    const __amdgpu_buffer_rsrc_t ry = make_rsrc(SAVED ? p.ymask : p.dy, (size_t)g.N * q.Hs * q.Ws * q.CR * 2);
+    constexpr int HELD = CBP > 1 ? 2 : 3;   // copies of a wave per window: LDS holds no more
+    u32x4 hg[SAVED ? CBP * HELD : 1], hy[SAVED ? CBP * HELD : 1];
     auto issue_windows = [&](int round) {   // the CBP windows of a round; a channel block past the last is not read
 #pragma unroll
         for (int b = 0; b < CBP; ++b) {
             const int cb = round * CBP + b;
             const unsigned dst = lds_win + ((round & 1) * CBP + b) * win_bytes + wave * 1024;
 #pragma unroll
-            for (int i = 0; i < IW; ++i) {
-                if (i >= iw) break;
+            for (int i = 0; i < (SAVED ? HELD : IW); ++i) {
+                if (!SAVED && i >= iw) break;   // SAVED: always as many loads, those past the window's end out of range
                 const int row = (i * kWaves + wave) * 8 + lane / 8, c = (lane % 8) ^ ((row >> 1) & 7);
-                const bool out = cb >= q.ncb || (cb == q.ncb - 1 && c * 8 >= tail);
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void)(size_t)(dst + i * kWaves * 1024), 16, out ? OOR : voffW[i], cb < q.ncb ? cb * 128 : 0, 0, 0);
+                const bool out = cb >= q.ncb || (cb == q.ncb - 1 && c * 8 >= tail) || (SAVED && i >= iw);
+                if constexpr (SAVED) {
+                    hg[b * HELD + i] = __builtin_amdgcn_raw_buffer_load_b128(rs, out ? OOR : voffW[i], cb < q.ncb ? cb * 128 : 0, 0);
+                    hy[b * HELD + i] = __builtin_amdgcn_raw_buffer_load_b128(ry, out ? OOR : voffW[i], cb < q.ncb ? cb * 128 : 0, 0);
+                } else
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void)(size_t)(dst + i * kWaves * 1024), 16, out ? OOR : voffW[i], cb < q.ncb ? cb * 128 : 0, 0, 0);
             }
         }
+    };
+    auto store_windows = [&](int round) {   // SAVED: what issue_windows asked for
+#pragma unroll
+        for (int b = 0; b < CBP; ++b)
+#pragma unroll
+            for (int i = 0; i < HELD; ++i) {
+                if (i >= iw) break;
+                const u32x4 v = apply_mask(hg[b * HELD + i], hy[b * HELD + i]);
+                asm volatile("ds_write_b128 %0, %1" ::"v"(lds_win + ((round & 1) * CBP + b) * win_bytes + (i * kWaves + wave) * 1024 + lane * 16), "v"(v) : "memory");
+            }
     };
     // this wave's weights of one tap and channel block, four copies.  Forward: 32 rows (output channels) of 64 reduction channels; backward-data:
     // reduction rows of 32 FA input channels, for the transpose read (four 64-byte rows meet all banks, 128-byte rows are swizzled)
@@ -204,20 +225,25 @@ __global__ __launch_bounds__(kThreads) void k_conv_win(const KArgs p, const WinA
         return win + row * 128u + ((((unsigned)lane >> 5) ^ (unsigned)(2 * SL * sp) ^ ((row >> 1) & 7u)) << 4);
     };
 
+    if constexpr (SAVED) {
+        store_windows(0);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
     // Copies complete in order.  Behind the weights of step s the wave has issued at most those of step s + 1 and, in a round's first two
     // steps, the next round's windows (issued at the round's start).
     const int r0 = tap0 / g.S, c0 = tap0 - r0 * g.S;
-    const int iwb = iw * CBP;
+    const int iwb = SAVED ? 0 : iw * CBP;   // loads to registers are the compiler's to count: the waits below take them as landed, which costs little
     wait_copies(4 * min(2, nsteps));
     __builtin_amdgcn_s_barrier();
     int s = 0;
     for (int round = 0; round < rounds; ++round) {
         const bool next = round + 1 < rounds;
+        if constexpr (SAVED) wait_copies(s + 1 < nsteps ? 4 : 0);   // the weights of step s, before loads that are not counted
         if (next) issue_windows(round + 1);
         if (round * CBP + cbp < q.ncb && nt > 0) {
             const unsigned win = lds_win + ((round & 1) * CBP + cbp) * win_bytes;
             int tr = r0, ts = c0;
-            wait_copies((s + 1 < nsteps ? 4 : 0) + (next ? iwb : 0));
+            if constexpr (!SAVED) wait_copies((s + 1 < nsteps ? 4 : 0) + (next ? iwb : 0));
             s0.template read<0>(fa, (s & 1) * kSlot, pixels(win, tr * q.P + ts));
             for (int j = 0; j < nt; ++j, ++s) {
                 const unsigned sa = (s & 1) * kSlot, pix = pixels(win, tr * q.P + ts);
@@ -234,6 +260,9 @@ __global__ __launch_bounds__(kThreads) void k_conv_win(const KArgs p, const WinA
                     multiply(s0);
                     s1.landed();
                 }
+                // in a round's last step: the loads have had the round to land, and what is younger is waited for below in any case
+                if constexpr (SAVED)
+                    if (next && j + 1 == nt) store_windows(round + 1);
                 // the slot has been read: it takes step s + 2
                 if (s + 2 < nsteps) issue_weights();
                 if (j + 1 < nt) {
@@ -243,7 +272,9 @@ __global__ __launch_bounds__(kThreads) void k_conv_win(const KArgs p, const WinA
                 multiply(s1);
             }
         }
+        else if (SAVED && next) store_windows(round + 1);
         if (next) {
+            if constexpr (SAVED) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             wait_copies(4 * max(0, min(min(2, nt), nsteps - s + nt - 2)));   // the next round's windows have landed: at most this many weight copies are younger
             __builtin_amdgcn_s_barrier();
         }
@@ -307,18 +338,18 @@ typedef void (*WinFn)(const KArgs, const WinArgs);
 struct WinVariant { int WA, CBP, FB; };
 const WinVariant kWin[] = {{4, 1, 4}, {2, 1, 2}, {1, 2, 1}, {2, 2, 2}, {4, 1, 2}, {2, 1, 4}, {3, 1, 2}, {3, 1, 3}, {3, 1, 4}};
 constexpr int kNumWin = 9;
-template <bool DG> WinFn pick(int v)
+template <bool DG, bool SAVED = false> WinFn pick(int v)
 {
     switch (v) {
-    case 0: return k_conv_win<DG, 4, 1, 4>;
-    case 1: return k_conv_win<DG, 2, 1, 2>;
-    case 2: return k_conv_win<DG, 1, 2, 1>;
-    case 3: return k_conv_win<DG, 2, 2, 2>;
-    case 4: return k_conv_win<DG, 4, 1, 2>;
-    case 5: return k_conv_win<DG, 2, 1, 4>;
-    case 6: return k_conv_win<DG, 3, 1, 2>;
-    case 7: return k_conv_win<DG, 3, 1, 3>;
-    default: return k_conv_win<DG, 3, 1, 4>;
+    case 0: return k_conv_win<DG, 4, 1, 4, SAVED>;
+    case 1: return k_conv_win<DG, 2, 1, 2, SAVED>;
+    case 2: return k_conv_win<DG, 1, 2, 1, SAVED>;
+    case 3: return k_conv_win<DG, 2, 2, 2, SAVED>;
+    case 4: return k_conv_win<DG, 4, 1, 2, SAVED>;
+    case 5: return k_conv_win<DG, 2, 1, 4, SAVED>;
+    case 6: return k_conv_win<DG, 3, 1, 2, SAVED>;
+    case 7: return k_conv_win<DG, 3, 1, 3, SAVED>;
+    default: return k_conv_win<DG, 3, 1, 4, SAVED>;
     }
 }
 
@@ -341,7 +372,7 @@ bool win_args(const ConvGeom &g, bool dg, const WinVariant &d, WinArgs *q, long 
     q->ncb = (q->CR + 63) / 64;
     *slots = (long long)g.N * q->HP * q->P;
     const long long wrows = (TB + (long long)(g.R - 1) * q->P + g.S - 1 + 7) / 8 * 8;
-    if (*slots >= 0x3fffffffLL || wrows > kMaxWindowCopies * kWaves * 8) return false;
+    if (*slots >= 0x3fffffffLL || wrows > (d.CBP > 1 ? 2 : kMaxWindowCopies) * kWaves * 8) return false;   // no plan that LDS holds
     q->wrows = (int)wrows;
     const int sums = kWaves * (d.FB % 2 != 0 ? 1 : 2) * kSlot + TB * (TA + 8) * 2, tiles = kWeightBytes + 2 * d.CBP * q->wrows * 128, extra = (TB + TA) * 4;
     if (sums > tiles || tiles + extra > kLdsBytes) return false;   // the row map and the bias behind the tiles outlive the sums
@@ -354,7 +385,7 @@ bool win_args(const ConvGeom &g, bool dg, const WinVariant &d, WinArgs *q, long 
 hipError_t win_init()
 {
     for (int v = 0; v < kNumWin; ++v)
-        for (WinFn k : {pick<false>(v), pick<true>(v)}) {
+        for (WinFn k : {pick<false>(v), pick<true>(v), pick<true, true>(v)}) {
             hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
             if (e != hipSuccess) return e;
         }
@@ -388,10 +419,10 @@ bool win_work(const ConvGeom &g, int pass, int variant, int *rounds, int *rows)
     return true;
 }
 
-void win_kernel_name(int pass, const GemmPlan &pl, char *name, size_t name_bytes)
+void win_kernel_name(int pass, const GemmPlan &pl, bool saved, char *name, size_t name_bytes)
 {
     const WinVariant &d = kWin[pl.variant];
-    snprintf(name, name_bytes, "k_conv_win<%s, %d, %d, %d>", pass == PASS_DGRAD ? "true" : "false", d.WA, d.CBP, d.FB);
+    snprintf(name, name_bytes, "k_conv_win<%s, %d, %d, %d, %s>", pass == PASS_DGRAD ? "true" : "false", d.WA, d.CBP, d.FB, pass == PASS_DGRAD && saved ? "true" : "false");
 }
 
 hipError_t win_launch(const ConvArgs &a, hipStream_t st)
@@ -407,10 +438,11 @@ hipError_t win_launch(const ConvArgs &a, hipStream_t st)
     p.tilesA = a.plan.tilesA; p.tilesB = a.plan.tilesB;
     p.steps_total = p.steps_per_split = a.plan.steps_total; p.splits = 1;
     p.flags = a.flags;
-    p.x = a.x; p.w = a.w; p.dy = a.dy; p.ymask = nullptr; p.bias = a.bias; p.out = a.out; p.partial = nullptr; p.dbp = nullptr;
+    p.x = a.x; p.w = a.w; p.dy = a.dy; p.ymask = dg ? a.ymask : nullptr; p.bias = a.bias; p.out = a.out; p.partial = nullptr; p.dbp = nullptr;
     p.tickets = nullptr;
     p.ph_on = 0;
-    hipLaunchKernelGGL(dg ? pick<true>(a.plan.variant) : pick<false>(a.plan.variant), dim3((unsigned)(p.tilesA * p.tilesB)), dim3(kThreads), lds, st, p, q);
+    const WinFn kern = !dg ? pick<false>(a.plan.variant) : p.ymask != nullptr ? pick<true, true>(a.plan.variant) : pick<true>(a.plan.variant);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(p.tilesA * p.tilesB)), dim3(kThreads), lds, st, p, q);
     dp_trace_main_kernel_done(st);
     return hipGetLastError();
 }

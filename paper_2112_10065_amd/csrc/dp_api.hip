@@ -237,8 +237,19 @@ void plan_uncached(const ConvGeom &g, int pass, int fv, int fs, GemmPlan *pl, in
             time = flat_time;
         }
         const bool window = pass == PASS_FWD ? !(restr & RESTR_ORDER) : pass == PASS_DGRAD && !(restr & (RESTR_BASE | 1));   // bit 0: fp32 gradients
-        if (fs <= 0 && window && pixel_window_plan(g, pass, *pl, time, &flat)) {
-            flat.over_generic = pl->over_generic;
+        // With a saved output the window kernel saves the other fast kernels' pass over dy: 2.8 us and 0.4 us per MB of dy (34 layers).  The generic kernel
+        // masks while it loads; where it stands in for a flat kernel only to save that pass, it took 0.74 and more of both together, and the
+        // window kernel is measured against the flat one (432 <- 80 on 18 x 18: 17.6 -> 6.8 us; not below seven steps, where the generic one is as fast).
+        const bool saved = pass == PASS_DGRAD && (restr & RESTR_SAVED);
+        GemmPlan stand_in = *pl;
+        if (saved && !pl->fast && fs <= 0 && window && g.R * g.S * g.K >= 7 * 64 && backward_flat_plan(g, *pl, time, restr & ~RESTR_SAVED, &flat, &flat_time)) {
+            flat.over_generic = true;
+            stand_in = flat;
+            time = flat_time;
+        }
+        const double mask_us = saved && pl->fast ? 2.8 + 0.4e-6 * (double)g.N * g.Ho * g.Wo * g.K * 2.0 : 0.0;
+        if (fs <= 0 && window && pixel_window_plan(g, pass, stand_in, time, saved, mask_us, &flat)) {
+            flat.over_generic = stand_in.over_generic;
             *pl = flat;
         }
         if (fs <= 0 && pass == PASS_WGRAD && !(restr & RESTR_BASE) && wgrad_window_plan(g, *pl, time, &flat)) *pl = flat;
@@ -478,7 +489,8 @@ hipError_t launch_entry(ConvArgs &a, PlanEntry &pe, hipStream_t st, TraceScope &
     }
     if (ts.idx >= 0) {
         char nm[96];
-        plan_kernel_name(a.pass, a.plan, (a.flags & KF_MASK_IN) != 0, nm, sizeof(nm));
+        if (a.pass == PASS_DGRAD && a.plan.win) win_kernel_name(a.pass, a.plan, a.ymask != nullptr, nm, sizeof(nm));
+        else plan_kernel_name(a.pass, a.plan, (a.flags & KF_MASK_IN) != 0, nm, sizeof(nm));
         ts.name(nm, a.pass != PASS_WGRAD && dma_plan_fuses_reduce(a.plan) ? -a.plan.splits : a.plan.splits);
     }
     if (prep) {
@@ -593,7 +605,7 @@ size_t dgrad_need(const ConvGeom &g, PlanEntry &pe, bool saved)
 // not there (the flat kernels and the rules after them may ask for more than the kernels they replace).
 PlanRef dgrad_choice(const ConvGeom &g, int restr, bool saved, size_t ws_bytes, size_t *need)
 {
-    if (saved && g.K % 64 != 0) restr |= RESTR_SAVED;   // the plans of other layers do not depend on it
+    if (saved && (g.K % 64 != 0 || (g.sh == 1 && g.sw == 1 && g.R * g.S > 2))) restr |= RESTR_SAVED;   // the plans of other layers do not depend on it
     PlanRef ep = plan_entry(g, PASS_DGRAD, restr);
     *need = dgrad_need(g, *ep, saved);
     if (ws_bytes >= *need) return ep;
@@ -618,6 +630,12 @@ size_t dgrad_least_ws_bytes(const ConvGeom &g, int restr)
     dgrad_choice(g, restr, true, 0, &with);
     dgrad_choice(g, restr, false, 0, &without);
     return std::max(with, without);
+}
+
+bool overlaps(const void *a, size_t a_bytes, const void *b, size_t b_bytes)
+{
+    const uintptr_t a0 = reinterpret_cast<uintptr_t>(a), b0 = reinterpret_cast<uintptr_t>(b);
+    return a0 < b0 + b_bytes && b0 < a0 + a_bytes;
 }
 
 // xin: the layer's saved input when flags has DP_RELU_IN (dx *= [xin > 0]), else ignored
@@ -661,7 +679,14 @@ dp_status run_dgrad(const ConvGeom &g, int dtype, unsigned flags, const void *dy
     a.plan = current_plan(pe);
     if (need > 0 && (ws == nullptr || ws_bytes < need)) return fail(DP_ERR_WORKSPACE, "backward-data needs %zu workspace bytes, got %zu", need, ws_bytes);
     a.dy = (const bf16_t *)dy; a.ymask = (const bf16_t *)ym; a.w = (const bf16_t *)w; a.out = dx; a.partial = (float *)ws;
-    if (a.plan.fast && ym != nullptr) {
+    // the window kernel masks dy itself, once its plan is settled (the measured choice runs its candidates on one masked copy); not where the
+    // gradient goes over what the other blocks still read
+    bool masks = false;
+    if (ym != nullptr && a.plan.win && !overlaps(dx, (size_t)g.N * g.H * g.W * g.C * 2, dy, ybytes(g)) && !overlaps(dx, (size_t)g.N * g.H * g.W * g.C * 2, ym, ybytes(g))) {
+        std::lock_guard<std::mutex> lock(pe.mu);
+        masks = pe.tuned && pe.plan.win;
+    }
+    if (a.plan.fast && ym != nullptr && !masks) {
         // the fast kernel takes a pre-masked gradient: materialise g = dy * [y_saved > 0] once
         void *gbuf = (char *)ws + round256(pe.part_cap);
         hipError_t e = rbg_launch((long long)g.N * g.Ho * g.Wo, g.K, true, dy, ym, gbuf, nullptr, nullptr, st);

@@ -88,7 +88,7 @@ hipError_t wstrip_launch(const ConvArgs &a, hipStream_t st);
 // conv_win.hip
 hipError_t win_init();
 bool win_plan(const ConvGeom &g, int pass, int variant, GemmPlan *pl);
-void win_kernel_name(int pass, const GemmPlan &pl, char *name, size_t name_bytes);
+void win_kernel_name(int pass, const GemmPlan &pl, bool saved, char *name, size_t name_bytes);
 hipError_t win_launch(const ConvArgs &a, hipStream_t st);
 bool win_work(const ConvGeom &g, int pass, int variant, int *rounds, int *rows);   // channel rounds of a block, window rows copied in each
 
@@ -159,8 +159,8 @@ bool forward_flat_plan(const ConvGeom &g, const GemmPlan &base, GemmPlan *plan, 
 // backward-data: a flat-walk plan faster than `base`, whose price is `time`
 bool backward_flat_plan(const ConvGeom &g, const GemmPlan &base, double time, int restr, GemmPlan *plan, double *flat_time);
 // forward / backward-data: the window kernel's two cheapest plans, and whether it takes the place of `base`, whose price is `time`
-int pixel_window_plans(const ConvGeom &g, int pass, GemmPlan out[2], double times[2]);
-bool pixel_window_plan(const ConvGeom &g, int pass, const GemmPlan &base, double time, GemmPlan *out);
+int pixel_window_plans(const ConvGeom &g, int pass, GemmPlan out[2], double times[2], bool saved = false);
+bool pixel_window_plan(const ConvGeom &g, int pass, const GemmPlan &base, double time, bool saved, double mask_us, GemmPlan *out);
 // filter gradient: the window kernel's two cheapest plans, and whether it takes the place of `base`, whose price is `time`
 int wgrad_window_plans(const ConvGeom &g, GemmPlan out[2], double times[2]);
 bool wgrad_window_plan(const ConvGeom &g, const GemmPlan &base, double time, GemmPlan *out);

@@ -309,8 +309,12 @@ const WindowPrice kWindowPrice[2][9] = {
      {1.3f, 5.3f, 0.18f, 0.189f, 0.0017f}, {1.0f, 5.5f, 0.34f, 0.160f, 0.0015f},
      {1.3f, 3.6f, 0.18f, 0.200f, 0.0006f}, {1.0f, 5.1f, 0.17f, 0.213f, 0.0013f}, {0.4f, 5.9f, 0.0f, 0.262f, 0.0024f}}};
 
+// What masking dy by the saved output on its way into the window costs: two loads and an LDS store in the place of a copy (median of 31 - 75 layers
+// per tile; 1.08 - 1.28 for nine of ten)
+const float kMaskedWindow[9] = {1.045f, 1.13f, 1.165f, 1.135f, 1.085f, 1.08f, 1.14f, 1.125f, 1.06f};
+
 // its two cheapest plans, best first; returns how many there are
-int pixel_window_plans(const ConvGeom &g, int pass, GemmPlan out[2], double times[2])
+int pixel_window_plans(const ConvGeom &g, int pass, GemmPlan out[2], double times[2], bool saved)
 {
     int n = 0;
     for (int v = 0; v < 9; ++v) {
@@ -320,6 +324,7 @@ int pixel_window_plans(const ConvGeom &g, int pass, GemmPlan out[2], double time
         const WindowPrice &c = kWindowPrice[pass == PASS_FWD ? 0 : 1][v];
         const double waves = std::ceil((double)pl.tilesA * pl.tilesB / 256.0);
         double t = c.c0 + waves * (c.c1 + rounds * (c.c2 + c.c3 * g.R * g.S + c.c4 * rows));
+        if (saved) t *= kMaskedWindow[v];
         // backward-data with 32 channels to a tile fetches half a line per weight row: beyond the 4 MB of an L2 that counts twice
         // (14 x 14, 512 -> 512, one sample: 14.7 us for a fitted 10.5)
         if (v == 2 && pass == PASS_DGRAD && (long long)g.K * g.R * g.S * g.C * 2 > 2000000) t *= 1.4;
@@ -337,18 +342,18 @@ int pixel_window_plans(const ConvGeom &g, int pass, GemmPlan out[2], double time
 
 // The window kernel in the place of `base` (price `time`), where its own price lies 8 % below what the other's is worth: the prices were made to rank
 // the kernels among themselves and are off by a launch's floor and a factor, fitted per family to 510 passes timed both ways (median error 3 - 6 %;
-// register-staged and flat kernels by a factor alone).
-bool pixel_window_plan(const ConvGeom &g, int pass, const GemmPlan &base, double time, GemmPlan *out)
+// register-staged and flat kernels by a factor alone).  `mask_us`: what a pass over dy in front of `base` takes, which the window kernel does without.
+bool pixel_window_plan(const ConvGeom &g, int pass, const GemmPlan &base, double time, bool saved, double mask_us, GemmPlan *out)
 {
     GemmPlan pl[2];
     double t[2];
-    if (!base.fast || time <= 0.0 || pixel_window_plans(g, pass, pl, t) == 0) return false;
+    if (!base.fast || time <= 0.0 || pixel_window_plans(g, pass, pl, t, saved) == 0) return false;
     const bool fwd = pass == PASS_FWD, split = base.splits > 1;
     if (!fwd && base.BK == 32 && pl[0].variant >= 6 && g.R * g.S < 5) return false;   // 96-channel tiles were fitted from 7 taps on
-    double floor_us = 0.0, factor = 0.0;   // not in the place of unsplit register-staged kernels forward, nor of flat ones backward with few taps
+    double floor_us = 0.0, factor = 0.0;   // not in the place of unsplit register-staged kernels forward, nor of flat ones backward with few taps or short reductions
     if (base.halo) { floor_us = fwd ? 0.3 : -1.6; factor = fwd ? 1.13 : 1.34; }
     else if (dma_plan_is_strip(base)) { floor_us = -4.4; factor = fwd ? 1.11 : 1.16; }
-    else if (dma_plan_is_flat(base)) factor = fwd || g.R * g.S > 8 ? 1.0 : 0.0;   // backward-data: 3x3 and 5x5 1.17 - 1.78 times as fast, fewer taps 1.1 - 1.4 and no further checked
+    else if (dma_plan_is_flat(base)) factor = fwd || (g.R * g.S > 8 && g.R * g.S * g.K >= 512) ? 1.0 : 0.0;   // backward-data: 1.17 - 1.78 times as fast
     else if (!base.dma) { floor_us = fwd ? 0.0 : -3.6; factor = !fwd ? 1.03 : split ? 0.76 : 0.0; }
     else if (fwd) { floor_us = split ? -7.0 : -4.6; factor = split ? 1.3 : 1.08; }
     else { floor_us = split ? -6.0 : -4.4; factor = split ? 1.3 : 1.25; }
@@ -359,7 +364,7 @@ bool pixel_window_plan(const ConvGeom &g, int pass, const GemmPlan &base, double
     // the shortest layers lie at the floor of a launch
     const long long tiles = (long long)pl[0].tilesA * pl[0].tilesB;
     const double margin = g.R * g.S < 5 ? 0.75 : tiles > 512 ? 0.78 : tiles > 256 ? 0.85 : 0.92;
-    if (t[0] >= margin * worth) return false;
+    if (t[0] >= margin * (worth + mask_us)) return false;
     *out = pl[0];
     return true;
 }

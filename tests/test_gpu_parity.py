@@ -844,12 +844,39 @@ def test_pixel_window_kernel(env, variant):
                 # outputs rounded to bf16: relative error 2^-9 each, half of that in the mean
                 assert U.errs(U.to_np(y), orc.conv2d_fwd(case.x, case.w, case.b if front else None, relu=front, pad=pd))[0] <= 2.5e-3, (tag, front)
                 assert U.errs(U.to_np(dx), ref)[0] <= 2.5e-3, (tag, front)
+        for tag, n, h, w, c, k, r, s, pd in (("pw_a", 2, 7, 7, 64, 64, 3, 3, (1, 1)), ("pw_c", 2, 9, 30, 200, 136, 3, 3, (1, 1)), ("pw_d", 1, 4, 56, 72, 128, 3, 3, (1, 1)),
+                                             ("pw_f", 2, 17, 17, 160, 192, 1, 7, (0, 3)), ("pw_i", 1, 9, 9, 8, 16, 2, 5, (1, 3)), ("pw_k", 4, 31, 20, 96, 320, 3, 3, (0, 0))):
+            # dy masked by a saved output on its way into the window, alone and with the mask of the ReLU in front
+            case = U.ConvCase(tag, n, h, w, c, k, r, s, (1, 1), pd, bf16=True, bias=True, relu=True)
+            y = case.run_fwd(case.ws())
+            dx, dx_in = case.run_dgrad(y), case.run_dgrad_relu_in(y)
+            torch.cuda.synchronize()
+            ref = orc.conv2d_bwd_data(case.dy, case.w, case.x.shape, y_saved=U.to_np(y), pad=pd)
+            assert U.errs(U.to_np(dx), ref)[0] <= 2.5e-3, tag
+            assert U.errs(U.to_np(dx_in), ref * (case.x > 0))[0] <= 2.5e-3, tag
         for tag, c, st, dx_f32 in (("pw_s2", 64, (2, 2), False), ("pw_c12", 12, (1, 1), False), ("pw_f32", 64, (1, 1), True)):   # not this kernel's
             case = U.ConvCase(tag, 1, 9, 9, c, 64, 3, 3, st, (1, 1), bf16=True, bias=True, relu=True, dx_f32=dx_f32)
             assert "k_conv_win" not in dp.dp_conv2d_kernel_info(case.desc, 1)[0]
     finally:
         for p in (0, 1):
             dp.dp_set_override(p, -1, 0)
+
+
+def test_backward_data_over_its_own_gradient_masks_first(env):
+    """The window kernel masks dy while it reads it.  Where dx lies over dy or over the saved output, the masked copy is made first, as ever."""
+    dp, U, orc = env
+    dp.dp_set_override(1, 251, 0)
+    try:
+        case = U.ConvCase("pw_over", 2, 14, 14, 64, 64, 3, 3, (1, 1), (1, 1), bf16=True, bias=True, relu=True)
+        y = case.run_fwd()
+        want = case.run_dgrad(y)
+        for over in (case.dyd.clone(), y.clone()):
+            is_dy = torch.equal(over, case.dyd)
+            dp.dp_conv2d_bwd_data(case.desc, over if is_dy else case.dyd, y if is_dy else over, case.wd, over, case.ws())
+            torch.cuda.synchronize()
+            assert torch.equal(over, want)
+    finally:
+        dp.dp_set_override(1, -1, 0)
 
 
 def test_forward_that_keeps_its_mask_keeps_the_order_of_its_sums(env):
