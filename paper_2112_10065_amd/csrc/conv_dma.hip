@@ -16,6 +16,7 @@
 //          step i-1 used ; matrix cores on stage i % NS.
 #include "dma_common.h"
 #include <type_traits>
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <atomic>
@@ -1019,6 +1020,22 @@ __global__ __launch_bounds__(64 * WA * WB) void k_wgrad_dma(const KArgs p)
 // backward-data (c_out % BK == 0; any stride) with the same pipeline: A = weights, reduction-major
 // [BK c_out rows][TA c_in] read through the LDS transpose read; B = dy pixel rows, K-major.
 // ---------------------------------------------------------------------------------------
+// The `at`-th B tile in launch order where the tiles are laid out phase by phase: the phases take turns as long as all have tiles left (p.ph_turns each).
+// A compute die gets a contiguous range of the order, and of a 3x3 filter at stride 2 the phases walk 1, 2, 2 and 4 taps: phase after phase
+// two of the dies would have nearly half of the work.  The four phases of a neighbourhood also read the same dy.
+DEVFN int phase_tile(const KArgs &p, int at)
+{
+    const int phases = p.g.sh * p.g.sw, turn = at / phases;
+    if (turn < p.ph_turns) return p.ph_tile0[at - turn * phases] + turn;
+    int rest = at - phases * p.ph_turns, c = 0;
+    for (; c + 1 < phases; ++c) {
+        const int left = p.ph_tile0[c + 1] - p.ph_tile0[c] - p.ph_turns;
+        if (rest < left) break;
+        rest -= left;
+    }
+    return p.ph_tile0[c] + p.ph_turns + rest;
+}
+
 // KG: reduction groups per block, as in k_fwd_dma.  MIX: c_out in whole 8s that BK does not divide, reduction walked flat over (tap,
 // c_out).  Eight reduction rows share a tap, and the rows a copy of the weights fills lie within eight, so the weights' walk is
 // wave-uniform (scalar); the pixel chunks carry a position per lane, as forward.  Strided layers only by phase (or 1x1).
@@ -1043,7 +1060,10 @@ DEVFN void dgrad_dma_body(const KArgs &p)
     const ConvGeom &g = p.g;
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), grp = wv / NW, wave = wv % NW;   // wave-uniform: scalar registers
     const int tile = logical_block(blockIdx.x, gridDim.x);
-    const int a0 = (tile % p.tilesA) * TA, tb = tile / p.tilesA, b0 = tb * TB;
+    int tb = tile / p.tilesA;
+    const int a0 = (tile - tb * p.tilesA) * TA;
+    if (p.ph_on && p.ph_turns > 0) tb = phase_tile(p, tb);
+    const int b0 = tb * TB;
     // Stride phases (p.ph_on): a tile holds input pixels of one phase (h % sh, w % sw) = (pa, pb) only.  Of the R*S taps
     // only those with r = (pa + ph) mod sh, s = (pb + pw) mod sw can hit the output grid for such a pixel, so the
     // reduction walks that sub-lattice of taps: 1/(sh*sw) of the steps the masked form multiplies.
@@ -1631,6 +1651,15 @@ hipError_t dma_launch(const ConvArgs &a, hipStream_t st)
             int max_steps;
             phase_layout(a.g, a.plan.TB, a.plan.BK, p.ph_tile0, &max_steps);
             p.ph_on = a.plan.fill ? 2 : 1;
+            // The phases take turns where there is more than a round of blocks and enough work that a die can fall behind: 64 x 56 x 56, 128 -> 128 57.3 -> 51.3 us,
+            // 5x5 416 <- 304 on 85 x 85, 6 samples 152 -> 132; grids below cost the 0.6 us that the order takes to work out (45 layers: 1.00 - 1.15 above the line,
+            // 0.90 - 1.03 below it).  Launches with tiles of the first phase only keep their order.
+            p.ph_turns = 0;
+            const long long tiles = (long long)p.tilesA * p.tilesB;
+            if (p.ph_on == 1 && tiles > 256 && tiles * max_steps >= 6000) {
+                p.ph_turns = p.ph_tile0[1];
+                for (int c = 1; c < a.g.sh * a.g.sw; ++c) p.ph_turns = std::min(p.ph_turns, p.ph_tile0[c + 1] - p.ph_tile0[c]);
+            }
         } else {   // fp32 gradients: the same tiles in natural pixel order, all taps (masked)
             p.tilesB = (p.rowsB + a.plan.TB - 1) / a.plan.TB;
             p.steps_total = p.steps_per_split = (p.red + a.plan.BK - 1) / a.plan.BK;

@@ -28,6 +28,7 @@ struct KArgs {
     // w % sw), each padded to whole tiles; B tiles ph_tile0[c] .. ph_tile0[c+1]-1 belong to phase c = a*sw + b
     int ph_on;
     int ph_tile0[5];
+    int ph_turns;   // B tiles of each phase that the launch order takes in turn; 0: phase after phase
 };
 
 DEVFN u32x4 ldg16(const bf16_t *p) { return *reinterpret_cast<const u32x4 *>(p); }

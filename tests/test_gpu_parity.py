@@ -478,6 +478,25 @@ def test_strided_backward_data_by_phase(env, spec):
         dp.dp_set_override(1, -1, 0)
     U.assert_bf16_close(U.to_np(dx32), orc.conv2d_bwd_data(case32.dy, case32.w, case32.x.shape, y_saved=U.to_np(y), stride=st, pad=pd), f"{tag} fp32 dx")
 
+@pytest.mark.parametrize("n,h,w,c,k,st,tiles", [(5, 23, 37, 200, 384, (2, 2), (18, 17, 17, 16)), (4, 9, 300, 520, 64, (2, 2), (47, 47, 38, 38)), (2, 54, 80, 136, 192, (2, 1), (68, 68)),
+                                                (1, 1, 9000, 264, 320, (2, 2), (71, 71, 0, 0)), (1, 31, 17, 72, 64, (2, 2), (3, 2, 3, 2)), (7, 5, 5, 72, 64, (2, 2), (1, 1, 1, 1))])
+def test_backward_data_phases_take_turns(env, n, h, w, c, k, st, tiles):
+    """Strided backward-data by phase: the tiles of the phases in turn, with phases that have tiles more than others and without any, and grids too
+    small for it."""
+    dp, U, orc = env
+    rows = [n * len(range(a, h, st[0])) * len(range(b, w, st[1])) for a in range(st[0]) for b in range(st[1])]
+    assert tuple((r + 63) // 64 for r in rows) == tiles   # tiles of 64 pixels
+    dp.dp_set_override(1, 207, 1)
+    try:
+        case = U.ConvCase("phases", n, h, w, c, k, 3, 3, st, (1, 1), bf16=True, bias=False, relu=False)
+        assert dp.dp_conv2d_kernel_info(case.desc, 1)[0].startswith("k_dgrad_dma<64, 64, 64")
+        dx = case.run_dgrad(None)
+        torch.cuda.synchronize()
+        # bf16 outputs: relative error 2^-9 each, half of that in the mean
+        assert U.errs(U.to_np(dx), orc.conv2d_bwd_data(case.dy, case.w, case.x.shape, stride=st, pad=(1, 1)))[0] <= 2.5e-3
+    finally:
+        dp.dp_set_override(1, -1, 0)
+
 
 @pytest.mark.parametrize("blocks", [0, 3, 40])
 def test_input_patch_filter_gradient_all_taps_per_wave(env, blocks):
