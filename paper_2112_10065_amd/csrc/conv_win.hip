@@ -16,7 +16,7 @@
 // backward-data 41.7 -> 36.6; 4 samples 28.2 -> 24.0 and 29.6 -> 25.2; 512 -> 512 on 14 x 14, 8 samples 22.5 -> 15.6 and 25.6 -> 17.9; 288 -> 384 on
 // 35 x 35, 4 samples 32.4 -> 18.4 and 23.3 -> 19.5.  Tiles of 96 channels (three waves side by side, four tap groups) for channel counts that 64 and 128
 // divide badly, or that fill the chip better so: backward-data 192 -> 80 on 73 x 73, 4 samples 23.6 -> 14.5; forward 272 -> 96 there 25.3 -> 19.4,
-// 384 -> 288 on 26 x 26, 11 samples 28.3 -> 21.6, 512 -> 512 on 28 x 28, 8 samples 33 -> 28.  What bounds it: LDS (reads of 1.25 - 1.5 fragments per matrix instruction and the copies,
+// 384 -> 288 on 26 x 26, 11 samples 28.3 -> 21.6.  What bounds it: LDS (reads of 1.25 - 1.5 fragments per matrix instruction and the copies,
 // 115 bytes per clock together), and 6 us of launch, first copies, sums and stores.
 #include "dma_common.h"
 #include <cstdio>
@@ -81,8 +81,8 @@ template <bool DG, int WA, int FB> constexpr int win_fa() { return DG && WA % 2 
 
 // SAVED (backward-data): dy counts where the saved output p.ymask is positive.  The window then goes through registers, dy and the saved output side by
 // side, and is masked on its way to LDS: once per window, in the place of a pass over dy in memory and the launch of it.
-// The kernel takes 5 - 16 % longer for it, the pass 2.8 us and 0.4 us per MB of dy: 192 -> 80 on 73 x 73, 4 samples 22.5 -> 15.6 us with the pass,
-// 192 -> 64 on 48 x 48, 7 samples 17.4 -> 13.1, 128 -> 64 on 29 x 29, 14 samples 13.4 -> 10.0.
+// The kernel takes 5 - 16 % longer for it, the pass 2.8 us and 0.4 us per MB of dy (with it, us): 192 -> 64 on 48 x 48,
+// 7 samples 17.4 -> 13.1, 128 -> 64 on 29 x 29, 14 samples 13.4 -> 10.0; all passes of 80 -> 192 on 73 x 73, 4 samples 64.5 -> 60.7.
 template <bool DG, int WA, int CBP, int FB, bool SAVED>
 __global__ __launch_bounds__(kThreads) void k_conv_win(const KArgs p, const WinArgs q)
 {
