@@ -939,6 +939,40 @@ def test_filter_gradient_window_kernel(env, slots, splits):
         dp.dp_set_override(2, -1, 0)
 
 
+@pytest.mark.parametrize("slots,splits", [(128, 1), (128, 3), (256, 1), (256, 2)])
+def test_filter_gradient_window_kernel_keeps_non_finite_values_where_their_taps_reach(env, slots, splits):
+    """The window kernel multiplies padding slots of dy by what lies in x beside them.  An infinite or NaN pixel of the first and last rows and columns,
+    of x or of dy, reaches the taps that pair it and no others; what it does not reach is as close to the reference as ever."""
+    dp, U, orc = env
+    dp.dp_set_override(2, 317 if slots == 128 else 318, splits)
+    try:
+        for tag, n, h, w, c, k, r, s, pd in (("winf_a", 2, 7, 7, 64, 64, 3, 3, (1, 1)), ("winf_b", 1, 14, 14, 40, 72, 3, 3, (0, 0)), ("winf_c", 3, 9, 30, 32, 136, 3, 3, (1, 1)),
+                                             ("winf_d", 1, 4, 110, 72, 8, 3, 3, (1, 0)), ("winf_e", 20, 2, 3, 40, 64, 3, 3, (2, 2)), ("winf_f", 2, 17, 17, 48, 40, 1, 7, (0, 3)),
+                                             ("winf_g", 1, 17, 17, 32, 64, 7, 1, (3, 0)), ("winf_h", 2, 11, 12, 24, 64, 5, 5, (2, 2)), ("winf_i", 2, 31, 37, 64, 64, 3, 3, (1, 1))):
+            case = U.ConvCase(tag, n, h, w, c, k, r, s, (1, 1), pd, bf16=True, bias=True, relu=False)
+            if not dp.dp_conv2d_kernel_info(case.desc, 2)[0].startswith(f"k_wgrad_win<{slots}"):
+                assert slots == 256 and (r, s) != (3, 3)
+                continue
+            for at, (i, row, col, val) in enumerate(((0, 0, 0, np.inf), (n - 1, h - 1, w - 1, np.nan), (0, h // 2, w - 1, -np.inf), (n - 1, 0, w // 2, np.nan), (n // 2, h - 1, 0, np.inf))):
+                case.x[i, row, col, at] = val
+                case.xd[i, row, col, at] = float(val)
+            for at, (i, row, col, val) in enumerate(((0, 0, 0, np.nan), (n - 1, case.ho - 1, case.wo - 1, np.inf), (0, case.ho // 2, case.wo - 1, np.nan))):
+                case.dy[i, row, col, at] = val
+                case.dyd[i, row, col, at] = float(val)
+            dw, _ = case.run_wgrad(None)
+            torch.cuda.synchronize()
+            got = U.to_np(dw)
+            with np.errstate(invalid="ignore"):
+                ref, _ = orc.conv2d_bwd_filter(case.x, case.dy, case.w.shape, y_saved=None, stride=(1, 1), pad=pd, want_db=True)
+            assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref)), tag
+            ok = np.isfinite(ref)
+            assert ok.any() and not ok.all() and np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+            # sums of at most 2^13 exact products of bf16 numbers in fp32
+            assert U.errs(got[ok], ref[ok])[0] <= 2e-6, tag
+    finally:
+        dp.dp_set_override(2, -1, 0)
+
+
 def test_filter_gradient_window_kernel_by_default_and_with_less_scratch(env):
     """A middle layer takes the window kernel by itself; with the scratch that the kernels without it ask for or less, the call still runs
     wherever one of the two fits, and gives the same gradients."""
