@@ -528,17 +528,18 @@ ConvGeom im2col_geom(const ConvGeom &g, int kpad)
 size_t xcol_bytes(const ConvGeom &g, int kpad) { return round256((size_t)g.N * g.Ho * g.Wo * kpad * 2); }
 bool use_small_c(const ConvGeom &g, int pass) { return g_force_variant[pass].load() < 0 && small_c_kpad(g) > 0; }
 
-size_t fwd_ws_bytes(const ConvGeom &g)
+// scratch of one forward call; `restr` from fwd_restr
+size_t fwd_need(const ConvGeom &g, int restr)
 {
     if (use_small_c(g, PASS_FWD) && (small_c_direct(g) || small_c_stem(g))) return 0;
     if (use_small_c(g, PASS_FWD)) {
         const int kpad = small_c_kpad(g);
-        return xcol_bytes(g, kpad) + round256((size_t)g.K * kpad * 2) + fwd_ws_bytes(im2col_geom(g, kpad));
+        return xcol_bytes(g, kpad) + round256((size_t)g.K * kpad * 2) + fwd_need(im2col_geom(g, kpad), restr);
     }
-    // the query does not depend on the flags: what either plan takes (a plan with partials is not the window kernel's, so the two are one)
-    const size_t part = plan_entry(g, PASS_FWD)->part_cap;
-    return part > 0 ? part : plan_entry(g, PASS_FWD, RESTR_ORDER)->part_cap;
+    return plan_entry(g, PASS_FWD, restr)->part_cap;
 }
+// The query holds for any flags: the larger of the two.  (The candidates of a measured choice differ: the window kernel's take places of others.)
+size_t fwd_ws_bytes(const ConvGeom &g) { return std::max(fwd_need(g, 0), fwd_need(g, RESTR_ORDER)); }
 
 // ---- the three passes on a validated geometry --------------------------------------
 dp_status run_fwd(const ConvGeom &g, int dtype, unsigned flags, const void *x, const void *w, const float *bias, void *y,
@@ -572,7 +573,7 @@ dp_status run_fwd(const ConvGeom &g, int dtype, unsigned flags, const void *x, c
     }
     if (use_small_c(g, PASS_FWD)) {
         const int kpad = small_c_kpad(g);
-        const size_t need = fwd_ws_bytes(g);
+        const size_t need = fwd_need(g, fwd_restr(flags));
         if (ws == nullptr || ws_bytes < need) return fail(DP_ERR_WORKSPACE, "forward needs %zu workspace bytes, got %zu", need, ws_bytes);
         bf16_t *xcol = (bf16_t *)ws, *wpad = (bf16_t *)((char *)ws + xcol_bytes(g, kpad));
         const size_t used = xcol_bytes(g, kpad) + round256((size_t)g.K * kpad * 2);
@@ -1059,7 +1060,7 @@ dp_status dp_conv2d_fwd(const dp_conv_desc *desc, const void *x, const void *w, 
     if (desc->flags & DP_BIAS) { if ((s = check_ptr(bias, "bias")) != DP_OK) return s; }
     if ((s = check_opt(ws, "ws")) != DP_OK) return s;
     if (desc->io_dtype == DP_BF16) {
-        size_t need = fwd_ws_bytes(g);
+        size_t need = fwd_need(g, fwd_restr(desc->flags));
         if (need > 0 && (ws == nullptr || ws_bytes < need)) return fail(DP_ERR_WORKSPACE, "forward needs %zu workspace bytes, got %zu", need, ws_bytes);
     }
     if ((s = ensure_init()) != DP_OK) return s;

@@ -307,3 +307,33 @@ def test_strided_1x1_fp32_gradient_plan_is_the_one_that_runs(dp):
         return dp.dp_conv2d_kernel_info(d, 1)
     assert info(10, 53, 96, 448, dp.DP_DX_F32) == ("k_dgrad_dma<64, 128, 64, 2, 2, 2, 1>", 1)
     assert info(10, 53, 96, 448)[0] != info(10, 53, 96, 448, dp.DP_DX_F32)[0]
+
+
+@pytest.mark.parametrize("mode", [0, 1, 2])
+def test_forward_takes_the_scratch_of_its_query_with_any_flags(dp, mode):
+    """The query knows no flags, the call's kernel choice does: what the query says is enough for every call, over the layers of the tracked
+    networks and every choice mode.  Valid calls get as far as the missing GPU."""
+    import torch
+    from paper_2112_10065_amd import workloads as W
+    if torch.cuda.is_available():
+        pytest.skip("would launch on the addresses made up here")
+    differ = 0
+    dp.dp_set_autotune(mode)
+    try:
+        for l in W.vgg16_convs() + W.resnet50_convs() + W.inception_convs() + W.wrn101_2_convs():
+            for n in W.BATCHES:
+                asked = []
+                for flags in (0, dp.DP_BIAS | dp.DP_RELU, dp.DP_RELU | dp.DP_RELU_IN, dp.DP_RELU | dp.DP_DETERMINISTIC):
+                    d = dp.conv_desc(n, l.h, l.w, l.c, l.k, l.r, l.s, (l.sh, l.sw), (l.ph, l.pw), dp.DP_BF16, flags)
+                    need = dp.dp_conv2d_workspace_bytes(d, 0)
+                    assert dp.lib.dp_conv2d_fwd(C.byref(d), A, A, A, A, A if need else None, need, None) == dp.DP_ERR_HIP, (l, n, flags)
+                    if not flags & dp.DP_DETERMINISTIC:
+                        asked.append(need)
+                    if dp.lib.dp_conv2d_fwd(C.byref(d), A, A, A, A, None, 0, None) == dp.DP_ERR_WORKSPACE:
+                        least = int(re.search(rb"needs (\d+) workspace", dp.lib.dp_last_error()).group(1))
+                        assert least <= need
+                        differ += least < need
+                assert len(set(asked)) == 1
+    finally:
+        dp.dp_set_autotune(0)
+    assert mode != 2 or differ > 0   # calls that need less than others exist

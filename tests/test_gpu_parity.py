@@ -1114,6 +1114,26 @@ def test_measured_kernel_choice(env, mode):
         dp.dp_set_autotune(False)
 
 
+def test_measured_choice_with_cold_caches_takes_the_scratch_of_its_query(env):
+    """A forward that masks by its own output measures other candidates than the query without flags counts; what the query says is enough for it."""
+    dp, U, orc = env
+    case = U.ConvCase("cold_ws", 2, 56, 56, 256, 256, 3, 3, (1, 1), (1, 1), bf16=True, bias=True, relu=True)
+    y = case.run_fwd()
+    dp.dp_set_autotune(2)
+    try:
+        ws = U.workspace(dp.dp_conv2d_workspace_bytes(case.desc, 0))
+        for rep in range(2):
+            got = case.run_fwd(ws)
+            torch.cuda.synchronize()
+            # two roundings of nearly the same sums to bf16: 2^-9 each
+            assert U.errs(U.to_np(got), U.to_np(y))[0] <= 2.0 ** -8
+        for flags in (dp.DP_BIAS | dp.DP_RELU, dp.DP_BIAS | dp.DP_RELU | dp.DP_RELU_IN):
+            d = dp.conv_desc(2, 13, 13, 1024, 1024, 3, 3, (1, 1), (1, 1), dp.DP_BF16, flags)
+            assert dp.dp_profile_layer(conv=d, batches=(2,), warmup=1, iters=2)[0]["fwd_us"] > 0
+    finally:
+        dp.dp_set_autotune(False)
+
+
 def test_dense_forward_kernel_names(env):
     """Which forward kernel a dense layer gets (names as the profiler shows them)."""
     dp, U, orc = env
