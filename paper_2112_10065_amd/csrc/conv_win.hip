@@ -102,7 +102,7 @@ __global__ __launch_bounds__(kThreads) void k_conv_win(const KArgs p, const WinA
     const unsigned lds0 = lds_offset(smem), lds_win = lds0 + kWeightBytes, lds_a = lds0 + wave * 2 * kSlot;
     const __amdgpu_buffer_rsrc_t rw = make_rsrc(p.w, (size_t)g.K * RSC * 2), rs = make_rsrc(DG ? p.dy : p.x, (size_t)g.N * q.Hs * q.Ws * q.CR * 2);
 
-    // slot -> image position: a few hundred slots behind a uniform first one; one scalar division, then reciprocals (exact below 2^21)
+    // slot -> image position: a few hundred slots behind a uniform first one; one scalar division, then reciprocals (exact below 2^21; win_args keeps P and HP under half of that)
     const float rP = 1.0f / (float)q.P, rHP = 1.0f / (float)q.HP;
     auto place = [&](int first, int row, int &n, int &h, int &w) {
         const int img = q.HP * q.P;
@@ -372,6 +372,7 @@ bool win_args(const ConvGeom &g, bool dg, const WinVariant &d, WinArgs *q, long 
     q->ncb = (q->CR + 63) / 64;
     *slots = (long long)g.N * q->HP * q->P;
     const long long wrows = (TB + (long long)(g.R - 1) * q->P + g.S - 1 + 7) / 8 * 8;
+    if (q->P >= 1 << 20 || q->HP >= 1 << 20) return false;   // the kernel divides by reciprocals
     if (*slots >= 0x3fffffffLL || wrows > (d.CBP > 1 ? 2 : kMaxWindowCopies) * kWaves * 8) return false;   // no plan that LDS holds
     q->wrows = (int)wrows;
     const int sums = kWaves * (d.FB % 2 != 0 ? 1 : 2) * kSlot + TB * (TA + 8) * 2, tiles = kWeightBytes + 2 * d.CBP * q->wrows * 128, extra = (TB + TA) * 4;

@@ -337,3 +337,20 @@ def test_forward_takes_the_scratch_of_its_query_with_any_flags(dp, mode):
     finally:
         dp.dp_set_autotune(0)
     assert mode != 2 or differ > 0   # calls that need less than others exist
+
+
+def test_pixel_window_plan_keeps_to_rows_and_columns_that_its_reciprocals_divide(dp):
+    """The window kernel finds image rows by fp32 reciprocals, exact below 2^21 slots a row (or slot rows an image): longer rows and columns, which
+    the filters of one row or column would otherwise let through, have no such plan, not even forced."""
+    def name(h, w, r, s, pass_):
+        return dp.dp_conv2d_kernel_info(dp.conv_desc(1, h, w, 64, 64, r, s, (1, 1), (r // 2, s // 2), dp.DP_BF16, 0), pass_)[0]
+    for pass_ in (0, 1):
+        for variant in range(250, 259):
+            dp.dp_set_override(pass_, variant, 0)
+            try:
+                for size, runs in ((5000000, False), (1 << 20, False), (1000000, True)):
+                    assert name(1, size, 1, 3, pass_).startswith("k_conv_win<") == runs
+                    # columns of 32-row tiles: the window of a filter column is a few slots, whatever the height
+                    assert name(size, 1, 3, 1, pass_).startswith("k_conv_win<") == runs
+            finally:
+                dp.dp_set_override(pass_, -1, 0)
