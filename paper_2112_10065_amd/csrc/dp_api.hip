@@ -152,9 +152,9 @@ constexpr long long kMaxElems = (1ll << 31) - 1;
 constexpr unsigned kKnownFlags = DP_BIAS | DP_RELU | DP_DETERMINISTIC | DP_DX_F32 | DP_RELU_IN;
 // kernels a backward-data call may not use: bit 0 the input-patch kernels (they stage bf16, the caller wants fp32),
 // bit 1 the stationary-weight kernel (it has no fused input-ReLU mask); dgrad_choice adds bits 3 and 4 (dp_kernels.h)
-// a ReLU whose backward is left to the layer behind (DP_RELU_IN: x is such a layer's output) does not feel in which order y is summed
-int fwd_restr(unsigned flags) { return (flags & DP_RELU) && !(flags & DP_RELU_IN) ? RESTR_ORDER : 0; }
 int dgrad_restr(unsigned flags) { return ((flags & DP_DX_F32) ? 1 : 0) | ((flags & DP_RELU_IN) ? 2 : 0); }
+// RESTR_ORDER only where there is a window kernel to leave out: other layers have one plan, measured once
+int fwd_restr(const ConvGeom &g, unsigned flags) { return (flags & DP_RELU) && !(flags & DP_RELU_IN) && pixel_window_exists(g, PASS_FWD) ? RESTR_ORDER : 0; }
 
 dp_status check_conv(const dp_conv_desc *d, ConvGeom *g)
 {
@@ -539,7 +539,7 @@ size_t fwd_need(const ConvGeom &g, int restr)
     return plan_entry(g, PASS_FWD, restr)->part_cap;
 }
 // The query holds for any flags: the larger of the two.  (The candidates of a measured choice differ: the window kernel's take places of others.)
-size_t fwd_ws_bytes(const ConvGeom &g) { return std::max(fwd_need(g, 0), fwd_need(g, RESTR_ORDER)); }
+size_t fwd_ws_bytes(const ConvGeom &g) { return std::max(fwd_need(g, 0), fwd_need(g, fwd_restr(g, DP_RELU))); }
 
 // ---- the three passes on a validated geometry --------------------------------------
 dp_status run_fwd(const ConvGeom &g, int dtype, unsigned flags, const void *x, const void *w, const float *bias, void *y,
@@ -573,7 +573,7 @@ dp_status run_fwd(const ConvGeom &g, int dtype, unsigned flags, const void *x, c
     }
     if (use_small_c(g, PASS_FWD)) {
         const int kpad = small_c_kpad(g);
-        const size_t need = fwd_need(g, fwd_restr(flags));
+        const size_t need = fwd_need(g, fwd_restr(g, flags));
         if (ws == nullptr || ws_bytes < need) return fail(DP_ERR_WORKSPACE, "forward needs %zu workspace bytes, got %zu", need, ws_bytes);
         bf16_t *xcol = (bf16_t *)ws, *wpad = (bf16_t *)((char *)ws + xcol_bytes(g, kpad));
         const size_t used = xcol_bytes(g, kpad) + round256((size_t)g.K * kpad * 2);
@@ -584,7 +584,7 @@ dp_status run_fwd(const ConvGeom &g, int dtype, unsigned flags, const void *x, c
     }
     ConvArgs a{};
     a.g = g; a.pass = PASS_FWD; a.flags = kflags(flags, true);
-    const PlanRef pep = plan_entry(g, PASS_FWD, fwd_restr(flags));
+    const PlanRef pep = plan_entry(g, PASS_FWD, fwd_restr(g, flags));
     PlanEntry &pe = *pep;
     a.plan = current_plan(pe);
     size_t need = pe.part_cap;
@@ -606,7 +606,8 @@ size_t dgrad_need(const ConvGeom &g, PlanEntry &pe, bool saved)
 // not there (the flat kernels and the rules after them may ask for more than the kernels they replace).
 PlanRef dgrad_choice(const ConvGeom &g, int restr, bool saved, size_t ws_bytes, size_t *need)
 {
-    if (saved && (g.K % 64 != 0 || (g.sh == 1 && g.sw == 1 && g.R * g.S > 2))) restr |= RESTR_SAVED;   // the plans of other layers do not depend on it
+    // the plans of other layers do not depend on it
+    if (saved && (g.K % 64 != 0 || (!(restr & 1) && pixel_window_exists(g, PASS_DGRAD)))) restr |= RESTR_SAVED;
     PlanRef ep = plan_entry(g, PASS_DGRAD, restr);
     *need = dgrad_need(g, *ep, saved);
     if (ws_bytes >= *need) return ep;
@@ -1011,7 +1012,7 @@ dp_status dp_conv2d_kernel_info(const dp_conv_desc *desc, int pass, char *name, 
         return DP_OK;
     }
     if (pass != PASS_DGRAD && use_small_c(g, pass)) g = im2col_geom(g, small_c_kpad(g));
-    const GemmPlan pl = current_plan(*plan_entry(g, pass, pass == PASS_DGRAD ? dgrad_restr(desc->flags) : pass == PASS_FWD ? fwd_restr(desc->flags) : 0));
+    const GemmPlan pl = current_plan(*plan_entry(g, pass, pass == PASS_DGRAD ? dgrad_restr(desc->flags) : pass == PASS_FWD ? fwd_restr(g, desc->flags) : 0));
     if (name != nullptr && name_bytes > 0) plan_kernel_name(pass, pl, pass == PASS_DGRAD && (desc->flags & DP_RELU_IN) != 0, name, name_bytes);
     if (splits != nullptr) *splits = pass != PASS_WGRAD && dma_plan_fuses_reduce(pl) ? -pl.splits : pl.splits;
     return DP_OK;
@@ -1060,7 +1061,7 @@ dp_status dp_conv2d_fwd(const dp_conv_desc *desc, const void *x, const void *w, 
     if (desc->flags & DP_BIAS) { if ((s = check_ptr(bias, "bias")) != DP_OK) return s; }
     if ((s = check_opt(ws, "ws")) != DP_OK) return s;
     if (desc->io_dtype == DP_BF16) {
-        size_t need = fwd_need(g, fwd_restr(desc->flags));
+        size_t need = fwd_need(g, fwd_restr(g, desc->flags));
         if (need > 0 && (ws == nullptr || ws_bytes < need)) return fail(DP_ERR_WORKSPACE, "forward needs %zu workspace bytes, got %zu", need, ws_bytes);
     }
     if ((s = ensure_init()) != DP_OK) return s;

@@ -159,6 +159,7 @@ bool forward_flat_plan(const ConvGeom &g, const GemmPlan &base, GemmPlan *plan, 
 // backward-data: a flat-walk plan faster than `base`, whose price is `time`
 bool backward_flat_plan(const ConvGeom &g, const GemmPlan &base, double time, int restr, GemmPlan *plan, double *flat_time);
 // forward / backward-data: the window kernel's two cheapest plans, and whether it takes the place of `base`, whose price is `time`
+bool pixel_window_exists(const ConvGeom &g, int pass);   // some tile of the window kernel runs the layer
 int pixel_window_plans(const ConvGeom &g, int pass, GemmPlan out[2], double times[2], bool saved = false);
 bool pixel_window_plan(const ConvGeom &g, int pass, const GemmPlan &base, double time, bool saved, double mask_us, GemmPlan *out);
 // filter gradient: the window kernel's two cheapest plans, and whether it takes the place of `base`, whose price is `time`

@@ -313,6 +313,15 @@ const WindowPrice kWindowPrice[2][9] = {
 // per tile; 1.08 - 1.28 for nine of ten)
 const float kMaskedWindow[9] = {1.045f, 1.13f, 1.165f, 1.135f, 1.085f, 1.08f, 1.14f, 1.125f, 1.06f};
 
+bool pixel_window_exists(const ConvGeom &g, int pass)
+{
+    if (g.sh != 1 || g.sw != 1 || g.R * g.S < 3) return false;   // asked on every call
+    GemmPlan pl;
+    for (int v = 0; v < 9; ++v)
+        if (family_plan(g, pass, 250 + v, 1, &pl)) return true;
+    return false;
+}
+
 // its two cheapest plans, best first; returns how many there are
 int pixel_window_plans(const ConvGeom &g, int pass, GemmPlan out[2], double times[2], bool saved)
 {

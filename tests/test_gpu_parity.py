@@ -1114,6 +1114,22 @@ def test_measured_kernel_choice(env, mode):
         dp.dp_set_autotune(False)
 
 
+def test_measured_choice_is_one_for_layers_without_a_window_kernel(env):
+    """Only where the window kernel runs a layer does a forward that masks by its own output have a choice of its own; elsewhere one measurement serves
+    both."""
+    dp, U, orc = env
+    dp.dp_set_autotune(1)
+    try:
+        for n, h, c, k, r, st in ((4, 28, 256, 512, 1, 1), (4, 28, 512, 128, 1, 1), (2, 56, 64, 256, 1, 1), (3, 30, 128, 128, 3, 2), (2, 14, 1024, 256, 1, 1), (5, 33, 192, 256, 3, 2),
+                                  (1, 40, 320, 384, 1, 1), (8, 20, 128, 640, 1, 1)):
+            case = U.ConvCase("onechoice", n, h, h, c, k, r, r, (st, st), (r // 2, r // 2), bf16=True, bias=True, relu=False)
+            case.run_fwd()
+            own = dp.conv_desc(n, h, h, c, k, r, r, (st, st), (r // 2, r // 2), dp.DP_BF16, dp.DP_BIAS | dp.DP_RELU)
+            assert dp.dp_conv2d_kernel_info(own, 0) == dp.dp_conv2d_kernel_info(case.desc, 0)
+    finally:
+        dp.dp_set_autotune(False)
+
+
 def test_measured_choice_with_cold_caches_takes_the_scratch_of_its_query(env):
     """A forward that masks by its own output measures other candidates than the query without flags counts; what the query says is enough for it."""
     dp, U, orc = env
