@@ -340,7 +340,7 @@ PlanRef plan_entry(const ConvGeom &g, int pass, int restr = 0)
         if (window && n > 0 && fs <= 0) {
             GemmPlan win[2];
             double times[2];
-            const int m = pass == PASS_WGRAD ? wgrad_window_plans(g, win, times) : pixel_window_plans(g, pass, win, times);
+            const int m = pass == PASS_WGRAD ? wgrad_window_plans(g, win, times) : pixel_window_plans(g, pass, win, times, (restr & RESTR_SAVED) != 0);
             if (n + m > kTuneCandidates) n = kTuneCandidates - m;   // in the place of the model's last
             for (int i = 0; i < m; ++i) list[n++] = win[i];
         }
@@ -487,15 +487,15 @@ hipError_t launch_entry(ConvArgs &a, PlanEntry &pe, hipStream_t st, TraceScope &
         }
         a.plan = pe.plan;
     }
+    if (prep) {
+        hipError_t e = prep(a);
+        if (e != hipSuccess) return e;
+    }
     if (ts.idx >= 0) {
         char nm[96];
         if (a.pass == PASS_DGRAD && a.plan.win) win_kernel_name(a.pass, a.plan, a.ymask != nullptr, nm, sizeof(nm));
         else plan_kernel_name(a.pass, a.plan, (a.flags & KF_MASK_IN) != 0, nm, sizeof(nm));
         ts.name(nm, a.pass != PASS_WGRAD && dma_plan_fuses_reduce(a.plan) ? -a.plan.splits : a.plan.splits);
-    }
-    if (prep) {
-        hipError_t e = prep(a);
-        if (e != hipSuccess) return e;
     }
     ts.main_begins();
     return launch_plan(a, st);
@@ -681,21 +681,26 @@ dp_status run_dgrad(const ConvGeom &g, int dtype, unsigned flags, const void *dy
     a.plan = current_plan(pe);
     if (need > 0 && (ws == nullptr || ws_bytes < need)) return fail(DP_ERR_WORKSPACE, "backward-data needs %zu workspace bytes, got %zu", need, ws_bytes);
     a.dy = (const bf16_t *)dy; a.ymask = (const bf16_t *)ym; a.w = (const bf16_t *)w; a.out = dx; a.partial = (float *)ws;
-    // the window kernel masks dy itself, once its plan is settled (the measured choice runs its candidates on one masked copy); not where the
-    // gradient goes over what the other blocks still read
-    bool masks = false;
-    if (ym != nullptr && a.plan.win && !overlaps(dx, (size_t)g.N * g.H * g.W * g.C * 2, dy, ybytes(g)) && !overlaps(dx, (size_t)g.N * g.H * g.W * g.C * 2, ym, ybytes(g))) {
-        std::lock_guard<std::mutex> lock(pe.mu);
-        masks = pe.tuned && pe.plan.win;
+    // The window kernel masks dy itself, unless the gradient goes over what the other blocks still read; the other fast kernels take g = dy * [y_saved > 0],
+    // materialised before them (the generic one masks while it loads).  Where a layer may run either, which of the two is known only after the
+    // candidates have been measured, each with its own way of masking.
+    PrepFn mask;
+    if (a.plan.fast && ym != nullptr) {
+        bf16_t *gbuf = (bf16_t *)((char *)ws + round256(pe.part_cap));
+        const size_t dx_bytes = (size_t)g.N * g.H * g.W * g.C * 2;
+        const bool either = !(flags & DP_DX_F32) && pixel_window_exists(g, PASS_DGRAD) && !overlaps(dx, dx_bytes, dy, ybytes(g)) && !overlaps(dx, dx_bytes, ym, ybytes(g));
+        mask = [&, gbuf, either](ConvArgs &c) -> hipError_t {
+            if (either && c.plan.win) { c.dy = (const bf16_t *)dy; c.ymask = (const bf16_t *)ym; return hipSuccess; }
+            c.dy = gbuf; c.ymask = nullptr;
+            return rbg_launch((long long)g.N * g.Ho * g.Wo, g.K, true, dy, ym, gbuf, nullptr, nullptr, st);
+        };
+        if (!either) {
+            hipError_t e = mask(a);
+            if (e != hipSuccess) return hip_fail(e, "ReLU-gradient launch");
+            mask = PrepFn();
+        }
     }
-    if (a.plan.fast && ym != nullptr && !masks) {
-        // the fast kernel takes a pre-masked gradient: materialise g = dy * [y_saved > 0] once
-        void *gbuf = (char *)ws + round256(pe.part_cap);
-        hipError_t e = rbg_launch((long long)g.N * g.Ho * g.Wo, g.K, true, dy, ym, gbuf, nullptr, nullptr, st);
-        if (e != hipSuccess) return hip_fail(e, "ReLU-gradient launch");
-        a.dy = (const bf16_t *)gbuf; a.ymask = nullptr;
-    }
-    hipError_t e = launch_entry(a, pe, st, ts);
+    hipError_t e = launch_entry(a, pe, st, ts, mask);
     return e == hipSuccess ? DP_OK : hip_fail(e, "backward-data launch");
 }
 
