@@ -334,9 +334,9 @@ int pixel_window_plans(const ConvGeom &g, int pass, GemmPlan out[2], double time
         const double waves = std::ceil((double)pl.tilesA * pl.tilesB / 256.0);
         double t = c.c0 + waves * (c.c1 + rounds * (c.c2 + c.c3 * g.R * g.S + c.c4 * rows));
         if (saved) t *= kMaskedWindow[v];
-        // backward-data with 32 channels to a tile fetches half a line per weight row: beyond the 4 MB of an L2 that counts twice
-        // (14 x 14, 512 -> 512, one sample: 14.7 us for a fitted 10.5)
-        if (v == 2 && pass == PASS_DGRAD && (long long)g.K * g.R * g.S * g.C * 2 > 2000000) t *= 1.4;
+        // backward-data with 32 channels to a tile fetches half a line per weight row, which counts where the weights are more than an L2 holds (88 layers,
+        // measured / fitted: up to 4 MB 0.86 - 1.03, beyond 0.80 - 1.75, 1.12 in the middle)
+        if (v == 2 && pass == PASS_DGRAD && (long long)g.K * g.R * g.S * g.C * 2 > 4 << 20) t *= 1.15;
         if (n == 0 || t < times[0]) {
             if (n > 0) { out[1] = out[0]; times[1] = times[0]; }
             out[0] = pl; times[0] = t;

@@ -354,3 +354,16 @@ def test_pixel_window_plan_keeps_to_rows_and_columns_that_its_reciprocals_divide
                     assert name(size, 1, 3, 1, pass_).startswith("k_conv_win<") == runs
             finally:
                 dp.dp_set_override(pass_, -1, 0)
+
+
+def test_narrow_window_tiles_are_priced_by_what_an_l2_holds(dp):
+    """Host logic of the kernel choice (no GPU call): backward-data tiles of 32 channels fetch half lines of weights.  That costs them where the weights
+    exceed an L2, not below."""
+    def name(n, h, c, k):
+        return dp.dp_conv2d_kernel_info(dp.conv_desc(n, h, h, c, k, 3, 3, (1, 1), (1, 1), dp.DP_BF16, dp.DP_RELU | dp.DP_RELU_IN), 1)[0]
+    assert name(2, 10, 512, 384).startswith("k_conv_win<true, 1, 2, 1")    # 3.5 MB: 12.3 us in tiles of 64x64 with splits, 8.7
+    assert name(1, 19, 512, 256).startswith("k_conv_win<true, 1, 2, 1")    # 2.4 MB: 11.5, 7.8
+    assert name(1, 16, 736, 192).startswith("k_conv_win<true, 1, 2, 1")    # 2.5 MB: 10.6, 7.5
+    assert not name(1, 14, 512, 512).startswith("k_conv_win")              # 4.7 MB: 11.7, 13.8
+    assert not name(1, 14, 256, 1024).startswith("k_conv_win")             # 4.7 MB: 12.8, 19.8
+    assert not name(1, 13, 1024, 1024).startswith("k_conv_win<true, 1, 2, 1")   # 18.9 MB: 19.1, 27.9
