@@ -867,8 +867,14 @@ def test_pixel_window_kernel(env, variant):
                                              ("pw_f", 2, 17, 17, 160, 192, 1, 7, (0, 3)), ("pw_i", 1, 9, 9, 8, 16, 2, 5, (1, 3)), ("pw_k", 4, 31, 20, 96, 320, 3, 3, (0, 0))):
             # dy masked by a saved output on its way into the window, alone and with the mask of the ReLU in front
             case = U.ConvCase(tag, n, h, w, c, k, r, s, (1, 1), pd, bf16=True, bias=True, relu=True)
+            fits = "k_conv_win" in dp.dp_conv2d_kernel_info(case.desc, 1)[0]
+            assert fits or tag in {252: ("pw_d",), 253: ("pw_c", "pw_d")}.get(variant, ())
             y = case.run_fwd(case.ws())
+            dp.dp_trace_begin()
             dx, dx_in = case.run_dgrad(y), case.run_dgrad_relu_in(y)
+            rows = dp.dp_trace_end()
+            # the form that masks for itself, not a masked copy of dy before the other one
+            assert len(rows) == 2 and all(("k_conv_win<true" in row["kernel"] and row["kernel"].endswith(", true>")) == fits for row in rows), (tag, rows)
             torch.cuda.synchronize()
             ref = orc.conv2d_bwd_data(case.dy, case.w, case.x.shape, y_saved=U.to_np(y), pad=pd)
             assert U.errs(U.to_np(dx), ref)[0] <= 2.5e-3, tag
@@ -993,17 +999,22 @@ def test_filter_gradient_window_kernel_by_default_and_with_less_scratch(env):
         assert U.errs(U.to_np(dw), U.to_np(usual))[0] <= 2e-6
 
 
-@pytest.mark.parametrize("pass_,variant", [(0, 231), (0, 232), (1, 231), (1, 232), (1, 233), (2, 316), (2, 411)])
-def test_results_do_not_depend_on_other_streams(env, pass_, variant):
+# (pass, variant, saved output).  The window kernels 250 .. 258: on images whose windows leave room for a block of the other streams (251, 252, 256), and
+# others; the filter gradient's (317, 318) fills a compute unit alone
+@pytest.mark.parametrize("pass_,variant,saved", [(0, 231, False), (0, 232, False), (1, 231, False), (1, 232, False), (1, 233, False), (2, 316, False), (2, 411, False),
+                                                 (0, 250, False), (0, 251, False), (0, 252, False), (0, 256, False), (1, 251, False), (1, 252, False), (1, 256, False), (1, 258, False),
+                                                 (1, 251, True), (1, 253, True), (1, 256, True), (2, 317, False), (2, 318, False)])
+def test_results_do_not_depend_on_other_streams(env, pass_, variant, saved):
     """The kernels that hand-order their LDS reads, beside small blocks of other kernels on the same compute units (filter gradients on two
     other streams): bit for bit the result of the kernel alone.  An LDS read that was still in flight when the epilogue began used to
     overwrite a sum when those blocks delayed it."""
     dp, U, orc = env
-    n, h, c, k = (4, 112, 64, 128) if variant == 411 else (8, 56, 256, 256)
+    n, h, c, k = (4, 112, 64, 128) if variant == 411 else (32, 14, 256, 256) if 250 <= variant < 260 else (8, 56, 256, 256)
     g = torch.Generator(device=U.DEV)
     g.manual_seed(7)
     rnd = lambda *s: torch.randn(s, generator=g, device=U.DEV).to(torch.bfloat16)
     x, w, dy = rnd(n, h, h, c), rnd(k, 3, 3, c), rnd(n, h, h, k)
+    y = rnd(n, h, h, k) if saved else None
     d = dp.conv_desc(n, h, h, c, k, 3, 3, (1, 1), (1, 1), dp.DP_BF16, dp.DP_RELU_IN)
     bx, bdy = rnd(8, 56, 56, 256), rnd(8, 56, 56, 256)
     bd = dp.conv_desc(8, 56, 56, 256, 256, 3, 3, (1, 1), (1, 1), dp.DP_BF16, 0)
@@ -1014,6 +1025,8 @@ def test_results_do_not_depend_on_other_streams(env, pass_, variant):
     try:
         dp.dp_set_override(pass_, variant, 1)
         ws = U.workspace(dp.dp_conv2d_workspace_bytes(d, pass_))
+        window = {317: "k_wgrad_win<128", 318: "k_wgrad_win<256"}.get(variant, "k_conv_win" if 250 <= variant < 260 else "")
+        assert dp.dp_conv2d_kernel_info(d, pass_)[0].startswith(window)
 
         def launch():
             out = torch.empty((n, h, h, k) if pass_ == 0 else (n, h, h, c) if pass_ == 1 else (k, 3, 3, c), device=U.DEV,
@@ -1021,7 +1034,7 @@ def test_results_do_not_depend_on_other_streams(env, pass_, variant):
             if pass_ == 0:
                 dp.dp_conv2d_fwd(d, x, w, None, out, ws)
             elif pass_ == 1:
-                dp.dp_conv2d_bwd_data_relu(d, dy, None, w, x, out, ws)
+                dp.dp_conv2d_bwd_data_relu(d, dy, y, w, x, out, ws)
             else:
                 dp.dp_conv2d_bwd_filter(d, x, dy, None, out, None, ws)
             return out
