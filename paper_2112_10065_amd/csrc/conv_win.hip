@@ -8,16 +8,17 @@
 // traffic out of the L2.
 // Twelve waves, three per SIMD: WA of them over the channels, CBP over channel blocks and G = 12 / (WA CBP) over the taps.  A wave's weights are
 // its own (32 channels of its taps), so it streams them through two 4 KB buffers in LDS that only it waits for; the waves meet once
-// per channel block, for the window.  (With the weights shared and a barrier per tap the waves ran through copying, LDS reads and matrix
-// instructions in step, one after the other: 1300 clocks for 512 of matrix work.)  The sums of the tap and channel groups meet in
+// per channel block, for the window.  (With the weights shared and a barrier per tap the waves go through copying, LDS reads and matrix
+// instructions in step, one after the other.)  The sums of the tap and channel groups meet in
 // LDS at the end, in group order: the chip is filled by tiles alone, without a reduction split, partials in memory and a second kernel.
 // Where a copy's data lies depends on the tile only: all offsets are computed before the loop, steps ride in the scalar offset.
 // Measured (us, before: the best of the other kernels with their reduction kernel): 512 -> 512 on 28 x 28, 8 samples, forward 39.1 -> 34.5, masked
 // backward-data 41.7 -> 36.6; 4 samples 28.2 -> 24.0 and 29.6 -> 25.2; 512 -> 512 on 14 x 14, 8 samples 22.5 -> 15.6 and 25.6 -> 17.9; 288 -> 384 on
 // 35 x 35, 4 samples 32.4 -> 18.4 and 23.3 -> 19.5.  Tiles of 96 channels (three waves side by side, four tap groups) for channel counts that 64 and 128
 // divide badly, or that fill the chip better so: backward-data 192 -> 80 on 73 x 73, 4 samples 23.6 -> 14.5; forward 272 -> 96 there 25.3 -> 19.4,
-// 384 -> 288 on 26 x 26, 11 samples 28.3 -> 21.6.  What bounds it: LDS (reads of 1.25 - 1.5 fragments per matrix instruction and the copies,
-// 115 bytes per clock together), and 6 us of launch, first copies, sums and stores.
+// 384 -> 288 on 26 x 26, 11 samples 28.3 -> 21.6.  What bounds it (counters at 8 samples): waits for copies and LDS reads.  On 28 x 28, 512 -> 512
+// the matrix cores are busy for 0.52 of the time and the waves wait at counters and barriers for 0.42 of theirs; on 14 x 14 0.3 and 0.5, where the fixed
+// part of a launch (3 - 7 us of the fitted price: first copies, sums, stores) is most of it.
 #include "dma_common.h"
 #include <cstdio>
 

@@ -11,9 +11,8 @@
 // 32 x 32 in 96 accumulators; five fragment reads serve six matrix instructions.  The four slice groups' sums meet in LDS at the end, in
 // group order, so that a block needs no partials in memory for them: a 512 x 512 x 3 x 3 gradient fills the chip with two splits.
 // Measured with the reduction kernel (us; the pipelined tiles with one column tile per tap before): 512 -> 512 on 28 x 28, 8 samples 47.4 -> 40.5,
-// 32 samples 124 -> 112; 128 -> 128 on 112 x 112, 8 samples 48.0 -> 39.1, 32 samples 150 -> 112 (1.06 PFLOP/s).  What is left: the matrix cores
-// (two thirds of the loop), the LDS reads beside them, and 6 us per block before and behind the loop (first copies, the slice groups' sums 1.6 us,
-// the stores), which is why a layer under about 20 us keeps the other kernels.
+// 32 samples 124 -> 112; 128 -> 128 on 112 x 112, 8 samples 48.0 -> 39.1, 32 samples 150 -> 112 (1.06 PFLOP/s).  What is left (counters, four layers of
+// 14 x 14 to 112 x 112 at 8 samples): the matrix cores are busy for 0.50 of the time, the waves wait at counters and barriers for 0.40 of theirs; and the fixed part of the fitted price, 6.8 us (first copies, the slice groups' sums, the stores), which is why short layers keep the other kernels.
 // Both operands are reduction-major in LDS and go through the LDS transpose read; x rows are 64 bytes, so the four rows one read touches
 // are 256 consecutive bytes wherever a tap starts, and the taps differ by an address offset only.
 // Output: fp32 dW, or fp32 partials [split][k][r][s][c] for the split-reduce kernel.

@@ -153,7 +153,9 @@ constexpr unsigned kKnownFlags = DP_BIAS | DP_RELU | DP_DETERMINISTIC | DP_DX_F3
 // kernels a backward-data call may not use: bit 0 the input-patch kernels (they stage bf16, the caller wants fp32),
 // bit 1 the stationary-weight kernel (it has no fused input-ReLU mask); dgrad_choice adds bits 3 and 4 (dp_kernels.h)
 int dgrad_restr(unsigned flags) { return ((flags & DP_DX_F32) ? 1 : 0) | ((flags & DP_RELU_IN) ? 2 : 0); }
-// RESTR_ORDER only where there is a window kernel to leave out: other layers have one plan, measured once
+// A layer whose gradients are masked by its own y keeps the order in which y is summed (forward_flat_plan).  The flags tell such a layer only where it stands
+// alone: in a chain (DP_RELU_IN) the layer behind masks by this y, and its order is the window kernel's.  The measured choice goes by time and keeps
+// no order.  RESTR_ORDER only where there is a window kernel to leave out: other layers have one plan, measured once.
 int fwd_restr(const ConvGeom &g, unsigned flags) { return (flags & DP_RELU) && !(flags & DP_RELU_IN) && pixel_window_exists(g, PASS_FWD) ? RESTR_ORDER : 0; }
 
 dp_status check_conv(const dp_conv_desc *d, ConvGeom *g)

@@ -22,7 +22,7 @@ enum { PASS_FWD = 0, PASS_DGRAD = 1, PASS_WGRAD = 2 };
 // bits of the planner's `restr` (0 - 2: auto_plan_list)
 enum {
     RESTR_SAVED = 8,   // backward-data with a saved output to mask dy by: the generic kernel does that while it loads, the others need a pass
-    RESTR_ORDER = 32,  // forward of a layer that keeps its ReLU's mask to itself: the kernels may not add in another order (forward_flat_plan says why)
+    RESTR_ORDER = 32,  // forward with DP_RELU and without DP_RELU_IN: the default choice leaves out the kernel that adds in another order (forward_flat_plan)
     RESTR_BASE = 16,   // the kernels and prices that need least scratch: no flat-walk kernel in backward-data
 };
 

@@ -227,9 +227,9 @@ int auto_plan_list(const ConvGeom &g, int pass, int force_splits, GemmPlan *out,
 // Forward, channels that 64 does not divide: a flat-walk kernel in the place of `base` (32-wide steps), if one is faster.  It takes the
 // reduction apart exactly as `base` does: the same splits, each a whole number of 64-wide steps, either as partials or as the
 // reduction groups of a block.  Both walk (tap, channel) in 16-element slices, so the sums run in the same order and y is the same bit
-// for bit.  That is required, not only tidy: a layer that keeps its mask to itself takes its gradients through [y > 0], and an output whose
-// sum lies at zero changes side with the order of the additions (80 -> 192 3x3, 4 x 73 x 73: one of 3.9 M outputs in every
-// twentieth input set), which switches a whole term of dx on or off.
+// for bit.  That matters where gradients are taken through [y > 0]: an output whose sum lies at zero changes side with the order of the
+// additions (80 -> 192 3x3, 4 x 73 x 73: one of 3.9 M outputs in every twentieth input set), which switches a whole term of dx on or off.
+// The window kernel adds in another order; RESTR_ORDER leaves it out of the default choice of layers that mask by their own y.
 // Where it is faster (old / new with the same splits, 376 layers):
 //   generic kernel: from 3 steps on 1.02 - 1.73; below 0.81 - 1.36, the shortest layers lose
 //   64x64 tiles of 32-wide steps, unsplit: 1 step 0.91, 3 steps 0.98, 4 steps 1.01, 6 and more 1.06 - 1.17; split 1.01 - 1.24
