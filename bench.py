@@ -31,71 +31,79 @@ HBM_PEAK_GBS = 8000.0
 # HBM bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, scaled by a 1 GiB copy kernel), averaged over
 # the launches of each kernel at one per-GPU batch: profiles/vgg16_hbm_traffic.md
 TRAFFIC_BYTES_PER_LAUNCH = {   # key: "<kernel as the profiler prints it>@<per-GPU batch>"
-    "k_wgrad_dma<128, 128, 32, 2, 2, 2>@32": 275078599,
-    "k_reduce_flat@32": 60161969,
-    "k_wgrad_dma<256, 256, 64, 2, 4, 2>@32": 177667828,
-    "k_wgrad_dma<128, 128, 64, 2, 2, 2>@32": 259377408,
-    "k_reduce_pixel_major@32": 27174872,
-    "k_conv_strip<true, 224, 256>@32": 171644633,
-    "k_conv_strip<false, 224, 256>@32": 121469231,
-    "k_wgrad_halo9<true>@32": 320878204,
-    "k_conv_strip<true, 256, 128>@32": 185911535,
-    "k_halo_ws<0, false>@32": 283800783,
-    "k_dgrad_dma<64, 128, 64, 2, 2, 2, 1>@32": 164571708,
-    "k_halo_ws<1, true>@32": 618192570,
-    "k_fwd_dma<128, 128, 64, 2, 2, 2, 1>@32": 146734142,
-    "k_fwd_dma<64, 128, 64, 2, 2, 2, 1>@32": 95860080,
-    "k_dgrad_dma<64, 64, 64, 2, 2, 2, 2>@32": 157534286,
-    "k_conv_strip<false, 256, 128>@32": 147696706,
-    "k_conv_strip<true, 128, 256>@32": 132799145,
-    "k_reduce_flat_wide@32": 48001240,
-    "k_fwd_dma<64, 64, 64, 2, 2, 3, 1>@32": 99755382,
-    "k_wgrad_dma<64, 256, 32, 1, 4, 2>@32": 424924068,
-    "k_dgrad_dma<64, 64, 64, 2, 2, 3, 1>@32": 114982045,
-    "k_fwd_rgb3@32": 230225985,
-    "k_fwd_dma<64, 64, 64, 2, 2, 2, 4>@32": 74369407,
-    "k_wgrad_rgb3<true>@32": 220898337,
-    "k_dense_wgrad<true>@32": 69690728,
-    "k_dense_wgrad<false>@32": 18710094,
-    "k_dense_dgrad@32": 9297571,
-    "k_wgrad_direct_sum@32": 4291674,
-    "k_wgrad_dma<128, 128, 32, 2, 2, 2>@2": 131164048,
-    "k_wgrad_dma<128, 64, 32, 2, 2, 2>@2": 80393531,
-    "k_reduce_flat@2": 27498692,
-    "k_dgrad_dma<64, 64, 64, 2, 2, 2, 2>@2": 54995695,
-    "k_wgrad_dma<64, 128, 64, 2, 2, 2>@2": 39431809,
-    "k_reduce_pixel_major@2": 9790902,
-    "k_reduce_flat_wide@2": 22073797,
-    "k_wgrad_dma<64, 64, 32, 2, 2, 2>@2": 35385434,
-    "k_dgrad_dma<64, 64, 64, 2, 2, 2, 4>@2": 42727728,
-    "k_dgrad_dma<128, 64, 64, 2, 2, 2, 1>@2": 53431899,
-    "k_dgrad_dma<64, 64, 64, 2, 2, 3, 1>@2": 45686533,
-    "k_dgrad_dma<128, 64, 64, 2, 2, 2, 2>@2": 56822772,
-    "k_fwd_dma<64, 64, 64, 2, 2, 2, 2>@2": 31871907,
-    "k_conv_fast<0, 64, 64, 64, 2, 2>@2": 28739201,
-    "k_dense_fwd<1>@2": 82874842,
-    "k_fwd_dma<64, 64, 64, 2, 2, 2, 4>@2": 33982470,
-    "k_conv_fast<1, 128, 64, 64, 2, 2>@2": 68977417,
-    "k_fwd_dma<128, 64, 64, 2, 2, 2, 1>@2": 30056766,
-    "k_dgrad_dma<128, 64, 128, 2, 2, 2, 1>@2": 79696568,
-    "k_wgrad_halo@2": 45397162,
-    "k_fwd_dma<64, 64, 64, 2, 2, 3, 1>@2": 25019716,
-    "k_wgrad_halo9<true>@2": 34065730,
-    "k_dense_wgrad<true>@2": 67487480,
-    "k_conv_fast<0, 128, 64, 64, 2, 2>@2": 19960021,
-    "k_halo<0, 64, 1, 4, 3>@2": 17366213,
-    "k_halo<1, 64, 1, 4, 4>@2": 39682413,
-    "k_dgrad_dma<64, 64, 128, 2, 2, 3, 1>@2": 17234433,
-    "k_halo_ws<1, true>@2": 39764571,
-    "k_fwd_dma<64, 128, 128, 2, 2, 2, 1>@2": 14300926,
-    "k_fwd_dma<64, 64, 128, 2, 2, 3, 1>@2": 20039705,
-    "k_halo<0, 64, 1, 4, 2>@2": 20847855,
-    "k_dgrad_dma<64, 128, 128, 2, 2, 2, 1>@2": 18350732,
-    "k_dense_wgrad<false>@2": 16628633,
-    "k_fwd_rgb3@2": 14118188,
-    "k_wgrad_rgb3<true>@2": 15733105,
-    "k_dense_dgrad@2": 8326932,
-    "k_wgrad_direct_sum@2": 1706703,
+    "k_wgrad_win<256, true, true>@32": 127569146,
+    "k_reduce_flat@32": 52294683,
+    "k_wgrad_dma<128, 128, 32, 2, 2, 2>@32": 286655512,
+    "k_wgrad_dma<64, 128, 32, 2, 2, 2>@32": 341619182,
+    "k_reduce_pixel_major@32": 29336753,
+    "k_wgrad_halo9<true>@32": 320884004,
+    "k_conv_strip<true, 256, 128>@32": 178706789,
+    "k_conv_strip<false, 224, 256>@32": 121450898,
+    "k_halo_ws<1, true>@32": 618161814,
+    "k_conv_strip<true, 256, 256>@32": 187295508,
+    "k_wgrad_dma<256, 256, 64, 2, 4, 2>@32": 185763581,
+    "k_dgrad_dma<64, 128, 64, 2, 2, 2, 1>@32": 237909294,
+    "k_conv_strip<true, 224, 256>@32": 168290001,
+    "k_halo_ws<0, false>@32": 283802973,
+    "k_fwd_dma<128, 64, 64, 2, 2, 2, 1>@32": 139565410,
+    "k_fwd_dma<64, 128, 64, 2, 2, 2, 1>@32": 119270209,
+    "k_dgrad_dma<64, 64, 64, 2, 2, 2, 2>@32": 158298759,
+    "k_reduce_flat_wide@32": 42934085,
+    "k_conv_strip<false, 256, 128>@32": 153049340,
+    "k_conv_strip<true, 128, 256>@32": 147234829,
+    "k_dgrad_dma<64, 64, 64, 2, 2, 3, 1>@32": 116745837,
+    "k_fwd_dma<64, 64, 64, 2, 2, 2, 2>@32": 102692546,
+    "k_conv_win<true, 4, 1, 4, false>@32": 87346692,
+    "k_fwd_dma<128, 64, 64, 2, 2, 2, 2>@32": 103077448,
+    "k_fwd_dma<64, 64, 64, 2, 2, 2, 4>@32": 80126432,
+    "k_fwd_rgb3@32": 230222942,
+    "k_wgrad_rgb3<true>@32": 220907112,
+    "k_conv_win<false, 4, 1, 4, false>@32": 82119824,
+    "k_dense_wgrad<true>@32": 69700335,
+    "k_dense_wgrad<false>@32": 18720554,
+    "k_dense_dgrad@32": 9297713,
+    "k_wgrad_direct_sum@32": 4299933,
+    "k_wgrad_dma<64, 256, 32, 1, 4, 2>@2": 191732276,
+    "k_wgrad_dma<128, 128, 32, 2, 2, 2>@2": 87545288,
+    "k_reduce_flat@2": 25760300,
+    "k_wgrad_dma<256, 128, 32, 4, 2, 2>@2": 412140290,
+    "k_reduce_flat_wide@2": 21884618,
+    "k_wgrad_dma<64, 64, 32, 2, 2, 2>@2": 51490094,
+    "k_wgrad_dma<64, 128, 32, 2, 2, 2>@2": 71948277,
+    "k_wgrad_dma<64, 128, 64, 2, 2, 2>@2": 43617436,
+    "k_wgrad_dma<128, 64, 32, 2, 2, 2>@2": 59238217,
+    "k_wgrad_dma<128, 128, 64, 2, 2, 2>@2": 39471168,
+    "k_dense_fwd<1>@2": 82872492,
+    "k_dgrad_dma<64, 64, 64, 2, 2, 2, 4>@2": 33196345,
+    "k_wgrad_win<256, true, true>@2": 21817900,
+    "k_dense_both<32, false>@2": 207348122,
+    "k_dgrad_dma<64, 128, 64, 2, 2, 2, 1>@2": 32692226,
+    "k_conv_win<true, 1, 2, 1, false>@2": 36696596,
+    "k_conv_win<false, 2, 1, 2, false>@2": 34140881,
+    "k_fwd_dma<64, 64, 64, 2, 2, 2, 2>@2": 20381223,
+    "k_conv_win<false, 1, 2, 1, false>@2": 39076025,
+    "k_fwd_dma<64, 128, 64, 2, 2, 2, 1>@2": 24848608,
+    "k_dgrad_dma<64, 64, 64, 2, 2, 3, 1>@2": 25873620,
+    "k_conv_win<true, 2, 1, 2, false>@2": 22101749,
+    "k_fwd_dma<128, 128, 64, 2, 2, 2, 1>@2": 31122130,
+    "k_halo<1, 64, 1, 4, 4>@2": 39682654,
+    "k_dense_wgrad<true>@2": 67497306,
+    "k_conv_win<true, 2, 1, 4, false>@2": 19945647,
+    "k_conv_win<false, 3, 1, 2, false>@2": 31810636,
+    "k_halo<0, 64, 1, 4, 2>@2": 18770045,
+    "k_conv_win<false, 2, 1, 4, false>@2": 16756053,
+    "k_conv_fast<1, 64, 128, 64, 2, 2>@2": 24343434,
+    "k_dense_both<8, false>@2": 34689278,
+    "k_halo<0, 64, 1, 4, 3>@2": 22627941,
+    "k_dgrad_dma<128, 64, 128, 2, 2, 2, 1>@2": 29376845,
+    "k_conv_win<false, 4, 1, 2, false>@2": 13197510,
+    "k_fwd_rgb3@2": 14118310,
+    "k_dense_wgrad<false>@2": 16639386,
+    "k_wgrad_rgb3<true>@2": 15737341,
+    "k_halo_ws<1, true>@2": 39765058,
+    "k_dense_dgrad@2": 8326977,
+    "k_dense_both_sum@2": 1484767,
+    "k_wgrad_direct_sum@2": 1714904,
 }
 
 
