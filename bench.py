@@ -31,77 +31,77 @@ HBM_PEAK_GBS = 8000.0
 # HBM bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, scaled by a 1 GiB copy kernel), averaged over
 # the launches of each kernel at one per-GPU batch: profiles/vgg16_hbm_traffic.md
 TRAFFIC_BYTES_PER_LAUNCH = {   # key: "<kernel as the profiler prints it>@<per-GPU batch>"
-    "k_wgrad_win<256, true, true>@32": 127569146,
-    "k_reduce_flat@32": 52294683,
-    "k_wgrad_dma<128, 128, 32, 2, 2, 2>@32": 286655512,
-    "k_wgrad_dma<64, 128, 32, 2, 2, 2>@32": 341619182,
-    "k_reduce_pixel_major@32": 29336753,
-    "k_wgrad_halo9<true>@32": 320884004,
-    "k_conv_strip<true, 256, 128>@32": 178706789,
-    "k_conv_strip<false, 224, 256>@32": 121450898,
-    "k_halo_ws<1, true>@32": 618161814,
-    "k_conv_strip<true, 256, 256>@32": 187295508,
-    "k_wgrad_dma<256, 256, 64, 2, 4, 2>@32": 185763581,
-    "k_dgrad_dma<64, 128, 64, 2, 2, 2, 1>@32": 237909294,
-    "k_conv_strip<true, 224, 256>@32": 168290001,
-    "k_halo_ws<0, false>@32": 283802973,
-    "k_fwd_dma<128, 64, 64, 2, 2, 2, 1>@32": 139565410,
-    "k_fwd_dma<64, 128, 64, 2, 2, 2, 1>@32": 119270209,
-    "k_dgrad_dma<64, 64, 64, 2, 2, 2, 2>@32": 158298759,
-    "k_reduce_flat_wide@32": 42934085,
-    "k_conv_strip<false, 256, 128>@32": 153049340,
-    "k_conv_strip<true, 128, 256>@32": 147234829,
-    "k_dgrad_dma<64, 64, 64, 2, 2, 3, 1>@32": 116745837,
-    "k_fwd_dma<64, 64, 64, 2, 2, 2, 2>@32": 102692546,
-    "k_conv_win<true, 4, 1, 4, false>@32": 87346692,
-    "k_fwd_dma<128, 64, 64, 2, 2, 2, 2>@32": 103077448,
-    "k_fwd_dma<64, 64, 64, 2, 2, 2, 4>@32": 80126432,
-    "k_fwd_rgb3@32": 230222942,
-    "k_wgrad_rgb3<true>@32": 220907112,
-    "k_conv_win<false, 4, 1, 4, false>@32": 82119824,
-    "k_dense_wgrad<true>@32": 69700335,
-    "k_dense_wgrad<false>@32": 18720554,
+    "k_wgrad_win<256, true, true>@32": 107069726,
+    "k_conv_strip<false, 224, 256>@32": 111272838,
+    "k_wgrad_halo9<true>@32": 320884149,
+    "k_halo_ws<1, true>@32": 618229222,
+    "k_conv_strip<true, 256, 128>@32": 200718693,
+    "k_halo_ws<0, false>@32": 283802718,
+    "k_wgrad_dma<128, 128, 32, 2, 2, 2>@32": 424909438,
+    "k_conv_strip<true, 256, 256>@32": 170817672,
+    "k_wgrad_dma<64, 128, 32, 2, 2, 2>@32": 424480974,
+    "k_conv_strip<true, 224, 256>@32": 168279364,
+    "k_wgrad_dma<256, 256, 64, 2, 4, 2>@32": 160291430,
+    "k_fwd_rgb3@32": 230255220,
+    "k_fwd_dma<128, 64, 64, 2, 2, 2, 1>@32": 227014038,
+    "k_conv_strip<false, 256, 128>@32": 221710770,
+    "k_wgrad_rgb3<true>@32": 220906972,
+    "k_reduce_flat@32": 36440574,
+    "k_dgrad_dma<64, 128, 64, 2, 2, 2, 1>@32": 212756012,
+    "k_dgrad_dma<64, 64, 64, 2, 2, 2, 2>@32": 211272441,
+    "k_conv_win<true, 4, 1, 4, false>@32": 57687055,
+    "k_fwd_dma<64, 128, 64, 2, 2, 2, 1>@32": 51887320,
+    "k_reduce_flat_wide@32": 31901443,
+    "k_conv_strip<true, 128, 256>@32": 72420602,
+    "k_dense_wgrad<true>@32": 69701822,
+    "k_conv_win<false, 4, 1, 4, false>@32": 51290109,
+    "k_fwd_dma<128, 64, 64, 2, 2, 2, 2>@32": 40117663,
+    "k_dgrad_dma<64, 64, 64, 2, 2, 3, 1>@32": 40071370,
+    "k_fwd_dma<64, 64, 64, 2, 2, 2, 2>@32": 20975182,
+    "k_reduce_pixel_major@32": 4822608,
+    "k_dense_wgrad<false>@32": 18720447,
+    "k_fwd_dma<64, 64, 64, 2, 2, 2, 4>@32": 12047265,
     "k_dense_dgrad@32": 9297713,
     "k_wgrad_direct_sum@32": 4299933,
-    "k_wgrad_dma<64, 256, 32, 1, 4, 2>@2": 191732276,
-    "k_wgrad_dma<128, 128, 32, 2, 2, 2>@2": 87545288,
-    "k_reduce_flat@2": 25760300,
-    "k_wgrad_dma<256, 128, 32, 4, 2, 2>@2": 412140290,
-    "k_reduce_flat_wide@2": 21884618,
-    "k_wgrad_dma<64, 64, 32, 2, 2, 2>@2": 51490094,
-    "k_wgrad_dma<64, 128, 32, 2, 2, 2>@2": 71948277,
-    "k_wgrad_dma<64, 128, 64, 2, 2, 2>@2": 43617436,
-    "k_wgrad_dma<128, 64, 32, 2, 2, 2>@2": 59238217,
-    "k_wgrad_dma<128, 128, 64, 2, 2, 2>@2": 39471168,
-    "k_dense_fwd<1>@2": 82872492,
-    "k_dgrad_dma<64, 64, 64, 2, 2, 2, 4>@2": 33196345,
-    "k_wgrad_win<256, true, true>@2": 21817900,
+    "k_wgrad_dma<64, 256, 32, 1, 4, 2>@2": 227181982,
+    "k_wgrad_dma<256, 128, 32, 4, 2, 2>@2": 412135672,
+    "k_dense_fwd<1>@2": 82872272,
+    "k_wgrad_dma<64, 64, 32, 2, 2, 2>@2": 76681330,
     "k_dense_both<32, false>@2": 207348122,
-    "k_dgrad_dma<64, 128, 64, 2, 2, 2, 1>@2": 32692226,
-    "k_conv_win<true, 1, 2, 1, false>@2": 36696596,
-    "k_conv_win<false, 2, 1, 2, false>@2": 34140881,
-    "k_fwd_dma<64, 64, 64, 2, 2, 2, 2>@2": 20381223,
-    "k_conv_win<false, 1, 2, 1, false>@2": 39076025,
-    "k_fwd_dma<64, 128, 64, 2, 2, 2, 1>@2": 24848608,
-    "k_dgrad_dma<64, 64, 64, 2, 2, 3, 1>@2": 25873620,
-    "k_conv_win<true, 2, 1, 2, false>@2": 22101749,
-    "k_fwd_dma<128, 128, 64, 2, 2, 2, 1>@2": 31122130,
-    "k_halo<1, 64, 1, 4, 4>@2": 39682654,
-    "k_dense_wgrad<true>@2": 67497306,
-    "k_conv_win<true, 2, 1, 4, false>@2": 19945647,
+    "k_conv_win<true, 1, 2, 1, false>@2": 39462251,
+    "k_conv_win<false, 1, 2, 1, false>@2": 39076041,
+    "k_conv_win<false, 2, 1, 2, false>@2": 35257885,
+    "k_wgrad_dma<128, 128, 64, 2, 2, 2>@2": 52646550,
+    "k_dgrad_dma<64, 64, 64, 2, 2, 2, 4>@2": 44429771,
+    "k_reduce_flat_wide@2": 26284035,
+    "k_reduce_flat@2": 24450366,
+    "k_dense_wgrad<true>@2": 67497995,
     "k_conv_win<false, 3, 1, 2, false>@2": 31810636,
-    "k_halo<0, 64, 1, 4, 2>@2": 18770045,
-    "k_conv_win<false, 2, 1, 4, false>@2": 16756053,
-    "k_conv_fast<1, 64, 128, 64, 2, 2>@2": 24343434,
+    "k_wgrad_win<256, true, true>@2": 22615199,
+    "k_conv_win<true, 2, 1, 4, false>@2": 19945669,
+    "k_halo<1, 64, 1, 4, 4>@2": 39682824,
+    "k_wgrad_dma<128, 64, 32, 2, 2, 2>@2": 97404668,
+    "k_wgrad_dma<128, 128, 32, 2, 2, 2>@2": 38299195,
+    "k_conv_win<true, 2, 1, 2, false>@2": 17575604,
     "k_dense_both<8, false>@2": 34689278,
-    "k_halo<0, 64, 1, 4, 3>@2": 22627941,
-    "k_dgrad_dma<128, 64, 128, 2, 2, 2, 1>@2": 29376845,
+    "k_conv_win<false, 2, 1, 4, false>@2": 16756118,
+    "k_dgrad_dma<64, 128, 64, 2, 2, 2, 1>@2": 26639336,
+    "k_wgrad_dma<64, 128, 64, 2, 2, 2>@2": 23692340,
+    "k_fwd_dma<128, 128, 64, 2, 2, 2, 1>@2": 13527517,
+    "k_halo<0, 64, 1, 4, 3>@2": 26799808,
     "k_conv_win<false, 4, 1, 2, false>@2": 13197510,
-    "k_fwd_rgb3@2": 14118310,
-    "k_dense_wgrad<false>@2": 16639386,
-    "k_wgrad_rgb3<true>@2": 15737341,
+    "k_halo<0, 64, 1, 4, 2>@2": 20371546,
+    "k_fwd_dma<64, 64, 64, 2, 2, 2, 2>@2": 8935088,
+    "k_conv_fast<1, 64, 128, 64, 2, 2>@2": 22241941,
+    "k_fwd_rgb3@2": 14118036,
+    "k_dense_wgrad<false>@2": 16639420,
     "k_halo_ws<1, true>@2": 39765058,
+    "k_fwd_dma<64, 128, 64, 2, 2, 2, 1>@2": 15832992,
+    "k_wgrad_rgb3<true>@2": 15737294,
+    "k_wgrad_dma<64, 128, 32, 2, 2, 2>@2": 18585390,
+    "k_dgrad_dma<64, 64, 64, 2, 2, 3, 1>@2": 14595835,
     "k_dense_dgrad@2": 8326977,
+    "k_dgrad_dma<128, 64, 128, 2, 2, 2, 1>@2": 19832451,
     "k_dense_both_sum@2": 1484767,
     "k_wgrad_direct_sum@2": 1714904,
 }
