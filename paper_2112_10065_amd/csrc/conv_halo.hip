@@ -714,298 +714,246 @@ __global__ __launch_bounds__(256) void k_wgrad_halo9(const KArgs p, int tws, int
 
 // ---------------------------------------------------------------------------------------
 // 3x3 (nine-tap) forward / backward-data with 64 reduction channels per tap, weights stationary in
-// REGISTERS.  A block has four waves, one per SIMD, so each may use the whole register file: a wave
-// keeps the fragments of all 64 output channels for all nine taps (72 fragments, 288 registers) and
-// multiplies them with 64 pixels of the tile; nothing but the input patch goes through LDS (512 bytes
-// read per matrix instruction, half of what a 32-channel wave would need) and no barrier separates
-// the taps.  Blocks are persistent (one per CU and 64-channel tile) and keep three patch buffers:
-// while tile i is multiplied, the patches of tiles i+1 and i+2 are on their way.  The accumulators go
-// straight to the NHWC output: a lane pair exchanges halves so that each lane stores 16 bytes.  One
-// barrier per tile.
+// REGISTERS.  A block has four waves and a CU two blocks, so that two waves of different blocks share a
+// SIMD and one multiplies while the other waits, converts or stores.  A wave keeps the fragments of 32
+// output channels for all nine taps (36 fragments, 144 registers) and multiplies them with 64 of the
+// tile's 128 pixels (8 x 16); nothing but the input patch goes through LDS and no barrier separates the
+// taps.  Blocks are persistent (two per CU and 64-channel tile) and keep three patch buffers: while tile i
+// is multiplied, the patches of tiles i+1 and i+2 are on their way.  A wave's results are reordered in its own
+// share of the patch buffer that the tile has just left, and go out 64 bytes per pixel.  One barrier per tile.
+// Patch layout: the pixel in column pc has its chunk c at position c ^ ((pc >> 1) & 7): sixteen pixels of a row are
+// conflict-free, and a tap's row is an immediate offset.
+// What bounds it: with one wave per SIMD holding all 64 channels (288 registers) every wait, conversion and store of the wave was the
+// SIMD's; the LDS reads per matrix instruction have doubled and are still half of what LDS gives.  16 x 224 x 224, 64 -> 64 (us, back to back /
+// with flushed caches): forward 76 / 84 -> 56 / 68, masked backward-data 89 / 112 -> 64 / 102 (without its loads and stores 46 and 42: the matrix
+// instructions and LDS reads alone).  The faster of all kernels from a few tiles on (180 layers of 32 - 450 channels, 7 - 224 pixels: 0.95 - 1.4
+// times the best other; below 100 tiles 5.5 - 6.2 us like the others).
 // ---------------------------------------------------------------------------------------
-constexpr int WS_PATCH = HALO_PP * 128;   // 44 KiB per patch buffer
+constexpr int WS_TH = 8, WS_TW = 16, WS_TB = WS_TH * WS_TW, WS_PW = WS_TW + 2, WS_PP = (WS_TH + 2) * WS_PW;
+constexpr int WS_CPW = (WS_PP / 8 + 4) / 4;   // patch copies per wave, eight pixels each
+constexpr int WS_PATCH = 4 * WS_CPW * 1024;   // 24 KiB per patch buffer
 constexpr int WS_LDS = 3 * WS_PATCH + 64 * 4;
-constexpr int WS_DEPTH = 3;               // fragment reads run this many 16-channel slices ahead of the matrix cores
-constexpr int WS_CPW = HALO_PP / 8 / 4;   // patch copies per wave
-static_assert(WS_CPW * 4 * 8 == HALO_PP, "patch copies divide evenly over the four waves");
-static_assert(WS_PATCH + 9 * 8192 <= 3 * WS_PATCH, "the weights are staged behind the first patch buffer");
+static_assert(WS_PP <= 4 * WS_CPW * 8 && 2 * WS_LDS <= 160 * 1024, "a patch fits its copies, two blocks a CU");
+static_assert(3 * 8192 <= WS_PATCH && 64 * 64 <= WS_CPW * 1024, "three taps of weights, and a wave's results, fit a patch buffer");
+
+DEVFN void lds_write16(unsigned addr, u32x4 v) { asm volatile("ds_write_b128 %0, %1" ::"v"(addr), "v"(v) : "memory"); }
 
 template <int PASS, bool MASK = false>   // MASK (backward-data): fused backward of the ReLU in front of the layer
-__global__ __launch_bounds__(256) void k_halo_ws(const KArgs p, int tws, int tiles_x, int tiles_y, int tiles_all)
+__global__ __launch_bounds__(256, 2) void k_halo_ws(const KArgs p, int tiles_x, int tiles_y, int tiles_all)
 {
+#if __HIP_DEVICE_COMPILE__   // the host pass only needs the launch stub
+    constexpr int WS_DEPTH = MASK ? 2 : 3;   // fragment reads run this many 16-channel slices ahead of the matrix cores
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const ConvGeom &g = p.g;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int TW = 1 << tws, TH = HALO_TB >> tws, PW = TW + 2, PP = (TH + 2) * PW;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int hc = wave & 1, pg = wave >> 1;   // channel half, pixel group
     const int a0 = blockIdx.y * 64;
     const int IH = PASS == PASS_FWD ? g.H : g.Ho, IW = PASS == PASS_FWD ? g.W : g.Wo;
     const int OH = PASS == PASS_FWD ? g.Ho : g.H, OW = PASS == PASS_FWD ? g.Wo : g.W;
     const int RSC = 9 * g.C;
     const unsigned smem_base = lds_offset(smem);
     float *bias_lds = reinterpret_cast<float *>(smem + 3 * WS_PATCH);
-    __amdgpu_buffer_rsrc_t rin = PASS == PASS_FWD ? make_rsrc(p.x, (size_t)g.N * g.H * g.W * g.C * 2)
-                                                  : make_rsrc(p.dy, (size_t)g.N * g.Ho * g.Wo * g.K * 2);
-    __amdgpu_buffer_rsrc_t rw = make_rsrc(p.w, (size_t)g.K * RSC * 2);
-    if (tid < 64) bias_lds[tid] = (PASS == PASS_FWD && (p.flags & KF_BIAS) && a0 + tid < p.rowsA) ? p.bias[a0 + tid] : 0.f;
+    const __amdgpu_buffer_rsrc_t rin = PASS == PASS_FWD ? make_rsrc(p.x, (size_t)g.N * g.H * g.W * g.C * 2)
+                                                        : make_rsrc(p.dy, (size_t)g.N * g.Ho * g.Wo * g.K * 2);
+    const __amdgpu_buffer_rsrc_t rw = make_rsrc(p.w, (size_t)g.K * RSC * 2);
+    const size_t out_bytes = (size_t)g.N * OH * OW * p.rowsA * 2;
+    const __amdgpu_buffer_rsrc_t rout = make_rsrc(p.out, out_bytes), rx = make_rsrc(MASK ? (const void *)p.x : p.out, out_bytes);
 
-    // patch copies of this lane: copy q of a wave fills patch pixels (wave*WS_CPW + q)*8 .. +7; the lane's
-    // pixel (row, column) and channel chunk are fixed, only the tile origin changes
+    // weights, three taps at a time, on their way to registers.  Forward: step st is [64 c_out][64 c_in], chunk swizzle by row
+    // pair; backward-data: step st (filter tap 8 - st) is [64 c_out][64 c_in] with c_out the reduction, read transposed
+    auto issue_weights = [&](int part, int buf) {
+#pragma unroll
+        for (int q = 0; q < 6; ++q) {
+            const int id = wave * 6 + q, st = part * 3 + (id >> 3), row = (id & 7) * 8 + (lane >> 3);
+            unsigned voff;
+            if (PASS == PASS_FWD) {
+                const int c = (lane & 7) ^ ((row >> 1) & 7);
+                voff = a0 + row < p.rowsA ? ((unsigned)(a0 + row) * RSC + st * 64 + c * 8) * 2u : OOR;
+            } else {
+                const int c = (lane & 7) ^ (seg_swz<64>(row) << 2);
+                voff = a0 + c * 8 < p.rowsA ? ((unsigned)row * RSC + (8 - st) * g.C + a0 + c * 8) * 2u : OOR;
+            }
+            dma16(rw, smem_base + buf * WS_PATCH + id * 1024, voff);
+        }
+    };
+    // patch copies: copy q of a wave fills patch pixels (wave * WS_CPW + q) * 8 .. + 7; the lane's pixel and chunk are fixed, the tile's origin
+    // changes.  Past the patch the slots take its first pixels again.
     unsigned pk[WS_CPW];
 #pragma unroll
     for (int q = 0; q < WS_CPW; ++q) {
-        const int pp = (wave * WS_CPW + q) * 8 + (lane >> 3), c = (lane & 7) ^ ((pp >> 1) & 7);
-        const int pr = pp / PW, pc = pp - pr * PW;
-        pk[q] = (unsigned)pr | ((unsigned)pc << 8) | ((unsigned)c << 16) | (pp < PP ? 1u << 24 : 0u);
+        const int id = (wave * WS_CPW + q) * 8 + (lane >> 3), pp = id < WS_PP ? id : lane >> 3, pr = pp / WS_PW, pc = pp - pr * WS_PW;
+        pk[q] = (unsigned)pr | ((unsigned)pc << 8) | ((unsigned)((lane & 7) ^ ((pc >> 1) & 7)) << 20);
     }
-    auto issue_patch = [&](int tile, int buf) {
-        const int n = tile / (tiles_x * tiles_y), trem = tile - n * (tiles_x * tiles_y), ty = trem / tiles_x, tx = trem - ty * tiles_x;
-        const int h0 = PASS == PASS_FWD ? ty * TH - g.ph : ty * TH + g.ph - 2, w0 = PASS == PASS_FWD ? tx * TW - g.pw : tx * TW + g.pw - 2;
-        const int nbase = n * IH;
-#pragma unroll
-        for (int q = 0; q < WS_CPW; ++q) {
-            const int ih = h0 + (int)(pk[q] & 255u), iw = w0 + (int)((pk[q] >> 8) & 255u), c = (pk[q] >> 16) & 7;
-            const bool ok = (pk[q] >> 24) != 0 && (unsigned)ih < (unsigned)IH && (unsigned)iw < (unsigned)IW;
-            dma16(rin, smem_base + buf * WS_PATCH + (wave * WS_CPW + q) * 1024, ok ? (unsigned)(((nbase + ih) * IW + iw) * 64 + c * 8) * 2u : OOR);
-        }
+    struct Tile { int n, h, w; };
+    auto place = [&](int t) {
+        const int n = t / (tiles_x * tiles_y), rem = t - n * (tiles_x * tiles_y), ty = rem / tiles_x;
+        return Tile{n, ty * WS_TH, (rem - ty * tiles_x) * WS_TW};
     };
+    auto copy_one = [&](const Tile &t, int q, unsigned dst, bool on) {   // a tile past the last fetches nothing
+        const int h0 = PASS == PASS_FWD ? t.h - g.ph : t.h + g.ph - 2, w0 = PASS == PASS_FWD ? t.w - g.pw : t.w + g.pw - 2;
+        unsigned v = pk[q];
+        asm volatile("" : "+v"(v));   // stays packed in the loop
+        const int pr = (int)(v & 255u), pc = (int)((v >> 8) & 255u);
+        const bool row = (unsigned)(h0 + pr) < (unsigned)(on ? IH : 0), column = (unsigned)(w0 + pc) < (unsigned)IW;
+        const unsigned at = (unsigned)((t.n * IH + h0) * IW + w0) * 128u + (unsigned)(pr * IW + pc) * 128u + (v >> 16);
+        dma16(rin, dst + (wave * WS_CPW + q) * 1024, row & column ? at : OOR);
+    };
+
     const TileWalk tw = tile_walk(tiles_all);
     int tile = tw.first;
     const int stride = tw.stride, tiles = tw.end;   // this block's tiles: tile, tile + stride, ... below `tiles`
-    if (tile < tiles) issue_patch(tile, 0);
+    Tile now = place(tile), next = place(tile + stride);
+    issue_weights(0, 1);
+    issue_weights(1, 2);
+#pragma unroll
+    for (int q = 0; q < WS_CPW; ++q) copy_one(now, q, smem_base, tile < tiles);
+    if (tid < 64) bias_lds[tid] = (PASS == PASS_FWD && (p.flags & KF_BIAS) && a0 + tid < p.rowsA) ? p.bias[a0 + tid] : 0.f;
 
-    // ---- weights: through LDS (behind the first patch buffer) into registers ------------------------
-    // forward: the tile of step st is [64 c_out][64 c_in], chunk swizzle by row pair; backward-data: the tile
-    // of step st (filter tap 8 - st) is [64 c_out][64 c_in] with c_out the reduction, read transposed
-    const unsigned wst = smem_base + WS_PATCH;
+    u32x4 afr[9][4];   // [step][16-channel slice]
+    unsigned wad[4];   // this lane's weights of slice k of a step
+    if (PASS == PASS_FWD) {
+        const int row = hc * 32 + (lane & 31);
 #pragma unroll
-    for (int q = 0; q < 18; ++q) {
-        const int id = wave * 18 + q, st = id >> 3, row = (id & 7) * 8 + (lane >> 3);
-        unsigned voff;
-        if (PASS == PASS_FWD) {
-            const int c = (lane & 7) ^ ((row >> 1) & 7);
-            voff = a0 + row < p.rowsA ? ((unsigned)(a0 + row) * RSC + st * 64 + c * 8) * 2u : OOR;
-        } else {
-            const int c = (lane & 7) ^ (seg_swz<64>(row) << 2);
-            voff = a0 + c * 8 < p.rowsA ? ((unsigned)row * RSC + (8 - st) * g.C + a0 + c * 8) * 2u : OOR;
-        }
-        dma16(rw, wst + id * 1024, voff);
+        for (int ks = 0; ks < 4; ++ks) wad[ks] = smem_base + WS_PATCH + row * 128 + (((2 * ks + (lane >> 5)) ^ ((row >> 1) & 7)) << 4);
+    } else {
+        const int i16 = lane & 15, t = (lane >> 5) * 8 + (i16 >> 2), cl = ((lane >> 4) & 1) * 16 + (i16 & 3) * 4;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) wad[ks] = smem_base + WS_PATCH + (ks * 16 + t) * 128 + ((hc ^ seg_swz<64>(t)) << 6) + cl * 2;
     }
-    wait_vmcnt<0>();
-    __syncthreads();
-    // (plain LDS loads here: the compiler places their waits; the hand-counted reads start with the tile loop)
-    u32x4 afr[9][4][2];   // [step][slice][32-row half]
-    {
-        const char *wl = smem + WS_PATCH;
-        typedef short v4s __attribute__((ext_vector_type(4)));
-        typedef __attribute__((address_space(3))) v4s *lds_v4s;
-        const int i16 = lane & 15, tl = (lane >> 5) * 8 + (i16 >> 2), cl = ((lane >> 4) & 1) * 16 + (i16 & 3) * 4;
+    for_constant<3>([&](auto PART) {
+        constexpr int part = PART, buf = part == 1 ? WS_PATCH : 0;
+        if (part == 2) wait_vmcnt<0>();
+        else wait_vmcnt<6 + WS_CPW>();   // younger: the next part and the first patch
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        for_constant<3>([&](auto J) {
+            constexpr int st = part * 3 + J, off = buf + J * 8192;
+            u32x2 lo[4], hi[4];
 #pragma unroll
-        for (int st = 0; st < 9; ++st)
+            for (int ks = 0; ks < 4; ++ks) {
+                if constexpr (PASS == PASS_FWD) afr[st][ks] = lds_read16<off>(wad[ks]);
+                else { lo[ks] = lds_read_tr<off>(wad[ks]); hi[ks] = lds_read_tr<off + 512>(wad[ks]); }
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)");
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    if (PASS == PASS_FWD) {
-                        const int row = i * 32 + (lane & 31);
-                        afr[st][ks][i] = *reinterpret_cast<const u32x4 *>(wl + st * 8192 + row * 128 + (((2 * ks + (lane >> 5)) ^ ((row >> 1) & 7)) << 4));
-                    } else {
-                        const int t = ks * 16 + tl, col = i * 32 + cl;
-                        const char *a = wl + st * 8192 + t * 128 + ((((col >> 5) ^ seg_swz<64>(t)) << 6) | ((col & 31) << 1));
-                        const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(a));
-                        const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(a + 4 * 128));
-                        const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
-                        afr[st][ks][i] = u32x4{l2.x, l2.y, h2.x, h2.y};
-                    }
+            for (int ks = 0; ks < 4; ++ks) {
+                if constexpr (PASS == PASS_FWD) asm volatile("" : "+v"(afr[st][ks]));
+                else {
+                    asm volatile("" : "+v"(lo[ks]));
+                    asm volatile("" : "+v"(hi[ks]));
+                    afr[st][ks] = u32x4{lo[ks].x, lo[ks].y, hi[ks].x, hi[ks].y};
                 }
-    }
-    __syncthreads();   // the staging area is free for patches; the first patch has landed (waited above)
-    if (tile + stride < tiles) issue_patch(tile + stride, 1);
-
-    int pp0[2];
+            }
+        });
+        if (part != 1) __builtin_amdgcn_s_barrier();   // everyone has read the buffer that is filled next
+        if (part == 0) issue_weights(2, 1);
+    });
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int jj = wave * 64 + j * 32 + (lane & 31);
-        pp0[j] = (jj >> tws) * PW + (jj & (TW - 1));
-    }
-    const unsigned hsel = lane >> 5;
-    bf16_t *out = reinterpret_cast<bf16_t *>(p.out);
+    for (int q = 0; q < WS_CPW; ++q) copy_one(next, q, smem_base + WS_PATCH, tile + stride < tiles);
 
-    // A wave that issues a memory instruction into a full queue stalls, matrix instructions included, so the
-    // copies of the patch two tiles ahead and the stores of the previous tile's output (held packed in
-    // registers meanwhile) are spread over the 36 slices of the running tile instead of issued in a burst.
-    u32x4 ost[MASK ? 1 : 8];           // previous tile: [pixel fragment j][channel half i][group pair gp], 8 channels of one pixel each
-    bf16_t *optr[2] = {out, out};   // this lane's output row of fragment j (previous tile), at channel a0
-    bool ook[2] = {false, false};
-    bool have_prev = false;
-    // backward of the ReLU in front of the layer (KF_MASK_IN): the eight saved-input vectors that match this lane's eight output vectors of
-    // the running tile are requested before its first matrix instruction and used in its epilogue, behind the wait that every tile ends with
-    // (the masked form has no registers left to hold the previous tile's output as well: it stores each tile in its own epilogue)
-    constexpr bool mask_in = MASK;
-    u32x4 mk[MASK ? 8 : 1];
-    auto store_one = [&](int k) {
-        const int j = k >> 2, i = (k >> 1) & 1, gp = k & 1;
-        const int ch = i * 32 + 8 * (2 * gp + (int)hsel);
-        if (ook[j] && a0 + ch < p.rowsA) asm volatile("global_store_dwordx4 %0, %1, off" ::"v"(optr[j] + ch), "v"(ost[k]) : "memory");
-    };
+    // this lane's pixel of fragment 0 in column tap s, slice 0; slices differ in two bits, rows and fragments by immediates
+    unsigned col[3];
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+        const int pc = (lane & 15) + s, pr = pg * 4 + ((lane >> 4) & 1);
+        col[s] = smem_base + (pr * WS_PW + pc) * 128 + (((lane >> 5) ^ ((pc >> 1) & 7)) << 4);
+    }
+    // results: written by pixel fragment, read back four lanes to a pixel
+    const unsigned stg = smem_base + wave * WS_CPW * 1024;
+    const int wpx = lane & 31, rpx = lane >> 2;
+    const unsigned stw = stg + wpx * 64 + ((((lane >> 5)) ^ ((wpx >> 2) & 3)) << 4), str = stg + rpx * 64 + (((lane & 3) ^ ((rpx >> 2) & 3)) << 4);
+    const int och = a0 + hc * 32 + (lane & 3) * 8;
+    const unsigned bad = lds_offset(bias_lds) + (hc * 32 + 4 * (lane >> 5)) * 4;
 
     for (int it = 0; tile < tiles; tile += stride, ++it) {
-        // buffer (it + 2) % 3 held tile it - 1, which every wave had finished before the last barrier
-        const bool more1 = tile + stride < tiles, more2 = tile + 2 * stride < tiles;
-        int nh0 = 0, nw0 = 0, nnb = 0;   // origin of the patch two tiles ahead
-        if (more2) {
-            const int t2 = tile + 2 * stride;
-            const int n = t2 / (tiles_x * tiles_y), trem = t2 - n * (tiles_x * tiles_y), ty = trem / tiles_x, tx = trem - ty * tiles_x;
-            nh0 = PASS == PASS_FWD ? ty * TH - g.ph : ty * TH + g.ph - 2;
-            nw0 = PASS == PASS_FWD ? tx * TW - g.pw : tx * TW + g.pw - 2;
-            nnb = n * IH;
+        const unsigned base = (it % 3) * WS_PATCH, nbuf = smem_base + ((it + 2) % 3) * WS_PATCH;   // which tile it - 1 left before the last barrier
+        const Tile after = place(tile + 2 * stride);
+        const bool more = tile + 2 * stride < tiles;
+        // this lane's output vectors: row pg * 4 + i of the tile, pixel lane / 4
+        const int orow = now.h + pg * 4;
+        unsigned voff = now.w + rpx < OW && och < p.rowsA ? ((unsigned)((now.n * OH + orow) * OW + now.w + rpx) * (unsigned)p.rowsA + och) * 2u : OOR;
+        auto at = [&](int i) { return orow + i < OH && voff != OOR ? voff + (unsigned)(i * OW) * (unsigned)p.rowsA * 2u : OOR; };
+        u32x4 mk[4];
+        if constexpr (MASK) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) mk[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, at(i), 0, 0);
+            asm volatile("" : "+v"(voff));   // the four offsets are made again for the stores
         }
-        const unsigned nbuf = smem_base + ((it + 2) % 3) * WS_PATCH + wave * WS_CPW * 1024;
-        auto copy_one = [&](int q) {
-            const int ih = nh0 + (int)(pk[q] & 255u), iw = nw0 + (int)((pk[q] >> 8) & 255u), c = (pk[q] >> 16) & 7;
-            const bool ok = (pk[q] >> 24) != 0 && (unsigned)ih < (unsigned)IH && (unsigned)iw < (unsigned)IW;
-            dma16(rin, nbuf + q * 1024, ok ? (unsigned)(((nnb + ih) * IW + iw) * 64 + c * 8) * 2u : OOR);
-        };
-        const unsigned base = smem_base + (it % 3) * WS_PATCH;
-        if (mask_in) {
-            const int n = tile / (tiles_x * tiles_y), trem = tile - n * (tiles_x * tiles_y), ty = trem / tiles_x, tx = trem - ty * tiles_x;
+        unsigned cb[3];
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int pix = wave * 64 + j * 32 + (lane & 31);
-                const int pr = ty * TH + (pix >> tws), qc = tx * TW + (pix & (TW - 1));
-                const bool ok = pr < OH && qc < OW;
-                // a lane without an output pixel reads the first pixel instead: the load is issued by every lane, so the wait below counts right
-                const bf16_t *xrow = p.x + (ok ? ((size_t)(n * OH + pr) * OW + qc) * p.rowsA + a0 : (size_t)0);
+        for (int s = 0; s < 3; ++s) cb[s] = col[s] + base;
+        f32x16 acc[2];
 #pragma unroll
-                for (int i = 0; i < 2; ++i)
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
-                    for (int gp = 0; gp < 2; ++gp) {
-                        const int ch = i * 32 + 8 * (2 * gp + (int)hsel);
-                        const bf16_t *src = xrow + (ok && a0 + ch < p.rowsA ? ch : 0);
-                        asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(mk[j * 4 + i * 2 + gp]) : "v"(src) : "memory");
-                    }
-            }
-        }
-        asm volatile("" : "+v"(pp0[0]), "+v"(pp0[1]));   // keeps the 72 read addresses from being computed ahead of the loop
-        f32x16 acc[2][2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+            for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
         u32x4 fb[WS_DEPTH + 1][2];   // [buffer][pixel fragment]
-        // chunk (2*ks + hsel) ^ swz = ((hsel ^ swz) ^ 2*ks): the address of slice ks is the address of slice 0 with bits 5-6 flipped by ks,
-        // so a tap costs one address computation per pixel fragment and three exclusive-ors
-        unsigned b0[2] = {0, 0};
-        auto read_b = [&](int sl) {
-            const int st = sl >> 2, ks = sl & 3;
-            if (ks == 0) {
-                const int off = (st / 3) * PW + (st % 3);
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    const int pp = pp0[j] + off;
-                    b0[j] = base + pp * 128 + (((int)hsel ^ ((pp >> 1) & 7)) << 4);
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < 2; ++j) fb[sl % (WS_DEPTH + 1)][j] = lds_read16<0>(b0[j] ^ (unsigned)(ks << 5));
+        auto read_b = [&](auto SL) {
+            constexpr int st = SL / 4, ks = SL % 4, off = st / 3 * WS_PW * 128;
+            const unsigned ad = cb[st % 3] ^ (unsigned)(ks << 5);
+            fb[SL % (WS_DEPTH + 1)][0] = lds_read16<off>(ad);
+            fb[SL % (WS_DEPTH + 1)][1] = lds_read16<off + 2 * WS_PW * 128>(ad);
         };
-#pragma unroll
-        for (int sl = 0; sl < WS_DEPTH; ++sl) read_b(sl);
-#pragma unroll
-        for (int sl = 0; sl < 36; ++sl) {
-            if (sl + WS_DEPTH < 36) read_b(sl + WS_DEPTH);
-            constexpr int kFull = 2 * WS_DEPTH;
-            const int newer = 2 * (35 - sl < WS_DEPTH ? 35 - sl : WS_DEPTH);   // reads issued after this slice's
-            if (newer == kFull) asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(kFull));
-            else if (newer == 4) asm volatile("s_waitcnt lgkmcnt(4)");
-            else if (newer == 2) asm volatile("s_waitcnt lgkmcnt(2)");
-            else asm volatile("s_waitcnt lgkmcnt(0)");
-            const int cur = sl % (WS_DEPTH + 1);
+        for_constant<WS_DEPTH>([&](auto SL) { read_b(SL); });
+        for_constant<36>([&](auto SL) {
+            constexpr int sl = SL, cur = sl % (WS_DEPTH + 1), newer = 2 * (35 - sl < WS_DEPTH ? 35 - sl : WS_DEPTH);   // reads issued after this slice's
+            if constexpr (sl + WS_DEPTH < 36) read_b(std::integral_constant<int, sl + WS_DEPTH>{});
+            asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(newer));
             asm volatile("" : "+v"(fb[cur][0]));
             asm volatile("" : "+v"(fb[cur][1]));
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+            for (int j = 0; j < 2; ++j)
+                acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, afr[sl / 4][sl % 4]), __builtin_bit_cast(bf16x8, fb[cur][j]), acc[j], 0, 0, 0);
+            if constexpr (sl % 4 == 1 && sl / 4 < WS_CPW) copy_one(after, sl / 4, nbuf, more);
+        });
+        // of the loads after this wave's share of the next patch only the copies above may be outstanding
+        wait_vmcnt<WS_CPW>();
+        __builtin_amdgcn_s_barrier();   // all shares of the next patch have landed; this tile's buffer has been read
+        f32x4 bv[4];
+        if constexpr (PASS == PASS_FWD) {
+            bv[0] = __builtin_bit_cast(f32x4, lds_read16<0>(bad)); bv[1] = __builtin_bit_cast(f32x4, lds_read16<32>(bad));
+            bv[2] = __builtin_bit_cast(f32x4, lds_read16<64>(bad)); bv[3] = __builtin_bit_cast(f32x4, lds_read16<96>(bad));
+            asm volatile("s_waitcnt lgkmcnt(0)");
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, afr[sl >> 2][sl & 3][i]),
-                                                                       __builtin_bit_cast(bf16x8, fb[cur][j]), acc[i][j], 0, 0, 0);
-            if (sl % 3 == 1 && sl / 3 < WS_CPW) {
-                if (more2) copy_one(sl / 3);
-            }
-            if (!MASK && sl % 4 == 2 && sl / 4 < 8) {
-                if (have_prev) store_one(sl / 4);
-            }
+            for (int k = 0; k < 4; ++k) asm volatile("" : "+v"(bv[k]));
         }
-        // this wave's share of the next patch has landed: of the loads issued after it (the copies above) none can
-        // still be outstanding once at most that many operations are
-        if (more1) {
-            if (more2) wait_vmcnt<WS_CPW>();
-            else wait_vmcnt<0>();
-        } else if (mask_in) {
-            wait_vmcnt<0>();
-        }
-        // the saved-input vectors were requested before everything this tile issued, so they have landed as well
-        if (mask_in) {
+        // accumulator element v of lane l is channel 8*(v/4) + 4*(l/32) + v%4 of pixel l%32 of fragment j; the lanes l and
+        // l+32 swap halves of two channel groups, after which each holds 8 consecutive channels of one group
 #pragma unroll
-            for (int k = 0; k < 8; ++k) asm volatile("" : "+v"(mk[k]));
-        }
-        // accumulator element v of lane l is channel i*32 + 8*(v/4) + 4*(l/32) + v%4 of pixel l%32 of fragment j; the lanes
-        // l and l+32 swap halves of two channel groups, after which each holds 8 consecutive channels of one group
-        {
-            const int n = tile / (tiles_x * tiles_y), trem = tile - n * (tiles_x * tiles_y), ty = trem / tiles_x, tx = trem - ty * tiles_x;
-            // the eight bias vectors of this lane's channels, read together (one wait instead of eight round trips to LDS)
-            f32x4 bvv[2][4];
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+            for (int gp = 0; gp < 2; ++gp) {
+                unsigned pkd[2][2];   // [group 2gp, 2gp+1][channel pair]
 #pragma unroll
-                for (int gq = 0; gq < 4; ++gq)
-                    bvv[i][gq] = PASS == PASS_FWD ? *reinterpret_cast<const f32x4 *>(bias_lds + i * 32 + 8 * gq + 4 * hsel) : f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int gq = 0; gq < 4; ++gq) asm volatile("" : "+v"(bvv[i][gq]));   // all eight are in registers before the first is used
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int pix = wave * 64 + j * 32 + (lane & 31);
-                const int pr = ty * TH + (pix >> tws), qc = tx * TW + (pix & (TW - 1));
-                ook[j] = pr < OH && qc < OW;
-                optr[j] = out + ((size_t)(n * OH + pr) * OW + qc) * p.rowsA + a0;
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int gp = 0; gp < 2; ++gp) {
-                        unsigned pkd[2][2];   // [group 2gp, 2gp+1][channel pair]
-#pragma unroll
-                        for (int e = 0; e < 2; ++e) {
-                            const int gq = 2 * gp + e;
-                            const f32x4 bv = bvv[i][gq];
-                            float v0 = acc[i][j][4 * gq] + bv.x, v1 = acc[i][j][4 * gq + 1] + bv.y, v2 = acc[i][j][4 * gq + 2] + bv.z,
-                                  v3 = acc[i][j][4 * gq + 3] + bv.w;
-                            if (PASS == PASS_FWD && (p.flags & KF_RELU)) { v0 = fmaxf(v0, 0.f); v1 = fmaxf(v1, 0.f); v2 = fmaxf(v2, 0.f); v3 = fmaxf(v3, 0.f); }
-                            pkd[e][0] = pack_bf16(v0, v1);
-                            pkd[e][1] = pack_bf16(v2, v3);
-                        }
-                        const auto s0 = __builtin_amdgcn_permlane32_swap(pkd[0][0], pkd[1][0], false, false);
-                        const auto s1 = __builtin_amdgcn_permlane32_swap(pkd[0][1], pkd[1][1], false, false);
-                        const u32x4 packed = u32x4{s0[0], s1[0], s0[1], s1[1]};
-                        if constexpr (MASK) {
-                            ost[0] = apply_mask(packed, mk[j * 4 + i * 2 + gp]);
-                            const int ch = i * 32 + 8 * (2 * gp + (int)hsel);
-                            if (ook[j] && a0 + ch < p.rowsA) asm volatile("global_store_dwordx4 %0, %1, off" ::"v"(optr[j] + ch), "v"(ost[0]) : "memory");
-                        } else {
-                            ost[j * 4 + i * 2 + gp] = packed;
-                        }
+                for (int e = 0; e < 2; ++e) {
+                    const int gq = 2 * gp + e;
+                    float v0 = acc[j][4 * gq], v1 = acc[j][4 * gq + 1], v2 = acc[j][4 * gq + 2], v3 = acc[j][4 * gq + 3];
+                    if constexpr (PASS == PASS_FWD) {
+                        v0 += bv[gq].x; v1 += bv[gq].y; v2 += bv[gq].z; v3 += bv[gq].w;
+                        if (p.flags & KF_RELU) { v0 = fmaxf(v0, 0.f); v1 = fmaxf(v1, 0.f); v2 = fmaxf(v2, 0.f); v3 = fmaxf(v3, 0.f); }
                     }
+                    pkd[e][0] = pack_bf16(v0, v1);
+                    pkd[e][1] = pack_bf16(v2, v3);
+                }
+                const auto s0 = __builtin_amdgcn_permlane32_swap(pkd[0][0], pkd[1][0], false, false);
+                const auto s1 = __builtin_amdgcn_permlane32_swap(pkd[0][1], pkd[1][1], false, false);
+                // chunk 2 gp + lane / 32 of pixel j * 32 + lane % 32; (pixel >> 2) & 3 is the same for both fragments
+                lds_write16((stw ^ (unsigned)(gp << 5)) + base + j * 2048, u32x4{s0[0], s1[0], s0[1], s1[1]});
             }
-            have_prev = !MASK;
-        }
-        __builtin_amdgcn_s_barrier();   // all shares of the next patch have landed; this tile's buffer is free (no fence: copies and stores stay in flight)
-    }
-    if (have_prev) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        u32x4 o[4];
+        o[0] = lds_read16<0>(str + base); o[1] = lds_read16<1024>(str + base); o[2] = lds_read16<2048>(str + base); o[3] = lds_read16<3072>(str + base);
+        asm volatile("s_waitcnt lgkmcnt(0)");
 #pragma unroll
-        for (int k = 0; k < 8; ++k) store_one(k);
+        for (int i = 0; i < 4; ++i) {
+            asm volatile("" : "+v"(o[i]));
+            if constexpr (MASK) o[i] = apply_mask(o[i], mk[i]);
+            __builtin_amdgcn_raw_buffer_store_b128(o[i], rout, at(i), 0, 0);
+        }
+        now = next;
+        next = after;
     }
+#endif
 }
 
 struct HaloVariant { int TA, WA, WB, NS; };
@@ -1102,12 +1050,11 @@ bool halo_plan(const ConvGeom &g, int pass, int force_variant, int force_splits,
         if (g.sh != 1 || g.sw != 1 || g.R != 3 || g.S != 3 || red_c != 64 || (rowsA % 8) != 0) return false;
         if (pass == PASS_DGRAD && (g.ph > 2 || g.pw > 2)) return false;
         const int oh = pass == PASS_FWD ? g.Ho : g.H, ow = pass == PASS_FWD ? g.Wo : g.W;
-        const int tws = halo_tws(oh, ow), tw = 1 << tws, th = HALO_TB >> tws;
-        const long long tiles = (long long)g.N * ((oh + th - 1) / th) * ((ow + tw - 1) / tw);
+        const long long tiles = (long long)g.N * ((oh + WS_TH - 1) / WS_TH) * ((ow + WS_TW - 1) / WS_TW);
         if (tiles > 0x7fffff) return false;
         pl->variant = 4;
         pl->fast = true; pl->dma = true; pl->halo = true;
-        pl->TA = 64; pl->TB = HALO_TB; pl->BK = 64; pl->vecA = pl->vecB = true;
+        pl->TA = 64; pl->TB = WS_TB; pl->BK = 64; pl->vecA = pl->vecB = true;
         pl->tilesA = (rowsA + 63) / 64;
         pl->tilesB = (int)tiles;
         pl->steps_total = pl->steps_per_split = 9;
@@ -1180,22 +1127,22 @@ hipError_t halo_launch(const ConvArgs &a, hipStream_t st)
     p.flags = a.flags;
     p.x = a.x; p.w = a.w; p.dy = a.dy; p.ymask = nullptr; p.bias = a.bias; p.out = a.out; p.partial = a.partial;
     const int oh = fwd ? a.g.Ho : a.g.H, ow = fwd ? a.g.Wo : a.g.W;
-    const int tws = halo_tws(oh, ow), tw = 1 << tws, th = HALO_TB >> tws;
-    const int tiles_x = (ow + tw - 1) / tw, tiles_y = (oh + th - 1) / th;
     if (a.plan.variant == 4) {
-        int blocks = a.plan.blocks > 0 ? a.plan.blocks : 256 / p.tilesA;   // default: one persistent block per CU
+        int blocks = a.plan.blocks > 0 ? a.plan.blocks : 512 / p.tilesA;   // default: two persistent blocks per CU
         if (blocks < 1) blocks = 1;
         if (blocks > p.tilesB) blocks = p.tilesB;
-        void (*kern)(const KArgs, int, int, int, int) = k_halo_ws<PASS_FWD>;
+        void (*kern)(const KArgs, int, int, int) = k_halo_ws<PASS_FWD>;
         if (!fwd) {
             if (p.flags & KF_MASK_IN) kern = k_halo_ws<PASS_DGRAD, true>;
             else kern = k_halo_ws<PASS_DGRAD>;
         }
         hipLaunchKernelGGL(kern, dim3((unsigned)blocks, (unsigned)p.tilesA), dim3(256), WS_LDS, st, p,
-                           tws, tiles_x, tiles_y, p.tilesB);
+                           (ow + WS_TW - 1) / WS_TW, (oh + WS_TH - 1) / WS_TH, p.tilesB);
         dp_trace_main_kernel_done(st);
         return hipGetLastError();
     }
+    const int tws = halo_tws(oh, ow), tw = 1 << tws, th = HALO_TB >> tws;
+    const int tiles_x = (ow + tw - 1) / tw, tiles_y = (oh + th - 1) / th;
     const HaloVariant &h = kHalo[a.plan.variant];
     dim3 grid((unsigned)(p.tilesA * p.tilesB), 1, 1), block(64 * h.WA * h.WB, 1, 1);
     hipLaunchKernelGGL(pick_halo(a.pass, a.plan.variant), grid, block, halo_lds_bytes(h), st, p, tws, tiles_x, tiles_y);

@@ -50,7 +50,7 @@ const Candidate kPix[] = {
     {401, 2, 1.20f, 6.0f},   // same, 128 x 256
     {402, 2, 0.75f, 5.5f},
     {403, 2, 0.72f, 5.5f},
-    {404, 1, 0.50f, 0.8f},   // 3x3 only: persistent blocks, weights in registers
+    {404, 2, 0.40f, 0.8f},   // 3x3 only: persistent blocks, weights in registers (180 layers: 8 % in the median)
     {100, 2, 1.40f, 5.0f},   // register-staged fallbacks (also reduction step 32)
     {101, 3, 1.05f, 4.5f},
     {102, 3, 1.05f, 4.5f},
@@ -360,7 +360,8 @@ bool pixel_window_plan(const ConvGeom &g, int pass, const GemmPlan &base, double
     const bool fwd = pass == PASS_FWD, split = base.splits > 1;
     if (!fwd && base.BK == 32 && pl[0].variant >= 6 && g.R * g.S < 5) return false;   // 96-channel tiles were fitted from 7 taps on
     double floor_us = 0.0, factor = 0.0;   // not in the place of unsplit register-staged kernels forward, nor of flat ones backward with few taps or short reductions
-    if (base.halo) { floor_us = fwd ? 0.3 : -1.6; factor = fwd ? 1.13 : 1.34; }
+    if (base.halo && base.variant == 4) factor = 1.0;
+    else if (base.halo) { floor_us = fwd ? 0.3 : -1.6; factor = fwd ? 1.13 : 1.34; }
     else if (dma_plan_is_strip(base)) { floor_us = -4.4; factor = fwd ? 1.11 : 1.16; }
     else if (dma_plan_is_flat(base)) factor = fwd || (g.R * g.S > 8 && g.R * g.S * g.K >= 512) ? 1.0 : 0.0;   // backward-data: 1.17 - 1.78 times as fast
     else if (!base.dma) { floor_us = fwd ? 0.0 : -3.6; factor = !fwd ? 1.03 : split ? 0.76 : 0.0; }
