@@ -1534,6 +1534,7 @@ bool dma_plan(const ConvGeom &g, int pass, int force_variant, int force_splits, 
     int rowsA, rowsB, red;
     const DmaVariant *d;
     if (pass != PASS_WGRAD && force_variant >= 250 && force_variant < 260) return !f32_out && win_plan(g, pass, force_variant - 250, pl);
+    if (pass != PASS_WGRAD && force_variant >= 260 && force_variant < 263) return !f32_out && pw_plan(g, pass, force_variant - 260, force_splits, pl);
     if (pass == PASS_FWD) {
         if (force_variant < 200 || force_variant >= 200 + kNumDma) return false;
         d = &kDma[force_variant - 200];
@@ -1606,8 +1607,9 @@ bool dma_plan(const ConvGeom &g, int pass, int force_variant, int force_splits, 
     return true;
 }
 
-bool dma_plan_is_flat(const GemmPlan &plan) { return plan.dma && !plan.halo && !plan.wstrip && !plan.wwin && !plan.win && kDma[plan.variant].mix; }
-bool dma_plan_is_strip(const GemmPlan &plan) { return plan.dma && !plan.halo && !plan.wstrip && !plan.wwin && !plan.win && is_strip(plan.variant); }
+bool dma_plan_is_flat(const GemmPlan &plan) { return plan.dma && !plan.halo && !plan.wstrip && !plan.wwin && !plan.win && !plan.pw && kDma[plan.variant].mix; }
+int dma_plan_groups(const GemmPlan &plan) { return plan.dma && !plan.halo && !plan.wstrip && !plan.wwin && !plan.win && !plan.pw ? kDma[plan.variant].KG : 1; }
+bool dma_plan_is_strip(const GemmPlan &plan) { return plan.dma && !plan.halo && !plan.wstrip && !plan.wwin && !plan.win && !plan.pw && is_strip(plan.variant); }
 
 // Whether this forward / backward-data plan sums its reduction splits inside the main kernel: asked for by the plan, tiles in
 // natural pixel order, and few enough tiles that a range of the counter ring is not handed out again for at least 64 later launches.
@@ -1616,7 +1618,7 @@ bool dma_fused_reduce_fits(int rowsA, int rowsB, int splits) { return (rowsA & 3
 
 bool dma_plan_fuses_reduce(const GemmPlan &plan)
 {
-    return plan.fused_reduce && plan.dma && !plan.halo && !plan.wstrip && !plan.win && plan.splits > 1 && !is_strip(plan.variant) && !plan.phase &&
+    return plan.fused_reduce && plan.dma && !plan.halo && !plan.wstrip && !plan.win && !plan.pw && plan.splits > 1 && !is_strip(plan.variant) && !plan.phase &&
            plan.tilesA * plan.tilesB <= kTicketRing / 64;
 }
 

@@ -135,7 +135,8 @@ struct TraceScope {
 };
 void plan_kernel_name(int pass, const GemmPlan &pl, bool masked, char *name, size_t name_bytes)
 {
-    if (pl.halo) halo_kernel_name(pass, pl, masked, name, name_bytes);
+    if (pl.pw) pw_kernel_name(pass, pl, masked, name, name_bytes);
+    else if (pl.halo) halo_kernel_name(pass, pl, masked, name, name_bytes);
     else if (pl.dma) dma_kernel_name(pass, pl, name, name_bytes);
     else if (pl.fast) fast_kernel_name(pass, pl, name, name_bytes);
     else mfma_kernel_name(pass, pl, name, name_bytes);
@@ -216,6 +217,7 @@ void plan_uncached(const ConvGeom &g, int pass, int fv, int fs, GemmPlan *pl, in
     pl->wstrip = false;
     pl->wwin = false;
     pl->win = false;
+    pl->pw = false;
     pl->fused_reduce = false;
     pl->over_generic = false;
     // 1000 + v: variant v with the split reduction fused into the main kernel (pipelined forward / backward-data).  Only a forced
@@ -254,6 +256,7 @@ void plan_uncached(const ConvGeom &g, int pass, int fv, int fs, GemmPlan *pl, in
             flat.over_generic = stand_in.over_generic;
             *pl = flat;
         }
+        if (fs <= 0 && pass != PASS_WGRAD && !(restr & 1) && pointwise_plan(g, pass, *pl, (restr & 2) != 0, &flat)) *pl = flat;
         if (fs <= 0 && pass == PASS_WGRAD && !(restr & RESTR_BASE) && wgrad_window_plan(g, *pl, time, &flat)) *pl = flat;
         return;
     }
@@ -342,7 +345,8 @@ PlanRef plan_entry(const ConvGeom &g, int pass, int restr = 0)
         if (window && n > 0 && fs <= 0) {
             GemmPlan win[2];
             double times[2];
-            const int m = pass == PASS_WGRAD ? wgrad_window_plans(g, win, times) : pixel_window_plans(g, pass, win, times, (restr & RESTR_SAVED) != 0);
+            const int m = pass == PASS_WGRAD ? wgrad_window_plans(g, win, times) : g.R * g.S == 1 ? pointwise_plans(g, pass, (restr & 2) != 0, win, times)
+                                             : pixel_window_plans(g, pass, win, times, (restr & RESTR_SAVED) != 0);
             if (n + m > kTuneCandidates) n = kTuneCandidates - m;   // in the place of the model's last
             for (int i = 0; i < m; ++i) list[n++] = win[i];
         }
@@ -380,6 +384,7 @@ hipError_t launch_plan(const ConvArgs &a, hipStream_t st)
     if (a.plan.wstrip) return wstrip_launch(a, st);
     if (a.plan.wwin) return wwin_launch(a, st);
     if (a.plan.win) return win_launch(a, st);
+    if (a.plan.pw) return pw_launch(a, st);
     if (a.plan.dma) return dma_launch(a, st);
     return a.plan.fast ? fast_launch(a, st) : mfma_launch(a, st);
 }
@@ -513,7 +518,7 @@ size_t round256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 dp_status ensure_init()
 {
-    std::call_once(g_init_once, [] { g_init_err = mfma_init(); if (g_init_err == hipSuccess) g_init_err = fast_init(); if (g_init_err == hipSuccess) g_init_err = dma_init(); if (g_init_err == hipSuccess) g_init_err = halo_init(); if (g_init_err == hipSuccess) g_init_err = wstrip_init(); if (g_init_err == hipSuccess) g_init_err = wwin_init(); if (g_init_err == hipSuccess) g_init_err = win_init(); });
+    std::call_once(g_init_once, [] { g_init_err = mfma_init(); if (g_init_err == hipSuccess) g_init_err = fast_init(); if (g_init_err == hipSuccess) g_init_err = dma_init(); if (g_init_err == hipSuccess) g_init_err = halo_init(); if (g_init_err == hipSuccess) g_init_err = wstrip_init(); if (g_init_err == hipSuccess) g_init_err = wwin_init(); if (g_init_err == hipSuccess) g_init_err = win_init(); if (g_init_err == hipSuccess) g_init_err = pw_init(); });
     if (g_init_err != hipSuccess) return hip_fail(g_init_err, "library initialisation (is a gfx950 device present?)");
     return DP_OK;
 }

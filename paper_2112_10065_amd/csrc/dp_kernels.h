@@ -51,6 +51,8 @@ struct GemmPlan {
     bool fill = false;    // phase, 1x1 filter: only the first phase has tiles, they store the zeros of the others
     bool wstrip = false;  // filter gradient with the x strip shared by the taps of a filter row (conv_wstrip.hip); implies dma
     bool win = false;     // forward / backward-data with one window of pixels for all taps (conv_win.hip); implies dma
+    bool pw = false;      // 1x1 forward / backward-data with stationary weights (conv_pw.hip); implies dma
+    bool pw_gather = false;  // pw, forward: strided or padded
     bool wwin = false;    // filter gradient with one window of x for all taps of a block (conv_wwin.hip); implies dma
     bool row_taps = false;   // wwin: three taps of one filter row per wave
     bool db_wave = false; // input-patch filter gradient: one more wave per block can sum the bias gradient (at most 15 taps)
@@ -92,6 +94,13 @@ void win_kernel_name(int pass, const GemmPlan &pl, bool saved, char *name, size_
 hipError_t win_launch(const ConvArgs &a, hipStream_t st);
 bool win_work(const ConvGeom &g, int pass, int variant, int *rounds, int *rows);   // channel rounds of a block, window rows copied in each
 
+// conv_pw.hip
+hipError_t pw_init();
+bool pw_plan(const ConvGeom &g, int pass, int variant, int force_splits, GemmPlan *pl);
+void pw_kernel_name(int pass, const GemmPlan &pl, bool masked, char *name, size_t name_bytes);   // masked: with the fused input-ReLU mask
+int pw_blocks(const GemmPlan &pl);   // persistent blocks per channel tile
+hipError_t pw_launch(const ConvArgs &a, hipStream_t st);
+
 // conv_wwin.hip
 hipError_t wwin_init();
 bool wwin_plan(const ConvGeom &g, int slots_per_chunk, int force_splits, GemmPlan *pl);
@@ -127,6 +136,7 @@ hipError_t halo_init();
 bool halo_plan(const ConvGeom &g, int pass, int force_variant, int force_splits, GemmPlan *plan);
 hipError_t halo_launch(const ConvArgs &a, hipStream_t st);
 bool dma_plan_is_flat(const GemmPlan &plan);    // the kernels that walk the reduction flat over (tap, channel)
+int dma_plan_groups(const GemmPlan &plan);      // reduction groups of a block (1: the kernel has none)
 bool dma_plan_is_strip(const GemmPlan &plan);   // the pixel-strip forward / backward-data kernels (no fused split reduction)
 bool dma_fused_reduce_fits(int rowsA, int rowsB, int splits);
 bool dma_plan_fuses_reduce(const GemmPlan &plan);   // the splits are summed by the main kernel: no reduction kernel follows
@@ -162,6 +172,9 @@ bool backward_flat_plan(const ConvGeom &g, const GemmPlan &base, double time, in
 bool pixel_window_exists(const ConvGeom &g, int pass);   // some tile of the window kernel runs the layer
 int pixel_window_plans(const ConvGeom &g, int pass, GemmPlan out[2], double times[2], bool saved = false);
 bool pixel_window_plan(const ConvGeom &g, int pass, const GemmPlan &base, double time, bool saved, double mask_us, GemmPlan *out);
+// 1x1 layers by the kernel with stationary weights: its two cheapest plans, and whether it takes the place of `base` (masked: with the fused input-ReLU mask)
+int pointwise_plans(const ConvGeom &g, int pass, bool masked, GemmPlan out[2], double times[2]);
+bool pointwise_plan(const ConvGeom &g, int pass, const GemmPlan &base, bool masked, GemmPlan *out);
 // filter gradient: the window kernel's two cheapest plans, and whether it takes the place of `base`, whose price is `time`
 int wgrad_window_plans(const ConvGeom &g, GemmPlan out[2], double times[2]);
 bool wgrad_window_plan(const ConvGeom &g, const GemmPlan &base, double time, GemmPlan *out);

@@ -93,6 +93,7 @@ bool family_plan(const ConvGeom &g, int pass, int code, int splits, GemmPlan *pl
     pl->wstrip = false;
     pl->wwin = false;
     pl->win = false;
+    pl->pw = false;
     if (code >= 400) return halo_plan(g, pass, code, splits, pl);
     if (code >= 200) return dma_plan(g, pass, code, splits, pl, (restr & 1) != 0);
     return fast_plan(g, pass, code, splits, pl);
@@ -375,6 +376,60 @@ bool pixel_window_plan(const ConvGeom &g, int pass, const GemmPlan &base, double
     const long long tiles = (long long)pl[0].tilesA * pl[0].tilesB;
     const double margin = g.R * g.S < 5 ? 0.75 : tiles > 512 ? 0.78 : tiles > 256 ? 0.85 : 0.92;
     if (t[0] >= margin * (worth + mask_us)) return false;
+    *out = pl[0];
+    return true;
+}
+
+// 1x1 layers by the kernel with stationary weights (conv_pw.hip), us with cold caches, fitted to 768 timings of 560 passes (64 - 512 reduction channels,
+// 16 - 2048 others, 7 - 100 pixels, 1 - 64 samples; median error 5 %, 13 % for nine of ten): a launch, the weights, then the longer of what a block does for
+// its buffers of pixels and what memory takes.  The cheapest tile by it is 1 % slower than the fastest in the mean, 5 % for nineteen of twenty.
+double price_pointwise(const ConvGeom &g, int pass, const GemmPlan &pl, bool masked)
+{
+    const bool fwd = pass == PASS_FWD;
+    const double rows = fwd ? (double)g.N * g.Ho * g.Wo : (double)g.N * g.H * g.W, red = fwd ? g.C : g.K, outs = fwd ? g.K : g.C;
+    const int tc = pl.steps_total, aw = pl.variant == 2 ? 2 : 1, groups = pl.TB / 32, frags = pl.variant == 0 ? groups / 2 : groups, blocks = pw_blocks(pl);
+    const double waves = std::max(1.0, (double)blocks * pl.tilesA / 512.0), buffers = std::ceil((double)pl.tilesB / blocks);
+    const int per_cu = std::min(2, (blocks * pl.tilesA + 255) / 256);
+    const double work = buffers * waves * (0.38 + frags * aw * (0.097 * tc * per_cu + 0.20 + (masked ? 0.21 : 0.0)) + (pl.pw_gather ? 0.35 * groups : 0.0));
+    const double memory = (0.27 * rows * (red + outs * (masked ? 2 : 1)) + 0.022 * rows * red * (pl.tilesA - 1)) * 2e-6;
+    return 5.8 + 0.31 * tc * aw * waves + std::sqrt(std::sqrt(std::pow(work, 4) + std::pow(memory, 4)));
+}
+
+// its two cheapest plans, best first; returns how many there are
+int pointwise_plans(const ConvGeom &g, int pass, bool masked, GemmPlan out[2], double times[2])
+{
+    int n = 0;
+    for (int v = 0; v < 3; ++v) {
+        GemmPlan pl;
+        if (!family_plan(g, pass, 260 + v, 0, &pl)) continue;
+        const double t = price_pointwise(g, pass, pl, masked);
+        if (n == 0 || t < times[0]) {
+            if (n > 0) { out[1] = out[0]; times[1] = times[0]; }
+            out[0] = pl; times[0] = t;
+            n = std::min(n + 1, 2);
+        } else if (n == 1 || t < times[1]) {
+            out[1] = pl; times[1] = t;
+            n = 2;
+        }
+    }
+    return n;
+}
+
+// The stationary-weight kernel in the place of `base`, 560 passes timed both ways (other / this, back to back):
+//   backward-data: 0.96 - 3.2, 1.33 in the middle, whatever the size (with flushed caches 0.93 - 2.0, 1.14)
+//   forward, from 8 MB of pixels on: 0.95 - 2.5, 1.21 in the middle; below, both lie at the floor of a launch or the tiles are faster (0.74 - 1.1).
+//   Up to 32 output channels half a tile and more is idle: 0.91 - 0.96.  Strided, from 16 MB on 0.97 - 1.6; below, the places of its pixels cost 0.77 - 1.0.
+// Forward keeps the order of its sums (forward_flat_plan), which is that of the tiles that take the reduction in one piece.
+bool pointwise_plan(const ConvGeom &g, int pass, const GemmPlan &base, bool masked, GemmPlan *out)
+{
+    GemmPlan pl[2];
+    double t[2];
+    if (pass == PASS_FWD) {
+        const double mb = (double)g.N * g.Ho * g.Wo * (g.C + g.K) * 2e-6;
+        if (g.K < 48 || mb < (g.sh > 1 || g.sw > 1 ? 16.0 : 8.0)) return false;
+        if (base.splits > 1 || dma_plan_groups(base) > 1) return false;
+    } else if ((long long)g.N * g.H * g.W < 256) return false;   // not timed
+    if (pointwise_plans(g, pass, masked, pl, t) == 0) return false;
     *out = pl[0];
     return true;
 }

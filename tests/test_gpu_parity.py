@@ -1567,3 +1567,66 @@ def test_calls_without_a_stream_take_the_current_one(env):
     with torch.cuda.stream(side):
         assert dp._stream(None) == side.cuda_stream != 0
     assert dp._stream(None) == torch.cuda.current_stream().cuda_stream
+
+
+@pytest.mark.parametrize("blocks", [0, 2, 9])
+@pytest.mark.parametrize("variant", [0, 1, 2])
+def test_pointwise_stationary_weights(env, variant, blocks):
+    """1x1 forward (strided and padded too) and unit-stride backward-data with the weights in registers: every reduction length, ragged
+    channels and pixels, fewer tiles than blocks and several per block (rings that turn over), with and without both masks.  The sums
+    run in the order of the unsplit 64x64 tiles, so both results are equal bit for bit."""
+    dp, U, orc = env
+
+    def both(pass_, case, run):
+        dp.dp_set_override(pass_, 207, 1)
+        assert "_dma<64, 64, 64, 2, 2, 3, 1>" in dp.dp_conv2d_kernel_info(case.desc, pass_)[0]
+        want = run()
+        dp.dp_set_override(pass_, 260 + variant, blocks)
+        name = dp.dp_conv2d_kernel_info(case.desc, pass_)[0]
+        got = run()
+        torch.cuda.synchronize()
+        return name, U.to_np(got), U.to_np(want)
+
+    try:
+        for red in range(64, 513, 64):
+            for tag, n, h, w, out, st, pd in (("a", 2, 13, 12, 72, (1, 1), (0, 0)), ("b", 1, 21, 43, 264, (1, 1), (0, 0)), ("c", 3, 1, 1, 8, (1, 1), (0, 0)),
+                                              ("d", 2, 17, 30, 136, (2, 2), (0, 0)), ("e", 1, 9, 11, 64, (2, 1), (1, 2))):
+                tag = f"pw_{red}_{tag}"
+                runs = red <= 256 or variant == 1
+                case = U.ConvCase(tag, n, h, w, red, out, 1, 1, st, pd, bf16=True, bias=True, relu=True)
+                name, got, want = both(0, case, case.run_fwd)
+                assert ("k_pointwise<0, " in name) == runs
+                assert np.array_equal(got, want) or not runs, tag
+                U.assert_bf16_close(got, orc.conv2d_fwd(case.x, case.w, case.b, relu=True, stride=st, pad=pd), tag)
+                case = U.ConvCase(tag, n, h, w, out, red, 1, 1, st, pd, bf16=True, bias=True, relu=True)
+                dp.dp_set_override(0, -1, 0)
+                y = case.run_fwd()
+                for run, masked in ((lambda: case.run_dgrad(y), False), (lambda: case.run_dgrad_relu_in(y), True)):
+                    name, got, want = both(1, case, run)
+                    assert ("k_pointwise<1, " in name) == (runs and st == (1, 1))   # strided and padded backward-data are not this kernel's
+                    assert np.array_equal(got, want) or "k_pointwise" not in name, tag
+                    ref = orc.conv2d_bwd_data(case.dy, case.w, case.x.shape, y_saved=U.to_np(y), stride=st, pad=pd)
+                    U.assert_bf16_close(got, orc.relu_in_backward(ref, case.x) if masked else ref, tag)
+        case = U.ConvCase("pw_f32", 2, 13, 12, 72, 128, 1, 1, (1, 1), (0, 0), bf16=True, bias=True, relu=True, dx_f32=True)
+        assert "k_pointwise" not in dp.dp_conv2d_kernel_info(case.desc, 1)[0]
+    finally:
+        for p in (0, 1):
+            dp.dp_set_override(p, -1, 0)
+
+
+def test_pointwise_choice(env):
+    """The default choice of 1x1 layers: backward-data from 256 pixels on, forward where there is enough to stream and the sums
+    keep their order (the tiles that split the reduction inside a block stay)."""
+    dp, U, orc = env
+    name = lambda d, p: dp.dp_conv2d_kernel_info(d, p)[0]
+    conv = lambda n, h, c, k, st, flags: dp.conv_desc(n, h, h, c, k, 1, 1, (st, st), (0, 0), dp.DP_BF16, flags)
+    for flags in (0, dp.DP_RELU, dp.DP_RELU | dp.DP_RELU_IN):
+        assert "k_pointwise<0, 4, " in name(conv(64, 56, 256, 128, 1, flags), 0)
+        assert "k_pointwise<0, 4, " in name(conv(64, 56, 256, 512, 2, flags), 0) and ", true>" in name(conv(64, 56, 256, 512, 2, flags), 0)
+        assert "k_pointwise" not in name(conv(1, 14, 256, 128, 1, flags), 0)
+        assert "k_pointwise" not in name(conv(64, 56, 1024, 128, 1, flags), 0)
+        assert "k_pointwise<1, 2, " in name(conv(64, 56, 256, 128, 1, flags), 1)
+        assert "k_pointwise" not in name(conv(1, 14, 256, 128, 1, flags), 1)
+        assert "k_pointwise" not in name(conv(64, 56, 256, 512, 2, flags), 1)
+        assert "k_pointwise" not in name(conv(64, 56, 256, 128, 1, flags | dp.DP_DX_F32), 1)
+        assert "k_fwd_dma<64, 64, 64, 2, 2, 2, 2>" in name(conv(4, 56, 256, 128, 1, flags), 0)
