@@ -448,268 +448,183 @@ __global__ __launch_bounds__(1024) void k_wgrad_halo(const KArgs p, int tws, int
 }
 
 // ---------------------------------------------------------------------------------------
-// The 3x3 form of the kernel above with all nine taps in ONE wave.  With a wave per tap every wave reads
-// the same dy fragments and one x fragment per matrix instruction: 1 KB of LDS reads per matrix
-// instruction, which is the LDS port's whole bandwidth at the matrix cores' full rate, and ten waves sit
-// 3-3-2-2 on the SIMDs.  Here a block has four waves, one per SIMD: wave (pg, ch) takes every second
-// 16-pixel slice of the tile (pixel group pg) and c_in half ch for all 64 output channels and all nine
-// taps (18 accumulator tiles, 288 registers): per slice it reads the two dy fragments once and one x
-// fragment per tap, 11 fragments for 18 matrix instructions (0.61 KB each), and the four SIMDs carry
-// the same load.  The (slice, tap) pairs form one stream of items; the transpose reads of item i+4 are
-// issued before the matrix instructions of item i (ring of six x fragments, two dy fragment pairs; at
-// most 14 reads in flight, the counter holds 15).  The two pixel groups' sums meet in LDS once, at the
-// end of the kernel.  The bias gradient (dy x ones) rides in the ch = 0 waves, two more matrix
-// instructions per slice.  Tile walk, LDS layout, copies and the per-block partial are the kernel's above.
+// The 3x3 form of the kernel above with all nine taps in ONE wave.  A block has eight waves, two per SIMD: wave (pg, kh, ch) takes rows
+// 4 pg .. 4 pg + 3 of an 8 x 16 pixel tile, half kh of the 64 output channels and half ch of the input channels, for all nine taps
+// (nine accumulator tiles, 144 registers).  A row of the tile is one 16-pixel slice, so the fragment of patch row y shifted by s
+// serves the taps (r, s) of the rows y - r: 18 x fragments and four dy fragments for 36 matrix instructions, and every address is a
+// base of three (one per s) and an immediate.  The reads of fragment i + 4 are issued before the matrix instructions of fragment i.
+// Tiles come through four LDS buffers, three of them on their way; one barrier per tile.  The two row halves' sums meet in LDS once, at the
+// end of the kernel.  The bias gradient (one small matrix instruction per row) rides in the ch = 0 waves.
+// Patch layout: the pixel in column pc has its 64-byte segment sg at sg ^ ((pc >> 1) & 1).
+// What bounds it: memory, 4.6 - 4.9 TB/s of tiles with their halo, and for few tiles the partials (38 MB for 64 x 64 channels).  With one wave per SIMD, two
+// buffers of 16 x 16 pixels and a fragment read per tap it was the one tile in flight and the address arithmetic.  16 x 224 x 224, 64 -> 64 with its reduction, us
+// back to back / with flushed caches: 84 / 96 -> 62 / 88; 28 x 206 x 209, 64 -> 256: 375 / 364 -> 312 / 305; 32 x 112 x 112, 64 -> 128: 75 / 81 -> 57 / 72.
 // ---------------------------------------------------------------------------------------
-// The matrix instructions are pinned (mfma_in_regs) to the accumulation registers or to the vector registers: 18 + 2 accumulator
-// tiles are 320 registers, more than the 256 accumulation registers, and the compiler, left to itself, keeps them all there and
-// copies tiles back and forth around every instruction (six copies per matrix instruction).
-template <int OFF, bool AG> DEVFN void lds_write_f32(unsigned addr, float v)   // AG: the value sits in an accumulation register
-{
-    if constexpr (AG) asm volatile("ds_write_b32 %0, %1 offset:%2" : : "v"(addr), "a"(v), "n"(OFF) : "memory");
-    else asm volatile("ds_write_b32 %0, %1 offset:%2" : : "v"(addr), "v"(v), "n"(OFF) : "memory");
-}
-template <int OFF> DEVFN float lds_read_f32(unsigned addr)
-{
-    float v;
-    asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF));
-    return v;
-}
+constexpr int W9_TH = 8, W9_TW = 16, W9_PW = W9_TW + 2, W9_PP = (W9_TH + 2) * W9_PW, W9_SLOTS = 192;   // patch pixels, and those its copies fill
+constexpr int W9_DY = W9_SLOTS * 128, W9_BUF = W9_DY + W9_TH * W9_TW * 128, W9_NB = 4, W9_CPW = W9_BUF / 1024 / 8;
+static_assert(W9_PP <= W9_SLOTS && W9_CPW * 8 * 1024 == W9_BUF && W9_NB * W9_BUF <= 160 * 1024, "the copies divide evenly over the eight waves");
+constexpr int W9_XCH = 4 * 9 * 4096;   // exchange: nine tiles of each of the four (kh, ch) pairs, then the bias gradient's
+static_assert(W9_XCH + 2 * 64 * 16 <= W9_NB * W9_BUF, "the exchange fits the buffers");
+
+template <int OFF> DEVFN void lds_write_f32x4(unsigned addr, f32x4 v) { asm volatile("ds_write_b128 %0, %1 offset:%2" ::"v"(addr), "v"(v), "n"(OFF) : "memory"); }
 
 template <bool DB>
-__global__ __launch_bounds__(256) void k_wgrad_halo9(const KArgs p, int tws, int tiles_x, int tiles_y, int tiles)
+__global__ __launch_bounds__(512, 2) void k_wgrad_halo9(const KArgs p, int tiles_x, int tiles_y, int tiles)
 {
+#if __HIP_DEVICE_COMPILE__   // the host pass only needs the launch stub
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const ConvGeom &g = p.g;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int pg = wave >> 1, ch = wave & 1;
-    const int TW = 1 << tws, TH = HALO_TB >> tws, PW = TW + 2, PP = (TH + 2) * PW;
+    const int pg = wave >> 2, kh = (wave >> 1) & 1, ch = wave & 1;
     const int a0 = blockIdx.y * 64;
     const unsigned smem_base = lds_offset(smem);
-    __amdgpu_buffer_rsrc_t rdy = make_rsrc(p.dy, (size_t)g.N * g.Ho * g.Wo * g.K * 2);
-    __amdgpu_buffer_rsrc_t rx = make_rsrc(p.x, (size_t)g.N * g.H * g.W * g.C * 2);
-    // Copies of a tile (8 LDS rows each): 44 of the patch, 32 of the dy slice; wave w issues patch copies w, w+4, ... and dy copies
-    // w, w+4, ...  One wave per SIMD has nobody to hide the address arithmetic behind, so everything that does not depend on the
-    // tile is computed once: the byte offset of the lane's 16 bytes relative to the tile's first patch / dy pixel and the pixel's
-    // row and column in the patch / tile (packed; 0xffff rows mark lanes that never copy).  Per tile and copy that leaves two range
-    // checks and an addition, and the copies of the next tile are dealt out over the items of this one.
-    constexpr int NCP = HALO_PP / 8 / 4, NCD = HALO_TB / 8 / 4;
-    static_assert(NCP * 32 == HALO_PP && NCD * 32 == HALO_TB, "the copies divide evenly over the four waves");
-    unsigned xrel[NCP], xrc[NCP], drel[NCD], drc[NCD];
+    const __amdgpu_buffer_rsrc_t rdy = make_rsrc(p.dy, (size_t)g.N * g.Ho * g.Wo * g.K * 2), rx = make_rsrc(p.x, (size_t)g.N * g.H * g.W * 128);
+
+    // Copies of a tile, eight pixels each: 24 of the patch (three per wave), 16 of the dy slice (two per wave).  What does not depend on the tile is
+    // computed once: the byte offset relative to the tile's first pixel, and the pixel's row and column (past the patch, past the channels: row 0xffff).
+    constexpr int NX = W9_SLOTS / 64;
+    unsigned rel[W9_CPW], rc[W9_CPW];
 #pragma unroll
-    for (int c = 0; c < NCP; ++c) {
-        const int pp = (wave + 4 * c) * 8 + (lane >> 3), chunk = (lane & 7) ^ (seg_swz<64>(pp) << 2);
-        const int pr = pp / PW, pc = pp - pr * PW;
-        xrel[c] = (unsigned)((pr * g.W + pc) * 64 + chunk * 8) * 2u;
-        xrc[c] = pp < PP ? (unsigned)(pr << 16 | pc) : 0xffff0000u;
-    }
-#pragma unroll
-    for (int c = 0; c < NCD; ++c) {
-        const int j = (wave + 4 * c) * 8 + (lane >> 3), chunk = (lane & 7) ^ (seg_swz<64>(j) << 2);
-        const int jr = j >> tws, jc = j & (TW - 1);
-        drel[c] = (unsigned)((jr * g.Wo + jc) * g.K + a0 + chunk * 8) * 2u;
-        drc[c] = a0 + chunk * 8 + 8 <= g.K ? (unsigned)(jr << 16 | jc) : 0xffff0000u;
-    }
-    // tile-dependent part, wave-uniform: first patch / dy pixel of the tile as byte offsets (the patch origin may lie outside the
-    // image: the sum wraps, and wraps back for every pixel that passes the range checks), and the tile's position
-    int nt_p0 = 0, nt_q0 = 0;
-    unsigned nt_xbase = 0, nt_dbase = 0, nt_lds = 0;
-    auto set_tile = [&](int tile, int buf) {
-        const int n = tile / (tiles_x * tiles_y), trem = tile - n * (tiles_x * tiles_y), ty = trem / tiles_x, tx = trem - ty * tiles_x;
-        nt_p0 = ty * TH; nt_q0 = tx * TW;
-        nt_xbase = (unsigned)(((n * g.H + nt_p0 - g.ph) * g.W + nt_q0 - g.pw) * 64) * 2u;
-        nt_dbase = (unsigned)(((n * g.Ho + nt_p0) * g.Wo + nt_q0) * g.K) * 2u;
-        nt_lds = smem_base + buf * WH_BUF;
-    };
-    auto issue_copy = [&](int c) {   // c: 0 .. NCP-1 patch copies, then NCD dy copies (compile-time)
-        if (c < NCP) {
-            const int ih = nt_p0 - g.ph + (int)(xrc[c] >> 16), iw = nt_q0 - g.pw + (int)(xrc[c] & 0xffffu);
-            const bool ok = (unsigned)ih < (unsigned)g.H && (unsigned)iw < (unsigned)g.W;
-            dma16(rx, nt_lds + (wave + 4 * c) * 1024, ok ? nt_xbase + xrel[c] : OOR);
+    for (int c = 0; c < W9_CPW; ++c) {
+        const int px = ((c < NX ? c : c - NX) * 8 + wave) * 8 + (lane >> 3);
+        if (c < NX) {
+            const int pr = px / W9_PW, pc = px - pr * W9_PW;
+            rel[c] = (unsigned)(pr * g.W + pc) * 128u + ((unsigned)((lane & 7) ^ (((pc >> 1) & 1) << 2)) << 4);
+            rc[c] = px < W9_PP ? (unsigned)(pr << 16 | pc) : 0xffff0000u;
         } else {
-            const int d = c - NCP;
-            const bool ok = nt_p0 + (int)(drc[d] >> 16) < g.Ho && nt_q0 + (int)(drc[d] & 0xffffu) < g.Wo;
-            dma16(rdy, nt_lds + HALO_PP * 128 + (wave + 4 * d) * 1024, ok ? nt_dbase + drel[d] : OOR);
+            const int pr = px / W9_TW, pc = px % W9_TW, k = a0 + ((lane & 7) ^ (((pc >> 1) & 1) << 2)) * 8;
+            rel[c] = ((unsigned)(pr * g.Wo + pc) * (unsigned)g.K + k) * 2u;
+            rc[c] = k + 8 <= g.K ? (unsigned)(pr << 16 | pc) : 0xffff0000u;
         }
-    };
-
-    f32x16 acc[9][2];   // [tap][c_out half]
-#pragma unroll
-    for (int t = 0; t < 9; ++t)
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[t][i][v] = 0.f;
-    f32x16 accdb[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) accdb[i][v] = 0.f;
-    const bool do_db = DB && ch == 0;   // wave-uniform
-    const u32x4 ones = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};   // bf16 1.0 in every element
-
-    // transpose-read lane roles: reduction row tl (+4 for the second read), operand columns cl .. cl+3
-    const int i16 = lane & 15, tl = (lane >> 5) * 8 + (i16 >> 2), cl = ((lane >> 4) & 1) * 16 + (i16 & 3) * 4;
-    unsigned a_lane[2];   // dy: row tl of slice 0, column half i; later slices add 16 rows = 2048 bytes
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int col = i * 32 + cl;
-        a_lane[i] = HALO_PP * 128 + tl * 128 + ((((col >> 5) ^ seg_swz<64>(tl)) << 6) | ((col & 31) << 1));
     }
-    const unsigned x_lane = (unsigned)(ch << 6) | (unsigned)(cl << 1);   // segment ch, columns cl .. cl+3 (the segment bit is swizzled per row)
-    int toff[9];   // patch pixels between tap (0,0) and tap t: wave-uniform
-#pragma unroll
-    for (int t = 0; t < 9; ++t) toff[t] = (t / 3) * PW + (t % 3);
-
-    u32x2 xlo[6], xhi[6], dlo[2][2], dhi[2][2];
-    // q: index of this wave's slice (slice pg + 2q of the tile); reads of one item: the x fragment of tap t of that slice
-    auto read_dy = [&](unsigned base, int q, int buf) {
-        const unsigned off = base + (unsigned)(pg + 2 * q) * 2048u;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            dlo[buf][i] = lds_read_tr<0>(off + a_lane[i]);
-            dhi[buf][i] = lds_read_tr<4 * 128>(off + a_lane[i]);
-        }
+    // the patch origin may lie outside the image: the offset wraps, and wraps back for every pixel that passes the range checks
+    struct Tile { int p0, q0; unsigned x, d; };
+    auto place = [&](int t) {
+        const int n = t / (tiles_x * tiles_y), rem = t - n * (tiles_x * tiles_y), ty = rem / tiles_x, p0 = ty * W9_TH, q0 = (rem - ty * tiles_x) * W9_TW;
+        return Tile{p0, q0, (unsigned)((n * g.H + p0 - g.ph) * g.W + q0 - g.pw) * 128u, (unsigned)((n * g.Ho + p0) * g.Wo + q0) * (unsigned)g.K * 2u};
     };
-    int tlv = tl;   // the lane's reduction row, made opaque once per slice: the fragment addresses are a few vector instructions per item,
-                    // and computed per item they cost no registers, whereas the compiler would hoist all 72 of a tile (and spill)
-    auto read_x = [&](unsigned base, int q, int t, int slot) {
-        const int j = (pg + 2 * q) * 16 + tlv;
-        const unsigned pp = (unsigned)((j >> tws) * PW + (j & (TW - 1)) + toff[t]);
-        const unsigned addr = base + (pp << 7) + (x_lane ^ ((pp & 2u) << 5));
-        xlo[slot] = lds_read_tr<0>(addr);
-        xhi[slot] = lds_read_tr<4 * 128>(addr);
+    auto copy_one = [&](const Tile &t, int c, unsigned buf, bool on) {   // a tile past the last fetches nothing
+        if (c < NX) {
+            const int ih = t.p0 - g.ph + (int)(rc[c] >> 16), iw = t.q0 - g.pw + (int)(rc[c] & 0xffffu);
+            const bool row = (unsigned)ih < (unsigned)(on ? g.H : 0), column = (unsigned)iw < (unsigned)g.W;
+            dma16(rx, buf + (c * 8 + wave) * 1024, row & column ? t.x + rel[c] : OOR);
+        } else {
+            const bool row = t.p0 + (int)(rc[c] >> 16) < (on ? g.Ho : 0), column = t.q0 + (int)(rc[c] & 0xffffu) < g.Wo;
+            dma16(rdy, buf + W9_DY + ((c - NX) * 8 + wave) * 1024, row & column ? t.d + rel[c] : OOR);
+        }
     };
 
     const TileWalk tw = tile_walk(tiles);
     int tile = tw.first;
-    if (tile < tw.end) {
-        set_tile(tile, 0);
+    for (int j = 0; j < W9_NB - 1; ++j) {
+        const Tile t = place(tile + j * tw.stride);
 #pragma unroll
-        for (int c = 0; c < NCP + NCD; ++c) issue_copy(c);
+        for (int c = 0; c < W9_CPW; ++c) copy_one(t, c, smem_base + j * W9_BUF, tile + j * tw.stride < tw.end);
     }
+
+    f32x16 acc[9];
+#pragma unroll
+    for (int t = 0; t < 9; ++t)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
+    f32x4 accdb = {0.f, 0.f, 0.f, 0.f};
+    const bool do_db = DB && ch == 0;   // wave-uniform
+    const bf16x8 selector = colsum_selector(lane);
+
+    // transpose-read lane roles: reduction row tl (+4 for the second read), operand columns cl .. cl+3
+    const int i16 = lane & 15, tl = (lane >> 5) * 8 + (i16 >> 2), cl = ((lane >> 4) & 1) * 16 + (i16 & 3) * 4;
+    const unsigned dcol = smem_base + W9_DY + (pg * 4 * W9_TW + tl) * 128 + ((kh ^ ((tl >> 1) & 1)) << 6) + cl * 2;
+    unsigned xcol[3];
+#pragma unroll
+    for (int s = 0; s < 3; ++s) xcol[s] = smem_base + (pg * 4 * W9_PW + tl + s) * 128 + ((ch ^ (((tl + s) >> 1) & 1)) << 6) + cl * 2;
+
     for (int it = 0; tile < tw.end; tile += tw.stride, ++it) {
-        wait_vmcnt<0>();
-        __builtin_amdgcn_s_barrier();   // tile `it` has landed everywhere; the other buffer is no longer read
-        const bool more = tile + tw.stride < tw.end;   // wave-uniform
-        if (more) set_tile(tile + tw.stride, (it + 1) & 1);
-        const unsigned base = smem_base + (it & 1) * WH_BUF;
-        read_dy(base, 0, 0);
+        wait_vmcnt<(W9_NB - 2) * W9_CPW>();
+        __builtin_amdgcn_s_barrier();   // tile `it` has landed everywhere; the buffer of the tile before is no longer read
+        const Tile ahead = place(tile + (W9_NB - 1) * tw.stride);
+        const bool more = tile + (W9_NB - 1) * tw.stride < tw.end;
+        const unsigned buf = it % W9_NB * W9_BUF, abuf = smem_base + (it + W9_NB - 1) % W9_NB * W9_BUF;
+        unsigned xb[3];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) read_x(base, 0, t, t);
-        for_constant<72>([&](auto ic) {   // every index below is a compile-time constant: registers, not indexed arrays
-            constexpr int i = decltype(ic)::value;
-            // reads of item i+4; past the tile's end the stream re-reads the last slice (never multiplied)
-            constexpr int j = i + 4, jq = j < 72 ? j / 9 : 7, jt = j % 9;
-            if constexpr (jt == 0) {
-                asm volatile("" : "+v"(tlv));
-                read_dy(base, jq, (j / 9) & 1);
-            }
-            read_x(base, jq, jt, j % 6);
-            // reads issued after item i's own: items i+1 .. i+4, two each, four more where a slice begins
-            constexpr int ti = i % 9;
-            if constexpr (ti >= 5) asm volatile("s_waitcnt lgkmcnt(12)");
-            else asm volatile("s_waitcnt lgkmcnt(8)");
-            constexpr int s6 = i % 6, db = (i / 9) & 1;
-            asm volatile("" : "+v"(xlo[s6])); asm volatile("" : "+v"(xhi[s6]));
+        for (int s = 0; s < 3; ++s) xb[s] = xcol[s] + buf;
+        const unsigned db = dcol + buf;
+        constexpr int DEPTH = 4;
+        u32x2 xlo[DEPTH + 1], xhi[DEPTH + 1], dlo[4], dhi[4];
+        // item i: the x fragment of patch row i / 3 (of this wave's six) shifted by i % 3; the dy fragment of row y comes with item 3 y
+        auto read_item = [&](auto I) {
+            constexpr int i = I, y = i / 3, s = i % 3;
+            if constexpr (s == 0 && y < 4) { dlo[y] = lds_read_tr<y * W9_TW * 128>(db); dhi[y] = lds_read_tr<y * W9_TW * 128 + 512>(db); }
+            xlo[i % (DEPTH + 1)] = lds_read_tr<y * W9_PW * 128>(xb[s]);
+            xhi[i % (DEPTH + 1)] = lds_read_tr<y * W9_PW * 128 + 512>(xb[s]);
+        };
+        for_constant<DEPTH>([&](auto I) { read_item(I); });
+        for_constant<18>([&](auto I) {
+            constexpr int i = I, y = i / 3, s = i % 3, sl = i % (DEPTH + 1), last = i + DEPTH < 17 ? i + DEPTH : 17;
+            // reads issued after item i's own: two per later item, two more where a row of dy begins
+            constexpr int rows = (last < 9 ? last / 3 : 3) - (i < 9 ? i / 3 : 3);
+            if constexpr (i + DEPTH < 18) read_item(std::integral_constant<int, i + DEPTH>{});
+            asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(2 * (last - i) + 2 * rows));
+            asm volatile("" : "+v"(xlo[sl])); asm volatile("" : "+v"(xhi[sl]));
+            if constexpr (s == 0 && y < 4) { asm volatile("" : "+v"(dlo[y])); asm volatile("" : "+v"(dhi[y])); }
+            const bf16x8 bv = __builtin_bit_cast(bf16x8, u32x4{xlo[sl].x, xlo[sl].y, xhi[sl].x, xhi[sl].y});
+            for_constant<3>([&](auto R) {
+                constexpr int r = R, q = y - r;
+                if constexpr (q >= 0 && q < 4) {
+                    const bf16x8 av = __builtin_bit_cast(bf16x8, u32x4{dlo[q].x, dlo[q].y, dhi[q].x, dhi[q].y});
+                    acc[r * 3 + s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc[r * 3 + s], 0, 0, 0);
+                    if constexpr (DB && r == 0 && s == 0)
+                        if (do_db) accdb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, selector, accdb, 0, 0, 0);
+                }
+            });
+            if constexpr (i % 3 == 1 && i / 3 < W9_CPW) copy_one(ahead, i / 3, abuf, more);
+        });
+    }
+    // Wave pg = 0 finishes taps 0 - 4 and its partner pg = 1 taps 5 - 8; each leaves the other's tiles in LDS, sixteen values of a lane as four
+    // vectors.  Accumulator element v of lane l: row 8*(v/4) + 4*(l/32) + v%4, column l%32.
+    wait_vmcnt<0>();
+    __syncthreads();
+    const int pair = kh * 2 + ch;
+    const unsigned xch = smem_base + pair * (9 * 4096) + lane * 16;
+    const unsigned dxch = smem_base + W9_XCH + (kh * 64 + lane) * 16;
+    for_constant<9>([&](auto T) {
+        constexpr int t = T;
+        if ((t < 5) != (pg == 0))
+            for_constant<4>([&](auto V) {
+                constexpr int v = V;
+                lds_write_f32x4<t * 4096 + v * 1024>(xch, f32x4{acc[t][4 * v], acc[t][4 * v + 1], acc[t][4 * v + 2], acc[t][4 * v + 3]});
+            });
+    });
+    if (do_db && pg == 1) lds_write_f32x4<0>(dxch, accdb);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __syncthreads();
+    float *out = p.partial + ((size_t)blockIdx.x * p.rowsA + a0 + kh * 32) * 576 + ch * 32 + (lane & 31);
+    for_constant<9>([&](auto T) {
+        constexpr int t = T;
+        if ((t < 5) == (pg == 0)) {
+            u32x4 o[4];
+            for_constant<4>([&](auto V) { o[V] = lds_read16<t * 4096 + V * 1024>(xch); });
+            asm volatile("s_waitcnt lgkmcnt(0)");
 #pragma unroll
-            for (int k = 0; k < 2; ++k) { asm volatile("" : "+v"(dlo[db][k])); asm volatile("" : "+v"(dhi[db][k])); }
-            const u32x4 bv = {xlo[s6].x, xlo[s6].y, xhi[s6].x, xhi[s6].y};
+            for (int v = 0; v < 4; ++v) {
+                asm volatile("" : "+v"(o[v]));
+                const f32x4 of = __builtin_bit_cast(f32x4, o[v]);
+                const float sums[4] = {acc[t][4 * v] + of.x, acc[t][4 * v + 1] + of.y, acc[t][4 * v + 2] + of.z, acc[t][4 * v + 3] + of.w};
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const u32x4 av = {dlo[db][k].x, dlo[db][k].y, dhi[db][k].x, dhi[db][k].y};
-                if constexpr (ti < 8) mfma_in_regs<true>(acc[ti][k], av, bv);    // taps 0-7: the 256 accumulation registers
-                else mfma_in_regs<false>(acc[ti][k], av, bv);                    // tap 8 and the bias gradient: vector registers
-            }
-            if constexpr (ti == 0) {
-                if (do_db) {
-#pragma unroll
-                    for (int k = 0; k < 2; ++k) {
-                        const u32x4 av = {dlo[db][k].x, dlo[db][k].y, dhi[db][k].x, dhi[db][k].y};
-                        mfma_in_regs<false>(accdb[k], av, ones);
-                    }
+                for (int e = 0; e < 4; ++e) {
+                    const int row = 8 * v + 4 * (lane >> 5) + e;
+                    if (a0 + kh * 32 + row < p.rowsA) out[(size_t)row * 576 + t * 64] = sums[e];
                 }
             }
-            // one copy of the next tile after each of the first 19 items: memory latency under load is a good part of a tile's time
-            // (issued after every second item: 170 us instead of 162 for conv1_2 at batch 32; two per item: no faster)
-            if constexpr (i < NCP + NCD) { if (more) issue_copy(i); }
-        });
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the stream's reads past the end have returned,
-        // and their registers were not free for anything else until now
-#pragma unroll
-        for (int s = 0; s < 6; ++s) { asm volatile("" : "+v"(xlo[s])); asm volatile("" : "+v"(xhi[s])); }
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            asm volatile("" : "+v"(dlo[0][k])); asm volatile("" : "+v"(dhi[0][k]));
-            asm volatile("" : "+v"(dlo[1][k])); asm volatile("" : "+v"(dhi[1][k]));
         }
-    }
-    // the last matrix instructions have written their results before anything reads them (16 passes of 4 clocks)
-    asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
-
-    // Epilogue, one round per half of the 64 output channels (nine accumulator tiles and one bias-gradient tile per wave): pixel
-    // group 1 puts its tiles into an exchange area (lane-major: no bank conflicts), pixel group 0 adds its own and writes the sums in
-    // the partial's layout [32 c_out][9 taps x 64 c_in] into the result area, and all four waves copy that out, 16 bytes per lane and
-    // whole rows at a time.  The sums never go back into the accumulators (with all 320 of them live, adding in place made the
-    // compiler spill accumulators; LDS float atomics instead of the exchange measured 30 us slower per block; storing from registers,
-    // 4 bytes per lane with an address pair per store, spilled too).  The two areas (80 KB + 72 KB) are the 152 KB the tile buffers
-    // held; they swap ends between the rounds.  Accumulator element v of lane l: row 8*(v/4) + 4*(l/32) + v%4, column l%32.
-    constexpr int kXchBytes = 2 * 10 * 16 * 64 * 4, kResBytes = 32 * 576 * 4;
-    static_assert(kXchBytes + kResBytes <= 2 * WH_BUF, "exchange and result areas fit in the two tile buffers");
-    // The LDS traffic of the exchange is inline assembly: volatile statements keep their order, so at most one tile's values are in
-    // flight and the register allocator has nothing to spill.
-    for_constant<2>([&](auto ic) {
-        constexpr int i = decltype(ic)::value;
-        const unsigned xaddr = smem_base + (i == 0 ? kResBytes : 0) + ch * (10 * 16 * 256) + lane * 4;   // this lane's column of the exchange area
-        float *res = reinterpret_cast<float *>(smem + (i == 0 ? 0 : kXchBytes));
-        const unsigned raddr = smem_base + (i == 0 ? 0 : kXchBytes) + (unsigned)((4 * (lane >> 5)) * 576 + ch * 32 + (lane & 31)) * 4u;
-        __syncthreads();   // round 0: every wave is past its last tile; round 1: the first half has been copied out
-        if (pg == 1) {
-            for_constant<10>([&](auto fc) {
-                constexpr int f = decltype(fc)::value;
-                const f32x16 &src = f < 9 ? acc[f < 9 ? f : 0][i] : accdb[i];
-                for_constant<16>([&](auto vc) {
-                    constexpr int v = decltype(vc)::value;
-                    lds_write_f32<(f * 16 + v) * 256, (f < 8)>(xaddr, src[v]);   // taps 0-7 straight from the accumulation registers
-                });
-            });
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        }
-        __syncthreads();
-        if (pg == 0) {
-            for_constant<10>([&](auto fc) {
-                constexpr int f = decltype(fc)::value;
-                if (f == 9 && !(do_db && p.dbp != nullptr)) return;
-                const f32x16 &mine = f < 9 ? acc[f < 9 ? f : 0][i] : accdb[i];
-                f32x16 sum;
-                for_constant<2>([&](auto hc) {   // eight values at a time (the counter of LDS operations in flight holds 15)
-                    constexpr int h = decltype(hc)::value;
-                    float tv[8];
-                    for_constant<8>([&](auto vc) {
-                        constexpr int w = decltype(vc)::value;
-                        tv[w] = lds_read_f32<(f * 16 + h * 8 + w) * 256>(xaddr);
-                    });
-                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                    for_constant<8>([&](auto vc) {
-                        constexpr int w = decltype(vc)::value, v = h * 8 + w;
-                        asm volatile("" : "+v"(tv[w]));
-                        float mv = mine[v];
-                        if (f < 8) asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(mv) : "a"(mine[v]));   // in order: read early, these get spilled
-                        sum[v] = mv + tv[w];
-                        if (f < 9) lds_write_f32<((8 * (v >> 2) + (v & 3)) * 576 + (f < 9 ? f : 0) * 64) * 4, false>(raddr, sum[v]);
-                    });
-                });
-                if (f == 9) store_db_fragment(sum, p.dbp + (size_t)blockIdx.x * p.rowsA, a0 + i * 32, p.rowsA, lane);
-            });
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        }
-        __syncthreads();
-        // partial[block][c_out][tap][c_in]: rows a0 + 32 i .. + 31 of it, 144 chunks of 16 bytes per row
-        float *out = p.partial + ((size_t)blockIdx.x * p.rowsA + a0 + 32 * i) * 576;
-        const int rows = min(32, p.rowsA - a0 - 32 * i);
-        for (int c = tid; c < rows * 144; c += 256)
-            *reinterpret_cast<f32x4 *>(out + (size_t)c * 4) = *reinterpret_cast<const f32x4 *>(res + c * 4);
     });
+    if (do_db && pg == 0 && p.dbp != nullptr) {
+        const f32x4 o = __builtin_bit_cast(f32x4, lds_read16<0>(dxch));
+        asm volatile("s_waitcnt lgkmcnt(0)");
+        u32x4 ov = __builtin_bit_cast(u32x4, o);
+        asm volatile("" : "+v"(ov));
+        store_colsum_fragment(accdb + __builtin_bit_cast(f32x4, ov), p.dbp + (size_t)blockIdx.x * p.rowsA, a0 + kh * 32, p.rowsA, lane);
+    }
+#endif
 }
 
 // ---------------------------------------------------------------------------------------
@@ -998,9 +913,9 @@ hipError_t halo_init()
     {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_wgrad_halo), hipFuncAttributeMaxDynamicSharedMemorySize, 2 * WH_BUF);
         if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_wgrad_halo9<true>), hipFuncAttributeMaxDynamicSharedMemorySize, 2 * WH_BUF);
+            e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_wgrad_halo9<true>), hipFuncAttributeMaxDynamicSharedMemorySize, W9_NB * W9_BUF);
         if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_wgrad_halo9<false>), hipFuncAttributeMaxDynamicSharedMemorySize, 2 * WH_BUF);
+            e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_wgrad_halo9<false>), hipFuncAttributeMaxDynamicSharedMemorySize, W9_NB * W9_BUF);
         if (e != hipSuccess) return e;
     }
     {
@@ -1026,20 +941,21 @@ bool halo_plan(const ConvGeom &g, int pass, int force_variant, int force_splits,
     if (pass == PASS_WGRAD) {   // 410: input-patch filter gradient, a wave per tap; 411: 3x3, all taps per wave; force_splits = number of persistent blocks
         if ((force_variant != 410 && force_variant != 411) || g.sh != 1 || g.sw != 1 || g.C != 64 || (g.K % 8) != 0 || g.R * g.S > 16) return false;
         if (force_variant == 411 && (g.R != 3 || g.S != 3)) return false;
-        const int tws = halo_tws(g.Ho, g.Wo), tw = 1 << tws, th = HALO_TB >> tws;
-        if ((th + g.R - 1) * (tw + g.S - 1) > HALO_PP) return false;
+        const bool nine = force_variant == 411;
+        const int tws = halo_tws(g.Ho, g.Wo), tw = nine ? W9_TW : 1 << tws, th = nine ? W9_TH : HALO_TB >> tws, tb = tw * th;
+        if (!nine && (th + g.R - 1) * (tw + g.S - 1) > HALO_PP) return false;
         const long long tiles = (long long)g.N * ((g.Ho + th - 1) / th) * ((g.Wo + tw - 1) / tw);
         const int ktiles = (g.K + 63) / 64;
         int blocks = force_splits > 1 ? force_splits : 256 / ktiles;   // default: one persistent block per CU
         if (blocks > tiles) blocks = (int)tiles;
         if (blocks < 2) return false;   // the split-reduce kernel writes the result
         pl->variant = force_variant - 400;
-        pl->db_wave = force_variant == 411 || g.R * g.S <= 15;   // 16 waves per block at most; the nine-tap kernel sums it in its own waves
+        pl->db_wave = nine || g.R * g.S <= 15;   // 16 waves per block at most; the nine-tap kernel sums it in its own waves
         pl->fast = true; pl->dma = true; pl->halo = true;
         pl->TA = 64; pl->TB = 64 * g.R * g.S; pl->BK = 16; pl->vecA = pl->vecB = true;
         pl->tilesA = ktiles; pl->tilesB = 1;
-        pl->steps_total = (int)tiles * (HALO_TB / 16);
-        pl->steps_per_split = (int)((tiles + blocks - 1) / blocks) * (HALO_TB / 16);
+        pl->steps_total = (int)tiles * (tb / 16);
+        pl->steps_per_split = (int)((tiles + blocks - 1) / blocks) * (tb / 16);
         pl->splits = blocks;
         return true;
     }
@@ -1106,10 +1022,10 @@ hipError_t halo_launch(const ConvArgs &a, hipStream_t st)
         const int tws = halo_tws(g.Ho, g.Wo), tw = 1 << tws, th = HALO_TB >> tws;
         const int tiles_x = (g.Wo + tw - 1) / tw, tiles_y = (g.Ho + th - 1) / th;
         if (a.plan.variant == 11) {
-            void (*kern)(const KArgs, int, int, int, int) = k_wgrad_halo9<false>;
+            void (*kern)(const KArgs, int, int, int) = k_wgrad_halo9<false>;
             if (db) kern = k_wgrad_halo9<true>;
-            hipLaunchKernelGGL(kern, dim3((unsigned)a.plan.splits, (unsigned)a.plan.tilesA), dim3(256), 2 * WH_BUF, st, p, tws, tiles_x, tiles_y,
-                               g.N * tiles_x * tiles_y);
+            const int nx = (g.Wo + W9_TW - 1) / W9_TW, ny = (g.Ho + W9_TH - 1) / W9_TH;
+            hipLaunchKernelGGL(kern, dim3((unsigned)a.plan.splits, (unsigned)a.plan.tilesA), dim3(512), W9_NB * W9_BUF, st, p, nx, ny, g.N * nx * ny);
         } else
             hipLaunchKernelGGL(k_wgrad_halo, dim3((unsigned)a.plan.splits, (unsigned)a.plan.tilesA), dim3(64 * (g.R * g.S + (db ? 1 : 0))), 2 * WH_BUF, st, p, tws,
                                tiles_x, tiles_y, g.N * tiles_x * tiles_y);

@@ -79,7 +79,7 @@ const Candidate kWg[] = {
     {312, 1, 2.90f, 7.0f},   // 256x256x64, 8 waves
     {316, 1, 1.60f, 9.0f},   // 3x3 stride 1: 256 x (3 taps x 64 channels), x strip shared by the taps, padded pixel slots
     {410, 1, 0.13f, 6.0f},   // input patch in LDS, persistent blocks (64 input channels, stride 1); a step = 16 pixels
-    {411, 1, 0.10f, 6.0f},   // the same for 3x3 filters with all nine taps in one wave (four waves per block)
+    {411, 1, 0.10f, 8.0f},   // the same for 3x3 filters with all nine taps in one wave
     {100, 3, 1.30f, 4.0f},
     {101, 3, 1.00f, 3.5f},
     {102, 3, 1.00f, 3.5f},
@@ -459,16 +459,36 @@ int wgrad_window_plans(const ConvGeom &g, GemmPlan out[2], double times[2])
     return n;
 }
 
+// The nine-tap filter gradient of 64-channel layers (conv_halo.hip) by its own price, whole passes in us: fitted to 125 timings (median error 6 %, 11 % for nine
+// of ten).  False: another layer.
+bool nine_tap_plan(const ConvGeom &g, GemmPlan *out, double *time)
+{
+    bool found = false;
+    for (int blocks : {256, 192, 128}) {
+        GemmPlan pl;
+        const int per_tile = std::max(blocks / ((g.K + 63) / 64), 2);
+        if (!family_plan(g, PASS_WGRAD, 411, per_tile, &pl)) return found;
+        const double t = 10.1 + 0.173 * pl.steps_per_split + 1.26e-6 * (pl.splits + 1) * g.K * g.R * g.S * g.C;
+        if (!found || t < *time) { *out = pl; *time = t; found = true; }
+    }
+    return found;
+}
+
 // Filter gradient: the window kernel in the place of `base` (price `time`) where its price lies that far below.  The factors are what the
 // other kernels' prices are worth on 230 layers timed both ways: pipelined tiles take 0.7 - 1.1 of their price split and down to 0.6 unsplit,
-// register-staged ones 1.1 - 1.6, the input-patch kernels 1.4 - 2.2.  Taken on 48 of 175 layers that both run: 0.98 - 2.0 times as fast.
+// register-staged ones 1.1 - 1.6, the input-patch kernel with a wave per tap 1.4 - 2.2.  Taken on 48 of 175 layers that both run: 0.98 - 2.0 times as fast.
 bool wgrad_window_plan(const ConvGeom &g, const GemmPlan &base, double time, GemmPlan *out)
 {
     GemmPlan pl[2];
     double t[2];
     if (!base.fast || wgrad_window_plans(g, pl, t) == 0) return false;
     const double worth = !pl[0].row_taps ? 0.8 : base.halo ? 1.35 : !base.dma ? 1.0 : base.splits == 1 ? 0.75 : 0.92;
-    if (t[0] >= worth * time) return false;
+    const bool nine = base.halo && base.variant == 11;
+    if (!nine && t[0] >= worth * time) return false;
+    // Both by prices of their own.  With flushed caches the window kernel loses 10 - 50 % more (40 layers nearer than that to each other back to back)
+    GemmPlan nine_pl;
+    double nine_time;
+    if (nine_tap_plan(g, &nine_pl, &nine_time) && t[0] >= 0.96 * nine_time) { *out = nine_pl; return true; }
     *out = pl[0];
     return true;
 }
