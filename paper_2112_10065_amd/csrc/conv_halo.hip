@@ -646,30 +646,37 @@ __global__ __launch_bounds__(512, 2) void k_wgrad_halo9(const KArgs p, int tiles
 // instructions and LDS reads alone).  The faster of all kernels from a few tiles on (180 layers of 32 - 450 channels, 7 - 224 pixels: 0.95 - 1.4
 // times the best other; below 100 tiles 5.5 - 6.2 us like the others).
 // ---------------------------------------------------------------------------------------
+// 128 reduction channels (RH = 2), us back to back / with flushed caches, the best other kernel -> this one: 32 x 112 x 112, 128 -> 128 forward 145 / 156 ->
+// 107 / 115 (1.1 PFLOP/s), masked backward-data 159 / 170 -> 114 / 132; 64 <- 128 93 / 128 -> 59 / 75, at 8 samples 41 / 53 -> 23 / 30, at 2 12.7 / 16.7 -> 8.4 / 12.8.
+// 240 passes: 1.06 - 1.27 times the best other in the middle from half a round of tiles on, 0.8 below a fifth (the weights are its fixed cost).
 constexpr int WS_TH = 8, WS_TW = 16, WS_TB = WS_TH * WS_TW, WS_PW = WS_TW + 2, WS_PP = (WS_TH + 2) * WS_PW;
 constexpr int WS_CPW = (WS_PP / 8 + 4) / 4;   // patch copies per wave, eight pixels each
 constexpr int WS_PATCH = 4 * WS_CPW * 1024;   // 24 KiB per patch buffer
-constexpr int WS_LDS = 3 * WS_PATCH + 64 * 4;
-static_assert(WS_PP <= 4 * WS_CPW * 8 && 2 * WS_LDS <= 160 * 1024, "a patch fits its copies, two blocks a CU");
+constexpr int WS_LDS = 3 * WS_PATCH + 64 * 4, WS_LDS2 = 6 * WS_PATCH + 64 * 4;   // one and two blocks of reduction channels
+static_assert(WS_PP <= 4 * WS_CPW * 8 && 2 * WS_LDS <= 160 * 1024 && WS_LDS2 <= 160 * 1024 && 4096 + 2048 <= WS_CPW * 1024, "a patch fits its copies, two blocks a CU");
 static_assert(3 * 8192 <= WS_PATCH && 64 * 64 <= WS_CPW * 1024, "three taps of weights, and a wave's results, fit a patch buffer");
 
 DEVFN void lds_write16(unsigned addr, u32x4 v) { asm volatile("ds_write_b128 %0, %1" ::"v"(addr), "v"(v) : "memory"); }
 
-template <int PASS, bool MASK = false>   // MASK (backward-data): fused backward of the ReLU in front of the layer
-__global__ __launch_bounds__(256, 2) void k_halo_ws(const KArgs p, int tiles_x, int tiles_y, int tiles_all)
+// MASK (backward-data): fused backward of the ReLU in front of the layer.  RH: blocks of 64 reduction channels.  With two of them a block has eight waves and a
+// CU one block: waves 4 - 7 hold the weights of the second 64 channels and multiply the same pixels; each wave hands the sums of one of its two pixel
+// fragments to its partner through LDS (in the share of the patch buffer that the partner refills itself) and finishes the other.
+template <int PASS, bool MASK = false, int RH = 1>
+__global__ __launch_bounds__(256 * RH, 2) void k_halo_ws(const KArgs p, int tiles_x, int tiles_y, int tiles_all)
 {
 #if __HIP_DEVICE_COMPILE__   // the host pass only needs the launch stub
-    constexpr int WS_DEPTH = MASK ? 2 : 3;   // fragment reads run this many 16-channel slices ahead of the matrix cores
+    constexpr int WS_DEPTH = MASK || RH > 1 ? 2 : 3;   // fragment reads run this many 16-channel slices ahead of the matrix cores
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const ConvGeom &g = p.g;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int hc = wave & 1, pg = wave >> 1;   // channel half, pixel group
+    const int hc = wave & 1, pg = (wave >> 1) & 1, rh = RH > 1 ? wave >> 2 : 0, share = wave & 3;   // channel half, pixel group, reduction block
+    constexpr int PATCH = RH * WS_PATCH, PB = RH * 128, NF = RH > 1 ? 1 : 2;   // bytes of a patch buffer and of a pixel; pixel fragments that a wave finishes
     const int a0 = blockIdx.y * 64;
     const int IH = PASS == PASS_FWD ? g.H : g.Ho, IW = PASS == PASS_FWD ? g.W : g.Wo;
     const int OH = PASS == PASS_FWD ? g.Ho : g.H, OW = PASS == PASS_FWD ? g.Wo : g.W;
     const int RSC = 9 * g.C;
     const unsigned smem_base = lds_offset(smem);
-    float *bias_lds = reinterpret_cast<float *>(smem + 3 * WS_PATCH);
+    float *bias_lds = reinterpret_cast<float *>(smem + 3 * PATCH);
     const __amdgpu_buffer_rsrc_t rin = PASS == PASS_FWD ? make_rsrc(p.x, (size_t)g.N * g.H * g.W * g.C * 2)
                                                         : make_rsrc(p.dy, (size_t)g.N * g.Ho * g.Wo * g.K * 2);
     const __amdgpu_buffer_rsrc_t rw = make_rsrc(p.w, (size_t)g.K * RSC * 2);
@@ -681,16 +688,16 @@ __global__ __launch_bounds__(256, 2) void k_halo_ws(const KArgs p, int tiles_x, 
     auto issue_weights = [&](int part, int buf) {
 #pragma unroll
         for (int q = 0; q < 6; ++q) {
-            const int id = wave * 6 + q, st = part * 3 + (id >> 3), row = (id & 7) * 8 + (lane >> 3);
+            const int id = share * 6 + q, st = part * 3 + (id >> 3), row = (id & 7) * 8 + (lane >> 3);
             unsigned voff;
             if (PASS == PASS_FWD) {
                 const int c = (lane & 7) ^ ((row >> 1) & 7);
-                voff = a0 + row < p.rowsA ? ((unsigned)(a0 + row) * RSC + st * 64 + c * 8) * 2u : OOR;
+                voff = a0 + row < p.rowsA ? ((unsigned)(a0 + row) * RSC + (st * RH + rh) * 64 + c * 8) * 2u : OOR;
             } else {
                 const int c = (lane & 7) ^ (seg_swz<64>(row) << 2);
-                voff = a0 + c * 8 < p.rowsA ? ((unsigned)row * RSC + (8 - st) * g.C + a0 + c * 8) * 2u : OOR;
+                voff = a0 + c * 8 < p.rowsA ? ((unsigned)(rh * 64 + row) * RSC + (8 - st) * g.C + a0 + c * 8) * 2u : OOR;
             }
-            dma16(rw, smem_base + buf * WS_PATCH + id * 1024, voff);
+            dma16(rw, smem_base + buf * PATCH + rh * WS_PATCH + id * 1024, voff);
         }
     };
     // patch copies: copy q of a wave fills patch pixels (wave * WS_CPW + q) * 8 .. + 7; the lane's pixel and chunk are fixed, the tile's origin
@@ -698,7 +705,7 @@ __global__ __launch_bounds__(256, 2) void k_halo_ws(const KArgs p, int tiles_x, 
     unsigned pk[WS_CPW];
 #pragma unroll
     for (int q = 0; q < WS_CPW; ++q) {
-        const int id = (wave * WS_CPW + q) * 8 + (lane >> 3), pp = id < WS_PP ? id : lane >> 3, pr = pp / WS_PW, pc = pp - pr * WS_PW;
+        const int id = (share * WS_CPW + q) * 8 + (lane >> 3), pp = id < WS_PP ? id : lane >> 3, pr = pp / WS_PW, pc = pp - pr * WS_PW;
         pk[q] = (unsigned)pr | ((unsigned)pc << 8) | ((unsigned)((lane & 7) ^ ((pc >> 1) & 7)) << 20);
     }
     struct Tile { int n, h, w; };
@@ -712,8 +719,8 @@ __global__ __launch_bounds__(256, 2) void k_halo_ws(const KArgs p, int tiles_x, 
         asm volatile("" : "+v"(v));   // stays packed in the loop
         const int pr = (int)(v & 255u), pc = (int)((v >> 8) & 255u);
         const bool row = (unsigned)(h0 + pr) < (unsigned)(on ? IH : 0), column = (unsigned)(w0 + pc) < (unsigned)IW;
-        const unsigned at = (unsigned)((t.n * IH + h0) * IW + w0) * 128u + (unsigned)(pr * IW + pc) * 128u + (v >> 16);
-        dma16(rin, dst + (wave * WS_CPW + q) * 1024, row & column ? at : OOR);
+        const unsigned at = (unsigned)((t.n * IH + h0) * IW + w0) * (unsigned)PB + (unsigned)(pr * IW + pc) * (unsigned)PB + rh * 128 + (v >> 16);
+        dma16(rin, dst + rh * WS_PATCH + (share * WS_CPW + q) * 1024, row & column ? at : OOR);
     };
 
     const TileWalk tw = tile_walk(tiles_all);
@@ -731,25 +738,26 @@ __global__ __launch_bounds__(256, 2) void k_halo_ws(const KArgs p, int tiles_x, 
     if (PASS == PASS_FWD) {
         const int row = hc * 32 + (lane & 31);
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) wad[ks] = smem_base + WS_PATCH + row * 128 + (((2 * ks + (lane >> 5)) ^ ((row >> 1) & 7)) << 4);
+        for (int ks = 0; ks < 4; ++ks) wad[ks] = smem_base + PATCH + rh * WS_PATCH + row * 128 + (((2 * ks + (lane >> 5)) ^ ((row >> 1) & 7)) << 4);
     } else {
         const int i16 = lane & 15, t = (lane >> 5) * 8 + (i16 >> 2), cl = ((lane >> 4) & 1) * 16 + (i16 & 3) * 4;
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) wad[ks] = smem_base + WS_PATCH + (ks * 16 + t) * 128 + ((hc ^ seg_swz<64>(t)) << 6) + cl * 2;
+        for (int ks = 0; ks < 4; ++ks) wad[ks] = smem_base + PATCH + rh * WS_PATCH + (ks * 16 + t) * 128 + ((hc ^ seg_swz<64>(t)) << 6) + cl * 2;
     }
     for_constant<3>([&](auto PART) {
-        constexpr int part = PART, buf = part == 1 ? WS_PATCH : 0;
+        constexpr int part = PART;
+        constexpr unsigned buf = part == 1 ? PATCH : 0;
         if (part == 2) wait_vmcnt<0>();
         else wait_vmcnt<6 + WS_CPW>();   // younger: the next part and the first patch
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
         for_constant<3>([&](auto J) {
-            constexpr int st = part * 3 + J, off = buf + J * 8192;
+            constexpr int st = part * 3 + J, off = J * 8192;
             u32x2 lo[4], hi[4];
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) {
-                if constexpr (PASS == PASS_FWD) afr[st][ks] = lds_read16<off>(wad[ks]);
-                else { lo[ks] = lds_read_tr<off>(wad[ks]); hi[ks] = lds_read_tr<off + 512>(wad[ks]); }
+                if constexpr (PASS == PASS_FWD) afr[st][ks] = lds_read16<off>(wad[ks] + buf);
+                else { lo[ks] = lds_read_tr<off>(wad[ks] + buf); hi[ks] = lds_read_tr<off + 512>(wad[ks] + buf); }
             }
             asm volatile("s_waitcnt lgkmcnt(0)");
 #pragma unroll
@@ -766,34 +774,37 @@ __global__ __launch_bounds__(256, 2) void k_halo_ws(const KArgs p, int tiles_x, 
         if (part == 0) issue_weights(2, 1);
     });
 #pragma unroll
-    for (int q = 0; q < WS_CPW; ++q) copy_one(next, q, smem_base + WS_PATCH, tile + stride < tiles);
+    for (int q = 0; q < WS_CPW; ++q) copy_one(next, q, smem_base + PATCH, tile + stride < tiles);
 
     // this lane's pixel of fragment 0 in column tap s, slice 0; slices differ in two bits, rows and fragments by immediates
     unsigned col[3];
 #pragma unroll
     for (int s = 0; s < 3; ++s) {
-        const int pc = (lane & 15) + s, pr = pg * 4 + ((lane >> 4) & 1);
-        col[s] = smem_base + (pr * WS_PW + pc) * 128 + (((lane >> 5) ^ ((pc >> 1) & 7)) << 4);
+        const int pc = (lane & 15) + s, pr = pg * 4 + 2 * rh + ((lane >> 4) & 1);   // with two reduction blocks fragment 0 is the one this wave finishes
+        col[s] = smem_base + rh * WS_PATCH + (pr * WS_PW + pc) * 128 + (((lane >> 5) ^ ((pc >> 1) & 7)) << 4);
     }
     // results: written by pixel fragment, read back four lanes to a pixel
-    const unsigned stg = smem_base + wave * WS_CPW * 1024;
+    const unsigned own = smem_base + rh * WS_PATCH + share * WS_CPW * 1024, stg = own + (RH > 1 ? 4096 : 0);
+    const unsigned give = smem_base + (1 - rh) * WS_PATCH + share * WS_CPW * 1024;               // the partner's share
+    const unsigned other = rh == 0 ? 2 * WS_PW * 128 : 0u - 2 * WS_PW * 128;                    // bytes from fragment 0 to fragment 1
     const int wpx = lane & 31, rpx = lane >> 2;
     const unsigned stw = stg + wpx * 64 + ((((lane >> 5)) ^ ((wpx >> 2) & 3)) << 4), str = stg + rpx * 64 + (((lane & 3) ^ ((rpx >> 2) & 3)) << 4);
     const int och = a0 + hc * 32 + (lane & 3) * 8;
     const unsigned bad = lds_offset(bias_lds) + (hc * 32 + 4 * (lane >> 5)) * 4;
 
     for (int it = 0; tile < tiles; tile += stride, ++it) {
-        const unsigned base = (it % 3) * WS_PATCH, nbuf = smem_base + ((it + 2) % 3) * WS_PATCH;   // which tile it - 1 left before the last barrier
+        const unsigned base = (it % 3) * PATCH, nbuf = smem_base + ((it + 2) % 3) * PATCH;   // which tile it - 1 left before the last barrier
         const Tile after = place(tile + 2 * stride);
         const bool more = tile + 2 * stride < tiles;
         // this lane's output vectors: row pg * 4 + i of the tile, pixel lane / 4
-        const int orow = now.h + pg * 4;
+        const int orow = now.h + pg * 4 + 2 * rh;
         unsigned voff = now.w + rpx < OW && och < p.rowsA ? ((unsigned)((now.n * OH + orow) * OW + now.w + rpx) * (unsigned)p.rowsA + och) * 2u : OOR;
         auto at = [&](int i) { return orow + i < OH && voff != OOR ? voff + (unsigned)(i * OW) * (unsigned)p.rowsA * 2u : OOR; };
-        u32x4 mk[4];
+        constexpr int NV = 2 * NF;   // output vectors
+        u32x4 mk[NV];
         if constexpr (MASK) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) mk[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, at(i), 0, 0);
+            for (int i = 0; i < NV; ++i) mk[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, at(i), 0, 0);
             asm volatile("" : "+v"(voff));   // the four offsets are made again for the stores
         }
         unsigned cb[3];
@@ -809,7 +820,8 @@ __global__ __launch_bounds__(256, 2) void k_halo_ws(const KArgs p, int tiles_x, 
             constexpr int st = SL / 4, ks = SL % 4, off = st / 3 * WS_PW * 128;
             const unsigned ad = cb[st % 3] ^ (unsigned)(ks << 5);
             fb[SL % (WS_DEPTH + 1)][0] = lds_read16<off>(ad);
-            fb[SL % (WS_DEPTH + 1)][1] = lds_read16<off + 2 * WS_PW * 128>(ad);
+            if constexpr (RH > 1) fb[SL % (WS_DEPTH + 1)][1] = lds_read16<off>((cb[st % 3] + other) ^ (unsigned)(ks << 5));
+            else fb[SL % (WS_DEPTH + 1)][1] = lds_read16<off + 2 * WS_PW * 128>(ad);
         };
         for_constant<WS_DEPTH>([&](auto SL) { read_b(SL); });
         for_constant<36>([&](auto SL) {
@@ -826,6 +838,28 @@ __global__ __launch_bounds__(256, 2) void k_halo_ws(const KArgs p, int tiles_x, 
         // of the loads after this wave's share of the next patch only the copies above may be outstanding
         wait_vmcnt<WS_CPW>();
         __builtin_amdgcn_s_barrier();   // all shares of the next patch have landed; this tile's buffer has been read
+        if constexpr (RH > 1) {
+            unsigned l16 = lane * 16;
+            asm volatile("" : "+v"(l16));   // made here, not kept
+            // the last matrix instruction has written its result before the stores below, which the compiler does not know, read it (at most 18 wait states)
+            asm volatile("s_nop 15\n\ts_nop 15" : "+v"(acc[1]));
+            const unsigned to = give + base + l16;
+            for_constant<4>([&](auto V) {
+                constexpr int v = V;
+                lds_write16(to + v * 1024, __builtin_bit_cast(u32x4, f32x4{acc[1][4 * v], acc[1][4 * v + 1], acc[1][4 * v + 2], acc[1][4 * v + 3]}));
+            });
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            u32x4 got[4];
+            for_constant<4>([&](auto V) { got[V] = lds_read16<V * 1024>(own + base + l16); });
+            asm volatile("s_waitcnt lgkmcnt(0)");
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                asm volatile("" : "+v"(got[v]));
+                const f32x4 o = __builtin_bit_cast(f32x4, got[v]);
+                acc[0][4 * v] += o.x; acc[0][4 * v + 1] += o.y; acc[0][4 * v + 2] += o.z; acc[0][4 * v + 3] += o.w;
+            }
+        }
         f32x4 bv[4];
         if constexpr (PASS == PASS_FWD) {
             bv[0] = __builtin_bit_cast(f32x4, lds_read16<0>(bad)); bv[1] = __builtin_bit_cast(f32x4, lds_read16<32>(bad));
@@ -837,7 +871,7 @@ __global__ __launch_bounds__(256, 2) void k_halo_ws(const KArgs p, int tiles_x, 
         // accumulator element v of lane l is channel 8*(v/4) + 4*(l/32) + v%4 of pixel l%32 of fragment j; the lanes l and
         // l+32 swap halves of two channel groups, after which each holds 8 consecutive channels of one group
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < NF; ++j)
 #pragma unroll
             for (int gp = 0; gp < 2; ++gp) {
                 unsigned pkd[2][2];   // [group 2gp, 2gp+1][channel pair]
@@ -858,11 +892,11 @@ __global__ __launch_bounds__(256, 2) void k_halo_ws(const KArgs p, int tiles_x, 
                 lds_write16((stw ^ (unsigned)(gp << 5)) + base + j * 2048, u32x4{s0[0], s1[0], s0[1], s1[1]});
             }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        u32x4 o[4];
-        o[0] = lds_read16<0>(str + base); o[1] = lds_read16<1024>(str + base); o[2] = lds_read16<2048>(str + base); o[3] = lds_read16<3072>(str + base);
+        u32x4 o[NV];
+        for_constant<NV>([&](auto I) { o[I] = lds_read16<I * 1024>(str + base); });
         asm volatile("s_waitcnt lgkmcnt(0)");
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < NV; ++i) {
             asm volatile("" : "+v"(o[i]));
             if constexpr (MASK) o[i] = apply_mask(o[i], mk[i]);
             __builtin_amdgcn_raw_buffer_store_b128(o[i], rout, at(i), 0, 0);
@@ -926,6 +960,9 @@ hipError_t halo_init()
             e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_halo_ws<PASS_DGRAD>), hipFuncAttributeMaxDynamicSharedMemorySize, WS_LDS);
         if (e == hipSuccess)
             e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_halo_ws<PASS_DGRAD, true>), hipFuncAttributeMaxDynamicSharedMemorySize, WS_LDS);
+        for (const void *f : {reinterpret_cast<const void *>(&k_halo_ws<PASS_FWD, false, 2>), reinterpret_cast<const void *>(&k_halo_ws<PASS_DGRAD, false, 2>),
+                              reinterpret_cast<const void *>(&k_halo_ws<PASS_DGRAD, true, 2>)})
+            if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, WS_LDS2);
         if (e != hipSuccess) return e;
     }
     for (int pass = 0; pass < 2; ++pass)
@@ -963,19 +1000,19 @@ bool halo_plan(const ConvGeom &g, int pass, int force_variant, int force_splits,
     }
     if (pass != PASS_FWD && pass != PASS_DGRAD) return false;
     pl->blocks = 0;
-    if (force_variant == 404) {   // weights in registers, persistent blocks; force_splits = blocks per 64-row tile
+    if (force_variant == 404 || force_variant == 405) {   // weights in registers, persistent blocks; force_splits = blocks per 64-row tile; 405: 128 reduction channels
         const int red_c = pass == PASS_FWD ? g.C : g.K, rowsA = pass == PASS_FWD ? g.K : g.C;
-        if (g.sh != 1 || g.sw != 1 || g.R != 3 || g.S != 3 || red_c != 64 || (rowsA % 8) != 0) return false;
+        if (g.sh != 1 || g.sw != 1 || g.R != 3 || g.S != 3 || red_c != (force_variant == 404 ? 64 : 128) || (rowsA % 8) != 0) return false;
         if (pass == PASS_DGRAD && (g.ph > 2 || g.pw > 2)) return false;
         const int oh = pass == PASS_FWD ? g.Ho : g.H, ow = pass == PASS_FWD ? g.Wo : g.W;
         const long long tiles = (long long)g.N * ((oh + WS_TH - 1) / WS_TH) * ((ow + WS_TW - 1) / WS_TW);
         if (tiles > 0x7fffff) return false;
-        pl->variant = 4;
+        pl->variant = force_variant - 400;
         pl->fast = true; pl->dma = true; pl->halo = true;
         pl->TA = 64; pl->TB = WS_TB; pl->BK = 64; pl->vecA = pl->vecB = true;
         pl->tilesA = (rowsA + 63) / 64;
         pl->tilesB = (int)tiles;
-        pl->steps_total = pl->steps_per_split = 9;
+        pl->steps_total = pl->steps_per_split = red_c / 64 * 9;
         pl->splits = 1;
         pl->blocks = force_splits > 1 ? force_splits : 0;
         return true;
@@ -1002,7 +1039,10 @@ bool halo_plan(const ConvGeom &g, int pass, int force_variant, int force_splits,
 void halo_kernel_name(int pass, const GemmPlan &pl, bool masked, char *name, size_t name_bytes)
 {
     if (pass == PASS_WGRAD) { snprintf(name, name_bytes, pl.variant == 11 ? "k_wgrad_halo9<true>" : "k_wgrad_halo"); return; }
-    if (pl.variant == 4) { snprintf(name, name_bytes, "k_halo_ws<%d, %s>", pass, pass == PASS_DGRAD && masked ? "true" : "false"); return; }
+    if (pl.variant == 4 || pl.variant == 5) {
+        snprintf(name, name_bytes, pl.variant == 4 ? "k_halo_ws<%d, %s>" : "k_halo_ws<%d, %s, 2>", pass, pass == PASS_DGRAD && masked ? "true" : "false");
+        return;
+    }
     const HaloVariant &h = kHalo[pl.variant];
     snprintf(name, name_bytes, "k_halo<%d, %d, %d, %d, %d>", pass, h.TA, h.WA, h.WB, h.NS);
 }
@@ -1039,22 +1079,25 @@ hipError_t halo_launch(const ConvArgs &a, hipStream_t st)
     const bool fwd = a.pass == PASS_FWD;
     p.rowsA = fwd ? a.g.K : a.g.C;
     p.rowsB = fwd ? a.g.N * a.g.Ho * a.g.Wo : a.g.N * a.g.H * a.g.W;
-    p.red = a.g.R * a.g.S * 64;
+    p.red = a.g.R * a.g.S * (fwd ? a.g.C : a.g.K);
     p.tilesA = a.plan.tilesA; p.tilesB = a.plan.tilesB;
     p.steps_total = a.plan.steps_total; p.steps_per_split = a.plan.steps_per_split; p.splits = 1;
     p.flags = a.flags;
     p.x = a.x; p.w = a.w; p.dy = a.dy; p.ymask = nullptr; p.bias = a.bias; p.out = a.out; p.partial = a.partial;
     const int oh = fwd ? a.g.Ho : a.g.H, ow = fwd ? a.g.Wo : a.g.W;
-    if (a.plan.variant == 4) {
-        int blocks = a.plan.blocks > 0 ? a.plan.blocks : 512 / p.tilesA;   // default: two persistent blocks per CU
+    if (a.plan.variant == 4 || a.plan.variant == 5) {
+        const bool two = a.plan.variant == 5;
+        int blocks = a.plan.blocks > 0 ? a.plan.blocks : (two ? 256 : 512) / p.tilesA;   // default: two persistent blocks per CU, one of eight waves
         if (blocks < 1) blocks = 1;
         if (blocks > p.tilesB) blocks = p.tilesB;
         void (*kern)(const KArgs, int, int, int) = k_halo_ws<PASS_FWD>;
+        if (two) kern = k_halo_ws<PASS_FWD, false, 2>;
         if (!fwd) {
-            if (p.flags & KF_MASK_IN) kern = k_halo_ws<PASS_DGRAD, true>;
-            else kern = k_halo_ws<PASS_DGRAD>;
+            const bool masked = (p.flags & KF_MASK_IN) != 0;
+            if (two) { kern = k_halo_ws<PASS_DGRAD, false, 2>; if (masked) kern = k_halo_ws<PASS_DGRAD, true, 2>; }
+            else { kern = k_halo_ws<PASS_DGRAD>; if (masked) kern = k_halo_ws<PASS_DGRAD, true>; }
         }
-        hipLaunchKernelGGL(kern, dim3((unsigned)blocks, (unsigned)p.tilesA), dim3(256), WS_LDS, st, p,
+        hipLaunchKernelGGL(kern, dim3((unsigned)blocks, (unsigned)p.tilesA), dim3(two ? 512 : 256), two ? WS_LDS2 : WS_LDS, st, p,
                            (ow + WS_TW - 1) / WS_TW, (oh + WS_TH - 1) / WS_TH, p.tilesB);
         dp_trace_main_kernel_done(st);
         return hipGetLastError();

@@ -156,8 +156,12 @@ constexpr unsigned kKnownFlags = DP_BIAS | DP_RELU | DP_DETERMINISTIC | DP_DX_F3
 int dgrad_restr(unsigned flags) { return ((flags & DP_DX_F32) ? 1 : 0) | ((flags & DP_RELU_IN) ? 2 : 0); }
 // A layer whose gradients are masked by its own y keeps the order in which y is summed (forward_flat_plan).  The flags tell such a layer only where it stands
 // alone: in a chain (DP_RELU_IN) the layer behind masks by this y, and its order is the window kernel's.  The measured choice goes by time and keeps
-// no order.  RESTR_ORDER only where there is a window kernel to leave out: other layers have one plan, measured once.
-int fwd_restr(const ConvGeom &g, unsigned flags) { return (flags & DP_RELU) && !(flags & DP_RELU_IN) && pixel_window_exists(g, PASS_FWD) ? RESTR_ORDER : 0; }
+// no order.  RESTR_ORDER only where there is such a kernel (or the one that adds two halves of 128 channels) to leave out: other layers have one plan, measured once.
+int fwd_restr(const ConvGeom &g, unsigned flags)
+{
+    GemmPlan pl;
+    return (flags & DP_RELU) && !(flags & DP_RELU_IN) && (pixel_window_exists(g, PASS_FWD) || (g.C == 128 && halo_plan(g, PASS_FWD, 405, 0, &pl))) ? RESTR_ORDER : 0;
+}
 
 dp_status check_conv(const dp_conv_desc *d, ConvGeom *g)
 {
@@ -473,10 +477,12 @@ void tune_entry(ConvArgs a, PlanEntry &pe, hipStream_t st, const PrepFn &prep, i
     best = 1e30f;
     GemmPlan best_plan = pe.plan;
     // candidates come in the model's order: a later one has to win by more than the timing noise.  A backward-data kernel that wants a pass over dy in
-    // front of it wins by 10 %: its second launch costs the host 4 us and a gap on a busy stream, which a call timed alone does not show (224 <- 64 on
-    // 10 x 10, 16 samples, back to back / with flushed caches: stationary weights and pass 7.8 / 13.0 us, the window kernel with the mask inside 7.7 / 10.8)
+    // front of it wins by 5 %: its second launch costs the host 4 us and a gap on a busy stream, which a call timed alone does not show.  Timed on warm caches it
+    // wins by 25 %: with flushed ones the pair takes that much longer beside the window kernel (224 <- 64 on 10 x 10, 16 samples: stationary weights and pass
+    // 7.8 us warm, 13.0 cold, the window kernel with the mask inside 7.7 and 10.8; four such layers 1.17 - 1.25)
+    const float pass_factor = flush != nullptr ? 1.05f : 1.25f;
     for (size_t i = 0; i < pe.cands.size(); ++i) {
-        if (t[i] >= 0.f && a.pass == PASS_DGRAD && prep && !pe.cands[i].win) t[i] *= 1.10f;
+        if (t[i] >= 0.f && a.pass == PASS_DGRAD && prep && !pe.cands[i].win) t[i] *= pass_factor;
         if (t[i] >= 0.f && t[i] < 0.98f * best) { best = t[i]; best_plan = pe.cands[i]; }
     }
     (void)hipEventDestroy(e0);

@@ -51,6 +51,7 @@ const Candidate kPix[] = {
     {402, 2, 0.75f, 5.5f},
     {403, 2, 0.72f, 5.5f},
     {404, 2, 0.40f, 0.8f},   // 3x3 only: persistent blocks, weights in registers (180 layers: 8 % in the median)
+    {405, 1, 0.20f, 3.7f},   // the same for 128 reduction channels: see price()
     {100, 2, 1.40f, 5.0f},   // register-staged fallbacks (also reduction step 32)
     {101, 3, 1.05f, 4.5f},
     {102, 3, 1.05f, 4.5f},
@@ -112,6 +113,8 @@ double price_window(const ConvGeom &g, const GemmPlan &pl)
 double price(const ConvGeom &g, int pass, const Candidate &c, const GemmPlan &pl, int restr)
 {
     const double blocks = (double)pl.tilesA * pl.tilesB * pl.splits;
+    // Stationary weights of 128 reduction channels take 4.4 us and 4.1 per round of tiles (240 timings, 3 - 8 %), in the currency of the tiles beside them
+    if (c.code == 405) return 7.9 + 3.66 * std::ceil(blocks / 256.0);
     const double conc = 256.0 * c.bpc;
     double share = 1.0, waves;
     if (blocks <= conc) {
@@ -175,6 +178,7 @@ int auto_plan_list(const ConvGeom &g, int pass, int force_splits, GemmPlan *out,
     const Candidate *cands = pass == PASS_WGRAD ? kWg : kPix;
     const int ncand = pass == PASS_WGRAD ? (int)(sizeof(kWg) / sizeof(kWg[0])) : (int)(sizeof(kPix) / sizeof(kPix[0]));
     for (int ci = 0; ci < ncand; ++ci) {
+        if (pass == PASS_FWD && cands[ci].code == 405 && (restr & RESTR_ORDER)) continue;   // two halves of the reduction
         if (pass != PASS_WGRAD && cands[ci].code >= 400 && (restr & 1)) continue;   // the input-patch kernels store bf16 only
         if (pass == PASS_DGRAD && cands[ci].code >= 230 && cands[ci].code <= 233 && (restr & 1)) continue;   // bf16 staged epilogue only
         int last_splits = -1;
@@ -362,6 +366,7 @@ bool pixel_window_plan(const ConvGeom &g, int pass, const GemmPlan &base, double
     if (!fwd && base.BK == 32 && pl[0].variant >= 6 && g.R * g.S < 5) return false;   // 96-channel tiles were fitted from 7 taps on
     double floor_us = 0.0, factor = 0.0;   // not in the place of unsplit register-staged kernels forward, nor of flat ones backward with few taps or short reductions
     if (base.halo && base.variant == 4) factor = 1.0;
+    else if (base.halo && base.variant == 5) { floor_us = -4.5; factor = 1.12; }
     else if (base.halo) { floor_us = fwd ? 0.3 : -1.6; factor = fwd ? 1.13 : 1.34; }
     else if (dma_plan_is_strip(base)) { floor_us = -4.4; factor = fwd ? 1.11 : 1.16; }
     else if (dma_plan_is_flat(base)) factor = fwd || (g.R * g.S > 8 && g.R * g.S * g.K >= 512) ? 1.0 : 0.0;   // backward-data: 1.17 - 1.78 times as fast

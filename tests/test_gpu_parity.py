@@ -1630,3 +1630,39 @@ def test_pointwise_choice(env):
         assert "k_pointwise" not in name(conv(64, 56, 256, 512, 2, flags), 1)
         assert "k_pointwise" not in name(conv(64, 56, 256, 128, 1, flags | dp.DP_DX_F32), 1)
         assert "k_fwd_dma<64, 64, 64, 2, 2, 2, 2>" in name(conv(4, 56, 256, 128, 1, flags), 0)
+
+
+@pytest.mark.parametrize("blocks", [0, 2, 7])
+def test_input_patch_stationary_weights_of_128_channels(env, blocks):
+    """3x3, stride 1, 128 reduction channels: two groups of waves hold 64 of them each and add their sums through LDS.  Ragged tiles and channels, several
+    tiles per block, with and without both masks."""
+    dp, U, orc = env
+    for p in (0, 1):
+        dp.dp_set_override(p, 405, blocks)
+    try:
+        for tag, n, h, w, o, pd in (("ws2_a", 2, 13, 12, 96, (1, 1)), ("ws2_b", 1, 37, 40, 64, (1, 1)), ("ws2_c", 3, 20, 70, 200, (0, 0)), ("ws2_d", 2, 16, 16, 8, (2, 2)),
+                                    ("ws2_e", 1, 3, 3, 16, (1, 1))):
+            case = U.ConvCase(tag, n, h, w, 128, o, 3, 3, (1, 1), pd, bf16=True, bias=True, relu=True)
+            assert dp.dp_conv2d_kernel_info(case.desc, 0)[0] == "k_halo_ws<0, false, 2>"
+            y = case.run_fwd()
+            torch.cuda.synchronize()
+            U.assert_bf16_close(U.to_np(y), orc.conv2d_fwd(case.x, case.w, case.b, relu=True, pad=pd), f"{tag} blocks {blocks}")
+            case = U.ConvCase(tag, n, h, w, o, 128, 3, 3, (1, 1), pd, bf16=True, bias=True, relu=True)
+            assert dp.dp_conv2d_kernel_info(case.desc, 1)[0] == "k_halo_ws<1, false, 2>"
+            y = case.run_fwd()
+            ref = orc.conv2d_bwd_data(case.dy, case.w, case.x.shape, y_saved=U.to_np(y), pad=pd)
+            for dx, want in ((case.run_dgrad(y), ref), (case.run_dgrad_relu_in(y), orc.relu_in_backward(ref, case.x))):
+                torch.cuda.synchronize()
+                U.assert_bf16_close(U.to_np(dx), want, f"{tag} blocks {blocks} dx")
+        # other reductions and fp32 gradients are not this kernel's
+        for c, k, f32, p in ((64, 64, False, 0), (192, 64, False, 0), (64, 256, False, 1), (64, 128, True, 1)):
+            case = U.ConvCase("ws2_not", 1, 9, 9, c, k, 3, 3, (1, 1), (1, 1), bf16=True, bias=True, relu=True, dx_f32=f32)
+            assert "k_halo" not in dp.dp_conv2d_kernel_info(case.desc, p)[0]
+    finally:
+        for p in (0, 1):
+            dp.dp_set_override(p, -1, 0)
+    # the default choice: not where a layer masks by its own output, whose sums keep their order
+    own = dp.conv_desc(8, 112, 112, 128, 128, 3, 3, (1, 1), (1, 1), dp.DP_BF16, dp.DP_RELU)
+    chain = dp.conv_desc(8, 112, 112, 128, 128, 3, 3, (1, 1), (1, 1), dp.DP_BF16, dp.DP_RELU | dp.DP_RELU_IN)
+    assert "k_halo_ws" not in dp.dp_conv2d_kernel_info(own, 0)[0] and dp.dp_conv2d_kernel_info(chain, 0)[0] == "k_halo_ws<0, false, 2>"
+    assert dp.dp_conv2d_kernel_info(chain, 1)[0] == "k_halo_ws<1, true, 2>"
