@@ -286,17 +286,22 @@ def test_backward_data_tile_price_rules(dp):
     def name(n, h, w, c, k, r=1, pass_=1, pad=0):
         d = dp.conv_desc(n, h, w, c, k, r, r, (1, 1), (pad, pad), dp.DP_BF16, dp.DP_RELU | dp.DP_RELU_IN)
         return dp.dp_conv2d_kernel_info(d, pass_)[0].replace("k_dgrad_dma", "").replace("k_fwd_dma", "")
-    assert name(64, 56, 56, 256, 128) == "<128, 128, 64, 2, 2, 2, 1>"                  # 256x256: 59 us, 52
-    assert name(22, 37, 37, 256, 128) == "<128, 128, 64, 2, 2, 2, 1>"                  # 64x256: 17.3, 12.2
-    assert name(13, 138, 136, 64, 128, 3, pad=1) == "<64, 128, 64, 2, 2, 2, 1>"        # 64x256: 82, 59
-    assert name(54, 18, 18, 768, 192) == "<256, 256, 64, 2, 4, 2, 1>"                  # one round; 128x128: 19.5, 20.8
+    assert name(16, 65, 65, 256, 576) == "<128, 64, 64, 2, 2, 2, 1>"                   # 256x256 without the mask
+    assert name(13, 138, 136, 64, 192, 3, pad=1) == "<64, 128, 64, 2, 2, 2, 1>"        # as 128 channels were: 64x256 82, 59
+    assert name(54, 18, 18, 768, 576) == "<256, 256, 64, 2, 4, 2, 1>"                  # one round
     assert name(54, 48, 48, 192, 768) == "<256, 256, 64, 2, 4, 2, 1>"                  # two full rounds; 64x128: 72, 80
-    assert name(24, 65, 65, 256, 64) == "<256, 256, 64, 2, 4, 2, 1>"                   # input patch: 31, 46
-    assert name(11, 76, 71, 512, 64, 3, pad=1) == "<256, 256, 64, 2, 4, 2, 1>"         # input patch: 57, 87
+    # the kernels with stationary weights, each in the place of the tile that these rules had chosen (64 x 56 x 56, 256 <- 128: 57 us -> 38)
+    assert name(64, 56, 56, 256, 128) == "k_pointwise<1, 2, 2, 4, true>"
+    assert name(22, 37, 37, 256, 128) == "k_pointwise<1, 2, 1, 4, true>"
+    assert name(54, 18, 18, 768, 192) == "k_pointwise<1, 3, 1, 4, true>"
+    assert name(24, 65, 65, 256, 64) == "k_pointwise<1, 1, 2, 4, true>"
+    assert name(13, 138, 136, 64, 128, 3, pad=1) == "k_halo_ws<1, true, 2>"
+    assert name(11, 76, 71, 512, 64, 3, pad=1) == "k_halo_ws<1, true>"
+    assert name(23, 41, 42, 128, 192, 3, pass_=0, pad=1) == "k_halo_ws<0, false, 2>"
     assert name(27, 68, 61, 64, 192, 3, pad=1) == "<64, 256, 64, 1, 4, 2, 1>"          # 64x128: 53, 60
     assert name(14, 4, 4, 128, 512) == "<64, 64, 64, 2, 2, 2, 4>"                      # small grids: as without a mask
     assert name(1, 11, 11, 512, 128) == "<64, 64, 128, 2, 2, 3, 1>"
-    assert name(23, 41, 42, 128, 192, 3, pass_=0, pad=1) == "<64, 256, 64, 1, 4, 2, 1>"   # forward: as before
+    assert name(23, 41, 42, 192, 192, 3, pass_=0, pad=1) == "<64, 256, 64, 1, 4, 2, 1>"   # forward: as before
 
 
 def test_strided_1x1_fp32_gradient_plan_is_the_one_that_runs(dp):
