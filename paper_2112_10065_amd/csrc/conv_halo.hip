@@ -661,10 +661,10 @@ DEVFN void lds_write16(unsigned addr, u32x4 v) { asm volatile("ds_write_b128 %0,
 // MASK (backward-data): fused backward of the ReLU in front of the layer.  RH: blocks of 64 reduction channels.  With two of them a block has eight waves and a
 // CU one block: waves 4 - 7 hold the weights of the second 64 channels and multiply the same pixels; each wave hands the sums of one of its two pixel
 // fragments to its partner through LDS (in the share of the patch buffer that the partner refills itself) and finishes the other.
-template <int PASS, bool MASK = false, int RH = 1>
-__global__ __launch_bounds__(256 * RH, 2) void k_halo_ws(const KArgs p, int tiles_x, int tiles_y, int tiles_all)
+#if __HIP_DEVICE_COMPILE__   // the host pass only needs the launch stubs
+template <int PASS, bool MASK, int RH>
+DEVFN void halo_ws(const KArgs &p, int tiles_x, int tiles_y, int tiles_all)
 {
-#if __HIP_DEVICE_COMPILE__   // the host pass only needs the launch stub
     constexpr int WS_DEPTH = MASK || RH > 1 ? 2 : 3;   // fragment reads run this many 16-channel slices ahead of the matrix cores
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const ConvGeom &g = p.g;
@@ -904,6 +904,20 @@ __global__ __launch_bounds__(256 * RH, 2) void k_halo_ws(const KArgs p, int tile
         now = next;
         next = after;
     }
+}
+#endif
+template <int PASS, bool MASK = false>
+__global__ __launch_bounds__(256, 2) void k_halo_ws(const KArgs p, int tiles_x, int tiles_y, int tiles_all)
+{
+#if __HIP_DEVICE_COMPILE__
+    halo_ws<PASS, MASK, 1>(p, tiles_x, tiles_y, tiles_all);
+#endif
+}
+template <int PASS, bool MASK, int RH>
+__global__ __launch_bounds__(256 * RH, 2) void k_halo_ws(const KArgs p, int tiles_x, int tiles_y, int tiles_all)
+{
+#if __HIP_DEVICE_COMPILE__
+    halo_ws<PASS, MASK, RH>(p, tiles_x, tiles_y, tiles_all);
 #endif
 }
 
