@@ -290,6 +290,37 @@ DEVFN TileWalk tile_walk(int tiles)
     return {(int)((long long)tiles * x / 8) + (int)(blockIdx.x >> 3), (int)((long long)tiles * (x + 1) / 8), nb >> 3};
 }
 
+// Filter gradient, what a product over whole tiles does not give: a tile that reaches past the last row or column holds zeros of dy there, and they meet the
+// pixels of x that lie in the patch beside them (or padding's zeros meet a dy).  Zero times infinity is NaN, so a sum with a NaN is made again from the pairs
+// that the tap has: dW[row .. row + 3][tap][col] over this block's tiles of th x tw pixels.  Line by line, so that the sums stay as short as the
+// product's; a sum that is all NaN stays so.  The check costs up to 0.3 us (2 x 56 x 56, 64 -> 64: 15.3 -> 15.6), such a sum what a plain loop costs
+// (8 x 153 x 149, 64 -> 128 with one infinite pixel in the last column: 40 us -> 2.2 ms).
+DEVFN f32x4 sum_of_pairs(const KArgs &p, int tiles_x, int tiles_y, int tiles, int th, int tw, int row, int tap, int col)
+{
+    const ConvGeom &g = p.g;
+    const TileWalk walk = tile_walk(tiles);
+    const int r = tap / g.S - g.ph, s = tap % g.S - g.pw;
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+    for (int t = walk.first; t < walk.end; t += walk.stride) {
+        const int n = t / (tiles_x * tiles_y), rem = t - n * (tiles_x * tiles_y), ty = rem / tiles_x, q0 = (rem - ty * tiles_x) * tw;
+        const int h0 = max(ty * th, -r), h1 = min(min(ty * th + th, g.Ho), g.H - r), w0 = max(q0, -s), w1 = min(min(q0 + tw, g.Wo), g.W - s);
+        for (int h = h0; h < h1; ++h) {
+            const bf16_t *dy = p.dy + ((size_t)(n * g.Ho + h) * g.Wo) * g.K + row, *x = p.x + ((ptrdiff_t)(n * g.H + h + r) * g.W + s) * 64 + col;
+            f32x4 line = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+            for (int w = w0; w < w1; ++w) {
+                const u32x2 d = *reinterpret_cast<const u32x2 *>(dy + (size_t)w * g.K);
+                const float v = __uint_as_float((unsigned)*reinterpret_cast<const unsigned short *>(x + (ptrdiff_t)w * 64) << 16);
+                line.x = fmaf(__uint_as_float(d.x << 16), v, line.x); line.y = fmaf(__uint_as_float(d.x & 0xffff0000u), v, line.y);
+                line.z = fmaf(__uint_as_float(d.y << 16), v, line.z); line.w = fmaf(__uint_as_float(d.y & 0xffff0000u), v, line.w);
+            }
+            sum += line;
+        }
+        if (sum.x != sum.x && sum.y != sum.y && sum.z != sum.z && sum.w != sum.w) break;
+    }
+    return sum;
+}
+
 // ---------------------------------------------------------------------------------------
 // Backward-filter with the input patch in LDS (stride 1, 64 input channels, up to 16 taps).
 // The tiled kernel copies, for every 64 pixels of reduction, the x rows of each tap again; here a
@@ -436,6 +467,7 @@ __global__ __launch_bounds__(1024) void k_wgrad_halo(const KArgs p, int tws, int
     }
     // partial[block][c_out][tap][c_in]; accumulator element v of lane l: row 8*(v/4) + 4*(l/32) + v%4, column l%32
     float *out = p.partial + (size_t)blockIdx.x * p.rowsA * p.rowsB;
+    bool nan = false;   // among this lane's sums
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -444,7 +476,16 @@ __global__ __launch_bounds__(1024) void k_wgrad_halo(const KArgs p, int tws, int
             for (int v = 0; v < 16; ++v) {
                 const int k = a0 + i * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
                 if (k < p.rowsA) out[(size_t)k * p.rowsB + wave * 64 + jf * 32 + (lane & 31)] = acc[i][jf][v];
+                nan |= acc[i][jf][v] != acc[i][jf][v];
             }
+    if (__builtin_expect(!nan, 1)) return;
+    for (int j = 0; j < 16; ++j) {   // four rows of c_out each, in whole 8s
+        const int row = a0 + (j >> 1) * 8 + 4 * (lane >> 5), col = (j & 1) * 32 + (lane & 31);
+        float *o = out + (size_t)row * p.rowsB + wave * 64 + col;
+        if (row >= p.rowsA || !(__builtin_isunordered(o[0], o[p.rowsB]) || __builtin_isunordered(o[2 * p.rowsB], o[3 * p.rowsB]))) continue;
+        const f32x4 sum = sum_of_pairs(p, tiles_x, tiles_y, tiles, TH, TW, row, wave, col);
+        o[0] = sum.x; o[p.rowsB] = sum.y; o[2 * p.rowsB] = sum.z; o[3 * p.rowsB] = sum.w;
+    }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -467,6 +508,8 @@ constexpr int W9_XCH = 4 * 9 * 4096;   // exchange: nine tiles of each of the fo
 static_assert(W9_XCH + 2 * 64 * 16 <= W9_NB * W9_BUF, "the exchange fits the buffers");
 
 template <int OFF> DEVFN void lds_write_f32x4(unsigned addr, f32x4 v) { asm volatile("ds_write_b128 %0, %1 offset:%2" ::"v"(addr), "v"(v), "n"(OFF) : "memory"); }
+
+struct Halo9Arguments { KArgs p; int tiles_x, tiles_y, tiles; };   // the kernel's arguments as they lie in memory
 
 template <bool DB>
 __global__ __launch_bounds__(512, 2) void k_wgrad_halo9(const KArgs p, int tiles_x, int tiles_y, int tiles)
@@ -600,25 +643,27 @@ __global__ __launch_bounds__(512, 2) void k_wgrad_halo9(const KArgs p, int tiles
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __syncthreads();
     float *out = p.partial + ((size_t)blockIdx.x * p.rowsA + a0 + kh * 32) * 576 + ch * 32 + (lane & 31);
-    for_constant<9>([&](auto T) {
+    bool nan = false;   // among this lane's sums
+    auto finish = [&](auto T) {
         constexpr int t = T;
-        if ((t < 5) == (pg == 0)) {
-            u32x4 o[4];
-            for_constant<4>([&](auto V) { o[V] = lds_read16<t * 4096 + V * 1024>(xch); });
-            asm volatile("s_waitcnt lgkmcnt(0)");
+        u32x4 o[4];
+        for_constant<4>([&](auto V) { o[V] = lds_read16<t * 4096 + V * 1024>(xch); });
+        asm volatile("s_waitcnt lgkmcnt(0)");
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                asm volatile("" : "+v"(o[v]));
-                const f32x4 of = __builtin_bit_cast(f32x4, o[v]);
-                const float sums[4] = {acc[t][4 * v] + of.x, acc[t][4 * v + 1] + of.y, acc[t][4 * v + 2] + of.z, acc[t][4 * v + 3] + of.w};
+        for (int v = 0; v < 4; ++v) {
+            asm volatile("" : "+v"(o[v]));
+            const f32x4 of = __builtin_bit_cast(f32x4, o[v]);
+            const float sums[4] = {acc[t][4 * v] + of.x, acc[t][4 * v + 1] + of.y, acc[t][4 * v + 2] + of.z, acc[t][4 * v + 3] + of.w};
+            nan |= __builtin_isunordered(sums[0], sums[1]) | __builtin_isunordered(sums[2], sums[3]);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int row = 8 * v + 4 * (lane >> 5) + e;
-                    if (a0 + kh * 32 + row < p.rowsA) out[(size_t)row * 576 + t * 64] = sums[e];
-                }
+            for (int e = 0; e < 4; ++e) {
+                const int row = 8 * v + 4 * (lane >> 5) + e;
+                if (a0 + kh * 32 + row < p.rowsA) out[(size_t)row * 576 + t * 64] = sums[e];
             }
         }
-    });
+    };
+    if (pg == 0) for_constant<5>([&](auto T) { finish(T); });
+    else for_constant<4>([&](auto T) { finish(std::integral_constant<int, T + 5>{}); });
     if (do_db && pg == 0 && p.dbp != nullptr) {
         const f32x4 o = __builtin_bit_cast(f32x4, lds_read16<0>(dxch));
         asm volatile("s_waitcnt lgkmcnt(0)");
@@ -626,6 +671,19 @@ __global__ __launch_bounds__(512, 2) void k_wgrad_halo9(const KArgs p, int tiles
         asm volatile("" : "+v"(ov));
         store_colsum_fragment(accdb + __builtin_bit_cast(f32x4, ov), p.dbp + (size_t)blockIdx.x * p.rowsA, a0 + kh * 32, p.rowsA, lane);
     }
+    if (__builtin_expect(!nan, 1)) return;
+    // The arguments are read once more, and the sums from where they have been stored: kept for this, they would cost the loop registers
+    const Halo9Arguments *args = (const Halo9Arguments *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    const KArgs &pa = args->p;
+    const int c = ch * 32 + (lane & 31);
+    for (int t = pg == 0 ? 0 : 5; t < (pg == 0 ? 5 : 9); ++t)
+        for (int row = blockIdx.y * 64 + kh * 32 + 4 * (lane >> 5), i = 0; i < 4 && row < pa.rowsA; ++i, row += 8) {   // c_out in whole 8s
+            float *o = pa.partial + ((size_t)blockIdx.x * pa.rowsA + row) * 576 + t * 64 + c;
+            if (!(__builtin_isunordered(o[0], o[576]) || __builtin_isunordered(o[2 * 576], o[3 * 576]))) continue;
+            const f32x4 sum = sum_of_pairs(pa, args->tiles_x, args->tiles_y, args->tiles, W9_TH, W9_TW, row, t, c);
+            o[0] = sum.x; o[576] = sum.y; o[2 * 576] = sum.z; o[3 * 576] = sum.w;
+        }
 #endif
 }
 

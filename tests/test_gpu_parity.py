@@ -979,6 +979,42 @@ def test_filter_gradient_window_kernel_keeps_non_finite_values_where_their_taps_
         dp.dp_set_override(2, -1, 0)
 
 
+@pytest.mark.parametrize("variant,blocks", [(411, 0), (411, 3), (410, 0), (410, 3)])
+def test_input_patch_filter_gradient_keeps_non_finite_values_where_their_taps_reach(env, variant, blocks):
+    """The input-patch kernels multiply whole tiles: past the last row and column zeros of dy meet the pixels of x beside them.  An infinite or NaN value of
+    x or dy at the edges of images and tiles reaches the sums that pair it and no others, whatever the tiles leave over."""
+    dp, U, orc = env
+    dp.dp_set_override(2, variant, blocks)
+    try:
+        for tag, n, h, w, k, r, s, pd in (("patchf_a", 2, 13, 12, 96, 3, 3, (1, 1)), ("patchf_b", 1, 37, 40, 64, 3, 3, (1, 1)), ("patchf_c", 2, 17, 41, 40, 3, 3, (0, 0)),
+                                          ("patchf_d", 1, 9, 17, 136, 3, 3, (2, 2)), ("patchf_e", 3, 16, 32, 64, 3, 3, (1, 1)), ("patchf_f", 1, 31, 47, 8, 3, 3, (1, 0)),
+                                          ("patchf_g", 2, 9, 33, 72, 1, 7, (0, 3)), ("patchf_h", 1, 21, 19, 64, 3, 1, (1, 0))):
+            if variant == 411 and (r, s) != (3, 3):
+                continue
+            case = U.ConvCase(tag, n, h, w, 64, k, r, s, (1, 1), pd, bf16=True, bias=True, relu=False)
+            assert dp.dp_conv2d_kernel_info(case.desc, 2)[0] == ("k_wgrad_halo9<true>" if variant == 411 else "k_wgrad_halo")
+            # the last row and column of an image, the first, and both sides of a tile's last column
+            for at, (i, row, col, val) in enumerate(((0, 0, 0, np.inf), (n - 1, h - 1, w - 1, np.nan), (0, h // 2, w - 1, -np.inf), (n - 1, h - 1, w // 2, np.inf),
+                                                     (n // 2, h - 1, 0, np.nan), (0, h // 3, min(15, w - 2), np.inf), (n - 1, min(8, h - 2), min(16, w - 2), -np.inf))):
+                case.x[i, row, col, 9 * at] = val
+                case.xd[i, row, col, 9 * at] = float(val)
+            for at, (i, row, col, val) in enumerate(((0, 0, 0, np.nan), (n - 1, case.ho - 1, case.wo - 1, np.inf), (0, case.ho // 2, case.wo - 1, np.nan))):
+                case.dy[i, row, col, at] = val
+                case.dyd[i, row, col, at] = float(val)
+            dw, _ = case.run_wgrad(None)
+            torch.cuda.synchronize()
+            got = U.to_np(dw)
+            with np.errstate(invalid="ignore"):
+                ref, _ = orc.conv2d_bwd_filter(case.x, case.dy, case.w.shape, y_saved=None, stride=(1, 1), pad=pd, want_db=True)
+            assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref)), tag
+            ok = np.isfinite(ref)
+            assert ok.any() and not ok.all() and np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+            # sums of at most 2^12 exact products of bf16 numbers in fp32
+            assert U.errs(got[ok], ref[ok])[0] <= 2e-6, tag
+    finally:
+        dp.dp_set_override(2, -1, 0)
+
+
 def test_filter_gradient_window_kernel_by_default_and_with_less_scratch(env):
     """A middle layer takes the window kernel by itself; with the scratch that the kernels without it ask for or less, the call still runs
     wherever one of the two fits, and gives the same gradients."""
