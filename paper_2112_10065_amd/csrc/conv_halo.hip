@@ -625,8 +625,10 @@ __global__ __launch_bounds__(512, 2) void k_wgrad_halo9(const KArgs p, int tiles
     // Wave pg = 0 finishes taps 0 - 4 and its partner pg = 1 taps 5 - 8; each leaves the other's tiles in LDS, sixteen values of a lane as four
     // vectors.  Accumulator element v of lane l: row 8*(v/4) + 4*(l/32) + v%4, column l%32.
     wait_vmcnt<0>();
-    // the last matrix instructions have written their results before the stores below, which the compiler does not know, read them (at most 18 wait states)
-    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+    // The last matrix instructions have written their results before the stores below, which the compiler does not know, read them (at most 18 wait
+    // states).  The sums are operands: no matrix instruction moves past this
+    asm volatile("s_nop 15\n\ts_nop 15"
+                 : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(acc[4]), "+v"(acc[5]), "+v"(acc[6]), "+v"(acc[7]), "+v"(acc[8]), "+v"(accdb)::"memory");
     __syncthreads();
     const int pair = kh * 2 + ch;
     const unsigned xch = smem_base + pair * (9 * 4096) + lane * 16;
