@@ -36,7 +36,9 @@ std::atomic<int> g_force_variant[3] = {{-1}, {-1}, {-1}};
 std::atomic<int> g_force_splits[3] = {{0}, {0}, {0}};
 std::atomic<int> g_autotune{0};
 thread_local bool g_analytic_only = false;   // the descriptor of the running call asks for DP_DETERMINISTIC
-thread_local bool g_tight_splits = false;    // filter gradients in the form that asks for least scratch (TightSplits)
+// forms of a filter gradient, for calls whose scratch does not hold more (ScratchForm)
+enum { FORM_USUAL, FORM_WINDOW, FORM_LEAST };
+thread_local int g_scratch_form = FORM_USUAL;
 std::once_flag g_init_once;
 hipError_t g_init_err = hipSuccess;
 
@@ -261,7 +263,7 @@ void plan_uncached(const ConvGeom &g, int pass, int fv, int fs, GemmPlan *pl, in
             *pl = flat;
         }
         if (fs <= 0 && pass != PASS_WGRAD && !(restr & 1) && pointwise_plan(g, pass, *pl, (restr & 2) != 0, &flat)) *pl = flat;
-        if (fs <= 0 && pass == PASS_WGRAD && !(restr & RESTR_BASE) && wgrad_window_plan(g, *pl, time, &flat)) *pl = flat;
+        if (fs <= 0 && pass == PASS_WGRAD && !(restr & RESTR_BASE) && ((restr & RESTR_WINDOW) ? wgrad_window_form(g, &flat) : wgrad_window_plan(g, *pl, time, &flat))) *pl = flat;
         return;
     }
     // a forced input-patch variant the call may not use falls through to the next family
@@ -329,23 +331,24 @@ PlanRef plan_entry(const ConvGeom &g, int pass, int restr = 0)
     static std::unordered_map<PlanKey, PlanRef, PlanKeyHash> cache;
     const int fv = g_force_variant[pass].load(), fs = g_force_splits[pass].load();
     const int at = g_analytic_only ? 0 : g_autotune.load();
-    PlanKey key = {{g.N, g.H, g.W, g.C, g.K, g.R, g.S, g.sh, g.sw, g.ph, g.pw, g.Ho, g.Wo, pass, fv, fs, at | (restr << 2) | (g_tight_splits ? 1 << 8 : 0)}};
+    PlanKey key = {{g.N, g.H, g.W, g.C, g.K, g.R, g.S, g.sh, g.sw, g.ph, g.pw, g.Ho, g.Wo, pass, fv, fs, at | (restr << 2) | (pass == PASS_WGRAD ? g_scratch_form << 8 : 0)}};
     std::lock_guard<std::mutex> lock(g_plan_mu);
     auto it = cache.find(key);
     if (it != cache.end()) return it->second;
     if (cache.size() > 4096) cache.clear();
     PlanRef ep = std::make_shared<PlanEntry>();
     PlanEntry &e = *ep;
-    plan_uncached(g, pass, fv, fs, &e.plan, restr | (pass == PASS_WGRAD && g_tight_splits ? RESTR_BASE : 0));
-    const bool round_splits = pass == PASS_WGRAD && fv < 0 && fs <= 0 && !g_tight_splits;
+    const int form = pass == PASS_WGRAD ? g_scratch_form : FORM_USUAL;
+    plan_uncached(g, pass, fv, fs, &e.plan, restr | (form == FORM_LEAST ? RESTR_BASE : form == FORM_WINDOW ? RESTR_WINDOW : 0));
+    const bool round_splits = pass == PASS_WGRAD && fv < 0 && fs <= 0 && form != FORM_LEAST;
     if (round_splits) round_wgrad_splits(g, e.plan);
     e.part_cap = mfma_partial_bytes(g, pass, e.plan);
-    if (at != 0 && fv < 0 && e.plan.fast) {
+    if (at != 0 && fv < 0 && e.plan.fast && form != FORM_WINDOW) {
         GemmPlan list[kTuneCandidates];
         // a cold measurement judges for itself what the model's warm-cache prices cannot: more candidates, a wider price band
         int n = auto_plan_list(g, pass, fs, list, at == 2 ? kTuneCandidates : 12, restr | (at == 2 ? 4 : 0));
         if (pass != PASS_WGRAD && n > 0 && n < kTuneCandidates && dma_plan_is_flat(e.plan)) list[n++] = e.plan;   // not one of the list's
-        const bool window = pass == PASS_WGRAD ? !g_tight_splits : pass == PASS_FWD ? !(restr & RESTR_ORDER) : !(restr & (RESTR_BASE | 1));
+        const bool window = pass == PASS_WGRAD ? form == FORM_USUAL : pass == PASS_FWD ? !(restr & RESTR_ORDER) : !(restr & (RESTR_BASE | 1));
         if (window && n > 0 && fs <= 0) {
             GemmPlan win[2];
             double times[2];
@@ -721,13 +724,13 @@ dp_status run_dgrad(const ConvGeom &g, int dtype, unsigned flags, const void *dy
     return e == hipSuccess ? DP_OK : hip_fail(e, "backward-data launch");
 }
 
-// While it lives, filter gradients on this thread take the form that asks for least scratch (without the empty splits of round_wgrad_splits): for
-// calls whose scratch does not hold more
-struct TightSplits {
-    const bool before = g_tight_splits;
-    explicit TightSplits(bool on) { if (on) g_tight_splits = true; }
-    ~TightSplits() { g_tight_splits = before; }
-    TightSplits(const TightSplits &) = delete;
+// Gives back the form that filter gradients on this thread take.  Another than the fastest is for calls whose scratch does not hold that: the window kernel in the place
+// of the nine-tap one, or the kernels without either and without the empty splits of round_wgrad_splits.  Any of them may ask for least.
+struct ScratchForm {
+    const int before = g_scratch_form;
+    ScratchForm() {}
+    ~ScratchForm() { g_scratch_form = before; }
+    ScratchForm(const ScratchForm &) = delete;
 };
 
 size_t wgrad_ws_bytes(const ConvGeom &g, int dtype, bool with_db);
@@ -746,7 +749,7 @@ size_t stem_wgrad_ws_bytes(const ConvGeom &g, bool with_db)
 bool use_stem_wgrad(const ConvGeom &g, int dtype, bool with_db)
 {
     return use_small_c(g, PASS_WGRAD) && small_c_wgrad_stem_shape(g) &&
-           !(g_tight_splits && im2col_wgrad_ws_bytes(g, dtype, with_db) < stem_wgrad_ws_bytes(g, with_db));
+           !(g_scratch_form == FORM_LEAST && im2col_wgrad_ws_bytes(g, dtype, with_db) < stem_wgrad_ws_bytes(g, with_db));
 }
 
 size_t wgrad_ws_bytes(const ConvGeom &g, int dtype, bool with_db)
@@ -768,22 +771,38 @@ size_t wgrad_ws_bytes(const ConvGeom &g, int dtype, bool with_db)
     return need;
 }
 
+// the next form behind the current one that this layer has
+int next_form(const ConvGeom &g, int dtype)
+{
+    GemmPlan pl;
+    return g_scratch_form == FORM_USUAL && dtype == DP_BF16 && g_force_variant[PASS_WGRAD].load() < 0 && g_force_splits[PASS_WGRAD].load() <= 0 && wgrad_window_form(g, &pl)
+               ? FORM_WINDOW : FORM_LEAST;
+}
+
 // the least a call can do with
 size_t wgrad_least_ws_bytes(const ConvGeom &g, int dtype, bool with_db)
 {
-    const size_t usual = wgrad_ws_bytes(g, dtype, with_db);   // the window kernel's few splits may take less than the kernels without it
-    const TightSplits tight(true);
-    return std::min(usual, wgrad_ws_bytes(g, dtype, with_db));
+    const ScratchForm restore;
+    size_t need = wgrad_ws_bytes(g, dtype, with_db);
+    while (g_scratch_form != FORM_LEAST) {
+        g_scratch_form = next_form(g, dtype);
+        need = std::min(need, wgrad_ws_bytes(g, dtype, with_db));
+    }
+    return need;
 }
 
 // workspace layout: [split partials | masked gradient (fast path) | bias-gradient scratch]
 dp_status run_wgrad(const ConvGeom &g, int dtype, const void *x, const void *dy, const void *ym, float *dw, float *db,
                     void *ws, size_t ws_bytes, hipStream_t st)
 {
-    size_t need = wgrad_ws_bytes(g, dtype, db != nullptr);
-    const TightSplits tight(need > (ws != nullptr ? ws_bytes : 0));
-    if (g_tight_splits) need = wgrad_ws_bytes(g, dtype, db != nullptr);
-    if (need > 0 && (ws == nullptr || ws_bytes < need)) return fail(DP_ERR_WORKSPACE, "backward-filter needs %zu workspace bytes, got %zu", need, ws_bytes);
+    const ScratchForm restore;
+    size_t need = wgrad_ws_bytes(g, dtype, db != nullptr), least = need;
+    while (need > (ws != nullptr ? ws_bytes : 0) && g_scratch_form != FORM_LEAST) {
+        g_scratch_form = next_form(g, dtype);
+        need = wgrad_ws_bytes(g, dtype, db != nullptr);
+        least = std::min(least, need);
+    }
+    if (need > 0 && (ws == nullptr || ws_bytes < need)) return fail(DP_ERR_WORKSPACE, "backward-filter needs %zu workspace bytes, got %zu", least, ws_bytes);
     const long long rows = (long long)g.N * g.Ho * g.Wo;
     TraceScope ts(PASS_WGRAD, st);
     if (dtype == DP_F32) {
@@ -1139,8 +1158,8 @@ dp_status dp_conv2d_bwd_filter_noalloc(const dp_conv_desc *desc, const void *x, 
     g_analytic_only = true;
     if ((s = check_ptr(x, "x")) != DP_OK || (s = check_ptr(dy, "dy")) != DP_OK || (s = check_ptr(dw, "dw")) != DP_OK) return s;
     if ((s = check_opt(y_saved, "y_saved")) != DP_OK || (s = check_opt(dbias, "dbias")) != DP_OK) return s;
-    size_t need = wgrad_least_ws_bytes(g, desc->io_dtype, dbias != nullptr);
-    if (need > kNoAllocScratchBytes)
+    size_t need = wgrad_ws_bytes(g, desc->io_dtype, dbias != nullptr);
+    if (need > kNoAllocScratchBytes && (need = wgrad_least_ws_bytes(g, desc->io_dtype, dbias != nullptr)) > kNoAllocScratchBytes)
         return fail(DP_ERR_WORKSPACE, "backward-filter of this layer needs %zu scratch bytes, the built-in scratch holds %zu: use dp_conv2d_bwd_filter with a workspace",
                     need, kNoAllocScratchBytes);
     if ((s = ensure_init()) != DP_OK) return s;

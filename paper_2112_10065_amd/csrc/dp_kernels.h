@@ -24,6 +24,7 @@ enum {
     RESTR_SAVED = 8,   // backward-data with a saved output to mask dy by: the generic kernel does that while it loads, the others need a pass
     RESTR_ORDER = 32,  // forward with DP_RELU and without DP_RELU_IN: the default choice leaves out the kernel that adds in another order (forward_flat_plan)
     RESTR_BASE = 16,   // the kernels and prices that need least scratch: no flat-walk kernel in backward-data
+    RESTR_WINDOW = 64,   // filter gradient: the window kernel in the place of the nine-tap one, whose blocks ask for more scratch
 };
 
 // Geometry of one conv layer plus its implicit-GEMM view for one pass.
@@ -178,6 +179,7 @@ bool pointwise_plan(const ConvGeom &g, int pass, const GemmPlan &base, bool mask
 // filter gradient: the window kernel's two cheapest plans, and whether it takes the place of `base`, whose price is `time`
 int wgrad_window_plans(const ConvGeom &g, GemmPlan out[2], double times[2]);
 bool wgrad_window_plan(const ConvGeom &g, const GemmPlan &base, double time, GemmPlan *out);
+bool wgrad_window_form(const ConvGeom &g, GemmPlan *out);
 // the cheapest plans by the model, best first (input of the measured choice); returns the count
 // restr: kernels the call may not use (bit 0: input-patch kernels, bit 1: the stationary-weight kernel)
 int auto_plan_list(const ConvGeom &g, int pass, int force_splits, GemmPlan *out, int max_out, int restr = 0, double *times = nullptr);

@@ -479,6 +479,16 @@ bool nine_tap_plan(const ConvGeom &g, GemmPlan *out, double *time)
     return found;
 }
 
+// The window kernel's plan of a layer that the nine-tap kernel may take instead: what a call with less scratch than that asks for falls back to
+bool wgrad_window_form(const ConvGeom &g, GemmPlan *out)
+{
+    GemmPlan pl[2];
+    double t[2];
+    if (!family_plan(g, PASS_WGRAD, 411, 0, &pl[0]) || wgrad_window_plans(g, pl, t) == 0) return false;
+    *out = pl[0];
+    return true;
+}
+
 // Filter gradient: the window kernel in the place of `base` (price `time`) where its price lies that far below.  The factors are what the
 // other kernels' prices are worth on 230 layers timed both ways: pipelined tiles take 0.7 - 1.1 of their price split and down to 0.6 unsplit,
 // register-staged ones 1.1 - 1.6, the input-patch kernel with a wave per tap 1.4 - 2.2.  Taken on 48 of 175 layers that both run: 0.98 - 2.0 times as fast.

@@ -280,6 +280,29 @@ def test_filter_gradient_takes_the_scratch_that_was_enough_before(dp):
         assert dp.lib.dp_conv2d_bwd_filter(C.byref(d), A, A, None, A, A, A, enough - 256, None) == dp.DP_ERR_WORKSPACE
 
 
+def test_filter_gradient_of_nine_tap_layers_takes_the_window_kernels_scratch(dp):
+    """The nine-tap kernel, and the tiles that are faster than the window kernel, ask for more scratch than the window kernel.  A call with what that one asks for is
+    accepted, also without a workspace of its own where that fits the built-in scratch.  Valid calls get as far as the missing GPU."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("would launch on the addresses made up here")
+    # (n, h, w, c_out, pad, what the window kernel's plan asks for, whether that fits the 32 MiB built in)
+    for n, h, w, k, pad, enough, builtin in ((8, 153, 149, 128, 1, 65529856, False), (48, 35, 39, 8, 1, 2723584, True), (30, 26, 23, 384, 0, 28323840, True),
+                                             (6, 212, 217, 40, 1, 33315328, True), (21, 27, 29, 256, 1, 22509056, True), (10, 93, 92, 320, 1, 73845760, False)):
+        d = dp.conv_desc(n, h, w, 64, k, 3, 3, (1, 1), (pad, pad), dp.DP_BF16, 0)
+        for saved in (None, A):
+            assert dp.lib.dp_conv2d_bwd_filter(C.byref(d), A, A, saved, A, A, A, enough, None) == dp.DP_ERR_HIP, (n, h, w, k)
+        assert (dp.lib.dp_conv2d_bwd_filter_noalloc(C.byref(d), A, A, None, A, A, None) == dp.DP_ERR_HIP) == builtin
+        # the message names what is enough
+        assert dp.lib.dp_conv2d_bwd_filter(C.byref(d), A, A, None, A, A, None, 0, None) == dp.DP_ERR_WORKSPACE
+        least = int(re.search(rb"needs (\d+) workspace", dp.lib.dp_last_error()).group(1))
+        assert least <= enough and dp.lib.dp_conv2d_bwd_filter(C.byref(d), A, A, None, A, A, A, least, None) == dp.DP_ERR_HIP
+        assert dp.lib.dp_conv2d_bwd_filter(C.byref(d), A, A, None, A, A, A, least - 256, None) == dp.DP_ERR_WORKSPACE
+    # the query is what the fastest form takes
+    d = dp.conv_desc(8, 153, 149, 64, 128, 3, 3, (1, 1), (1, 1), dp.DP_BF16, 0)
+    assert dp.dp_conv2d_kernel_info(d, 2)[0] == "k_wgrad_halo9<true>" and dp.dp_conv2d_workspace_bytes(d, 2) > 65529856
+
+
 def test_backward_data_tile_price_rules(dp):
     """Host logic of the kernel choice (no GPU call): the mask of lone 256x256 tiles and the wide 64x256 tiles of short reductions are priced in
     for layers of more than one round of blocks, where the tiles that replace them are faster, and change nothing else."""

@@ -1035,6 +1035,38 @@ def test_filter_gradient_window_kernel_by_default_and_with_less_scratch(env):
         assert U.errs(U.to_np(dw), U.to_np(usual))[0] <= 2e-6
 
 
+@pytest.mark.parametrize("saved", [False, True])
+def test_nine_tap_layers_with_less_scratch(env, saved):
+    """A layer whose fastest filter gradient is the nine-tap kernel (or tiles that take the place of the window kernel), with less scratch than that asks for:
+    the window kernel and the kernels beside it give the same gradients, also from the scratch built into the library."""
+    dp, U, orc = env
+    for n, h, w, k in ((5, 137, 134, 72), (3, 60, 61, 272)):
+        case = U.ConvCase("short9", n, h, w, 64, k, 3, 3, (1, 1), (1, 1), bf16=True, bias=True, relu=saved)
+        y = case.run_fwd() if saved else None
+        need = dp.dp_conv2d_workspace_bytes(case.desc, 2)
+        dw, db = case.run_wgrad(y)
+        torch.cuda.synchronize()
+        kernels = set()
+        for nbytes in (need, need - 256, need * 3 // 4, need * 5 // 8):
+            dw2, db2 = torch.zeros_like(dw), torch.zeros_like(db)
+            dp.dp_trace_begin()
+            try:
+                dp.dp_conv2d_bwd_filter(case.desc, case.xd, case.dyd, y, dw2, db2, U.workspace(nbytes)[:nbytes])
+            except dp.DpError:
+                dp.dp_trace_end()
+                assert nbytes < need
+                continue
+            kernels.add(dp.dp_trace_end()[0]["kernel"].split("<")[0])
+            torch.cuda.synchronize()
+            # sums of at most 2^17 products in fp32, in two orders
+            assert U.errs(U.to_np(dw2), U.to_np(dw))[0] <= 4e-6 and U.errs(U.to_np(db2), U.to_np(db))[0] <= 4e-6
+        assert "k_wgrad_win" in kernels and len(kernels) > 1
+        dw2, db2 = torch.zeros_like(dw), torch.zeros_like(db)
+        dp.dp_conv2d_bwd_filter_noalloc(case.desc, case.xd, case.dyd, y, dw2, db2)
+        torch.cuda.synchronize()
+        assert U.errs(U.to_np(dw2), U.to_np(dw))[0] <= 4e-6 and U.errs(U.to_np(db2), U.to_np(db))[0] <= 4e-6
+
+
 # (pass, variant, saved output).  The window kernels 250 .. 258: on images whose windows leave room for a block of the other streams (251, 252, 256), and
 # others; the filter gradient's (317, 318) fills a compute unit alone
 @pytest.mark.parametrize("pass_,variant,saved", [(0, 231, False), (0, 232, False), (1, 231, False), (1, 232, False), (1, 233, False), (2, 316, False), (2, 411, False),
