@@ -479,13 +479,13 @@ void tune_entry(ConvArgs a, PlanEntry &pe, hipStream_t st, const PrepFn &prep, i
         }
     best = 1e30f;
     GemmPlan best_plan = pe.plan;
-    // candidates come in the model's order: a later one has to win by more than the timing noise.  A backward-data kernel that wants a pass over dy in
-    // front of it wins by 5 %: its second launch costs the host 4 us and a gap on a busy stream, which a call timed alone does not show.  Timed on warm caches it
-    // wins by 25 %: with flushed ones the pair takes that much longer beside the window kernel (224 <- 64 on 10 x 10, 16 samples: stationary weights and pass
-    // 7.8 us warm, 13.0 cold, the window kernel with the mask inside 7.7 and 10.8; four such layers 1.17 - 1.25)
-    const float pass_factor = flush != nullptr ? 1.05f : 1.25f;
+    // Candidates come in the model's order: a later one has to win by more than the timing noise.  A backward-data kernel that wants a pass over dy in front of
+    // it wins by 5 %: its second launch costs the host 4 us and a gap on a busy stream, which a call timed alone does not show.  Timed on warm caches it is also
+    // charged what the pair takes longer than the window kernel with flushed ones, 1.5 us whatever the size (14 layers of 8 - 12 us: 0.5 - 2.2, 1.5 in the middle;
+    // 90 of 17 - 144 us: as often shorter).
+    const float pass_ms = flush != nullptr ? 0.f : 1.5e-3f;
     for (size_t i = 0; i < pe.cands.size(); ++i) {
-        if (t[i] >= 0.f && a.pass == PASS_DGRAD && prep && !pe.cands[i].win) t[i] *= pass_factor;
+        if (t[i] >= 0.f && a.pass == PASS_DGRAD && prep && !pe.cands[i].win) t[i] = 1.05f * t[i] + pass_ms;
         if (t[i] >= 0.f && t[i] < 0.98f * best) { best = t[i]; best_plan = pe.cands[i]; }
     }
     (void)hipEventDestroy(e0);
