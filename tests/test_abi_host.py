@@ -327,6 +327,18 @@ def test_backward_data_tile_price_rules(dp):
     assert name(23, 41, 42, 192, 192, 3, pass_=0, pad=1) == "<64, 256, 64, 1, 4, 2, 1>"   # forward: as before
 
 
+def test_few_tiles_of_64_channels_keep_the_smallest_window_tile(dp):
+    """Host logic of the kernel choice (no GPU call): where the smallest tile of the window kernel is its cheapest, a layer of 64 reduction channels has too few tiles
+    for the kernel that keeps nine taps of weights in registers."""
+    def name(n, h, c, k, pass_, flags=dp.DP_RELU_IN):
+        return dp.dp_conv2d_kernel_info(dp.conv_desc(n, h, h, c, k, 3, 3, (1, 1), (1, 1), dp.DP_BF16, dp.DP_RELU | flags), pass_)[0]
+    assert name(1, 17, 64, 16, 0) == "k_conv_win<false, 1, 2, 1, false>"     # 8.6 us, 8.1 with flushed caches
+    assert name(4, 9, 64, 256, 0) == "k_conv_win<false, 1, 2, 1, false>"     # 8.9, 8.2
+    assert name(2, 16, 256, 64, 1) == "k_conv_win<true, 1, 2, 1, false>"     # 8.5, 8.3
+    assert name(3, 59, 64, 64, 0) == "k_halo_ws<0, false>"                   # 9.2 for the 10.2 of wider window tiles
+    assert name(4, 9, 64, 256, 0, 0) == "k_halo_ws<0, false>"                # masks by its own y: keeps the order of its sums
+
+
 def test_strided_1x1_fp32_gradient_plan_is_the_one_that_runs(dp):
     """A strided 1x1 layer's fp32 input gradient goes in natural pixel order with all its blocks: its tiles and splits are priced as that
     (as the quarter of the blocks that a bf16 gradient takes, 96 <- 448 ran 31.5 us instead of 17.2)."""
