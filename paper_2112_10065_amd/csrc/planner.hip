@@ -124,6 +124,9 @@ double price(const ConvGeom &g, int pass, const Candidate &c, const GemmPlan &pl
     } else {
         const double w = blocks / conc;
         waves = w >= 4.0 ? w : 0.5 * (w + std::ceil(w));
+        // A persistent block's tiles come one after another: 10.2 us for 1.03 tiles per block as for 2, 14 for 2.02 as for 3.  Up to three rounds; beyond, where its price
+        // also stands against the 128-wide input-patch tiles (theirs is too low: they take 1.2 - 1.9 times as long), the mean of both as for the others
+        if (c.code == 404 && w < 3.0) waves = std::ceil((double)pl.tilesB / std::max(512 / pl.tilesA, 1));
     }
     // a step of reduction length 32 costs about half of a 64 step for the pixel passes
     double t_step = c.t_step;

@@ -339,6 +339,21 @@ def test_few_tiles_of_64_channels_keep_the_smallest_window_tile(dp):
     assert name(4, 9, 64, 256, 0, 0) == "k_halo_ws<0, false>"                # masks by its own y: keeps the order of its sums
 
 
+def test_stationary_weights_of_64_channels_are_priced_by_whole_rounds(dp):
+    """Host logic of the kernel choice (no GPU call): a layer with a little more than one or two tiles per persistent block pays for the next round; tiles or
+    the window kernel, which fill the chip evenly, run it.  Just below, and from three rounds on, it is the faster one."""
+    def name(n, h, w, c, k, pass_, pad=1, flags=dp.DP_RELU_IN):
+        return dp.dp_conv2d_kernel_info(dp.conv_desc(n, h, w, c, k, 3, 3, (1, 1), (pad, pad), dp.DP_BF16, dp.DP_RELU | flags), pass_)[0].split("<")[0]
+    assert name(25, 20, 20, 64, 240, 0, 0, 0) == "k_fwd_dma"         # 1.17 rounds: 10.7 us, 8.2; masks by its own y: no window kernel
+    assert name(22, 22, 19, 64, 232, 0, 0) == "k_fwd_dma"            # 1.03 rounds: 10.2, 7.9
+    assert name(19, 49, 49, 64, 128, 0) == "k_fwd_dma"               # 2.08 rounds: 14.7, 12.5
+    assert name(12, 46, 47, 64, 80, 0, 2) == "k_conv_win"            # 1.12 rounds: 10.3, 9.5
+    assert name(15, 41, 40, 128, 64, 1) == "k_conv_win"              # 1.05 rounds, backward-data: 10.8, 10.0
+    assert name(2, 79, 83, 64, 160, 0) == "k_halo_ws"                # 0.8 rounds
+    assert name(21, 67, 65, 64, 256, 0, 1, 0) == "k_halo_ws"         # 7.4 rounds: 33.5 for the 42.2 of 256x256 tiles
+    assert name(31, 35, 33, 64, 192, 0, 1, 0) == "k_halo_ws"         # 2.7 rounds: 15.3 for 20.6
+
+
 def test_strided_1x1_fp32_gradient_plan_is_the_one_that_runs(dp):
     """A strided 1x1 layer's fp32 input gradient goes in natural pixel order with all its blocks: its tiles and splits are priced as that
     (as the quarter of the blocks that a bf16 gradient takes, 96 <- 448 ran 31.5 us instead of 17.2)."""
