@@ -183,6 +183,10 @@ FORCED = [
     ("conv2_1", 32, 0, 403, 0, "k_halo<0, 64, 1, 4, 4>"), ("conv2_1", 2, 0, 401, 0, "k_halo<0, 128, 2, 2, 2>"),
     ("conv1_2", 32, 2, 410, 0, "k_wgrad_halo"), ("conv2_1", 32, 2, 410, 0, "k_wgrad_halo"), ("conv1_2", 2, 2, 410, 0, "k_wgrad_halo"),
     ("conv1_2", 32, 2, 411, 0, "k_wgrad_halo9<true>"), ("conv2_1", 16, 2, 411, 0, "k_wgrad_halo9<true>"), ("conv1_2", 1, 2, 411, 0, "k_wgrad_halo9<true>"),
+    # stationary weights, two blocks of 64 reduction channels
+    ("conv2_2", 32, 0, 405, 0, "k_halo_ws<0, false, 2>"), ("conv2_2", 32, 1, 405, 0, "k_halo_ws<1, true, 2>"), ("conv2_2", 1, 1, 405, 0, "k_halo_ws<1, true, 2>"),
+    ("conv3_1", 8, 0, 405, 0, "k_halo_ws<0, false, 2>"), ("conv2_1", 32, 1, 405, 0, "k_halo_ws<1, true, 2>"), ("conv1_2", 32, 1, 404, 0, "k_halo_ws<1, true>"),
+    ("conv2_1", 32, 0, 404, 0, "k_halo_ws<0, false>"),
     # pipelined tiles of the large batches and their filter-gradient forms with many splits
     ("conv2_2", 32, 0, 200, 1, "k_fwd_dma<128, 128, 64, 2, 2, 2, 1>"), ("conv4_2", 32, 1, 208, 1, "k_dgrad_dma<256, 256, 64, 2, 4, 2, 1>"),
     ("conv2_2", 32, 2, 300, 16, "k_wgrad_dma<128, 128, 32, 2, 2, 2>"), ("conv4_2", 32, 2, 312, 8, "k_wgrad_dma<256, 256, 64, 2, 4, 2>"),
@@ -211,6 +215,47 @@ def test_kernel_family_at_full_size(env, name, n, pas, variant, splits, kernel):
         check_conv_point(dp, U, orc, L, n, f"{name} N={n} {kernel} x{got_splits}", masked_forms=False, passes=(pas,))
     finally:
         dp.dp_set_override(pas, -1, 0)
+
+
+# (n, h, c, k, stride, pass, variant code): the 1x1 layers of the residual block that changes resolution, and the longest reduction
+POINTWISE = [(64, 56, 256, 128, 1, 0, 261), (64, 56, 256, 128, 1, 1, 262), (64, 28, 128, 512, 1, 0, 262), (64, 28, 128, 512, 1, 1, 261), (64, 56, 256, 512, 2, 0, 262),
+             (64, 56, 64, 256, 1, 0, 260), (64, 28, 512, 512, 1, 0, 261), (64, 28, 512, 512, 1, 1, 261)]
+
+
+@pytest.mark.parametrize("n,h,c,k,st,pas,variant", POINTWISE, ids=["_".join(map(str, p)) for p in POINTWISE])
+def test_pointwise_stationary_weights_at_full_size(env, n, h, c, k, st, pas, variant):
+    """The 1x1 kernels with stationary weights at the block's whole batch: bit for bit the result of the unsplit 64x64 tiles, and sampled against the oracle."""
+    dp, U, orc = env
+    ho = (h - 1) // st + 1
+    g = torch.Generator(device=U.DEV)
+    g.manual_seed(n + h + c + k + st)
+    rnd = lambda *s: torch.randn(s, generator=g, device=U.DEV)
+    x, w, b, dy = rnd(n, h, h, c).relu_().bfloat16(), (rnd(k, 1, 1, c) * (2.0 / c) ** 0.5).bfloat16(), rnd(k), rnd(n, ho, ho, k).bfloat16()
+    d = dp.conv_desc(n, h, h, c, k, 1, 1, (st, st), (0, 0), dp.DP_BF16, dp.DP_BIAS | dp.DP_RELU | dp.DP_RELU_IN)
+    outs = []
+    try:
+        for code, splits, name in ((variant, 0, "k_pointwise<"), (207, 1, "k_fwd_dma<64, 64, " if pas == 0 else "k_dgrad_dma<64, 64, ")):
+            dp.dp_set_override(pas, code, splits)
+            assert dp.dp_conv2d_kernel_info(d, pas)[0].startswith(name)
+            out = torch.full((n, ho, ho, k) if pas == 0 else (n, h, h, c), 3.0, dtype=torch.bfloat16, device=U.DEV)
+            ws = U.workspace(dp.dp_conv2d_workspace_bytes(d, pas))
+            if pas == 0:
+                dp.dp_conv2d_fwd(d, x, w, b, out, ws)
+            else:
+                dp.dp_conv2d_bwd_data_relu(d, dy, None, w, x, out, ws)
+            outs.append(out)
+        torch.cuda.synchronize()
+    finally:
+        dp.dp_set_override(pas, -1, 0)
+    assert torch.equal(outs[0], outs[1])
+    idx = _sample(np.random.default_rng(n + c + k), outs[0].numel(), 3000, 64)
+    got = U.to_np(outs[0].flatten()[torch.from_numpy(idx).to(U.DEV)])
+    xh, wh, dyh = U.to_np(x), U.to_np(w), U.to_np(dy)
+    if pas == 0:
+        want = orc.conv2d_fwd_at(xh, wh, U.to_np(b), True, (st, st), (0, 0), idx)
+    else:
+        want = orc.relu_in_backward(orc.conv2d_bwd_data_at(dyh, wh, xh.shape, None, (st, st), (0, 0), idx), xh.ravel()[idx])
+    assert U.errs(got, want)[0] <= 2.5e-3   # bf16 outputs: relative error 2^-9 each at most, half of that in the mean
 
 
 @pytest.mark.parametrize("name", [l.name for l in _linears()])

@@ -500,9 +500,9 @@ def test_backward_data_phases_take_turns(env, n, h, w, c, k, st, tiles):
 
 @pytest.mark.parametrize("blocks", [0, 3, 40])
 def test_input_patch_filter_gradient_all_taps_per_wave(env, blocks):
-    """The 3x3 form of the input-patch filter gradient with all nine taps in one wave (four waves: two pixel groups x two halves of
-    c_in; sums of the pixel groups meet in LDS at the end): both tile shapes, ragged edges, c_out below / above one 64-row tile,
-    padding 0 and 1, one block with many tiles and more blocks than tiles, with and without the fused bias gradient."""
+    """The 3x3 form of the input-patch filter gradient with all nine taps in one wave (eight waves: two pixel groups x two halves of
+    c_out x two halves of c_in; sums of the pixel groups meet in LDS at the end): ragged 8 x 16 tiles, c_out below / above one 64-row tile,
+    padding 0 and 1, blocks with many tiles and more blocks than tiles, with and without the fused bias gradient."""
     dp, U, orc = env
     dp.dp_set_override(2, 411, blocks)
     try:
@@ -608,7 +608,7 @@ RELU_IN_CASES = [
 @pytest.mark.parametrize("spec", RELU_IN_CASES, ids=[c[0] for c in RELU_IN_CASES])
 def test_backward_data_with_fused_input_relu(env, spec):
     """DP_RELU_IN: dx * [x > 0] leaves in the epilogue of every backward-data kernel family (staged and direct
-    stores, split reductions, input-patch kernels; the stationary-weight kernel hands over to another one)."""
+    stores, split reductions, input-patch and stationary-weight kernels)."""
     dp, U, orc = env
     tag, n, h, w, c, k, r, s_, st, pd, bf16, dxf, overrides = spec
     case = U.ConvCase(tag, n, h, w, c, k, r, s_, st, pd, bf16=bf16, bias=True, relu=True, dx_f32=dxf)
@@ -663,10 +663,10 @@ def test_dense_backward_with_fused_input_relu(env):
         assert np.array_equal(U.to_np(dx) == 0, want == 0)
 
 
-@pytest.mark.parametrize("blocks", [0, 1, 7])
+@pytest.mark.parametrize("blocks", [0, 1, 2, 7])
 def test_input_patch_stationary_weights(env, blocks):
-    """3x3, stride 1, 64 reduction channels: persistent kernel with the weight fragments in registers.  Block
-    counts below the tile count make every block walk several tiles (both patch buffers, delayed stores)."""
+    """3x3, stride 1, 64 reduction channels: persistent kernel with the weight fragments in registers.  Block counts (2, 7; 0 and 1 are the
+    default) below the tile count make every block walk several tiles, so that its three patch buffers turn over, with and without both masks."""
     dp, U, orc = env
     dp.dp_set_override(0, 404, blocks)
     dp.dp_set_override(1, 404, blocks)
@@ -683,9 +683,10 @@ def test_input_patch_stationary_weights(env, blocks):
             case = U.ConvCase(tag, n, h, w, c, 64, 3, 3, (1, 1), pd, bf16=True, bias=True, relu=True)
             assert "k_halo_ws<1, " in dp.dp_conv2d_kernel_info(case.desc, 1)[0]
             y = case.run_fwd()
-            dx = case.run_dgrad(y)
-            torch.cuda.synchronize()
-            U.assert_bf16_close(U.to_np(dx), orc.conv2d_bwd_data(case.dy, case.w, case.x.shape, y_saved=U.to_np(y), pad=pd), f"{tag} blocks {blocks} dx")
+            ref = orc.conv2d_bwd_data(case.dy, case.w, case.x.shape, y_saved=U.to_np(y), pad=pd)
+            for dx, want in ((case.run_dgrad(y), ref), (case.run_dgrad_relu_in(y), orc.relu_in_backward(ref, case.x))):
+                torch.cuda.synchronize()
+                U.assert_bf16_close(U.to_np(dx), want, f"{tag} blocks {blocks} dx")
         # other filter shapes and fp32 gradients are not this kernel's
         case = U.ConvCase("ws_1x7", 1, 9, 33, 64, 64, 1, 7, (1, 1), (0, 3), bf16=True, bias=True, relu=True)
         assert "k_halo_ws" not in dp.dp_conv2d_kernel_info(case.desc, 0)[0]
@@ -1068,22 +1069,30 @@ def test_nine_tap_layers_with_less_scratch(env, saved):
 
 
 # (pass, variant, saved output).  The window kernels 250 .. 258: on images whose windows leave room for a block of the other streams (251, 252, 256), and
-# others; the filter gradient's (317, 318) fills a compute unit alone
+# others; the filter gradient's (317, 318) fills a compute unit alone.  Stationary weights (404, 260 .. 262) with one block per compute unit, 74 - 80 KB; 405 fills
+# one alone, its blocks with three tiles each
 @pytest.mark.parametrize("pass_,variant,saved", [(0, 231, False), (0, 232, False), (1, 231, False), (1, 232, False), (1, 233, False), (2, 316, False), (2, 411, False),
                                                  (0, 250, False), (0, 251, False), (0, 252, False), (0, 256, False), (1, 251, False), (1, 252, False), (1, 256, False), (1, 258, False),
-                                                 (1, 251, True), (1, 253, True), (1, 256, True), (2, 317, False), (2, 318, False)])
+                                                 (1, 251, True), (1, 253, True), (1, 256, True), (2, 317, False), (2, 318, False),
+                                                 (0, 404, False), (1, 404, False), (1, 404, True), (0, 405, False), (1, 405, False), (1, 405, True),
+                                                 (0, 260, False), (0, 261, False), (0, 262, False), (1, 260, False), (1, 261, False), (1, 262, False), (1, 261, True)])
 def test_results_do_not_depend_on_other_streams(env, pass_, variant, saved):
     """The kernels that hand-order their LDS reads, beside small blocks of other kernels on the same compute units (filter gradients on two
     other streams): bit for bit the result of the kernel alone.  An LDS read that was still in flight when the epilogue began used to
     overwrite a sum when those blocks delayed it."""
     dp, U, orc = env
     n, h, c, k = (4, 112, 64, 128) if variant == 411 else (32, 14, 256, 256) if 250 <= variant < 260 else (8, 56, 256, 256)
+    red = {404: 64, 405: 128, 260: 128, 261: 128, 262: 128}.get(variant)   # stationary weights: reduction channels
+    if red:
+        n, h, c, k = (8, 112, red, 128) if pass_ == 0 else (8, 112, 128, red)
+    r = 1 if 260 <= variant <= 262 else 3
+    blocks = {404: 128, 405: 128, 260: 128, 261: 256, 262: 256}.get(variant, 1)   # per tile of 64 (262: 256, 261: 128) channels
     g = torch.Generator(device=U.DEV)
     g.manual_seed(7)
     rnd = lambda *s: torch.randn(s, generator=g, device=U.DEV).to(torch.bfloat16)
-    x, w, dy = rnd(n, h, h, c), rnd(k, 3, 3, c), rnd(n, h, h, k)
+    x, w, dy = rnd(n, h, h, c), rnd(k, r, r, c), rnd(n, h, h, k)
     y = rnd(n, h, h, k) if saved else None
-    d = dp.conv_desc(n, h, h, c, k, 3, 3, (1, 1), (1, 1), dp.DP_BF16, dp.DP_RELU_IN)
+    d = dp.conv_desc(n, h, h, c, k, r, r, (1, 1), (r // 2, r // 2), dp.DP_BF16, dp.DP_RELU_IN)
     bx, bdy = rnd(8, 56, 56, 256), rnd(8, 56, 56, 256)
     bd = dp.conv_desc(8, 56, 56, 256, 256, 3, 3, (1, 1), (1, 1), dp.DP_BF16, 0)
     dp.dp_set_override(2, 303, 0)    # blocks of 28 KB of LDS: they fit beside a block of the strip kernels
@@ -1091,10 +1100,12 @@ def test_results_do_not_depend_on_other_streams(env, pass_, variant, saved):
     bdw = [torch.empty((256, 3, 3, 256), device=U.DEV) for _ in range(2)]
     streams = [torch.cuda.Stream() for _ in range(2)]
     try:
-        dp.dp_set_override(pass_, variant, 1)
+        dp.dp_set_override(pass_, variant, blocks)
         ws = U.workspace(dp.dp_conv2d_workspace_bytes(d, pass_))
-        window = {317: "k_wgrad_win<128", 318: "k_wgrad_win<256"}.get(variant, "k_conv_win" if 250 <= variant < 260 else "")
-        assert dp.dp_conv2d_kernel_info(d, pass_)[0].startswith(window)
+        kernel = {317: "k_wgrad_win<128", 318: "k_wgrad_win<256", 411: "k_wgrad_halo9<", 404: "k_halo_ws<", 405: "k_halo_ws<"}.get(
+            variant, "k_conv_win" if 250 <= variant < 260 else "k_pointwise<" if r == 1 else "")
+        name = dp.dp_conv2d_kernel_info(d, pass_)[0]
+        assert name.startswith(kernel) and (not kernel.startswith("k_halo_ws") or name.endswith(", 2>") == (variant == 405)), name
 
         def launch():
             out = torch.empty((n, h, h, k) if pass_ == 0 else (n, h, h, c) if pass_ == 1 else (k, 3, 3, c), device=U.DEV,
@@ -1116,7 +1127,7 @@ def test_results_do_not_depend_on_other_streams(env, pass_, variant, saved):
             for s, sw, o in zip(streams, bws, bdw):
                 for _ in range(3):
                     dp.dp_conv2d_bwd_filter(bd, bx, bdy, None, o, None, sw, stream=s)
-            dp.dp_set_override(pass_, variant, 1)
+            dp.dp_set_override(pass_, variant, blocks)
             outs += [launch() for _ in range(3)]
             torch.cuda.synchronize()
             wrong += sum(int(not torch.equal(o, ref)) for o in outs)
