@@ -276,20 +276,6 @@ __global__ __launch_bounds__(64 * WA * WB) void k_halo(const KArgs p, int tws, i
     }
 }
 
-// Tiles of a persistent block.  Consecutive block ids go round-robin to the 8 XCDs, each with an L2 of its own: XCD x (blocks x,
-// x + 8, ...) walks one contiguous eighth of the tile list, its blocks side by side, so that tiles that share halo pixels (left /
-// right neighbours, and the row of tiles above / below) run on one XCD at about the same time and the second reader of a halo pixel
-// finds it in that L2.  (Dealing the tiles out block by block over the whole chip, every halo pixel was fetched from memory again: L2
-// hit rate 0.09 on conv1_2, and the copies of a CU are bound by its ~64 outstanding misses.)
-struct TileWalk { int first, end, stride; };
-DEVFN TileWalk tile_walk(int tiles)
-{
-    const int nb = gridDim.x;
-    if ((nb & 7) != 0) return {(int)blockIdx.x, tiles, nb};
-    const int x = blockIdx.x & 7;
-    return {(int)((long long)tiles * x / 8) + (int)(blockIdx.x >> 3), (int)((long long)tiles * (x + 1) / 8), nb >> 3};
-}
-
 // Filter gradient, what a product over whole tiles does not give: a tile that reaches past the last row or column holds zeros of dy there, and they meet the
 // pixels of x that lie in the patch beside them (or padding's zeros meet a dy).  Zero times infinity is NaN, so a sum with a NaN is made again from the pairs
 // that the tap has: dW[row .. row + 3][tap][col] over this block's tiles of th x tw pixels.  Line by line, so that the sums stay as short as the
@@ -695,7 +681,7 @@ __global__ __launch_bounds__(512, 2) void k_wgrad_halo9(const KArgs p, int tiles
 // SIMD and one multiplies while the other waits, converts or stores.  A wave keeps the fragments of 32
 // output channels for all nine taps (36 fragments, 144 registers) and multiplies them with 64 of the
 // tile's 128 pixels (8 x 16); nothing but the input patch goes through LDS and no barrier separates the
-// taps.  Blocks are persistent (two per CU and 64-channel tile) and keep three patch buffers: while tile i
+// taps.  Blocks are persistent (two per CU over all 64-channel tiles) and keep three patch buffers: while tile i
 // is multiplied, the patches of tiles i+1 and i+2 are on their way.  A wave's results are reordered in its own
 // share of the patch buffer that the tile has just left, and go out 64 bytes per pixel.  One barrier per tile.
 // Patch layout: the pixel in column pc has its chunk c at position c ^ ((pc >> 1) & 7): sixteen pixels of a row are
@@ -703,8 +689,9 @@ __global__ __launch_bounds__(512, 2) void k_wgrad_halo9(const KArgs p, int tiles
 // What bounds it: with one wave per SIMD holding all 64 channels (288 registers) every wait, conversion and store of the wave was the
 // SIMD's; the LDS reads per matrix instruction have doubled and are still half of what LDS gives.  16 x 224 x 224, 64 -> 64 (us, back to back /
 // with flushed caches): forward 76 / 84 -> 56 / 68, masked backward-data 89 / 112 -> 64 / 102 (without its loads and stores 46 and 42: the matrix
-// instructions and LDS reads alone).  The faster of all kernels from a few tiles on (180 layers of 32 - 450 channels, 7 - 224 pixels: 0.95 - 1.4
-// times the best other; below 100 tiles 5.5 - 6.2 us like the others).
+// instructions and LDS reads alone).  180 layers of 32 - 450 channels, 7 - 224 pixels: 0.95 - 1.4 times as fast as the best other.  Not where a block has little more
+// than one or two tiles (price()), nor below 80 tiles, where the smallest window tile is (pixel_window_plan).  The 128-wide input-patch tiles take 1.2 - 1.9 times
+// as long, but their price is too low and still keeps some layers of many tiles with them (15 x 221 x 214, 64 -> 128 forward).
 // ---------------------------------------------------------------------------------------
 // 128 reduction channels (RH = 2), us back to back / with flushed caches, the best other kernel -> this one: 32 x 112 x 112, 128 -> 128 forward 145 / 156 ->
 // 107 / 115 (1.1 PFLOP/s), masked backward-data 159 / 170 -> 114 / 132; 64 <- 128 93 / 128 -> 59 / 75, at 8 samples 41 / 53 -> 23 / 30, at 2 12.7 / 16.7 -> 8.4 / 12.8.
@@ -715,8 +702,6 @@ constexpr int WS_PATCH = 4 * WS_CPW * 1024;   // 24 KiB per patch buffer
 constexpr int WS_LDS = 3 * WS_PATCH + 64 * 4, WS_LDS2 = 6 * WS_PATCH + 64 * 4;   // one and two blocks of reduction channels
 static_assert(WS_PP <= 4 * WS_CPW * 8 && 2 * WS_LDS <= 160 * 1024 && WS_LDS2 <= 160 * 1024 && 4096 + 2048 <= WS_CPW * 1024, "a patch fits its copies, two blocks a CU");
 static_assert(3 * 8192 <= WS_PATCH && 64 * 64 <= WS_CPW * 1024, "three taps of weights, and a wave's results, fit a patch buffer");
-
-DEVFN void lds_write16(unsigned addr, u32x4 v) { asm volatile("ds_write_b128 %0, %1" ::"v"(addr), "v"(v) : "memory"); }
 
 // MASK (backward-data): fused backward of the ReLU in front of the layer.  RH: blocks of 64 reduction channels.  With two of them a block has eight waves and a
 // CU one block: waves 4 - 7 hold the weights of the second 64 channels and multiply the same pixels; each wave hands the sums of one of its two pixel
@@ -1048,7 +1033,7 @@ hipError_t halo_init()
     return hipSuccess;
 }
 
-// variant override 400 + v; forward needs c_in == 64, backward-data c_out == 64; stride 1; no reduction split
+// variant override 400 + v; forward needs c_in == 64, backward-data c_out == 64 (405: 128); stride 1; no reduction split
 bool halo_plan(const ConvGeom &g, int pass, int force_variant, int force_splits, GemmPlan *pl)
 {
     if (pass == PASS_WGRAD) {   // 410: input-patch filter gradient, a wave per tap; 411: 3x3, all taps per wave; force_splits = number of persistent blocks

@@ -2,7 +2,7 @@
 //
 // These layers stream: 64 x 56 x 56, 256 -> 128 channels moves 154 MB for 13 GFLOP.  A tiled kernel spends a block on each tile,
 // with weights, a pipeline to fill and an epilogue of its own for 2 - 8 reduction steps, and reads the pixels once per channel tile.
-// Here blocks are persistent (two per CU and channel tile, so that one multiplies or stores while the other waits): a wave keeps
+// Here blocks are persistent (two per CU over all channel tiles, so that one multiplies or stores while the other waits): a wave keeps
 // the weights of its 32 or 64 output channels for the whole reduction (up to 512 channels) and the pixels go by through a ring of
 // LDS buffers, NB - 1 of them on their way at any time.  One barrier per buffer; results are reordered in the wave's own staging area and
 // go out 64 or 128 bytes per pixel; the saved input of a masked tile is asked for a whole buffer ahead.
@@ -33,18 +33,6 @@ template <int TC, int AW, int WC> struct Pw {
 
 // out of range of any tensor, and so is what is added to it: tensors are smaller than 2 GiB
 constexpr unsigned FAR = 0x80000000u;
-
-DEVFN void lds_write16(unsigned addr, u32x4 v) { asm volatile("ds_write_b128 %0, %1" ::"v"(addr), "v"(v) : "memory"); }
-
-// contiguous eighths of the tiles per compute die, as the dies take the blocks in turn
-struct Walk { int first, end, stride; };
-DEVFN Walk walk(int tiles)
-{
-    const int nb = gridDim.x;
-    if ((nb & 7) != 0) return {(int)blockIdx.x, tiles, nb};
-    const int x = blockIdx.x & 7;
-    return {(int)((long long)tiles * x / 8) + (int)(blockIdx.x >> 3), (int)((long long)tiles * (x + 1) / 8), nb >> 3};
-}
 
 // OPT: forward: the input is strided or padded; backward-data: fused backward of the ReLU in front of the layer
 template <int PASS, int TC, int AW, int WC, bool OPT>
@@ -148,7 +136,7 @@ __global__ __launch_bounds__(256, 2) void k_pointwise(const KArgs p, int tiles)
     });
     __builtin_amdgcn_s_barrier();   // the ring is free
 
-    const Walk tw = walk(tiles);
+    const TileWalk tw = tile_walk(tiles);
     int tile = tw.first;
 #pragma unroll
     for (int j = 0; j < NB - 1; ++j) copy_tile(tile + j * tw.stride, smem_base + j * D::BUF, tile + j * tw.stride < tw.end);

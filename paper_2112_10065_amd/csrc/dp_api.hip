@@ -153,8 +153,8 @@ bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 
 constexpr long long kMaxElems = (1ll << 31) - 1;
 constexpr unsigned kKnownFlags = DP_BIAS | DP_RELU | DP_DETERMINISTIC | DP_DX_F32 | DP_RELU_IN;
-// kernels a backward-data call may not use: bit 0 the input-patch kernels (they stage bf16, the caller wants fp32),
-// bit 1 the stationary-weight kernel (it has no fused input-ReLU mask); dgrad_choice adds bits 3 and 4 (dp_kernels.h)
+// backward-data: bit 0: fp32 gradients, which the input-patch, pixel-strip and stationary-weight kernels do not store; bit 1: the saved input masks the
+// gradient, which is priced; dgrad_choice adds bits 3 and 4 (dp_kernels.h)
 int dgrad_restr(unsigned flags) { return ((flags & DP_DX_F32) ? 1 : 0) | ((flags & DP_RELU_IN) ? 2 : 0); }
 // A layer whose gradients are masked by its own y keeps the order in which y is summed (forward_flat_plan).  The flags tell such a layer only where it stands
 // alone: in a chain (DP_RELU_IN) the layer behind masks by this y, and its order is the window kernel's.  The measured choice goes by time and keeps

@@ -132,7 +132,7 @@ bool dma_plan(const ConvGeom &g, int pass, int force_variant, int force_splits, 
 hipError_t dma_launch(const ConvArgs &a, hipStream_t st);
 void dma_kernel_name(int pass, const GemmPlan &plan, char *name, size_t name_bytes);
 
-// conv_halo.hip : input patch with halo resident in LDS (stride 1, 64 reduction channels per tap)
+// conv_halo.hip : input patch with halo resident in LDS (stride 1, 64 reduction channels per tap; 3x3 also 128)
 hipError_t halo_init();
 bool halo_plan(const ConvGeom &g, int pass, int force_variant, int force_splits, GemmPlan *plan);
 hipError_t halo_launch(const ConvArgs &a, hipStream_t st);
@@ -181,7 +181,7 @@ int wgrad_window_plans(const ConvGeom &g, GemmPlan out[2], double times[2]);
 bool wgrad_window_plan(const ConvGeom &g, const GemmPlan &base, double time, GemmPlan *out);
 bool wgrad_window_form(const ConvGeom &g, GemmPlan *out);
 // the cheapest plans by the model, best first (input of the measured choice); returns the count
-// restr: kernels the call may not use (bit 0: input-patch kernels, bit 1: the stationary-weight kernel)
+// restr: bit 0: fp32 gradients (not from kernels that stage bf16), bit 1: masked by the saved input, bit 2: the caller measures with cold caches; others above
 int auto_plan_list(const ConvGeom &g, int pass, int force_splits, GemmPlan *out, int max_out, int restr = 0, double *times = nullptr);
 
 // small_c.hip : explicit im2col for layers with very few input channels (c_in % 8 != 0, R*S*C <= 256)

@@ -51,7 +51,7 @@ const Candidate kPix[] = {
     {402, 2, 0.75f, 5.5f},
     {403, 2, 0.72f, 5.5f},
     {404, 2, 0.40f, 0.8f},   // 3x3 only: persistent blocks, weights in registers (180 layers: 8 % in the median)
-    {405, 1, 0.20f, 3.7f},   // the same for 128 reduction channels: see price()
+    {405, 1, 3.66f, 7.9f},   // the same for 128 reduction channels, by rounds of tiles: 4.4 us and 4.1 a round (240 timings, 3 - 8 %) in the currency of the tiles above
     {100, 2, 1.40f, 5.0f},   // register-staged fallbacks (also reduction step 32)
     {101, 3, 1.05f, 4.5f},
     {102, 3, 1.05f, 4.5f},
@@ -80,7 +80,9 @@ const Candidate kWg[] = {
     {312, 1, 2.90f, 7.0f},   // 256x256x64, 8 waves
     {316, 1, 1.60f, 9.0f},   // 3x3 stride 1: 256 x (3 taps x 64 channels), x strip shared by the taps, padded pixel slots
     {410, 1, 0.13f, 6.0f},   // input patch in LDS, persistent blocks (64 input channels, stride 1); a step = 16 pixels
-    {411, 1, 0.10f, 8.0f},   // the same for 3x3 filters with all nine taps in one wave
+    // the same for 3x3 filters with all nine taps in one wave.  With 6.0 it was the cheapest more often, and the window kernel then took its place by 1.35 of its price;
+    // at 8.0 split tiles are, and stay (147 of 24000 layers: 0.82 - 1.08 of the window kernel's time, 0.91 in the middle, with flushed caches 0.94)
+    {411, 1, 0.10f, 8.0f},
     {100, 3, 1.30f, 4.0f},
     {101, 3, 1.00f, 3.5f},
     {102, 3, 1.00f, 3.5f},
@@ -113,8 +115,7 @@ double price_window(const ConvGeom &g, const GemmPlan &pl)
 double price(const ConvGeom &g, int pass, const Candidate &c, const GemmPlan &pl, int restr)
 {
     const double blocks = (double)pl.tilesA * pl.tilesB * pl.splits;
-    // Stationary weights of 128 reduction channels take 4.4 us and 4.1 per round of tiles (240 timings, 3 - 8 %), in the currency of the tiles beside them
-    if (c.code == 405) return 7.9 + 3.66 * std::ceil(blocks / 256.0);
+    if (c.code == 405) return c.t0 + c.t_step * std::ceil(blocks / 256.0);
     const double conc = 256.0 * c.bpc;
     double share = 1.0, waves;
     if (blocks <= conc) {
