@@ -31,79 +31,82 @@ HBM_PEAK_GBS = 8000.0
 # HBM bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, scaled by a 1 GiB copy kernel), averaged over
 # the launches of each kernel at one per-GPU batch: profiles/vgg16_hbm_traffic.md
 TRAFFIC_BYTES_PER_LAUNCH = {   # key: "<kernel as the profiler prints it>@<per-GPU batch>"
-    "k_wgrad_win<256, true, true>@32": 107069726,
-    "k_conv_strip<false, 224, 256>@32": 111272838,
-    "k_wgrad_halo9<true>@32": 320884149,
-    "k_halo_ws<1, true>@32": 618229222,
-    "k_conv_strip<true, 256, 128>@32": 200718693,
-    "k_halo_ws<0, false>@32": 283802718,
-    "k_wgrad_dma<128, 128, 32, 2, 2, 2>@32": 424909438,
-    "k_conv_strip<true, 256, 256>@32": 170817672,
-    "k_wgrad_dma<64, 128, 32, 2, 2, 2>@32": 424480974,
-    "k_conv_strip<true, 224, 256>@32": 168279364,
-    "k_wgrad_dma<256, 256, 64, 2, 4, 2>@32": 160291430,
-    "k_fwd_rgb3@32": 230255220,
-    "k_fwd_dma<128, 64, 64, 2, 2, 2, 1>@32": 227014038,
-    "k_conv_strip<false, 256, 128>@32": 221710770,
-    "k_wgrad_rgb3<true>@32": 220906972,
-    "k_reduce_flat@32": 36440574,
-    "k_dgrad_dma<64, 128, 64, 2, 2, 2, 1>@32": 212756012,
-    "k_dgrad_dma<64, 64, 64, 2, 2, 2, 2>@32": 211272441,
-    "k_conv_win<true, 4, 1, 4, false>@32": 57687055,
-    "k_fwd_dma<64, 128, 64, 2, 2, 2, 1>@32": 51887320,
-    "k_reduce_flat_wide@32": 31901443,
-    "k_conv_strip<true, 128, 256>@32": 72420602,
-    "k_dense_wgrad<true>@32": 69701822,
-    "k_conv_win<false, 4, 1, 4, false>@32": 51290109,
-    "k_fwd_dma<128, 64, 64, 2, 2, 2, 2>@32": 40117663,
-    "k_dgrad_dma<64, 64, 64, 2, 2, 3, 1>@32": 40071370,
-    "k_fwd_dma<64, 64, 64, 2, 2, 2, 2>@32": 20975182,
-    "k_reduce_pixel_major@32": 4822608,
-    "k_dense_wgrad<false>@32": 18720447,
-    "k_fwd_dma<64, 64, 64, 2, 2, 2, 4>@32": 12047265,
-    "k_dense_dgrad@32": 9297713,
-    "k_wgrad_direct_sum@32": 4299933,
-    "k_wgrad_dma<64, 256, 32, 1, 4, 2>@2": 227181982,
-    "k_wgrad_dma<256, 128, 32, 4, 2, 2>@2": 412135672,
-    "k_dense_fwd<1>@2": 82872272,
-    "k_wgrad_dma<64, 64, 32, 2, 2, 2>@2": 76681330,
-    "k_dense_both<32, false>@2": 207348122,
-    "k_conv_win<true, 1, 2, 1, false>@2": 39462251,
-    "k_conv_win<false, 1, 2, 1, false>@2": 39076041,
-    "k_conv_win<false, 2, 1, 2, false>@2": 35257885,
-    "k_wgrad_dma<128, 128, 64, 2, 2, 2>@2": 52646550,
-    "k_dgrad_dma<64, 64, 64, 2, 2, 2, 4>@2": 44429771,
-    "k_reduce_flat_wide@2": 26284035,
-    "k_reduce_flat@2": 24450366,
-    "k_dense_wgrad<true>@2": 67497995,
-    "k_conv_win<false, 3, 1, 2, false>@2": 31810636,
-    "k_wgrad_win<256, true, true>@2": 22615199,
-    "k_conv_win<true, 2, 1, 4, false>@2": 19945669,
-    "k_halo<1, 64, 1, 4, 4>@2": 39682824,
-    "k_wgrad_dma<128, 64, 32, 2, 2, 2>@2": 97404668,
-    "k_wgrad_dma<128, 128, 32, 2, 2, 2>@2": 38299195,
-    "k_conv_win<true, 2, 1, 2, false>@2": 17575604,
-    "k_dense_both<8, false>@2": 34689278,
-    "k_conv_win<false, 2, 1, 4, false>@2": 16756118,
-    "k_dgrad_dma<64, 128, 64, 2, 2, 2, 1>@2": 26639336,
-    "k_wgrad_dma<64, 128, 64, 2, 2, 2>@2": 23692340,
-    "k_fwd_dma<128, 128, 64, 2, 2, 2, 1>@2": 13527517,
-    "k_halo<0, 64, 1, 4, 3>@2": 26799808,
-    "k_conv_win<false, 4, 1, 2, false>@2": 13197510,
-    "k_halo<0, 64, 1, 4, 2>@2": 20371546,
-    "k_fwd_dma<64, 64, 64, 2, 2, 2, 2>@2": 8935088,
-    "k_conv_fast<1, 64, 128, 64, 2, 2>@2": 22241941,
-    "k_fwd_rgb3@2": 14118036,
-    "k_dense_wgrad<false>@2": 16639420,
-    "k_halo_ws<1, true>@2": 39765058,
-    "k_fwd_dma<64, 128, 64, 2, 2, 2, 1>@2": 15832992,
-    "k_wgrad_rgb3<true>@2": 15737294,
-    "k_wgrad_dma<64, 128, 32, 2, 2, 2>@2": 18585390,
-    "k_dgrad_dma<64, 64, 64, 2, 2, 3, 1>@2": 14595835,
-    "k_dense_dgrad@2": 8326977,
-    "k_dgrad_dma<128, 64, 128, 2, 2, 2, 1>@2": 19832451,
-    "k_dense_both_sum@2": 1484767,
-    "k_wgrad_direct_sum@2": 1714904,
+    "k_wgrad_win<256, true, true>@32": 109323900,
+    "k_conv_strip<false, 224, 256>@32": 118621361,
+    "k_wgrad_halo9<true>@32": 320668100,
+    "k_halo_ws<1, true>@32": 635401455,
+    "k_conv_strip<true, 224, 256>@32": 156280267,
+    "k_halo_ws<0, false>@32": 305979010,
+    "k_halo_ws<1, true, 2>@32": 258832090,
+    "k_wgrad_dma<128, 128, 32, 2, 2, 2>@32": 235826022,
+    "k_wgrad_dma<64, 256, 32, 1, 4, 2>@32": 424928320,
+    "k_wgrad_dma<64, 128, 32, 2, 2, 2>@32": 424319778,
+    "k_conv_strip<true, 256, 256>@32": 174735134,
+    "k_halo_ws<0, false, 2>@32": 170686989,
+    "k_conv_win<true, 2, 1, 4, false>@32": 96966144,
+    "k_fwd_rgb3@32": 230261476,
+    "k_reduce_flat@32": 39593917,
+    "k_fwd_dma<128, 128, 64, 2, 2, 2, 1>@32": 227056090,
+    "k_conv_strip<true, 256, 128>@32": 111436693,
+    "k_fwd_dma<64, 64, 64, 2, 2, 3, 1>@32": 222735923,
+    "k_wgrad_rgb3<true>@32": 220909295,
+    "k_dgrad_dma<64, 64, 64, 2, 2, 3, 1>@32": 211057280,
+    "k_dgrad_dma<128, 64, 64, 2, 2, 2, 2>@32": 211055616,
+    "k_conv_win<true, 4, 1, 4, false>@32": 57688366,
+    "k_conv_win<false, 4, 1, 4, false>@32": 51291415,
+    "k_wgrad_dma<256, 256, 64, 2, 4, 2>@32": 135421764,
+    "k_reduce_flat_wide@32": 31902214,
+    "k_dense_wgrad<true>@32": 69701777,
+    "k_fwd_dma<64, 64, 64, 2, 2, 2, 2>@32": 24564924,
+    "k_dgrad_dma<64, 64, 64, 2, 2, 2, 2>@32": 37972992,
+    "k_dgrad_dma<64, 64, 64, 2, 2, 2, 4>@32": 37969920,
+    "k_dense_wgrad<false>@32": 18720365,
+    "k_reduce_pixel_major@32": 3505929,
+    "k_dense_dgrad@32": 9298057,
+    "k_wgrad_direct_sum@32": 4300032,
+    "k_wgrad_dma<128, 128, 32, 2, 2, 2>@2": 421155379,
+    "k_wgrad_dma<128, 64, 32, 2, 2, 2>@2": 172220439,
+    "k_wgrad_dma<64, 128, 64, 2, 2, 2>@2": 89388336,
+    "k_dense_fwd<1>@2": 82874007,
+    "k_dense_both<32, false>@2": 207353555,
+    "k_conv_win<true, 1, 2, 1, false>@2": 39565470,
+    "k_conv_win<true, 2, 1, 2, false>@2": 30669338,
+    "k_conv_win<false, 1, 2, 1, false>@2": 39076958,
+    "k_reduce_flat@2": 35858569,
+    "k_conv_win<false, 2, 1, 2, false>@2": 41960602,
+    "k_wgrad_halo9<true>@2": 35888597,
+    "k_dense_wgrad<true>@2": 67493871,
+    "k_reduce_flat_wide@2": 20725083,
+    "k_fwd_dma<64, 64, 64, 2, 2, 2, 2>@2": 18940590,
+    "k_wgrad_dma<64, 64, 32, 2, 2, 2>@2": 18031206,
+    "k_wgrad_dma<128, 128, 64, 2, 2, 2>@2": 48336896,
+    "k_wgrad_win<256, true, true>@2": 24089472,
+    "k_wgrad_halo@2": 43279360,
+    "k_dgrad_dma<64, 128, 128, 2, 2, 2, 1>@2": 19954244,
+    "k_halo<1, 64, 1, 4, 4>@2": 39683072,
+    "k_halo<1, 64, 1, 4, 2>@2": 39677286,
+    "k_halo_ws<1, true, 2>@2": 19256503,
+    "k_dgrad_dma<64, 64, 64, 2, 2, 3, 1>@2": 18095445,
+    "k_dense_both<8, false>@2": 34690150,
+    "k_fwd_dma<64, 128, 64, 2, 2, 2, 2>@2": 16642756,
+    "k_halo<0, 64, 1, 4, 4>@2": 26804565,
+    "k_halo<0, 64, 1, 4, 2>@2": 26797423,
+    "k_fwd_dma<64, 64, 64, 2, 2, 3, 1>@2": 13248000,
+    "k_wgrad_dma<64, 128, 32, 2, 2, 2>@2": 25822293,
+    "k_fwd_dma<64, 64, 128, 2, 2, 4, 1>@2": 21901824,
+    "k_conv_win<false, 3, 1, 2, false>@2": 21790558,
+    "k_fwd_rgb3@2": 14118030,
+    "k_dense_wgrad<false>@2": 16639315,
+    "k_halo_ws<0, false>@2": 16347136,
+    "k_wgrad_rgb3<true>@2": 15737617,
+    "k_halo_ws<0, false, 2>@2": 15724826,
+    "k_fwd_dma<128, 64, 64, 2, 2, 2, 1>@2": 13431808,
+    "k_conv_fast<0, 64, 64, 64, 2, 2>@2": 13243127,
+    "k_dgrad_dma<64, 64, 128, 2, 2, 4, 1>@2": 11870208,
+    "k_fwd_dma<128, 64, 64, 2, 2, 2, 2>@2": 9950106,
+    "k_dense_dgrad@2": 8327168,
+    "k_dense_both_sum@2": 1484945,
+    "k_wgrad_direct_sum@2": 1714944,
 }
 
 
