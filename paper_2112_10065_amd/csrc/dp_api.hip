@@ -37,7 +37,7 @@ std::atomic<int> g_force_splits[3] = {{0}, {0}, {0}};
 std::atomic<int> g_autotune{0};
 thread_local bool g_analytic_only = false;   // the descriptor of the running call asks for DP_DETERMINISTIC
 // forms of a filter gradient, for calls whose scratch does not hold more (ScratchForm)
-enum { FORM_USUAL, FORM_WINDOW, FORM_LEAST };
+enum { FORM_USUAL, FORM_WINDOW, FORM_LEAST, FORM_PATCH, FORM_NONE };
 thread_local int g_scratch_form = FORM_USUAL;
 std::once_flag g_init_once;
 hipError_t g_init_err = hipSuccess;
@@ -339,11 +339,11 @@ PlanRef plan_entry(const ConvGeom &g, int pass, int restr = 0)
     PlanRef ep = std::make_shared<PlanEntry>();
     PlanEntry &e = *ep;
     const int form = pass == PASS_WGRAD ? g_scratch_form : FORM_USUAL;
-    plan_uncached(g, pass, fv, fs, &e.plan, restr | (form == FORM_LEAST ? RESTR_BASE : form == FORM_WINDOW ? RESTR_WINDOW : 0));
-    const bool round_splits = pass == PASS_WGRAD && fv < 0 && fs <= 0 && form != FORM_LEAST;
+    plan_uncached(g, pass, fv, fs, &e.plan, restr | (form == FORM_LEAST ? RESTR_BASE : form == FORM_PATCH ? RESTR_BASE | RESTR_PATCH : form == FORM_WINDOW ? RESTR_WINDOW : 0));
+    const bool round_splits = pass == PASS_WGRAD && fv < 0 && fs <= 0 && (form == FORM_USUAL || form == FORM_WINDOW);
     if (round_splits) round_wgrad_splits(g, e.plan);
     e.part_cap = mfma_partial_bytes(g, pass, e.plan);
-    if (at != 0 && fv < 0 && e.plan.fast && form != FORM_WINDOW) {
+    if (at != 0 && fv < 0 && e.plan.fast && (form == FORM_USUAL || form == FORM_LEAST)) {
         GemmPlan list[kTuneCandidates];
         // a cold measurement judges for itself what the model's warm-cache prices cannot: more candidates, a wider price band
         int n = auto_plan_list(g, pass, fs, list, at == 2 ? kTuneCandidates : 12, restr | (at == 2 ? 4 : 0));
@@ -725,7 +725,8 @@ dp_status run_dgrad(const ConvGeom &g, int dtype, unsigned flags, const void *dy
 }
 
 // Gives back the form that filter gradients on this thread take.  Another than the fastest is for calls whose scratch does not hold that: the window kernel in the place
-// of the nine-tap one, or the kernels without either and without the empty splits of round_wgrad_splits.  Any of them may ask for least.
+// of the nine-tap one, the kernels without the window kernel and without the empty splits of round_wgrad_splits, or those with the nine-tap kernel's blocks for larger
+// tiles.  Any of them may ask for least.
 struct ScratchForm {
     const int before = g_scratch_form;
     ScratchForm() {}
@@ -749,7 +750,7 @@ size_t stem_wgrad_ws_bytes(const ConvGeom &g, bool with_db)
 bool use_stem_wgrad(const ConvGeom &g, int dtype, bool with_db)
 {
     return use_small_c(g, PASS_WGRAD) && small_c_wgrad_stem_shape(g) &&
-           !(g_scratch_form == FORM_LEAST && im2col_wgrad_ws_bytes(g, dtype, with_db) < stem_wgrad_ws_bytes(g, with_db));
+           !(g_scratch_form >= FORM_LEAST && im2col_wgrad_ws_bytes(g, dtype, with_db) < stem_wgrad_ws_bytes(g, with_db));
 }
 
 size_t wgrad_ws_bytes(const ConvGeom &g, int dtype, bool with_db)
@@ -771,12 +772,12 @@ size_t wgrad_ws_bytes(const ConvGeom &g, int dtype, bool with_db)
     return need;
 }
 
-// the next form behind the current one that this layer has
+// the next form behind the current one that this layer has; FORM_NONE: there is none
 int next_form(const ConvGeom &g, int dtype)
 {
     GemmPlan pl;
-    return g_scratch_form == FORM_USUAL && dtype == DP_BF16 && g_force_variant[PASS_WGRAD].load() < 0 && g_force_splits[PASS_WGRAD].load() <= 0 && wgrad_window_form(g, &pl)
-               ? FORM_WINDOW : FORM_LEAST;
+    const bool nine = dtype == DP_BF16 && g_force_variant[PASS_WGRAD].load() < 0 && g_force_splits[PASS_WGRAD].load() <= 0 && wgrad_window_form(g, &pl);
+    return g_scratch_form == FORM_USUAL ? (nine ? FORM_WINDOW : FORM_LEAST) : g_scratch_form == FORM_WINDOW ? FORM_LEAST : g_scratch_form == FORM_LEAST && nine ? FORM_PATCH : FORM_NONE;
 }
 
 // the least a call can do with
@@ -784,8 +785,8 @@ size_t wgrad_least_ws_bytes(const ConvGeom &g, int dtype, bool with_db)
 {
     const ScratchForm restore;
     size_t need = wgrad_ws_bytes(g, dtype, with_db);
-    while (g_scratch_form != FORM_LEAST) {
-        g_scratch_form = next_form(g, dtype);
+    for (int form; (form = next_form(g, dtype)) != FORM_NONE;) {
+        g_scratch_form = form;
         need = std::min(need, wgrad_ws_bytes(g, dtype, with_db));
     }
     return need;
@@ -797,8 +798,8 @@ dp_status run_wgrad(const ConvGeom &g, int dtype, const void *x, const void *dy,
 {
     const ScratchForm restore;
     size_t need = wgrad_ws_bytes(g, dtype, db != nullptr), least = need;
-    while (need > (ws != nullptr ? ws_bytes : 0) && g_scratch_form != FORM_LEAST) {
-        g_scratch_form = next_form(g, dtype);
+    for (int form; need > (ws != nullptr ? ws_bytes : 0) && (form = next_form(g, dtype)) != FORM_NONE;) {
+        g_scratch_form = form;
         need = wgrad_ws_bytes(g, dtype, db != nullptr);
         least = std::min(least, need);
     }

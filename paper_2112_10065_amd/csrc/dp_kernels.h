@@ -25,6 +25,7 @@ enum {
     RESTR_ORDER = 32,  // forward with DP_RELU and without DP_RELU_IN: the default choice leaves out the kernel that adds in another order (forward_flat_plan)
     RESTR_BASE = 16,   // the kernels and prices that need least scratch: no flat-walk kernel in backward-data
     RESTR_WINDOW = 64,   // filter gradient: the window kernel in the place of the nine-tap one, whose blocks ask for more scratch
+    RESTR_PATCH = 128,   // filter gradient, with RESTR_BASE: blocks and price of the nine-tap kernel as with the 256-pixel tiles of the wave-per-tap one
 };
 
 // Geometry of one conv layer plus its implicit-GEMM view for one pass.

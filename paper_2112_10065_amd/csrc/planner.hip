@@ -202,7 +202,12 @@ int auto_plan_list(const ConvGeom &g, int pass, int force_splits, GemmPlan *out,
             if (!(restr & 4) && cands[ci].code >= 230 && cands[ci].code <= 233 && (long long)cand.tilesA * cand.tilesB * cand.splits < 160) continue;
             last_splits = cand.splits;
             if (force_splits <= 0 && cand.splits > 1 && cand.steps_per_split < 4) break;
-            if (n < 512) { all[n].t = price(g, pass, cands[ci], cand, restr); all[n].pl = cand; all[n].code = cands[ci].code; ++n; }
+            double t = price(g, pass, cands[ci], cand, restr);
+            GemmPlan w;
+            // The nine-tap kernel had tiles of 256 pixels, fewer blocks and less scratch in some layers: a buffer that was enough for it then is enough
+            if (cands[ci].code == 411 && (restr & RESTR_PATCH) && family_plan(g, pass, 410, cand.splits, &w) && family_plan(g, pass, 411, w.splits, &cand))
+                t = price(g, pass, {411, 1, 0.10f, 6.0f}, w, restr);
+            if (n < 512) { all[n].t = t; all[n].pl = cand; all[n].code = cands[ci].code; ++n; }
         }
     }
     // selection sort of the few that are wanted; per tile variant only its two cheapest splits

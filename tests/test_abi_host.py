@@ -281,14 +281,16 @@ def test_filter_gradient_takes_the_scratch_that_was_enough_before(dp):
 
 
 def test_filter_gradient_of_nine_tap_layers_takes_the_window_kernels_scratch(dp):
-    """The nine-tap kernel, and the tiles that are faster than the window kernel, ask for more scratch than the window kernel.  A call with what that one asks for is
-    accepted, also without a workspace of its own where that fits the built-in scratch.  Valid calls get as far as the missing GPU."""
+    """The nine-tap kernel, and the tiles that are faster than the window kernel, ask for more scratch than the window kernel, and the nine-tap kernel for more than
+    with larger tiles.  A call with what those ask for is accepted, also without a workspace of its own where that fits the built-in scratch.  Valid calls get as far as the missing GPU."""
     import torch
     if torch.cuda.is_available():
         pytest.skip("would launch on the addresses made up here")
     # (n, h, w, c_out, pad, what the window kernel's plan asks for, whether that fits the 32 MiB built in)
     for n, h, w, k, pad, enough, builtin in ((8, 153, 149, 128, 1, 65529856, False), (48, 35, 39, 8, 1, 2723584, True), (30, 26, 23, 384, 0, 28323840, True),
-                                             (6, 212, 217, 40, 1, 33315328, True), (21, 27, 29, 256, 1, 22509056, True), (10, 93, 92, 320, 1, 73845760, False)):
+                                             (6, 212, 217, 40, 1, 33315328, True), (21, 27, 29, 256, 1, 22509056, True), (10, 93, 92, 320, 1, 73845760, False),
+                                             # the nine-tap kernel's plan with fewer blocks
+                                             (2, 193, 174, 32, 1, 11441920, True), (3, 109, 110, 192, 1, 28361472, True), (16, 16, 16, 440, 1, 12615680, True)):
         d = dp.conv_desc(n, h, w, 64, k, 3, 3, (1, 1), (pad, pad), dp.DP_BF16, 0)
         for saved in (None, A):
             assert dp.lib.dp_conv2d_bwd_filter(C.byref(d), A, A, saved, A, A, A, enough, None) == dp.DP_ERR_HIP, (n, h, w, k)

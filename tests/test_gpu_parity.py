@@ -1041,21 +1041,21 @@ def test_nine_tap_layers_with_less_scratch(env, saved):
     """A layer whose fastest filter gradient is the nine-tap kernel (or tiles that take the place of the window kernel), with less scratch than that asks for:
     the window kernel and the kernels beside it give the same gradients, also from the scratch built into the library."""
     dp, U, orc = env
-    for n, h, w, k in ((5, 137, 134, 72), (3, 60, 61, 272)):
+    for n, h, w, k, fewer_blocks in ((5, 137, 134, 72, None), (3, 60, 61, 272, None), (2, 193, 174, 32, 11441920)):
         case = U.ConvCase("short9", n, h, w, 64, k, 3, 3, (1, 1), (1, 1), bf16=True, bias=True, relu=saved)
         y = case.run_fwd() if saved else None
         need = dp.dp_conv2d_workspace_bytes(case.desc, 2)
         dw, db = case.run_wgrad(y)
         torch.cuda.synchronize()
         kernels = set()
-        for nbytes in (need, need - 256, need * 3 // 4, need * 5 // 8):
+        for nbytes in (need, need - 256, need * 3 // 4, need * 5 // 8, fewer_blocks or need):
             dw2, db2 = torch.zeros_like(dw), torch.zeros_like(db)
             dp.dp_trace_begin()
             try:
                 dp.dp_conv2d_bwd_filter(case.desc, case.xd, case.dyd, y, dw2, db2, U.workspace(nbytes)[:nbytes])
             except dp.DpError:
                 dp.dp_trace_end()
-                assert nbytes < need
+                assert nbytes < need and nbytes != fewer_blocks
                 continue
             kernels.add(dp.dp_trace_end()[0]["kernel"].split("<")[0])
             torch.cuda.synchronize()
