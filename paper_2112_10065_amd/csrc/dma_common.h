@@ -107,7 +107,8 @@ DEVFN unsigned tap_mask(int hb, int wb, int sg, int R, int S, int Hlim, int Wlim
 // x + 8, ...) walks one contiguous eighth of the tile list, its blocks side by side, so that tiles that share halo pixels (left /
 // right neighbours, and the row of tiles above / below) run on one XCD at about the same time and the second reader of a halo pixel
 // finds it in that L2.  (Dealing the tiles out block by block over the whole chip, every halo pixel was fetched from memory again: L2
-// hit rate 0.09 on conv1_2, and the copies of a CU are bound by its ~64 outstanding misses.)
+// hit rate 0.09 on conv1_2, and the copies of a CU are bound by its ~64 outstanding misses.)  Other counts of blocks than whole eighths, which the
+// 3x3 kernels take with 3, 5, 6 or 7 channel tiles, are dealt out that way all the same.
 struct TileWalk { int first, end, stride; };
 DEVFN TileWalk tile_walk(int tiles)
 {

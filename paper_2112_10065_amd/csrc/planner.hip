@@ -512,7 +512,8 @@ bool wgrad_window_plan(const ConvGeom &g, const GemmPlan &base, double time, Gem
     const double worth = !pl[0].row_taps ? 0.8 : base.halo ? 1.35 : !base.dma ? 1.0 : base.splits == 1 ? 0.75 : 0.92;
     const bool nine = base.halo && base.variant == 11;
     if (!nine && t[0] >= worth * time) return false;
-    // Both by prices of their own.  With flushed caches the window kernel loses 10 - 50 % more (40 layers nearer than that to each other back to back)
+    // Both by prices of their own, where the window kernel has won against `base` or that is the nine-tap kernel.  With flushed caches the window kernel loses
+    // 10 - 50 % more (40 layers nearer than that to each other back to back; 60 layers that went to the nine-tap kernel: 1.04 of its time warm in the middle, 0.92 cold)
     GemmPlan nine_pl;
     double nine_time;
     if (nine_tap_plan(g, &nine_pl, &nine_time) && t[0] >= 0.96 * nine_time) { *out = nine_pl; return true; }
